@@ -1,64 +1,14 @@
-// act_lift_quant: fused per-token quantisation + activation lifting (Alg. 1), and
-// slide_prune_quant: offline (2N-2):2N magnitude pruning + per-channel quantisation.
+// act_lift_quant: fused per-token quantisation + activation lifting (Alg. 1).
 //
-// Both kernels stream a row through one workgroup: the row is read from HBM once, kept in
+// The kernel streams a row through one workgroup: the row is read from HBM once, kept in
 // registers while the wavefronts reduce the absmax, quantised element-wise into LDS, and the
 // lifted windows are then gathered from LDS so that every source element is quantised once
 // and every output store is a coalesced 16-byte vector.  HBM traffic per token is therefore
 // the algorithmic minimum: K input elements in, K' output elements + one scale out.
 #include "ss_common.h"
+#include "quant_common.h"
 
 namespace ss {
-
-constexpr int LQ_THREADS = 256;
-
-template <typename T> struct InVec;
-template <> struct InVec<float> {
-    static constexpr int N = 4; typedef float4 V;
-    __device__ static void unpack(const V& v, float* f) { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
-};
-template <> struct InVec<uint16_t> {          // bf16 bits
-    static constexpr int N = 8; typedef uint4 V;
-    __device__ static void unpack(const V& v, float* f)
-    {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { f[2 * i] = __uint_as_float(w[i] << 16); f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
-    }
-};
-__device__ inline float load_scalar(const float* p) { return *p; }
-__device__ inline float load_scalar(const uint16_t* p) { return bf16_bits_to_f32(*p); }
-
-template <int THREADS> __device__ inline float block_absmax(float v, float* red)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
-    __syncthreads();
-    float m = red[0];
-#pragma unroll
-    for (int w = 1; w < THREADS / 64; ++w) m = fmaxf(m, red[w]);
-    return m;
-}
-
-// quantise one element: OUT 0 = int8, 1 = fp8 e4m3, 2 = bf16 (no scale), 3 = half (no scale)
-template <int OUT> __device__ inline uint32_t quant1(float x, float r)
-{
-    if constexpr (OUT == 0) {
-        float q = rintf(x * r);
-        q = fminf(fmaxf(q, -127.0f), 127.0f);
-        return (uint32_t)(int)q & 0xFFu;
-    } else if constexpr (OUT == 1) {
-        float q = x * r;
-        q = fminf(fmaxf(q, -448.0f), 448.0f);
-        return f32_to_e4m3(q);
-    } else if constexpr (OUT == 2) {
-        return f32_to_bf16_bits(x);
-    } else {
-        return f32_to_f16_bits(x);
-    }
-}
 
 // MAXV > 0: vector loads, row kept in registers (needs K <= MAXV * THREADS * VecN, 16-byte
 // aligned rows).  MAXV == 0: scalar loads, second pass re-reads the row.  Long rows take more
@@ -247,52 +197,6 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     return launch_status();
 }
 
-// ------------------------------------------------------------------------------------------
-// Offline: magnitude pruning to (2N-2):2N followed by per-output-channel quantisation.
-// One workgroup per weight row; thread per 2N block in the second pass.
-template <typename TIN, int OUT>
-__global__ __launch_bounds__(LQ_THREADS) void k_prune_quant(const TIN* __restrict__ W, int K, int N, uint8_t* __restrict__ Wq,
-                                                             float* __restrict__ s_w)
-{
-    constexpr int ES = OUT >= 2 ? 2 : 1;
-    __shared__ float red[LQ_THREADS / 64];
-    const int64_t o = blockIdx.x;
-    const TIN* w = W + o * (int64_t)K;
-    const int t = threadIdx.x;
-    float r = 0.0f;
-    if constexpr (OUT < 2) {
-        float amax = 0.0f;
-        for (int k = t; k < K; k += LQ_THREADS) amax = fmaxf(amax, fabsf(load_scalar(w + k)));
-        amax = block_absmax<LQ_THREADS>(amax, red);   // the row maximum always survives pruning
-        constexpr float QMAX = OUT == 0 ? 127.0f : 448.0f;
-        float s = 1.0f;
-        if (amax > 0.0f) { r = QMAX / amax; s = amax / QMAX; }
-        if (t == 0) s_w[o] = s;
-    }
-    const int L = 2 * N, ng = (K + L - 1) / L;            // a partial last block is completed with zeros
-    for (int g = t; g < ng; g += LQ_THREADS) {
-        float v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = (k < L && g * L + k < K) ? load_scalar(w + g * L + k) : 0.0f;
-        // the two entries dropped are the last two in the order (|w| descending, index ascending)
-        int d1 = 0, d2 = -1;
-        float m1 = fabsf(v[0]);
-#pragma unroll
-        for (int k = 1; k < 16; ++k) if (k < L && fabsf(v[k]) <= m1) { m1 = fabsf(v[k]); d1 = k; }
-        float m2 = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) if (k < L && k != d1 && (d2 < 0 || fabsf(v[k]) <= m2)) { m2 = fabsf(v[k]); d2 = k; }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (k < L && g * L + k < K) {
-                const uint32_t q = (k == d1 || k == d2) ? 0u : quant1<OUT>(v[k], r);
-                if constexpr (ES == 1) Wq[o * (int64_t)K + g * L + k] = (uint8_t)q;
-                else reinterpret_cast<uint16_t*>(Wq)[o * (int64_t)K + g * L + k] = (uint16_t)q;
-            }
-        }
-    }
-}
-
 }  // namespace ss
 
 using namespace ss;
@@ -332,34 +236,4 @@ extern "C" ss_status act_lift_quant(const void* X, ss_act_dtype in_dtype, int64_
     if (out == SS_FP8_E4M3) return launch_lift<uint16_t, 1>(X, M, K, ldx, N, X_lifted, s_x, st);
     if (out == SS_BF16) return launch_lift<uint16_t, 2>(X, M, K, ldx, N, X_lifted, s_x, st);
     return launch_lift<uint16_t, 3>(X, M, K, ldx, N, X_lifted, s_x, st);
-}
-
-template <typename TIN, int OUT>
-static ss_status launch_prune(const void* W, int64_t O, int64_t K, int N, void* Wq, float* s_w, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_prune_quant<TIN, OUT>), dim3((unsigned)O), dim3(LQ_THREADS), 0, st, static_cast<const TIN*>(W), (int)K, N,
-                       static_cast<uint8_t*>(Wq), s_w);
-    return launch_status();
-}
-
-extern "C" ss_status slide_prune_quant(const void* W, ss_act_dtype in_dtype, int64_t O, int64_t K, int N, ss_dtype dtype,
-                                       void* Wq, float* s_w, void* stream)
-{
-    if (!valid_N(N)) return SS_ERR_BAD_PATTERN_N;
-    if (O < 0 || K <= 0 || K > (1 << 24) || O > 0x7FFFFFFF) return SS_ERR_SHAPE;
-    if (in_dtype != SS_IN_F32 && in_dtype != SS_IN_BF16) return SS_ERR_DTYPE;
-    if (!valid_dtype(dtype)) return SS_ERR_DTYPE;
-    if (O == 0) return SS_OK;
-    if (!W || !Wq || (!unscaled(dtype) && !s_w)) return SS_ERR_NULL;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (in_dtype == SS_IN_F32) {
-        if (dtype == SS_I8) return launch_prune<float, 0>(W, O, K, N, Wq, s_w, st);
-        if (dtype == SS_FP8_E4M3) return launch_prune<float, 1>(W, O, K, N, Wq, s_w, st);
-        if (dtype == SS_BF16) return launch_prune<float, 2>(W, O, K, N, Wq, s_w, st);
-        return launch_prune<float, 3>(W, O, K, N, Wq, s_w, st);
-    }
-    if (dtype == SS_I8) return launch_prune<uint16_t, 0>(W, O, K, N, Wq, s_w, st);
-    if (dtype == SS_FP8_E4M3) return launch_prune<uint16_t, 1>(W, O, K, N, Wq, s_w, st);
-    if (dtype == SS_BF16) return launch_prune<uint16_t, 2>(W, O, K, N, Wq, s_w, st);
-    return launch_prune<uint16_t, 3>(W, O, K, N, Wq, s_w, st);
 }

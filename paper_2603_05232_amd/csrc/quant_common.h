@@ -1,0 +1,69 @@
+// Pieces shared by the two quantisation kernels (lift_quant.hip, prune_quant.hip).
+#pragma once
+#include "ss_common.h"
+
+namespace ss {
+
+template <typename T> struct InVec;
+template <> struct InVec<float> {
+    static constexpr int N = 4; typedef float4 V;
+    __device__ static void unpack(const V& v, float* f) { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
+};
+template <> struct InVec<uint16_t> {          // bf16 bits
+    static constexpr int N = 8; typedef uint4 V;
+    __device__ static void unpack(const V& v, float* f)
+    {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { f[2 * i] = __uint_as_float(w[i] << 16); f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+    }
+};
+__device__ inline float load_scalar(const float* p) { return *p; }
+__device__ inline float load_scalar(const uint16_t* p) { return bf16_bits_to_f32(*p); }
+
+template <int THREADS> __device__ inline float block_absmax(float v, float* red)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) red[wave] = v;
+    __syncthreads();
+    float m = red[0];
+#pragma unroll
+    for (int w = 1; w < THREADS / 64; ++w) m = fmaxf(m, red[w]);
+    return m;
+}
+
+// quantise one element: OUT 0 = int8, 1 = fp8 e4m3, 2 = bf16 (no scale), 3 = half (no scale)
+template <int OUT> __device__ inline uint32_t quant1(float x, float r)
+{
+    if constexpr (OUT == 0) {
+        float q = rintf(x * r);
+        q = fminf(fmaxf(q, -127.0f), 127.0f);
+        return (uint32_t)(int)q & 0xFFu;
+    } else if constexpr (OUT == 1) {
+        float q = x * r;
+        q = fminf(fmaxf(q, -448.0f), 448.0f);
+        return f32_to_e4m3(q);
+    } else if constexpr (OUT == 2) {
+        return f32_to_bf16_bits(x);
+    } else {
+        return f32_to_f16_bits(x);
+    }
+}
+
+// The same codes with fewer instructions, for kernels where the conversion counts: only the low byte (OUT < 2) or half
+// of the result is meaningful.  INT8: adding 1.5 * 2^23 to the clamped product rounds it to nearest even and leaves its
+// two's complement in the low mantissa bits (clamping before or after the rounding is the same, 127 being an integer).
+template <int OUT> __device__ inline uint32_t quant_bits(float x, float r)
+{
+    if constexpr (OUT == 0) return __float_as_uint(fminf(fmaxf(x * r, -127.0f), 127.0f) + 12582912.0f);
+    else return quant1<OUT>(x, r);
+}
+// the low bytes of four words
+__device__ inline uint32_t pack_bytes(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3)
+{
+    return __builtin_amdgcn_perm(b1, b0, 0x0C0C0400u) | __builtin_amdgcn_perm(b3, b2, 0x04000C0Cu);
+}
+
+}  // namespace ss
