@@ -1,8 +1,7 @@
 // slide_decompose: Sliding Window Decomposition (Alg. 2, greedy residual allocation) fused
-// with 2:4 compression, written output-oriented: one thread produces one lane's worth of
-// sparse-operand registers (16 bytes of stored values + one index word), so every store is coalesced.
-// A thread re-runs the greedy over the few earlier windows of the same 2N block to recover
-// the carry; the block is at most 16 elements, so this costs a handful of integer ops.
+// with 2:4 compression, in the packed form the GEMM kernels read (k_decompose_packed) and in a
+// plain one for inspection (k_decompose_canonical: a thread per window re-runs the greedy over
+// the few earlier windows of its 2N block to recover what they took).
 #include "ss_common.h"
 #include "packed_layout.h"
 
@@ -68,121 +67,203 @@ __global__ __launch_bounds__(256) void k_decompose_canonical(const typename Elem
     if (violations && nnz > 2 * N - 2) atomicAdd(violations, 1);
 }
 
-// One 2N block of a row with its decomposition: the block's elements (zero beyond the row), the positions each of
-// its N-1 windows takes (Alg. 2, greedy in window order) and its non-zero count.  Loading and decomposing a block once
-// and reading several windows from it is what the packed kernel does: a lane's windows come in runs of consecutive
-// windows, so it touches two to four blocks instead of re-reading one per window.
-template <int ES> struct SlideBlock {
-    typedef typename Elem<ES>::T T;
-    T v[16];
-    uint32_t taken[7];                                   // per window: 4-bit mask of the offsets it stores
-    int nnz;
-
-    __device__ void load(const T* row, int K, int N, int g, bool fp)
-    {
-        const T* blk = row + (int64_t)g * 2 * N;
-        const int left = K - g * 2 * N;                  // elements of this block inside the row (<= 0: none)
-        constexpr int PER = 4 / ES;                      // elements per 32-bit word
-        if (left >= 2 * N && (((uintptr_t)blk) & 3) == 0 && ((2 * N) % PER) == 0) {
-            const uint32_t* w = reinterpret_cast<const uint32_t*>(blk);
-#pragma unroll
-            for (int i = 0; i < 16 / PER; ++i) {
-                const uint32_t x = i * PER < 2 * N ? w[i] : 0u;
-#pragma unroll
-                for (int e = 0; e < PER; ++e) v[i * PER + e] = (T)(x >> (8 * ES * e));
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < 16; ++p) v[p] = (p < 2 * N && p < left) ? blk[p] : (T)0;
-        }
-        uint32_t nzmask = 0;
-#pragma unroll
-        for (int p = 0; p < 16; ++p) nzmask |= (uint32_t)(p < 2 * N && Elem<ES>::nz(v[p], fp)) << p;
-        nnz = __popc(nzmask);
-        uint32_t used = 0;
-#pragma unroll
-        for (int w = 0; w < 7; ++w) {                    // windows in ascending order; each takes its first <= 2 unused non-zeros
-            uint32_t t = 0;
-            int cnt = 0;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int p = 2 * w + d;
-                if (w < N - 1 && ((nzmask >> p) & 1u) && !((used >> p) & 1u) && cnt < 2) { used |= 1u << p; t |= 1u << d; ++cnt; }
-            }
-            taken[w] = t;
-        }
-    }
-
-    // window l: stored values and their positions i0 < i1 (padded with the lowest offsets that hold no stored non-zero)
-    __device__ void window(int l, T& v0, T& v1, uint32_t& i0, uint32_t& i1) const
-    {
-        uint32_t t = 0;
-#pragma unroll
-        for (int w = 0; w < 7; ++w) t = w == l ? taken[w] : t;
-        uint32_t chosen = t;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) if (__popc(chosen) < 2) chosen |= 1u << d;
-        i0 = __ffs(chosen) - 1;
-        i1 = 31 - __clz(chosen);
-        const int p0 = 2 * l + (int)i0, p1 = 2 * l + (int)i1;
-        T e0 = 0, e1 = 0;
-#pragma unroll
-        for (int p = 0; p < 16; ++p) { e0 = p == p0 ? v[p] : e0; e1 = p == p1 ? v[p] : e1; }
-        v0 = ((t >> i0) & 1u) ? e0 : (T)0;
-        v1 = ((t >> i1) & 1u) ? e1 : (T)0;
-    }
+// ---- packed form ------------------------------------------------------------------------------------------
+// Bound by HBM (the quantised matrix in, 15/16 of it out for 6:8 in 8 bits), so the kernel is built around whole cache
+// lines on both sides.  A group is 16 / ES blocks of a row = 32 N bytes = N - 1 steps of the packed form: the smallest
+// run of blocks that fills whole steps in either window order.  A workgroup owns one group of the 128 rows of a panel:
+// it copies 128 x 32N bytes to LDS with 16-byte loads (consecutive lanes along a row), thread t decomposes the group of
+// packed row t (fragment t / 32, row t % 32), which yields the operand registers of lanes i and i + 32 of its fragment
+// for N - 1 steps; the values go out as runs of 32 x 16 bytes, the index words meet in LDS and go out lane-major.
+//
+// Alg. 2's greedy as a state machine: a window sees the two elements it shares with its predecessor (those not taken
+// yet) and two new ones, takes the first two non-zeros of the four and hands on what is left of the last two.  Everything
+// that depends on the four availability bits (positions, byte selectors that fetch the values and write zeros where
+// nothing is stored, the hand-over) is one entry of a 16-entry LDS table, so a window costs one table read, one byte
+// permute and a few bit operations.
+// Measured, 37888 x 3584 INT8 6:8, window order of the fused GEMM: 221 -> 58 us (4.5 TB/s) (a thread per lane of
+// the packed form, which loads its two to four blocks straight from rows K bytes apart and runs the greedy bit by bit,
+// before).
+template <int ES, int N> struct PackGroup {
+    static constexpr int BLOCKS = 16 / ES;
+    static constexpr int BYTES = 32 * N;
+    static constexpr int STEPS = N - 1;
+    static constexpr int ROW = BYTES + 16;               // LDS bytes per row: an odd number of 16-byte chunks, so the chunk reads of 16 lanes spread over all banks
+    static constexpr int WORDS = BYTES / 4;
+    static constexpr int MASKS = WORDS * (4 / ES) / 32 + 1;     // words of one non-zero bit per element
 };
 
-// packed form: one thread per (panel, 64-byte step, fragment, lane).  FUSED: the window order of the GEMM that lifts
-// the activations itself (N = 4; fused_window in packed_layout.h) instead of the order of the lifted row.
-template <int ES, bool FUSED>
-__global__ __launch_bounds__(256) void k_decompose_packed(const typename Elem<ES>::T* __restrict__ Wq, int64_t O, int K, int N, bool fp,
-                                                           uint4* __restrict__ vals, uint32_t* __restrict__ meta, int64_t nslots,
-                                                           int nsteps, int32_t* __restrict__ violations)
+// entry of the table for availability bits av: 8-bit types: bits 15..0 two byte selectors into the window's four
+// bytes; 16-bit types: the upper word of the entry, four byte selectors into its eight.  0x0C selects a zero byte.
+// Bits 27..24 the two positions (ascending, padded with the lowest offsets that hold no stored non-zero), bits 31..30
+// the availability of the last two elements for the next window.
+template <int ES> __device__ inline uint2 pack_entry(uint32_t av)
 {
-    typedef typename Elem<ES>::T T;
-    constexpr int NW = 8 / ES;                           // windows per lane
-    const int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (slot >= nslots) return;
-    const int lane = (int)(slot & 63);
-    const int f = (int)((slot >> 6) & 3);
-    const int64_t ps = slot >> 8;
-    const int64_t panel = ps / nsteps;
-    const int step = (int)(ps - panel * nsteps);
-    const int64_t o = panel * PANEL + panel_row(f, lane & 31);
-    const int qa = lane >> 5;
-    uint32_t v[4] = {0, 0, 0, 0};
-    uint32_t m = ES == 1 ? 0x44444444u : 0x4444u;        // positions (0, 1) everywhere: an all-zero fragment
-    if (o < O) {
-        m = 0;
-        int bad = 0;
-        SlideBlock<ES> B;
-        int g_held = -1;
-        const T* row = Wq + o * (int64_t)K;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            int g, l;
-            if constexpr (FUSED) fused_window<ES>(step, qa, w, g, l);
-            else {
-                const int j = step * (2 * NW) + step_window<ES>(qa, w);
-                g = j / (N - 1);
-                l = j - g * (N - 1);
-            }
-            if (g != g_held) {                           // windows of one block are neighbours in a lane, so every block is loaded once
-                B.load(row, K, N, g, fp);
-                g_held = g;
-            }
-            T v0, v1; uint32_t i0, i1;
-            B.window(l, v0, v1, i0, i1);
-            if constexpr (ES == 1) v[w >> 1] |= ((uint32_t)v0 | ((uint32_t)v1 << 8)) << (16 * (w & 1));
-            else v[w] = (uint32_t)v0 | ((uint32_t)v1 << 16);
-            m |= (i0 | (i1 << 2)) << (4 * w);
-            bad += (l == 0 && B.nnz > 2 * N - 2);       // pattern check, counted by the lane that holds the block's first window
-        }
-        if (violations && bad) atomicAdd(violations, bad);
+    uint32_t taken = av & (0u - av);                     // first non-zero ...
+    const uint32_t rest = av & ~taken;
+    taken |= rest & (0u - rest);                         // ... and the second
+    uint32_t chosen = taken;
+    for (int d = 0; d < 4; ++d) if (__popc(chosen) < 2) chosen |= 1u << d;
+    const uint32_t i0 = __ffs(chosen) - 1, i1 = 31 - __clz(chosen);
+    const bool s0 = (taken >> i0) & 1u, s1 = (taken >> i1) & 1u;
+    uint32_t lo = ((i0 | (i1 << 2)) << 24) | ((av & ~taken) >> 2) << 30, hi = 0;
+    if (ES == 1) lo |= (s0 ? i0 : 0x0Cu) | (s1 ? i1 : 0x0Cu) << 8;
+    else hi = (s0 ? (2 * i0) | (2 * i0 + 1) << 8 : 0x0C0Cu) | (s1 ? (2 * i1) | (2 * i1 + 1) << 8 : 0x0C0Cu) << 16;
+    return make_uint2(lo, hi);
+}
+
+// where window l of block b of a group goes: step of the group, lane half qa, window slot w (inverse of step_window /
+// fused_window in packed_layout.h)
+struct PackSlot { int step, qa, w; };
+template <int ES, int N, bool FUSED> __device__ constexpr PackSlot pack_slot(int b, int l)
+{
+    constexpr int HW = 4 / ES, BL = 8 / ES;
+    if (FUSED) {
+        const int qb = b / BL, bb = b % BL, J = l == 1 ? 2 : bb / (BL / 2), wsl = l == 1 ? bb : 2 * (bb % (BL / 2)) + (l >> 1);
+        return {J, wsl / HW, qb * HW + wsl % HW};
     }
-    vals[slot] = make_uint4(v[0], v[1], v[2], v[3]);
-    meta[(ps * 64 + lane) * FRAGS_PER_PANEL + f] = m;   // index words lane-major: one 16-byte read gives a lane all four
+    const int j = b * (N - 1) + l, wi = j % (4 * HW), rem = wi % (2 * HW);
+    return {j / (4 * HW), rem / HW, (wi / (2 * HW)) * HW + rem % HW};
+}
+
+// Bytes [k0, k0 + 4) of a row of `row_bytes` bytes, zero beyond its end.  The row may start at any byte: the two aligned
+// words around them are read and shifted into place; a word that sticks out of the matrix [mat, mat_end) is read byte by byte.
+__device__ inline uint32_t row_word(const uint8_t* mat, const uint8_t* mat_end, const uint8_t* row, int row_bytes, int k0)
+{
+    const int left = row_bytes - k0;
+    if (left <= 0) return 0;
+    const uint8_t* p = row + k0;
+    const int sh = (int)((uintptr_t)p & 3);
+    auto word = [&](const uint8_t* q) -> uint32_t {
+        if (q >= mat && q + 4 <= mat_end) return *reinterpret_cast<const uint32_t*>(q);
+        uint32_t w = 0;
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) if (q + e >= mat && q + e < mat_end) w |= (uint32_t)q[e] << (8 * e);
+        return w;
+    };
+    const uint32_t lo = word(p - sh), hi = sh && left > 4 - sh ? word(p - sh + 4) : 0u;
+    const uint32_t v = __builtin_amdgcn_alignbyte(hi, lo, sh);
+    return left < 4 ? v & ((1u << (8 * left)) - 1u) : v;
+}
+
+template <int ES, int N, bool FUSED>
+__global__ __launch_bounds__(PANEL) void k_decompose_packed(const uint8_t* __restrict__ Wq, int64_t O, int K, bool fp, uint4* __restrict__ vals,
+                                                             uint32_t* __restrict__ meta, int nsteps, int ngroups, bool aligned,
+                                                             int32_t* __restrict__ violations)
+{
+    typedef PackGroup<ES, N> PG;
+    constexpr int NW = 8 / ES, CHUNKS = PG::BYTES / 16;
+    __shared__ __attribute__((aligned(16))) uint8_t rows[PANEL * PG::ROW];
+    __shared__ __attribute__((aligned(16))) uint32_t words[PG::STEPS * 64 * FRAGS_PER_PANEL];
+    __shared__ uint2 table[16];
+    const int t = threadIdx.x;
+    const int panel = blockIdx.x / ngroups, group = blockIdx.x - panel * ngroups;
+    const int row_bytes = K * ES;
+    // ---- the rows of the panel, in packed order
+    if (t < 16) table[t] = pack_entry<ES>(t);
+    if (aligned) {
+        uint4 in[CHUNKS];
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            const int id = c * PANEL + t, slot = id / CHUNKS, part = id - slot * CHUNKS;
+            const int64_t o = (int64_t)panel * PANEL + panel_row(slot >> 5, slot & 31);
+            const int k0 = group * PG::BYTES + part * 16;
+            in[c] = make_uint4(0, 0, 0, 0);
+            if (o < O && k0 < row_bytes) in[c] = *reinterpret_cast<const uint4*>(Wq + o * row_bytes + k0);
+        }
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            const int id = c * PANEL + t, slot = id / CHUNKS, part = id - slot * CHUNKS;
+            *reinterpret_cast<uint4*>(rows + slot * PG::ROW + part * 16) = in[c];
+        }
+    } else {
+#pragma unroll 4
+        for (int c = 0; c < 4 * CHUNKS; ++c) {
+            const int id = c * PANEL + t, slot = id / (4 * CHUNKS), part = id - slot * (4 * CHUNKS);
+            const int64_t o = (int64_t)panel * PANEL + panel_row(slot >> 5, slot & 31);
+            *reinterpret_cast<uint32_t*>(rows + slot * PG::ROW + part * 4) =
+                o < O ? row_word(Wq, Wq + O * row_bytes, Wq + o * row_bytes, row_bytes, group * PG::BYTES + part * 4) : 0u;
+        }
+    }
+    __syncthreads();
+    // ---- one group of one row per thread
+    uint32_t x[PG::WORDS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        const uint4 q = *reinterpret_cast<const uint4*>(rows + t * PG::ROW + c * 16);
+        x[4 * c] = q.x; x[4 * c + 1] = q.y; x[4 * c + 2] = q.z; x[4 * c + 3] = q.w;
+    }
+    // non-zero bits, one per element: the top bit of every element of a word, gathered by a byte dot product with
+    // powers of two (8 elements per round, which leaves them 7 bits up)
+    uint32_t nz[PG::MASKS] = {};
+    const uint32_t any = ES == 1 ? 0x7F7F7F7Fu : 0x7FFF7FFFu, top = ES == 1 ? 0x80808080u : 0x80008000u;
+    const uint32_t sign = fp ? 0u : 0xFFFFFFFFu;          // the sign bit counts as a value bit for integers only
+#pragma unroll
+    for (int j = 0; j < PG::WORDS * (4 / ES) / 8; ++j) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 2 * ES; ++i) {
+            const uint32_t w = x[j * 2 * ES + i], f = (((w & any) + any) | (w & sign)) & top;
+            const uint32_t weights = ES == 1 ? (i ? 0x80402010u : 0x08040201u) : (0x02000100u << (2 * i));
+            m = __builtin_amdgcn_udot4(f, weights, m, false);
+        }
+        m >>= 7;
+        nz[j / 4] |= m << (8 * (j % 4));
+    }
+    const int f = t >> 5, i = t & 31;
+    uint32_t v[PG::STEPS][2][4], meta_w[PG::STEPS][2];
+#pragma unroll
+    for (int s = 0; s < PG::STEPS; ++s)
+#pragma unroll
+        for (int qa = 0; qa < 2; ++qa) {
+            meta_w[s][qa] = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[s][qa][k] = 0;
+        }
+#pragma unroll
+    for (int b = 0; b < PG::BLOCKS; ++b) {
+        const int e0 = b * 2 * N;                         // first element of the block
+        auto pair = [&](int e) { return (nz[e >> 5] >> (e & 31)) & 3u; };       // e is even: a pair never straddles words
+        uint32_t carry = pair(e0);
+#pragma unroll
+        for (int l = 0; l < N - 1; ++l) {
+            const int e = e0 + 2 * l;
+            const uint32_t av = carry | pair(e + 2) << 2;
+            const uint2 q = table[av];
+            carry = q.x >> 30;
+            const PackSlot s = pack_slot<ES, N, FUSED>(b, l);
+            if constexpr (ES == 1) {
+                const uint32_t win = (e & 2) ? __builtin_amdgcn_alignbyte(x[(e >> 2) + 1 < PG::WORDS ? (e >> 2) + 1 : 0], x[e >> 2], 2) : x[e >> 2];
+                const uint32_t two = __builtin_amdgcn_perm(0, win, q.x);        // the two values in bytes 0, 1; the rest is the entry's other bits
+                uint32_t& d = v[s.step][s.qa][s.w >> 1];
+                d = (s.w & 1) ? __builtin_amdgcn_perm(two, d, 0x05040100u) : __builtin_amdgcn_perm(d, two, 0x07060100u);
+            } else
+                v[s.step][s.qa][s.w] = __builtin_amdgcn_perm(x[(e >> 1) + 1], x[e >> 1], q.y);
+            meta_w[s.step][s.qa] |= ((q.x >> 24) & 15u) << (4 * s.w);
+        }
+    }
+    if (violations) {                                     // blocks with more than 2N - 2 non-zeros
+        int bad = 0;
+#pragma unroll
+        for (int b = 0; b < PG::BLOCKS; ++b) {
+            const int e0 = b * 2 * N, w0 = e0 >> 5;
+            const uint64_t two = nz[w0] | (uint64_t)(w0 + 1 < PG::MASKS ? nz[w0 + 1] : 0u) << 32;
+            bad += __popc((uint32_t)(two >> (e0 & 31)) & ((1u << (2 * N)) - 1u)) > 2 * N - 2;
+        }
+        if (bad) atomicAdd(violations, bad);
+    }
+    // ---- out: values straight, index words through LDS
+    const int64_t ps0 = (int64_t)panel * nsteps + group * PG::STEPS;
+    const int left = nsteps - group * PG::STEPS;          // steps of this group that exist (the last group may stick out)
+#pragma unroll
+    for (int s = 0; s < PG::STEPS; ++s)
+#pragma unroll
+        for (int qa = 0; qa < 2; ++qa) {
+            if (s < left) vals[((ps0 + s) * FRAGS_PER_PANEL + f) * 64 + qa * 32 + i] = make_uint4(v[s][qa][0], v[s][qa][1], v[s][qa][2], v[s][qa][3]);
+            words[(s * 64 + qa * 32 + i) * FRAGS_PER_PANEL + f] = meta_w[s][qa];
+        }
+    __syncthreads();
+    for (int k = t; k < (PG::STEPS < left ? PG::STEPS : left) * 64; k += PANEL)
+        reinterpret_cast<uint4*>(meta)[ps0 * 64 + k] = reinterpret_cast<const uint4*>(words)[k];
 }
 
 }  // namespace ss
@@ -209,22 +290,30 @@ extern "C" ss_status slide_packed_sizes(int64_t O, int64_t K, int N, ss_dtype dt
     return SS_OK;
 }
 
-template <bool FUSED>
-static ss_status launch_packed(const void* Wq, int64_t O, int64_t K, int N, ss_dtype dtype, int64_t Kpb, void* w_vals, void* w_meta,
-                               int32_t* violations, void* stream)
+template <int ES, int N, bool FUSED>
+static ss_status launch_packed_n(const void* Wq, int64_t O, int64_t K, ss_dtype dtype, int nsteps, void* w_vals, void* w_meta, int32_t* violations,
+                                 hipStream_t stream)
 {
     const int64_t npanels = (O + PANEL - 1) / PANEL;
-    const int nsteps = (int)(Kpb / FRAG_KB);
-    const int64_t nslots = npanels * nsteps * FRAGS_PER_PANEL * 64;
-    const dim3 grid((unsigned)((nslots + 255) / 256)), block(256);
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (elem_size(dtype) == 2)
-        hipLaunchKernelGGL((k_decompose_packed<2, FUSED>), grid, block, 0, s, static_cast<const uint16_t*>(Wq), O, (int)K, N, true,
-                           static_cast<uint4*>(w_vals), static_cast<uint32_t*>(w_meta), nslots, nsteps, violations);
-    else
-        hipLaunchKernelGGL((k_decompose_packed<1, FUSED>), grid, block, 0, s, static_cast<const uint8_t*>(Wq), O, (int)K, N, dtype == SS_FP8_E4M3,
-                           static_cast<uint4*>(w_vals), static_cast<uint32_t*>(w_meta), nslots, nsteps, violations);
+    const int ngroups = (nsteps + N - 2) / (N - 1);
+    if (npanels * ngroups > 0x7FFFFFFF) return SS_ERR_SHAPE;
+    const bool aligned = (K * ES) % 16 == 0 && ((uintptr_t)Wq & 15) == 0;
+    hipLaunchKernelGGL((k_decompose_packed<ES, N, FUSED>), dim3((unsigned)(npanels * ngroups)), dim3(PANEL), 0, stream, static_cast<const uint8_t*>(Wq), O,
+                       (int)K, dtype != SS_I8, static_cast<uint4*>(w_vals), static_cast<uint32_t*>(w_meta), nsteps, ngroups, aligned, violations);
     return launch_status();
+}
+
+template <int ES>
+static ss_status launch_packed(const void* Wq, int64_t O, int64_t K, int N, ss_dtype dtype, bool fused, int64_t Kpb, void* w_vals, void* w_meta,
+                               int32_t* violations, void* stream)
+{
+    const int nsteps = (int)(Kpb / FRAG_KB);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (fused) return launch_packed_n<ES, 4, true>(Wq, O, K, dtype, nsteps, w_vals, w_meta, violations, s);
+#define SS_PK(N) case N: return launch_packed_n<ES, N, false>(Wq, O, K, dtype, nsteps, w_vals, w_meta, violations, s)
+    switch (N) { SS_PK(2); SS_PK(3); SS_PK(4); SS_PK(5); SS_PK(6); SS_PK(7); SS_PK(8); }
+#undef SS_PK
+    return SS_ERR_BAD_PATTERN_N;
 }
 
 extern "C" ss_status slide_decompose(const void* Wq, int64_t O, int64_t K, int N, ss_dtype dtype, void* w_vals, void* w_meta,
@@ -235,7 +324,8 @@ extern "C" ss_status slide_decompose(const void* Wq, int64_t O, int64_t K, int N
     const int64_t Kpb = lifted_ld(K, N, elem_size(dtype)) * elem_size(dtype);
     if (O == 0) return SS_OK;
     if (!Wq || !w_vals || !w_meta) return SS_ERR_NULL;
-    return launch_packed<false>(Wq, O, K, N, dtype, Kpb, w_vals, w_meta, violations, stream);
+    return elem_size(dtype) == 1 ? launch_packed<1>(Wq, O, K, N, dtype, false, Kpb, w_vals, w_meta, violations, stream)
+                                 : launch_packed<2>(Wq, O, K, N, dtype, false, Kpb, w_vals, w_meta, violations, stream);
 }
 
 // Fused order: lifted bytes per row = 192 per 128 unlifted bytes (whole super-units; columns at and beyond K are zero).
@@ -262,7 +352,9 @@ extern "C" ss_status slide_decompose_fused(const void* Wq, int64_t O, int64_t K,
     if (N != 4) return SS_ERR_BAD_PATTERN_N;
     if (O == 0) return SS_OK;
     if (!Wq || !w_vals || !w_meta) return SS_ERR_NULL;
-    return launch_packed<true>(Wq, O, K, N, dtype, fused_lifted_row_bytes(K, dtype), w_vals, w_meta, violations, stream);
+    const int64_t Kpb = fused_lifted_row_bytes(K, dtype);
+    return elem_size(dtype) == 1 ? launch_packed<1>(Wq, O, K, N, dtype, true, Kpb, w_vals, w_meta, violations, stream)
+                                 : launch_packed<2>(Wq, O, K, N, dtype, true, Kpb, w_vals, w_meta, violations, stream);
 }
 
 extern "C" ss_status slide_decompose_canonical(const void* Wq, int64_t O, int64_t K, int N, ss_dtype dtype, void* vals, uint8_t* idx,
