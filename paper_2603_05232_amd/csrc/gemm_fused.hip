@@ -382,8 +382,8 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     const int U = (int)(K * es / KSTEP);
     const int64_t ldxb = ldx * es;
     // kernel family by shape, as for the other two GEMMs; the k loop counts super-units of 128 unlifted bytes
-    const ss_plan p = plan_gemm(M, O, U, workspace_bytes);
-    if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
+    const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, U, workspace_bytes);
+    if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_fused_mid(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
 #define SS_F(DT) launch_fused<DT, 4>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, hs)
     switch (dtype) {

@@ -4,52 +4,55 @@
 // There the large-tile kernels leave most compute units idle (M = 256 on a 3584-channel layer is 14
 // tiles for 256 units), so these kernels use 128 (one weight panel) x 128 (tokens) tiles, one tile per
 // workgroup of four wavefronts, each wavefront accumulating 64 channels x 64 tokens (2 x 2 blocks of a
-// 32x32 matrix instruction).  Operands go HBM/L2 -> LDS with direct-to-LDS loads into a ring of
-// units of 128 k-bytes (all but one in flight while that one is computed: a lone workgroup on a compute
-// unit is bound by load latency, so the ring is as deep as LDS allows; one barrier per unit); the inner
-// loop is left to the compiler's scheduler: with at most a few tiles per compute unit the run time is
-// set by how many units are busy, not by the last percent of matrix-core issue.
-//   sparse: a unit is a 16 KB token tile plus the panel's 8 KB of stored values and 2 KB of index
-//           words, which are already in operand-register order (packed_layout.h);
-//   dense:  a unit is a 16 KB token tile plus a 16 KB tile of weight rows, both XOR-swizzled.
+// 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 and 32 tokens for calls that
+// have no more: a call of few tokens is a stream of weights, and every token row that does not exist would
+// be loaded, read and, with a split k range, written as partial sums all the same.  Operands go HBM/L2 -> LDS
+// with direct-to-LDS loads into a ring of units of 128 k-bytes, one barrier per unit.
+//   sparse: a unit is the token tile plus the panel's stored values and index words, which are already in
+//           operand-register order (packed_layout.h); software pipeline, see k_sparse_mid;
+//   dense:  a unit is a 16 KB token tile plus a 16 KB tile of weight rows, both XOR-swizzled; the inner loop
+//           is left to the compiler's scheduler.
 // The epilogue writes each lane's 16 consecutive channels of a token straight to Y.
 #include "ss_common.h"
 #include "packed_layout.h"
 #include "mma_types.h"
 #include "lds_pipe.h"
 #include "device_info.h"
+#include <type_traits>
 
 namespace ss {
 
 constexpr int MD_WAVES = 4;
 constexpr int MD_THREADS = 64 * MD_WAVES;
 constexpr int MD_TILE = 128;                        // output channels and tokens per workgroup
-constexpr int MD_S_RING = 3, MD_D_RING = 3;        // units of the operand rings (one computed, the others in flight)
+constexpr int MD_D_RING = 3;                        // units of the dense kernel's operand ring where a workgroup has a compute unit to itself
 constexpr int MD_ROWS_LOADS = MD_TILE / (8 * MD_WAVES);   // 8 rows per wavefront-wide load: 4 loads per wavefront and tile
 constexpr int MD_TOK = MD_TILE * ROWB;              // 16 KB
-constexpr int MD_AV = 8192, MD_AM = 2048;           // one unit of one panel: stored values, index words
-constexpr int MD_S_UNIT = MD_TOK + MD_AV + MD_AM;   // 26 KB
+// Tiles of TM = 128, 64 or 32 tokens (the last two for the sparse kernels only): a wavefront accumulates FW fragments of
+// 32 channels x TB blocks of 32 tokens, WT groups of wavefronts share out the tokens, the others the fragments.
+template <int TM> struct MidShape {
+    static constexpr int FW = TM == 32 ? 1 : 2, TB = TM == 128 ? 2 : 1, WT = TM == 32 ? 1 : 2;
+    static constexpr int ACC = FW * TB;
+    __device__ static int wo(int wave) { return WT == 2 ? wave & 1 : wave; }
+    __device__ static int wt(int wave) { return WT == 2 ? wave >> 1 : 0; }
+};
 constexpr int MD_D_UNIT = 2 * MD_TOK;               // 32 KB
-constexpr int MD_S_LPU = MD_ROWS_LOADS + 2 + 1;     // direct loads per wavefront and unit
-constexpr int MD_D_LPU = 2 * MD_ROWS_LOADS;
-// fused lifting (6:8): a unit is a super-unit of 128 unlifted bytes = three steps of one panel
-constexpr int MD_F_AV = 3 * 4096, MD_F_AM = 3 * 1024;
-constexpr int MD_F_UNIT = MD_TOK + MD_F_AV + MD_F_AM;   // 31 KB
-constexpr int MD_F_LPU = MD_ROWS_LOADS + 3 + 1;
+constexpr int MD_D_LPU = 2 * MD_ROWS_LOADS;         // direct loads per wavefront and unit
 
-// per-lane source offsets of the direct loads that fill a [128 x 128 B] swizzled tile; rows beyond the
+// per-lane source offsets of the direct loads that fill a [ROWS x 128 B] swizzled tile; rows beyond the
 // matrix are clamped to its last row (their products are never stored)
-struct MidRowLoader {
+template <int ROWS> struct MidRowLoader {
+    static constexpr int LOADS = ROWS / (8 * MD_WAVES);
     const uint8_t* base;                            // first row of the tile (wave-uniform)
-    uint32_t off[MD_ROWS_LOADS];
+    uint32_t off[LOADS];
     __device__ void init(const uint8_t* mat, int64_t ld, int64_t row0, int64_t nrows, int wave, int lane)
     {
         base = mat + row0 * ld;
         const int64_t left = nrows - row0;             // >= 1
-        const int last = left > MD_TILE - 1 ? MD_TILE - 1 : (int)left - 1;
+        const int last = left > ROWS - 1 ? ROWS - 1 : (int)left - 1;
         const uint32_t ld32 = (uint32_t)ld;             // 128 rows x ld fits 32 bits (row bytes <= 2^23)
 #pragma unroll
-        for (int i = 0; i < MD_ROWS_LOADS; ++i) {
+        for (int i = 0; i < LOADS; ++i) {
             const int row = (i * MD_WAVES + wave) * 8 + (lane >> 3);
             const int lc = (lane & 7) ^ swz(row);
             off[i] = (uint32_t)(row < last ? row : last) * ld32 + lc * 16;
@@ -58,61 +61,61 @@ struct MidRowLoader {
     __device__ void issue(int64_t k0, uint8_t* lds_tile, int wave) const
     {
 #pragma unroll
-        for (int i = 0; i < MD_ROWS_LOADS; ++i) lds_dma16(base + k0, off[i], lds_tile + (i * MD_WAVES + wave) * 8 * ROWB);
+        for (int i = 0; i < LOADS; ++i) lds_dma16(base + k0, off[i], lds_tile + (i * MD_WAVES + wave) * 8 * ROWB);
     }
 };
 
 // acc[f][tb][r] of lane (n = lane & 31, h = lane >> 5) is channel o_wave + 64 h + 16 f + r of token t_wave + 32 tb + n
-template <bool SCALED, typename ACC>
-__device__ inline void mid_store(const ACC (&acc)[2][2], const float* __restrict__ s_x, const float* __restrict__ s_w, uint16_t* __restrict__ Y,
+template <bool SCALED, typename ACC, int FW, int TB>
+__device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* __restrict__ s_x, const float* __restrict__ s_w, uint16_t* __restrict__ Y,
                                  int64_t ldy, int64_t M, int64_t O, int64_t o_wave, int64_t t_wave, int lane)
 {
     const int n = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < FW; ++f)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < TB; ++tb)
             store_block16<SCALED>(acc[f][tb], s_x, s_w, Y, ldy, M, O, o_wave + 64 * h + 16 * f, t_wave + tb * 32 + n);
 }
 
 // Split k: the raw accumulators of k-range s of tile `tile` go to the workspace as
-// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (64 KB per tile and range, coalesced).
-constexpr int MD_WS_TILE = MD_TILE * MD_TILE * 4;
-template <typename ACC>
-__device__ inline void mid_store_partial(const ACC (&acc)[2][2], void* ws, int64_t item, int wave, int lane)
+// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (512 TM bytes per tile and range, coalesced).
+template <typename ACC, int FW, int TB>
+__device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int64_t item, int wave, int lane)
 {
-    v4i* dst = static_cast<v4i*>(ws) + ((item * MD_WAVES + wave) * 16) * 64 + lane;
+    v4i* dst = static_cast<v4i*>(ws) + ((item * MD_WAVES + wave) * (4 * FW * TB)) * 64 + lane;
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < FW; ++f)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
                 const elem_t q[4] = {acc[f][tb][4 * r4], acc[f][tb][4 * r4 + 1], acc[f][tb][4 * r4 + 2], acc[f][tb][4 * r4 + 3]};
-                dst[((f * 2 + tb) * 4 + r4) * 64] = __builtin_bit_cast(v4i, q);
+                dst[((f * TB + tb) * 4 + r4) * 64] = __builtin_bit_cast(v4i, q);
             }
 }
 
 // Sum of the S partial accumulators of every tile in range order (bit-reproducible also for fp32) and the
 // scale epilogue.  One workgroup per (tile, wavefront of the GEMM kernel); thread (f, tb, register quad, lane) owns four
 // consecutive channels of one token, so a range costs it one 16-byte load and up to eight ranges are in flight at once.
-constexpr int MD_RED_THREADS = 1024;
-template <int DT>
-__global__ __launch_bounds__(MD_RED_THREADS) void k_mid_reduce(const v4i* __restrict__ ws, int S, int64_t ntiles, const float* __restrict__ s_x,
+template <int DT, int TM>
+__global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const v4i* __restrict__ ws, int S, int64_t ntiles, const float* __restrict__ s_x,
                                                                const float* __restrict__ s_w, int64_t M, int64_t O, uint16_t* __restrict__ Y,
                                                                int64_t ldy, int tiles_t)
 {
     typedef Mma<DT> MM;
+    typedef MidShape<TM> MS;
+    constexpr int TB = MS::TB, ACC = MS::ACC;
     typedef typename MM::acc_t acc_t;
     typedef decltype(acc_t{}[0] + acc_t{}[0]) elem_t;
     typedef elem_t quad_t __attribute__((ext_vector_type(4)));
     const int64_t tile = blockIdx.x / MD_WAVES;
-    const int wave = blockIdx.x % MD_WAVES, wo = wave & 1, wt = wave >> 1;
-    const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3, ft = threadIdx.x >> 8, f = ft >> 1, tb = ft & 1;
+    const int wave = blockIdx.x % MD_WAVES, wo = MS::wo(wave), wt = MS::wt(wave);
+    const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3, ft = threadIdx.x >> 8, f = ft / TB, tb = ft % TB;
     quad_t a = {0, 0, 0, 0};
-    const v4i* src = ws + ((tile * MD_WAVES + wave) * 16 + ft * 4 + r4) * 64 + lane;
-    const int64_t range_stride = ntiles * MD_WAVES * 16 * 64;             // 16-byte groups between consecutive k ranges
+    const v4i* src = ws + ((tile * MD_WAVES + wave) * (4 * ACC) + ft * 4 + r4) * 64 + lane;
+    const int64_t range_stride = ntiles * MD_WAVES * (4 * ACC) * 64;             // 16-byte groups between consecutive k ranges
     int s = 0;
     for (; s + 8 <= S; s += 8) {
         quad_t q[8];
@@ -137,190 +140,230 @@ __global__ __launch_bounds__(MD_RED_THREADS) void k_mid_reduce(const v4i* __rest
         for (int d = 0; d < 3; ++d)
             if (s + d < S) a += q[d];
     }
-    const int64_t panel = tile / tiles_t, t0 = (tile - panel * tiles_t) * MD_TILE;
-    store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo + 64 * (lane >> 5) + 16 * f + 4 * r4, t0 + wt * 64 + tb * 32 + (lane & 31));
+    const int64_t panel = tile / tiles_t, t0 = (tile - panel * tiles_t) * TM;
+    store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, panel * PANEL + 16 * MS::FW * wo + 64 * (lane >> 5) + 16 * f + 4 * r4, t0 + wt * (32 * TB) + tb * 32 + (lane & 31));
 }
 
-// Tile of this workgroup.  Workgroup ids go round-robin over the 8 XCDs; when the tile count allows, the tiles are
-// renumbered so that every XCD works on one contiguous run of tiles: the token tiles of a weight panel (consecutive
-// tile numbers) then share that panel's weights in one L2 instead of fetching them once per XCD.
-__device__ inline int mid_tile_of_block()
+// Work item of this workgroup: a tile of a k range.  Workgroup ids go round-robin over the 8 XCDs, so item numbers are
+// dealt out in one contiguous run per XCD, whatever their count; items are numbered range by range, a range in bands of
+// 8 token tiles, a band panel by panel.  The workgroups of an XCD then read few k ranges, few weight panels and few token
+// tiles, and share them in its L2.
+struct MidItem { int64_t panel; int tt, range; int64_t tile; };
+__device__ inline MidItem mid_item(int tiles_t)
 {
-    const int nt = gridDim.x, b = blockIdx.x;
-    return (nt & 7) == 0 ? (b & 7) * (nt >> 3) + (b >> 3) : b;
+    const int nt = gridDim.x, total = nt * gridDim.y, id = blockIdx.y * nt + blockIdx.x;
+    const int item = xcd_run(id, total);
+    const int range = item / nt, k = item - range * nt;
+    const int per_band = 8 * (nt / tiles_t), band = k / per_band, within = k - band * per_band;
+    const int bw = min(8, tiles_t - band * 8), panel = within / bw, tt = band * 8 + (within - panel * bw);
+    return {panel, tt, range, (int64_t)panel * tiles_t + tt};
 }
 
-template <typename ACC> __device__ inline void mid_zero(ACC (&acc)[2][2])
+template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&acc)[FW][TB])
 {
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < FW; ++f)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[f][tb][r] = 0;
 }
 
 // ---- sparse ---------------------------------------------------------------------------------------------
-template <int DT>
-__global__ __launch_bounds__(MD_THREADS) void k_sparse_mid(const uint8_t* __restrict__ XL, const float* __restrict__ s_x,
-                                                           const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
-                                                           const float* __restrict__ s_w, int64_t M, int64_t O, int64_t Kpb,
-                                                           uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
+// One unit of k is 128 bytes of a token row in LDS.  Lifted input: a piece of a row of X', two matrix-instruction steps
+// deep; B lane (n, qb) takes the 32 bytes [32 qb, 32 qb + 32) of each 64-byte step.  FUSED (6:8, weights packed by
+// slide_decompose_fused): a piece of an unlifted row, a super-unit of three steps; B lane (n, qb) takes the 64 bytes
+// [64 qb, 64 qb + 64), uses the first half in step 0, the second in step 1 and builds the eight middle windows of step 2
+// in registers (packed_layout.h, fused_window): the k loop is as long as the dense kernel's, with three sparse
+// instructions where that one issues four dense ones.
+//
+// A workgroup is one wavefront per SIMD, and a wavefront issues in order, so nothing overlaps by itself: requesting a
+// unit (26 or 31 KB at the 60 bytes a clock that a compute unit's direct loads reach), reading its operands from LDS and
+// the matrix instructions would add up.  The loop is therefore a software pipeline: while the matrix instructions of
+// unit u run on registers, the operands of unit u + 1 are read from LDS into a second set, and the direct loads of unit
+// u + RING go into the ring slot that unit u has left, one by one between the matrix instructions.  What is left is the
+// load path (a build with the loads alone takes 61 of the 73 us of 5003 -> 4099 fp16 8:10 at M = 777, one with everything
+// else 48).  Loop by loop against one that left the overlap to the compiler: that shape 81 -> 73 us, 14336 -> 4096 fp8 at
+// M = 1024 87 -> 73.
+template <int TM, bool FUSED> struct MidUnit {
+    typedef MidShape<TM> MS;
+    static constexpr int NS = FUSED ? 3 : 2;                              // steps
+    static constexpr int AV = NS * 4096, AM = NS * 1024;                  // values, index words of a panel
+    static constexpr int TOK = TM * ROWB;                                 // token rows
+    static constexpr int BYTES = TOK + AV + AM;                           // 26 or 31 KB (TM = 128), 18 or 23 (64), 14 or 19 (32)
+    static constexpr int RL = TM / 32;                                    // direct loads of token rows per wavefront (8 rows each)
+    static constexpr int LPU = RL + NS + 1;                               // direct loads per wavefront
+    static constexpr int NM = MS::ACC * NS;                               // matrix instructions per wavefront
+    static constexpr int NB = 4 * MS::TB;                                 // LDS reads of token chunks per wavefront
+    static constexpr int NR = NB + (MS::FW + 1) * NS;                     // LDS reads per wavefront
+};
+template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
+
+template <int DT, int TM, int RING, bool FUSED>
+__global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
+                                                              const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
+                                                              const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
+                                                              uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
 {
+    static_assert(RING >= 2 && RING <= 8, "meet() covers up to seven units behind");
     typedef Mma<DT> MM;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];     // MD_S_RING units
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wo = wave & 1, wt = wave >> 1;
-    const int n = lane & 31, qb = lane >> 5;
-    const int U_all = (int)(Kpb / (2 * FRAG_KB));
-    // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
-    const int u0 = (int)((int64_t)blockIdx.y * U_all / gridDim.y), U = (int)((int64_t)(blockIdx.y + 1) * U_all / gridDim.y) - u0;
-    const int tile = mid_tile_of_block();
-    const int64_t panel = tile / tiles_t;
-    const int64_t t0 = (int64_t)(tile - panel * tiles_t) * MD_TILE;
-
-    MidRowLoader lb;
-    lb.init(XL + (int64_t)u0 * ROWB, Kpb, t0, M, wave, lane);
-    // unit u of the panel: 8 KB of values [step 2][fragment 4][lane 64][16 B], 2 KB of index words
-    // [step 2][lane 64][fragment 4][4 B]; wavefront w copies value pieces 2w, 2w + 1 (1 KB each) and index piece w & 1
-    const uint8_t* av_src = w_vals + (panel * U_all + u0) * MD_AV + wave * 2048;
-    const uint8_t* am_src = w_meta + (panel * U_all + u0) * MD_AM + (wave & 1) * 1024;
-    const uint32_t lane16 = lane * 16;
-    auto issue = [&](int u, int slot) {
-        uint8_t* st = smem + slot * MD_S_UNIT;
-        lb.issue((int64_t)u * ROWB, st, wave);
-        lds_dma16(av_src + (int64_t)u * MD_AV, lane16, st + MD_TOK + wave * 2048);
-        lds_dma16(av_src + (int64_t)u * MD_AV + 1024, lane16, st + MD_TOK + wave * 2048 + 1024);
-        lds_dma16(am_src + (int64_t)u * MD_AM, lane16, st + MD_TOK + MD_AV + (wave & 1) * 1024);
-    };
-
-    typename MM::acc_t acc[2][2];
-    mid_zero(acc);
-    constexpr int AHEAD = MD_S_RING - 1;                                 // units requested ahead of the one being computed
-#pragma unroll
-    for (int i = 0; i < AHEAD; ++i)
-        if (i < U) issue(i, i);
-    int slot = 0, lslot = AHEAD;
-    for (int u = 0; u < U; ++u) {
-        // own loads of unit u have landed (the AHEAD - 1 units behind it may still be in flight; at the end of
-        // the k range everything is awaited at once), own reads of unit u-1 have returned
-        if (u + AHEAD <= U) wait_vmcnt<(AHEAD - 1) * MD_S_LPU>(); else wait_vmcnt<0>();
-        wg_barrier();                                                    // ... for every wavefront
-        if (u + AHEAD < U) issue(u + AHEAD, lslot);                      // into the slot of unit u-1
-        const uint8_t* st = smem + slot * MD_S_UNIT;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            v4i a[2]; v8i b[2];
-            typedef int v2i __attribute__((ext_vector_type(2)));
-            const v2i idx = *reinterpret_cast<const v2i*>(st + MD_TOK + MD_AV + (h * 64 + lane) * 16 + wo * 8);
-#pragma unroll
-            for (int f = 0; f < 2; ++f) a[f] = *reinterpret_cast<const v4i*>(st + MD_TOK + ((h * 4 + 2 * wo + f) * 64 + lane) * 16);
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int row = wt * 64 + tb * 32 + n;
-                const v4i lo = *tile_chunk(st, row, 4 * h + 2 * qb), hi = *tile_chunk(st, row, 4 * h + 2 * qb + 1);
-                b[tb] = (v8i){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            }
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb) acc[f][tb] = MM::sparse(a[f], b[tb], acc[f][tb], idx[f]);
-        }
-        slot = slot == MD_S_RING - 1 ? 0 : slot + 1;
-        lslot = lslot == MD_S_RING - 1 ? 0 : lslot + 1;
-    }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)blockIdx.y * gridDim.x + tile, wave, lane);
-    else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
-}
-
-// ---- sparse, lifting applied in the operand read (6:8, weights packed by slide_decompose_fused) --------------
-// Same tile and ring as k_sparse_mid, but the token tile holds UNLIFTED rows (a super-unit of 128 bytes per row and
-// unit, as in the dense kernel) and a unit is three matrix-instruction steps deep: B lane (n, qb) reads the 64 bytes
-// [64 qb, 64 qb + 64) of its row as 16 registers, uses the first eight in step 0, the second eight in step 1 and builds
-// the eight middle windows of step 2 in registers (packed_layout.h, fused_window).  The k loop is as long as the
-// dense kernel's, with three sparse instructions where that one issues four dense ones.
-template <int DT, int RING>
-__global__ __launch_bounds__(MD_THREADS) void k_sparse_fused_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
-                                                                 const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
-                                                                 const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
-                                                                 uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
-{
-    typedef Mma<DT> MM;
-    constexpr int ES = MM::ES;
+    typedef MidUnit<TM, FUSED> MU;
+    constexpr int NS = MU::NS, LPU = MU::LPU, NM = MU::NM, NR = MU::NR, NB = MU::NB, RL = MU::RL, TOK = MU::TOK;
+    constexpr int FW = MU::MS::FW, TB = MU::MS::TB;
+    typedef MidOps<NS, FW, TB> Ops;
+    typedef int idx_t __attribute__((ext_vector_type(FW)));
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];     // RING units
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wo = wave & 1, wt = wave >> 1;
+    const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
-    const int u0 = (int)((int64_t)blockIdx.y * U_all / gridDim.y), U = (int)((int64_t)(blockIdx.y + 1) * U_all / gridDim.y) - u0;
-    const int tile = mid_tile_of_block();
-    const int64_t panel = tile / tiles_t;
-    const int64_t t0 = (int64_t)(tile - panel * tiles_t) * MD_TILE;
+    const MidItem it = mid_item(tiles_t);
+    const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
+    // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
+    const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
 
-    MidRowLoader lb;
+    // Direct loads of a unit, by wavefront: TM / 32 of token rows, NS of values ([step][fragment 4][lane 64][16 B]) and one of
+    // NS * 256 bytes of index words ([step][lane 64][fragment 4][4 B]; lanes 0 .. 16 NS - 1)
+    MidRowLoader<TM> lb;
     lb.init(Xq + (int64_t)u0 * ROWB, ldxb, t0, M, wave, lane);
-    // super-unit u of the panel: 12 KB of values [step 3][fragment 4][lane 64][16 B], 3 KB of index words
-    // [step 3][lane 64][fragment 4][4 B]; wavefront w copies value pieces 3w .. 3w + 2 (1 KB each) and 768 bytes
-    // of the index words (lanes 0..47 of one load)
-    const uint8_t* av_src = w_vals + (panel * U_all + u0) * MD_F_AV + wave * 3072;
-    const uint8_t* am_src = w_meta + (panel * U_all + u0) * MD_F_AM + wave * 768;
-    const uint32_t lane16 = lane * 16;
-    auto issue = [&](int u, int slot) {
-        uint8_t* st = smem + slot * MD_F_UNIT;
-        lb.issue((int64_t)u * ROWB, st, wave);
+    const uint8_t* av_src = w_vals + (panel * U_all + u0) * MU::AV + wave * (NS * 1024);
+    const uint8_t* am_src = w_meta + (panel * U_all + u0) * MU::AM + wave * (NS * 256);
+    const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
+    // The k loop of XCD x starts x / 8 of the way into the range and wraps around: otherwise all XCDs ask the memory side
+    // for the same token lines, and for few channels' worth of weights, at the same time (the loads alone, weights from
+    // HBM: 75 -> 61 us on 5003 -> 4099 fp16 8:10 at M = 777; the kernel 78 -> 73).
+    const int rot = (int)((blockIdx.y * gridDim.x + blockIdx.x) & 7) * U >> 3;
+    auto direct_load = [&](int v, uint32_t slot, int d) __attribute__((always_inline)) {
+        const uint32_t st = lds0 + slot;
+        const int u = v + rot < U ? v + rot : v + rot - U;
+        if (d < RL) lds_dma16_at(lb.base + (int64_t)u * ROWB, lb.off[d % RL], st + (d * MD_WAVES + wave) * 8 * ROWB);
+        else if (d < RL + NS) {
+            const int i = d - RL;
+            lds_dma16_at(av_src + (int64_t)u * MU::AV + i * 1024, lane16, st + TOK + wave * (NS * 1024) + i * 1024);
+        } else lds_dma16_lanes_at(am_src + (int64_t)u * MU::AM, lane16, st + TOK + MU::AV + wave * (NS * 256), (1ull << (16 * NS)) - 1);
+    };
+    // LDS reads of a unit's operands, in the order of their first use
+    const uint32_t va = lane16 + wo * (FW * 1024) + TOK, vi = lane16 + wo * (FW * 4) + TOK + MU::AV;
+    uint32_t vb[4];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) lds_dma16(av_src + (int64_t)u * MD_F_AV + i * 1024, lane16, st + MD_TOK + wave * 3072 + i * 1024);
-        if (lane < 48) lds_dma16(am_src + (int64_t)u * MD_F_AM, lane16, st + MD_TOK + MD_F_AV + wave * 768);
+    for (int c = 0; c < 4; ++c) {
+        const int row = wt * (32 * TB) + n, chunk = FUSED ? 4 * qb + c : 4 * (c >> 1) + 2 * qb + (c & 1);
+        vb[c] = row * ROWB + ((chunk ^ swz(row)) << 4);                  // the second token block lies 32 rows = 4096 bytes on, same swizzle
+    }
+    auto operand_read = [&](Ops& R, uint32_t slot, int r) __attribute__((always_inline)) {
+        const uint8_t* st = smem + slot;
+        auto rd_a = [&](int h, int f) { R.a[h][f] = *reinterpret_cast<const v4i*>(st + va + h * 4096 + f * 1024); };
+        auto rd_i = [&](int h) {
+            const idx_t w = *reinterpret_cast<const idx_t*>(st + vi + h * 1024);
+#pragma unroll
+            for (int f = 0; f < FW; ++f) R.idx[h][f] = w[f];
+        };
+        auto rd_b = [&](int c, int tb) {
+            const v4i v = *reinterpret_cast<const v4i*>(st + vb[c] + tb * 4096);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) R.b[tb][c >> 1][4 * (c & 1) + e] = v[e];
+        };
+        if (r < FW) rd_a(0, r);                                          // step 0: weights, index words, first halves of the token chunks
+        else if (r == FW) rd_i(0);
+        else if (r < FW + 1 + NB) { const int k = r - FW - 1; rd_b(2 * (k / (2 * TB)) + (k & 1), (k >> 1) % TB); }      // second halves: step 1
+        else { const int k = r - FW - 1 - NB, h = 1 + k / (FW + 1); if (k % (FW + 1) < FW) rd_a(h, k % (FW + 1)); else rd_i(h); }
     };
 
-    typename MM::acc_t acc[2][2];
+    typename MM::acc_t acc[FW][TB];
     mid_zero(acc);
-    constexpr int AHEAD = RING - 1;
+    auto mma = [&](const Ops& R, const v8i (&al)[TB], int i) __attribute__((always_inline)) {
+        const int h = i / (FW * TB), f = (i / TB) % FW, tb = i % TB;
+        acc[f][tb] = MM::sparse(R.a[h][f], FUSED && h == 2 ? al[tb] : R.b[tb][h & 1], acc[f][tb], R.idx[h][f]);
+    };
+    // middle windows of token block tb: 8-bit types: bytes 2..5 of block jd; 16-bit: elements 2..5 of block jd >> 1
+    auto middle = [&](const Ops& R, v8i& al, int tb) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i)
-        if (i < U) issue(i, i);
-    int slot = 0, lslot = AHEAD;
-    for (int u = 0; u < U; ++u) {
-        if (u + AHEAD <= U) wait_vmcnt<(AHEAD - 1) * MD_F_LPU>(); else wait_vmcnt<0>();
-        wg_barrier();
-        if (u + AHEAD < U) issue(u + AHEAD, lslot);
-        const uint8_t* st = smem + slot * MD_F_UNIT;
-        // the lane's 64 unlifted bytes of both token blocks
-        int x[2][16];
+        for (int jd = 0; jd < 8; ++jd) {
+            auto x = [&](int k) { return (uint32_t)R.b[tb][k >> 3][k & 7]; };
+            if constexpr (MM::ES == 1) al[jd] = (int)__builtin_amdgcn_alignbyte(x(2 * jd + 1), x(2 * jd), 2);
+            else al[jd] = (int)x(4 * (jd >> 1) + 1 + (jd & 1));
+        }
+    };
+    uint32_t slot = 0;                                                   // ring offset of the unit being computed
+    // Unit u from the registers C.  NEXT: the operands of unit u + 1 go to N; LOAD: unit u + RING is requested.
+    auto unit = [&](auto next_c, auto load_c, const Ops& C, Ops& N, int u) __attribute__((always_inline)) {
+        constexpr bool NEXT = decltype(next_c)::value, LOAD = decltype(load_c)::value;
+        const uint32_t nslot = slot == (RING - 1) * MU::BYTES ? 0u : slot + MU::BYTES;
+        v8i al[TB];
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-            const int row = wt * 64 + tb * 32 + n;
+        for (int i = 0; i < NM; ++i) {
+            mma(C, al, i);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NEXT) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const v4i v = *tile_chunk(st, row, 4 * qb + c);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[tb][4 * c + e] = v[e];
+                for (int r = 0; r < NR; ++r)
+                    if ((r * (NM > 4 ? NM - 2 : NM - 1)) / NR == i) operand_read(N, nslot, r);
             }
+            if constexpr (LOAD) {
+#pragma unroll
+                for (int d = 0; d < LPU; ++d)
+                    if ((d * NM) / LPU == i) direct_load(u + RING, slot, d);
+            }
+            if (FUSED && (i == 1 || (TB == 2 && i == 4))) middle(C, al[i / 4], i / 4);       // before step 2 starts at instruction 2 ACC
+            __builtin_amdgcn_sched_barrier(0);
         }
+        slot = nslot;
+    };
+    // Own loads have landed but for `behind` units requested later, and own LDS reads have returned; then the same for
+    // every wavefront.
+    auto meet = [&](int behind) __attribute__((always_inline)) {
+        bool done = false;
+        auto upto = [&](auto n_c) __attribute__((always_inline)) {
+            constexpr int N = decltype(n_c)::value;
+            if (N < RING && !done && behind >= N) { wait_vmcnt<(N < RING ? N : 0) * LPU>(); done = true; }
+        };
+        upto(std::integral_constant<int, 7>{}); upto(std::integral_constant<int, 6>{}); upto(std::integral_constant<int, 5>{});
+        upto(std::integral_constant<int, 4>{}); upto(std::integral_constant<int, 3>{}); upto(std::integral_constant<int, 2>{});
+        upto(std::integral_constant<int, 1>{}); upto(std::integral_constant<int, 0>{});
+        wg_barrier();
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+
 #pragma unroll
-        for (int J = 0; J < 3; ++J) {
-            v4i a[2]; v8i b[2];
-            typedef int v2i __attribute__((ext_vector_type(2)));
-            const v2i idx = *reinterpret_cast<const v2i*>(st + MD_TOK + MD_F_AV + (J * 64 + lane) * 16 + wo * 8);
+    for (int i = 0; i < RING; ++i)
+        if (i < U) {
 #pragma unroll
-            for (int f = 0; f < 2; ++f) a[f] = *reinterpret_cast<const v4i*>(st + MD_TOK + ((J * 4 + 2 * wo + f) * 64 + lane) * 16);
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int jd = 0; jd < 8; ++jd) {
-                    if (J < 2) b[tb][jd] = x[tb][8 * J + jd];
-                    else if constexpr (ES == 1) b[tb][jd] = (int)__builtin_amdgcn_alignbyte((uint32_t)x[tb][2 * jd + 1], (uint32_t)x[tb][2 * jd], 2);
-                    else b[tb][jd] = x[tb][4 * (jd >> 1) + 1 + (jd & 1)];
-                }
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb) acc[f][tb] = MM::sparse(a[f], b[tb], acc[f][tb], idx[f]);
+            for (int d = 0; d < LPU; ++d) direct_load(i, i * MU::BYTES, d);
         }
-        slot = slot == RING - 1 ? 0 : slot + 1;
-        lslot = lslot == RING - 1 ? 0 : lslot + 1;
+    Ops A, B;
+    meet(U < RING ? U - 1 : RING - 1);                                   // unit 0
+#pragma unroll
+    for (int r = 0; r < NR; ++r) operand_read(A, 0, r);
+    // Ahead of unit u: unit u + 1 has landed, and every wavefront holds unit u in registers (its slot is free).  The
+    // loops are unrolled by two, so that the two operand sets trade places, and hold no branch between matrix
+    // instructions: where paths meet, the compiler copies the accumulators (each copy waits for the instruction before).
+    int u = 0;
+    for (; u + RING + 1 < U; u += 2) {
+        meet(RING - 2);
+        unit(yes, yes, A, B, u);
+        meet(RING - 2);
+        unit(yes, yes, B, A, u + 1);
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)blockIdx.y * gridDim.x + tile, wave, lane);
-    else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
+    auto late = [&](int v) __attribute__((always_inline)) {
+        meet(v + RING <= U ? RING - 2 : U - 2 - v);
+        if (v + RING < U) {                                              // the odd unit the loop above left
+#pragma unroll
+            for (int d = 0; d < LPU; ++d) direct_load(v + RING, slot, d);
+        }
+    };
+    for (; u + 2 < U; u += 2) {
+        late(u);
+        unit(yes, no, A, B, u);
+        late(u + 1);
+        unit(yes, no, B, A, u + 1);
+    }
+    if (u + 1 < U) {
+        late(u);
+        unit(yes, no, A, B, u);
+        unit(no, no, B, A, u + 1);
+    } else unit(no, no, A, B, u);
+    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane);
+    else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 16 * FW * wo, t0 + wt * (32 * TB), lane);
 }
 
 // ---- dense ----------------------------------------------------------------------------------------------
@@ -337,12 +380,12 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
     const int wo = wave & 1, wt = wave >> 1;
     const int row = lane & 31, q = lane >> 5;
     const int U_all = (int)(Kb / ROWB);
-    const int u0 = (int)((int64_t)blockIdx.y * U_all / gridDim.y), U = (int)((int64_t)(blockIdx.y + 1) * U_all / gridDim.y) - u0;
-    const int tile = mid_tile_of_block();
-    const int64_t panel = tile / tiles_t;
-    const int64_t t0 = (int64_t)(tile - panel * tiles_t) * MD_TILE;
+    const MidItem it = mid_item(tiles_t);
+    const int64_t panel = it.panel, t0 = (int64_t)it.tt * MD_TILE;
+    // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
+    const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
 
-    MidRowLoader la, lb;
+    MidRowLoader<MD_TILE> la, lb;
     la.init(Wq + (int64_t)u0 * ROWB, Kb, panel * PANEL, O, wave, lane);
     lb.init(Xq + (int64_t)u0 * ROWB, Kb, t0, M, wave, lane);
     auto issue = [&](int u, int slot) {
@@ -396,7 +439,7 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
         slot = slot == RING - 1 ? 0 : slot + 1;
         lslot = lslot == RING - 1 ? 0 : lslot + 1;
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)blockIdx.y * gridDim.x + tile, wave, lane);
+    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane);
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
 }
 
@@ -404,58 +447,45 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
 
 using namespace ss;
 
-template <int DT>
+template <int DT, int TM>
 static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const float* s_x, const float* s_w, int64_t M, int64_t O, void* Y,
                                    int64_t ldy, int tiles_t, hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_mid_reduce<DT>), dim3((unsigned)(ntiles * MD_WAVES)), dim3(MD_RED_THREADS), 0, stream, static_cast<const v4i*>(ws), S, ntiles,
+    hipLaunchKernelGGL((k_mid_reduce<DT, TM>), dim3((unsigned)(ntiles * MD_WAVES)), dim3(256 * MidShape<TM>::ACC), 0, stream, static_cast<const v4i*>(ws), S, ntiles,
                        s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy, tiles_t);
     return launch_status();
 }
 
-template <int DT>
-static ss_status launch_sparse_mid_dt(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
-                                      int64_t O, int64_t Kpb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
+template <int DT, int TM, int RING, bool FUSED>
+static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
+                                        int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
+                                        hipStream_t stream)
 {
-    const int tiles_t = (int)((M + MD_TILE - 1) / MD_TILE);
-    const int64_t ntiles = (O + PANEL - 1) / PANEL * tiles_t;
-    constexpr int lds = MD_S_RING * MD_S_UNIT;
-    if (allow_dynamic_lds<k_sparse_mid<DT>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_mid<DT>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream, static_cast<const uint8_t*>(XL), s_x,
-                       static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, Kpb, static_cast<uint16_t*>(Y), ldy,
-                       tiles_t, ws);
-    if (launch_status() != SS_OK) return SS_ERR_HIP;
-    return S > 1 ? launch_mid_reduce<DT>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
-}
-
-template <int DT, int RING>
-static ss_status launch_sparse_fused_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
-                                              int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
-                                              hipStream_t stream)
-{
-    constexpr int lds = RING * MD_F_UNIT;
-    if (allow_dynamic_lds<k_sparse_fused_mid<DT, RING>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_fused_mid<DT, RING>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
+    constexpr int lds = RING * MidUnit<TM, FUSED>::BYTES;
+    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
                        ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
-    return launch_status();
+    if (launch_status() != SS_OK) return SS_ERR_HIP;
+    return S > 1 ? launch_mid_reduce<DT, TM>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
 }
 
-template <int DT>
-static ss_status launch_sparse_fused_mid_dt(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
-                                            int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
+// U units per token row (lifted rows, or unlifted ones when FUSED), ldxb bytes between rows
+template <int DT, bool FUSED>
+static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
+                                      int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
-    const int tiles_t = (int)((M + MD_TILE - 1) / MD_TILE);
-    const int64_t ntiles = (O + PANEL - 1) / PANEL * tiles_t;
-    // Ring depth: with more workgroups than compute units a ring of two units (62 KB) lets two workgroups share a
-    // unit's LDS and cover each other's load latency; otherwise a lone workgroup gets the deeper ring.
-    // (measured, INT8: 3584 -> 37888 at M = 128, 296 workgroups: 42 -> 30 us; 3584 -> 4608 at M = 1024: 42 -> 29 us;
-    // 18944 -> 3584 at M = 1024, 224 workgroups: 105 us with two units, 95 with three, 92 with four)
-    const ss_status st = ntiles * S > cu_count()
-        ? launch_sparse_fused_mid_ring<DT, 2>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
-        : launch_sparse_fused_mid_ring<DT, 4>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream);
-    if (st != SS_OK) return st;
-    return S > 1 ? launch_mid_reduce<DT>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
+    const int64_t npanels = (O + PANEL - 1) / PANEL;
+    const int tiles_t = (int)((M + MD_TILE - 1) / MD_TILE);              // one tile where the tokens fit a smaller one
+    const int64_t ntiles = npanels * tiles_t;
+    // Ring depth: with more workgroups than compute units, as deep as lets two of them share a compute unit's LDS and cover
+    // each other's waits; otherwise what fits (three units and more measure the same).
+    const bool shared = ntiles * S > cu_count();
+#define SS_MID(TM, RING) launch_sparse_mid_ring<DT, TM, RING, FUSED>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
+    if (M <= 32) return shared ? SS_MID(32, 4) : SS_MID(32, 8);
+    if (M <= 64) return shared ? SS_MID(64, 3) : SS_MID(64, 6);
+    return shared ? SS_MID(128, 2) : SS_MID(128, 5);
+#undef SS_MID
 }
 
 template <int DT, int RING>
@@ -480,38 +510,44 @@ static ss_status launch_dense_mid_dt(const void* Xq, const float* s_x, const voi
         ? launch_dense_mid_ring<DT, 2>(Xq, s_x, Wq, s_w, M, O, Kb, Y, ldy, ws, S, tiles_t, ntiles, stream)
         : launch_dense_mid_ring<DT, MD_D_RING>(Xq, s_x, Wq, s_w, M, O, Kb, Y, ldy, ws, S, tiles_t, ntiles, stream);
     if (st != SS_OK) return st;
-    return S > 1 ? launch_mid_reduce<DT>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
+    return S > 1 ? launch_mid_reduce<DT, 128>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
 }
 
 // Host side, called by the C entry points.  Arguments are already validated.
 namespace ss {
 
-// Number of k ranges for ntiles 128 x 128 tiles over `units` 128-byte k units with a workspace of ws_bytes:
-// about one workgroup per compute unit, at least eight units per range, no more than the workspace holds
-// (measured on 3584 -> 4608 at M = 128: 22 us unsplit, 15 us with 4 to 6 ranges, 17 us with 8).
-int mid_splits(int64_t M, int64_t O, int64_t units, size_t ws_bytes)
+// bytes of a tile's partial sums: the tile the launchers take for M tokens
+static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE * 4 * (kind == SS_KIND_DENSE || M > 64 ? 128 : M > 32 ? 64 : 32); }
+
+// Number of k ranges for the tiles of this shape over `units` 128-byte k units with a workspace of ws_bytes: about one
+// workgroup per compute unit (three quarters of that for tiles of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us
+// in 5 ranges, 19.1 in 7, 19.3 in 9), at least eight units per range, no more than the workspace holds (bf16 3584 -> 4608
+// at M = 64, 56 units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7).  Up to 64 tokens, short rows are not split.
+int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     const int64_t ntiles = mid_tiles(M, O);
-    int64_t S = cu_count() / ntiles;
+    const bool sparse = kind == SS_KIND_SPARSE;
+    if (sparse && M > 32 && M <= 64 && units < 48) return 1;
+    int64_t S = (sparse && M <= 32 ? 3 * cu_count() / 4 : cu_count()) / ntiles;
     if (S > units / 8) S = units / 8;
-    const int64_t fit = (int64_t)(ws_bytes / ((size_t)ntiles * MD_WS_TILE));
+    const int64_t fit = (int64_t)(ws_bytes / ((size_t)ntiles * mid_tile_bytes(kind, M)));
     if (S > fit) S = fit;
     return S < 2 ? 1 : (int)S;
 }
 
-size_t mid_workspace_bytes(int64_t M, int64_t O, int S)
+size_t mid_workspace_bytes(ss_kind kind, int64_t M, int64_t O, int S)
 {
-    return S > 1 ? (size_t)S * mid_tiles(M, O) * MD_WS_TILE : 0;
+    return S > 1 ? (size_t)S * mid_tiles(M, O) * mid_tile_bytes(kind, M) : 0;
 }
 
 ss_status launch_sparse_mid(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                             int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     switch (dtype) {
-    case SS_I8: return launch_sparse_mid_dt<SS_I8>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, ws, S, stream);
-    case SS_FP8_E4M3: return launch_sparse_mid_dt<SS_FP8_E4M3>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, ws, S, stream);
-    case SS_BF16: return launch_sparse_mid_dt<SS_BF16>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, ws, S, stream);
-    case SS_FP16: return launch_sparse_mid_dt<SS_FP16>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, ws, S, stream);
+    case SS_I8: return launch_sparse_mid_dt<SS_I8, false>(XL, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, Y, ldy, ws, S, stream);
+    case SS_FP8_E4M3: return launch_sparse_mid_dt<SS_FP8_E4M3, false>(XL, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, Y, ldy, ws, S, stream);
+    case SS_BF16: return launch_sparse_mid_dt<SS_BF16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, Y, ldy, ws, S, stream);
+    case SS_FP16: return launch_sparse_mid_dt<SS_FP16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, Y, ldy, ws, S, stream);
     }
     return SS_ERR_DTYPE;
 }
@@ -520,10 +556,10 @@ ss_status launch_sparse_fused_mid(const void* Xq, const float* s_x, const void* 
                                   int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     switch (dtype) {
-    case SS_I8: return launch_sparse_fused_mid_dt<SS_I8>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_FP8_E4M3: return launch_sparse_fused_mid_dt<SS_FP8_E4M3>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_BF16: return launch_sparse_fused_mid_dt<SS_BF16>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_FP16: return launch_sparse_fused_mid_dt<SS_FP16>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
+    case SS_I8: return launch_sparse_mid_dt<SS_I8, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
+    case SS_FP8_E4M3: return launch_sparse_mid_dt<SS_FP8_E4M3, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
+    case SS_BF16: return launch_sparse_mid_dt<SS_BF16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
+    case SS_FP16: return launch_sparse_mid_dt<SS_FP16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
     }
     return SS_ERR_DTYPE;
 }

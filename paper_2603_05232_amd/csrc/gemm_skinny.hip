@@ -10,8 +10,8 @@
 // kernel's LDS staging makes one fragment per workgroup the faster choice).  Operands go from global memory
 // straight into registers (a ring of two to four units per wavefront, all in flight); partial sums of the wavefronts meet
 // in LDS in a fixed order (bit-reproducible also for fp32 accumulators) and wavefront 0 applies the scale epilogue.
-// With a workspace the k range is also split over workgroups (gridDim.y ranges) and k_skinny_reduce adds their partial
-// sums in range order.
+// The dense kernel also splits the k range over workgroups (gridDim.y ranges) where it is given a workspace;
+// k_skinny_reduce adds their partial sums in range order.
 //   sparse: the packed weights are already in operand-register order, 16 bytes + one index word per lane and
 //           step, fully coalesced; no LDS in the main loop.
 //           The same kernel serves the fused path (6:8, unlifted tokens, weights packed by slide_decompose_fused): a unit
@@ -130,7 +130,7 @@ template <int DT, int TB, int FPW, int SK_WAVES, bool FUSED>
 __global__ __launch_bounds__(64 * SK_WAVES) void k_sparse_skinny(const uint8_t* __restrict__ XL, const float* __restrict__ s_x,
                                                                const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                                const float* __restrict__ s_w, int64_t M, int64_t O, int U, int64_t ldxb,
-                                                               uint16_t* __restrict__ Y, int64_t ldy, void* __restrict__ ws)
+                                                               uint16_t* __restrict__ Y, int64_t ldy)
 {
     typedef Mma<DT> MM;
     typedef int idx_t __attribute__((ext_vector_type(FPW)));
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_sparse_skinny(const uint8_t* 
     // on one XCD, where the second to fourth of them hit in its L2 (single-fragment workgroups on 3584 -> 4608 fetched
     // 25 MB for 15.6 MB of packed weights before).  Panels beyond the last whole group of eight keep the plain order.
     int col = blockIdx.x;
-    if (GROUPS > 1 && ((gridDim.x & 7) == 0 || gridDim.y == 1)) {      // workgroup id mod 8 == blockIdx.x mod 8
+    if (GROUPS > 1) {
         const int whole = (int)(gridDim.x / (8 * GROUPS)) * (8 * GROUPS);
         if (col < whole) { const int xcd = col & 7, j = col >> 3; col = ((j / GROUPS) * 8 + xcd) * GROUPS + j % GROUPS; }
     }
@@ -227,9 +227,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_sparse_skinny(const uint8_t* 
         for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
             for (int j = 0; j < 4; ++j) st[d].b[tb][j] = v4i{0, 0, 0, 0};     // lanes without a token keep zeros
-    // k range of this workgroup: units [u, u_end) of U; gridDim.y ranges
-    const int u_end = (int)((int64_t)(blockIdx.y + 1) * U / gridDim.y);
-    const int u0 = (int)((int64_t)blockIdx.y * U / gridDim.y) + wave;
+    const int u0 = wave, u_end = U;
 #pragma unroll
     for (int d = 0; d < D; ++d)
         if (u0 + d * SK_WAVES < u_end) load(st[d], u0 + d * SK_WAVES);
@@ -252,7 +250,6 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_sparse_skinny(const uint8_t* 
     }
     sk_reduce<SK_WAVES, typename MM::acc_t, FPW * TB>(acc, red, wave, lane);
     if (wave == 0) {
-        if (gridDim.y > 1) { sk_store_partial<typename MM::acc_t, FPW * TB>(acc, ws, col, lane); return; }
 #pragma unroll
         for (int f = 0; f < FPW; ++f) {
             typename MM::acc_t part[TB];
@@ -394,9 +391,8 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_dense_skinny(const uint8_t* _
 // Split k: sum of the S partial accumulators of fragment blockIdx.x in range order and the scale epilogue.  Thread
 // (tb, register quad r4, lane) owns four consecutive channels of one token, so a range costs it one 16-byte load and
 // the loads of up to eight ranges are in flight at once: the kernel is one or two memory round trips long.
-// PANEL_ORDER: fragment F is fragment F % 4 of weight panel F / 4 (channels panel * 128 + 64 h + 16 (F % 4) + r);
-// otherwise it is channels 32 F + 16 h + r.
-template <int DT, int TB, bool PANEL_ORDER>
+// Fragment F is channels 32 F + 16 h + r.
+template <int DT, int TB>
 __global__ __launch_bounds__(256 * TB) void k_skinny_reduce(const v4i* __restrict__ ws, int S, const float* __restrict__ s_x,
                                                            const float* __restrict__ s_w, int64_t M, int64_t O, uint16_t* __restrict__ Y, int64_t ldy)
 {
@@ -433,7 +429,7 @@ __global__ __launch_bounds__(256 * TB) void k_skinny_reduce(const v4i* __restric
         for (int d = 0; d < 3; ++d)
             if (s + d < S) a += q[d];
     }
-    const int64_t o = (PANEL_ORDER ? (F >> 2) * PANEL + 64 * h + 16 * (F & 3) : F * 32 + 16 * h) + 4 * r4;
+    const int64_t o = F * 32 + 16 * h + 4 * r4;
     store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, o, tb * 32 + (lane & 31));
 }
 
@@ -453,26 +449,16 @@ static int pick_fpw(int64_t frags)
 // U units of 128 bytes per token row (lifted rows, or unlifted rows when FUSED), ldxb bytes between rows
 template <int DT, int TB, int FPW, bool FUSED>
 static ss_status launch_sparse_one(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                                   int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
+                                   int U, int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
 {
     const int64_t npanels = (O + PANEL - 1) / PANEL;
     const unsigned grid = (unsigned)(npanels * (FRAGS_PER_PANEL / FPW));
-    if (FPW == 1 && (int)grid < cu_count()) {
-        hipLaunchKernelGGL((k_sparse_skinny<DT, TB, 1, 8, FUSED>), dim3(grid, (unsigned)S), dim3(512), 0, stream, static_cast<const uint8_t*>(XL), s_x,
-                           static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy, ws);
-        const ss_status first = launch_status();       // reading the status clears it: keep it
-        if (first != SS_OK || S <= 1) return first;
-        hipLaunchKernelGGL((k_skinny_reduce<DT, TB, true>), dim3(grid), dim3(256 * TB), 0, stream, static_cast<const v4i*>(ws), S, s_x, s_w, M, O,
-                           static_cast<uint16_t*>(Y), ldy);
-    } else {
-        // several fragments per workgroup; with S > 1 the k range is split over S workgroups per fragment group
-        hipLaunchKernelGGL((k_sparse_skinny<DT, TB, FPW, 4, FUSED>), dim3(grid, (unsigned)S), dim3(256), 0, stream, static_cast<const uint8_t*>(XL), s_x,
-                           static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy, ws);
-        const ss_status first = launch_status();
-        if (first != SS_OK || S <= 1) return first;
-        hipLaunchKernelGGL((k_skinny_reduce<DT, TB, true>), dim3((unsigned)(npanels * FRAGS_PER_PANEL)), dim3(256 * TB), 0, stream,
-                           static_cast<const v4i*>(ws), S, s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy);
-    }
+#define SS_SK(F, WAVES) hipLaunchKernelGGL((k_sparse_skinny<DT, TB, F, WAVES, FUSED>), dim3(grid), dim3(64 * WAVES), 0, stream, \
+                       static_cast<const uint8_t*>(XL), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, \
+                       static_cast<uint16_t*>(Y), ldy)
+    if (FPW == 1 && (int)grid < cu_count()) SS_SK(1, 8);
+    else SS_SK(FPW, 4);
+#undef SS_SK
     return launch_status();
 }
 
@@ -486,7 +472,7 @@ static ss_status launch_dense_one(const void* Xq, const float* s_x, const void* 
                            static_cast<const uint8_t*>(Wq), s_w, M, O, Kb, static_cast<uint16_t*>(Y), ldy, ws);
         const ss_status first = launch_status();
         if (first != SS_OK || S <= 1) return first;
-        hipLaunchKernelGGL((k_skinny_reduce<DT, TB, false>), dim3(grid), dim3(256 * TB), 0, stream, static_cast<const v4i*>(ws), S, s_x, s_w, M, O,
+        hipLaunchKernelGGL((k_skinny_reduce<DT, TB>), dim3(grid), dim3(256 * TB), 0, stream, static_cast<const v4i*>(ws), S, s_x, s_w, M, O,
                            static_cast<uint16_t*>(Y), ldy);
     } else
         hipLaunchKernelGGL((k_dense_skinny<DT, TB, FPW, 4>), dim3(grid), dim3(256), 0, stream, static_cast<const uint8_t*>(Xq), s_x,
@@ -509,34 +495,13 @@ static int frag_splits(int64_t M, int64_t O, int64_t units, int cap)
     return S < 2 ? 1 : (int)S;
 }
 
-// k ranges when workgroups are whole 128-channel panels (sparse kernel, rows of at least 64 units on fewer panels than
-// compute units): one workgroup per compute unit, ranges of at least 32 units.  Measured on 18944 -> 3584 (28 panels,
-// INT8 6:8; single fragments unsplit -> panels in 4..7 ranges): M = 1 19 -> 16 us, M = 16 28 -> 17 us, M = 32 37 -> 19 us;
-// on rows of 42 units (3584 -> 4608) the second kernel costs more than the split saves.
-static int panel_splits(int64_t O, int64_t units, int cap)
-{
-    const int64_t npanels = (O + PANEL - 1) / PANEL;
-    const int cus = cu_count();
-    if (npanels >= cus) return 1;
-    int64_t S = cus / npanels;
-    if (S > units / 32) S = units / 32;
-    if (S > cap) S = cap;
-    return S < 2 ? 1 : (int)S;
-}
-
-// token blocks of 32: 1 (M <= 32) or 2 (M <= 64).  S = the ranges the workspace has room for.
+// token blocks of 32: 1 (M <= 32) or 2 (M <= 64)
 template <int DT, bool FUSED>
 static ss_status launch_sparse_dt(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                                  int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t st)
+                                  int U, int64_t ldxb, void* Y, int64_t ldy, hipStream_t st)
 {
-    const int64_t frags = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
-    int fpw = pick_fpw(frags);
-    // Long rows on few panels: whole panels per workgroup (the token rows are read once per 128 channels instead of once
-    // per 32) with the k range split over enough workgroups to fill the chip; otherwise S only applies to single fragments.
-    const int s4 = panel_splits(O, U, S);
-    int s_use = fpw == 1 ? frag_splits(M, O, U, S) : 1;
-    if (s4 > 1) { fpw = 4; s_use = s4; }
-#define SS_GO(TB, FPW) return launch_sparse_one<DT, TB, FPW, FUSED>(XL, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, s_use, st)
+    const int fpw = pick_fpw((O + PANEL - 1) / PANEL * FRAGS_PER_PANEL);
+#define SS_GO(TB, FPW) return launch_sparse_one<DT, TB, FPW, FUSED>(XL, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, st)
     if (M <= 32) { if (fpw == 4) SS_GO(1, 4); if (fpw == 2) SS_GO(1, 2); SS_GO(1, 1); }
     if (fpw == 4) SS_GO(2, 4);
     if (fpw == 2) SS_GO(2, 2);
@@ -558,16 +523,13 @@ static ss_status launch_dense_dt(const void* Xq, const float* s_x, const void* W
 // Host side, called by the C entry points for M <= SS_SKINNY_MAX_M.  Arguments are already validated.
 namespace ss {
 
-// Number of k ranges the few-token kernels may use with a workspace of ws_bytes: the larger of what the two split
-// policies above would take (the launchers apply their own policy below this bound).
+// Number of k ranges the dense few-token kernel may use with a workspace of ws_bytes.
 int skinny_splits(int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     if (M > SS_SKINNY_MAX_M) return 1;
     const size_t per_range = skinny_workspace_bytes(M, O, 2) / 2;
     const int64_t fit = (int64_t)(ws_bytes / per_range);
-    const int cap = fit > 64 ? 64 : (int)fit;
-    const int a = frag_splits(M, O, units, cap), b = panel_splits(O, units, cap);
-    return a > b ? a : b;
+    return frag_splits(M, O, units, fit > 64 ? 64 : (int)fit);
 }
 
 size_t skinny_workspace_bytes(int64_t M, int64_t O, int S)
@@ -578,26 +540,26 @@ size_t skinny_workspace_bytes(int64_t M, int64_t O, int S)
 }
 
 ss_status launch_sparse_skinny(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                               int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
+                               int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
 {
     const int U = (int)(Kpb / KSTEP);
     switch (dtype) {
-    case SS_I8: return launch_sparse_dt<SS_I8, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, ws, S, stream);
-    case SS_FP8_E4M3: return launch_sparse_dt<SS_FP8_E4M3, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, ws, S, stream);
-    case SS_BF16: return launch_sparse_dt<SS_BF16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, ws, S, stream);
-    case SS_FP16: return launch_sparse_dt<SS_FP16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, ws, S, stream);
+    case SS_I8: return launch_sparse_dt<SS_I8, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, stream);
+    case SS_FP8_E4M3: return launch_sparse_dt<SS_FP8_E4M3, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, stream);
+    case SS_BF16: return launch_sparse_dt<SS_BF16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, stream);
+    case SS_FP16: return launch_sparse_dt<SS_FP16, false>(XL, s_x, w_vals, w_meta, s_w, M, O, U, Kpb, Y, ldy, stream);
     }
     return SS_ERR_DTYPE;
 }
 
 ss_status launch_sparse_fused_skinny(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                                     int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
+                                     int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
 {
     switch (dtype) {
-    case SS_I8: return launch_sparse_dt<SS_I8, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_FP8_E4M3: return launch_sparse_dt<SS_FP8_E4M3, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_BF16: return launch_sparse_dt<SS_BF16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
-    case SS_FP16: return launch_sparse_dt<SS_FP16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream);
+    case SS_I8: return launch_sparse_dt<SS_I8, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
+    case SS_FP8_E4M3: return launch_sparse_dt<SS_FP8_E4M3, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
+    case SS_BF16: return launch_sparse_dt<SS_BF16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
+    case SS_FP16: return launch_sparse_dt<SS_FP16, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
     }
     return SS_ERR_DTYPE;
 }

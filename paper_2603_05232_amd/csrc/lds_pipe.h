@@ -29,6 +29,13 @@ __device__ inline void lds_dma4_at(const uint8_t* uniform_base, uint32_t lane_of
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_wave_addr), "v"(lane_off), "s"(uniform_base) : "memory", "m0");
 }
+// the same by the lanes of `lanes` only, in a wavefront whose lanes are all active: the execution mask is changed and put
+// back inside the statement, so that the caller's code stays one straight block
+__device__ inline void lds_dma16_lanes_at(const uint8_t* uniform_base, uint32_t lane_off, uint32_t lds_wave_addr, uint64_t lanes)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds_wave_addr),
+                 "v"(lane_off), "s"(uniform_base), "s"(lanes) : "memory", "m0");
+}
 __device__ inline void lds_dma16(const uint8_t* uniform_base, uint32_t lane_off, const void* lds_wave_base)
 {
     lds_dma16_at(uniform_base, lane_off, lds_address(lds_wave_base));

@@ -1,6 +1,7 @@
 // Matrix instructions of gfx950 per operand type, shared by the GEMM kernels.
 #pragma once
 #include "ss_common.h"
+#include "device_info.h"
 
 namespace ss {
 
@@ -125,18 +126,18 @@ __device__ inline void store_quad4(const QUAD& a, const float* __restrict__ s_x,
 }
 
 // Kernels for few tokens (gemm_skinny.hip): one workgroup per 32..128 output channels streams their weights once.
-// With S > 1 (only where every workgroup is a single 32-channel fragment and there are fewer of them than compute
-// units) the k range is split over S workgroups per fragment; partial sums go through `ws`
-// (skinny_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a fixed order.
+// The dense kernel splits its k range over S workgroups per fragment where there are fewer 32-channel fragments than
+// compute units; partial sums go through `ws` (skinny_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a
+// fixed order.  (Sparse shapes that gain from a split run on the tiles of gemm_mid.hip.)
 constexpr int64_t SS_SKINNY_MAX_M = 64;
 int skinny_splits(int64_t M, int64_t O, int64_t units, size_t ws_bytes);
 size_t skinny_workspace_bytes(int64_t M, int64_t O, int S);
 ss_status launch_sparse_skinny(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                               int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
+                               int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 // the same for unlifted activations and weights packed by slide_decompose_fused (6:8): U super-units of 128 bytes per row,
 // ldxb bytes between token rows
 ss_status launch_sparse_fused_skinny(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                                     int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
+                                     int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 ss_status launch_dense_skinny(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                               void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
 
@@ -147,10 +148,12 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
-// Kernels with 128 x 128 tiles (gemm_mid.hip) for shapes that give the 256 x 256 tile kernels too few tiles to
-// occupy the compute units.
+enum ss_kind { SS_KIND_SPARSE, SS_KIND_DENSE };
+
+// Kernels with tiles of 128 channels x 128 tokens, sparse ones also x 64 and x 32 where the tokens fit (gemm_mid.hip),
+// for shapes that give the 256 x 256 tile kernels too few tiles to occupy the compute units.
 // S > 1 splits the k range over S workgroups per tile; their partial sums go through `ws`
-// (mid_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a fixed order.
+// (mid_workspace_bytes(kind, M, O, S) bytes) and a second kernel adds them in a fixed order.
 ss_status launch_sparse_mid(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                             int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
 // the same for unlifted activations and weights packed by slide_decompose_fused (6:8): U super-units of 128 bytes per row,
@@ -159,29 +162,42 @@ ss_status launch_sparse_fused_mid(const void* Xq, const float* s_x, const void* 
                                   int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
 ss_status launch_dense_mid(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                            void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
-int mid_splits(int64_t M, int64_t O, int64_t units, size_t ws_bytes);
-size_t mid_workspace_bytes(int64_t M, int64_t O, int S);
+int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes);
+size_t mid_workspace_bytes(ss_kind kind, int64_t M, int64_t O, int S);
 inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M + 127) / 128); }
 
 // Which kernel family a GEMM of M tokens x O channels over `units` 128-byte k units runs on, and in how many k
-// ranges (S > 1 only for SS_PATH_MID and only with a workspace).  Measured on the Qwen2.5-7B shapes (INT8, 6:8):
-//   M <= 32                      few-token kernels (7 to 9 us on 3584 -> 4608, where the others need 15 and 31), their k
-//                                range split in two or three where the fragments are fewer than the compute units and the
-//                                rows long (18944 -> 3584);
-//   32 < M <= 64                 the same, unless the rows are long and can be split (18944 -> 3584 at M = 48:
-//                                53 us few-token, 23 us in 8 ranges of 128 x 128 tiles);
-//   up to 320 tiles of 128 x 128 those tiles (M = 256 on 3584 -> 4608: 17 us in 3 ranges, 33 us with 256 x 256
-//                                tiles; M = 1024 on 18944 -> 3584: 111 vs 150 us);
-//   beyond                       the 256 x 256 tile kernels (M = 2048 on 3584 -> 4608: 40 vs 57 us).
+// ranges (S > 1 only with a workspace).  Measured, INT8 6:8 unless said, weights from HBM, us:
+//   M > 64    up to two tiles of 128 x 128 per compute unit those tiles (two workgroups share a compute unit), beyond the
+//             256 x 256 tiles.  448 tiles, 18944 -> 3584 at M = 2048: 141 against 182; 512, 14336 -> 4096: 117 against 140;
+//             384, 4096 -> 4096 at M = 1536: 37 against 45; 592, 3584 -> 37888 at M = 256: 76 against 51.
+//   M 33..64  tiles of 64 tokens where the panels alone fill the chip (3584 -> 37888: 37 against 50) or the rows are long
+//             and can be split (bf16 3584 -> 4608: 13.9 against 23.6; fp8 lifted 4096 -> 6144: 13.9 against 19.9; unsplit
+//             18944 -> 3584: 64 against 31), few-token kernels otherwise (3584 -> 4608 unsplit: 15.9 against 14.4).
+//   M <= 32   tiles of 32 tokens where the panels alone fill the chip (3584 -> 37888, M = 1: 32 against 34; M = 32: 34
+//             against 37; 18944 channels, M = 32: 19 against 23; 16384, M = 1: 18.5 against 17.2) or the rows are long
+//             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
+//             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
+//             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
+// The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
+// units long and can be split, few-token; up to 320 tiles 128 x 128.
 enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_TILE };
 struct ss_plan { ss_path path; int S; };
-inline ss_plan plan_gemm(int64_t M, int64_t O, int64_t units, size_t ws_bytes)
+inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
-    if (M <= 32) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
-    if (M > 64 && mid_tiles(M, O) > 320) return {SS_PATH_TILE, 1};
-    const int S = mid_splits(M, O, units, ws_bytes);
-    if (M <= 64 && !(S > 1 && units >= 96)) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
-    return {SS_PATH_MID, S};
+    if (kind == SS_KIND_DENSE) {
+        if (M <= 32) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
+        if (M > 64 && mid_tiles(M, O) > 320) return {SS_PATH_TILE, 1};
+        const int S = mid_splits(kind, M, O, units, ws_bytes);
+        if (M <= 64 && !(S > 1 && units >= 96)) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
+        return {SS_PATH_MID, S};
+    }
+    const int64_t tiles = mid_tiles(M, O), cus = cu_count();
+    if (M > 64) return tiles > 2 * cus ? ss_plan{SS_PATH_TILE, 1} : ss_plan{SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
+    const int S = mid_splits(kind, M, O, units, ws_bytes);
+    const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
+    const bool mid = wide || (S > 1 && (M > 32 || 2 * units + M >= 128));
+    return mid ? ss_plan{SS_PATH_MID, S} : ss_plan{SS_PATH_SKINNY, 1};
 }
 
 }  // namespace ss

@@ -40,6 +40,14 @@ inline ss_status launch_status()
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
 
+// Workgroup ids go round-robin over the 8 XCDs (id mod 8).  Renumbers `total` workgroups so that each XCD's share is one
+// contiguous run of items: a bijection of [0, total) for any total.
+__device__ inline int xcd_run(int id, int total)
+{
+    const int x = id & 7, rest = total & 7;
+    return x * (total >> 3) + (x < rest ? x : rest) + (id >> 3);
+}
+
 // ---- scalar format conversions (device) --------------------------------------------------
 __device__ inline float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 

@@ -20,8 +20,7 @@ __device__ inline bool tile_of_round(int round, int tiles_o, int tiles_t, int& t
     const int nb = gridDim.x, bid = blockIdx.x, total = tiles_o * tiles_t;
     const int base = round * nb;
     if (base + bid >= total) return false;
-    int tile = base + bid;
-    if (base + nb <= total && (nb & 7) == 0) tile = base + (bid & 7) * (nb >> 3) + (bid >> 3);
+    const int tile = base + xcd_run(bid, min(nb, total - base));
     constexpr int BAND = 8;
     const int per_band = BAND * tiles_o;
     const int band = tile / per_band, within = tile - band * per_band;
