@@ -537,6 +537,16 @@ extern "C" ss_status dense_gemm(const void* Xq, const float* s_x, const void* Wq
     return dense_gemm_ws(Xq, s_x, Wq, s_w, M, O, K, dtype, Y, ldy, nullptr, 0, stream);
 }
 
+// channels [0, tile_o) on 256 x 256 tiles, the others on 128 x 128 tiles (tile_o is a multiple of both or all of O)
+static ss_status sparse_tile_and_rest(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                                      int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, int64_t tile_o, hipStream_t stream)
+{
+    const ss_status st = launch_sparse_tile(XL, s_x, w_vals, w_meta, s_w, M, tile_o, Kpb, dtype, Y, ldy, stream);
+    if (st != SS_OK || tile_o == O) return st;
+    return launch_sparse_mid(XL, s_x, static_cast<const uint8_t*>(w_vals) + tile_o * (Kpb / 2), static_cast<const uint8_t*>(w_meta) + tile_o * (Kpb / 8),
+                             s_w ? s_w + tile_o : s_w, M, O - tile_o, Kpb, dtype, static_cast<uint16_t*>(Y) + tile_o, ldy, nullptr, 1, stream);
+}
+
 extern "C" ss_status slide_sparse_gemm_ws(const void* X_lifted, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w,
                                           int64_t M, int64_t O, int64_t K_lifted, ss_dtype dtype, void* Y, int64_t ldy, void* workspace,
                                           size_t workspace_bytes, void* stream)
@@ -551,7 +561,7 @@ extern "C" ss_status slide_sparse_gemm_ws(const void* X_lifted, const float* s_x
     const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, Kpb / KSTEP, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, workspace, p.S, hs);
-    return launch_sparse_tile(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
+    return sparse_tile_and_rest(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, p.tile_o, hs);
 }
 
 extern "C" ss_status slide_sparse_gemm(const void* X_lifted, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w,
@@ -600,7 +610,7 @@ extern "C" ss_status slide_sparse_gemm_static(const void* X_lifted, const float*
     const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, Kpb / KSTEP, SS_STATIC_SCRATCH_BYTES);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, ws, p.S, hs);
-    return launch_sparse_tile(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
+    return sparse_tile_and_rest(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, p.tile_o, hs);
 }
 
 extern "C" const char* ss_status_string(ss_status s)

@@ -385,15 +385,20 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, U, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_fused_mid(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
-#define SS_F(DT) launch_fused<DT, 4>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, hs)
+    // channels [0, p.tile_o) on 256 x 256 tiles, the others on 128 x 128 tiles
+    ss_status st = SS_ERR_DTYPE;
+#define SS_F(DT) launch_fused<DT, 4>(Xq, s_x, w_vals, w_meta, s_w, M, p.tile_o, U, ldxb, Y, ldy, hs)
     switch (dtype) {
-    case SS_I8: return SS_F(SS_I8);
-    case SS_FP8_E4M3: return SS_F(SS_FP8_E4M3);
-    case SS_BF16: return SS_F(SS_BF16);
-    case SS_FP16: return SS_F(SS_FP16);
+    case SS_I8: st = SS_F(SS_I8); break;
+    case SS_FP8_E4M3: st = SS_F(SS_FP8_E4M3); break;
+    case SS_BF16: st = SS_F(SS_BF16); break;
+    case SS_FP16: st = SS_F(SS_FP16); break;
     }
 #undef SS_F
-    return SS_ERR_DTYPE;
+    if (st != SS_OK || p.tile_o == O) return st;
+    const int64_t row = (int64_t)U * 3 * FRAG_KB;        // lifted bytes of a weight row
+    return launch_sparse_fused_mid(Xq, s_x, static_cast<const uint8_t*>(w_vals) + p.tile_o * (row / 2), static_cast<const uint8_t*>(w_meta) + p.tile_o * (row / 8),
+                                   s_w ? s_w + p.tile_o : s_w, M, O - p.tile_o, U, ldxb, dtype, static_cast<uint16_t*>(Y) + p.tile_o, ldy, nullptr, 1, hs);
 }
 
 extern "C" ss_status slide_sparse_gemm_fused(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,

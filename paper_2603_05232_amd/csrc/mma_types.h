@@ -182,18 +182,29 @@ inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M 
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
 enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_TILE };
-struct ss_plan { ss_path path; int S; };
+struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 tiles
+// The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
+// full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
+// unit, the rest goes to those (M = 8192, 3584 -> 4608, 2.25 rounds: bf16 210 -> 194 us, INT8 120 -> 116).  With two of them per
+// compute unit (half a round) the two sides are level or worse: half a round runs at a higher clock (INT8 3584 -> 37888, 18.5
+// rounds: 797 against 835 us; 4096 -> 6144 at M = 4096: 97 against 102).
+inline int64_t tile_channels(int64_t M, int64_t O, int64_t cus)
+{
+    const int64_t tiles_o = (O + 255) / 256, tiles_t = (M + 255) / 256, rounds = tiles_o * tiles_t / cus, c = rounds * cus / tiles_t;
+    return c > 0 && c < tiles_o && mid_tiles(M, O - c * 256) <= cus ? c * 256 : O;
+}
 inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     if (kind == SS_KIND_DENSE) {
         if (M <= 32) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
-        if (M > 64 && mid_tiles(M, O) > 320) return {SS_PATH_TILE, 1};
+        if (M > 64 && mid_tiles(M, O) > 320) return {SS_PATH_TILE, 1, O};
         const int S = mid_splits(kind, M, O, units, ws_bytes);
         if (M <= 64 && !(S > 1 && units >= 96)) return {SS_PATH_SKINNY, skinny_splits(M, O, units, ws_bytes)};
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
-    if (M > 64) return tiles > 2 * cus ? ss_plan{SS_PATH_TILE, 1} : ss_plan{SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
+    if (M > 64 && tiles > 2 * cus) return {SS_PATH_TILE, 1, tile_channels(M, O, cus)};
+    if (M > 64) return {SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
     const int S = mid_splits(kind, M, O, units, ws_bytes);
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
     const bool mid = wide || (S > 1 && (M > 32 || 2 * units + M >= 128));

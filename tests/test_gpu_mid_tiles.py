@@ -67,3 +67,11 @@ def test_token_tiles_and_split_ranges(dtype, M, O, units, N, fused):
     if not fused:
         K = K * N // (2 * (N - 1)) - 3
     _linear(M, O, K, N, dtype, fused, True, M)
+
+
+# one round of 256 x 256 tiles and a small rest of the channels on 128 x 128 tiles (256 compute units: 13056 + 500 channels)
+@pytest.mark.parametrize("dtype,N,fused", [("i8", 4, True), ("bf16", 4, True), ("i8", 3, False), ("fp16", 5, False)])
+def test_rest_of_a_round(dtype, N, fused):
+    es = 1 if dtype == "i8" else 2
+    K = 3 * 128 // es
+    _linear(1100, 13556, K if fused else K * N // (2 * (N - 1)) - 3, N, dtype, fused, False, N)
