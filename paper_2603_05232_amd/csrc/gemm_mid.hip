@@ -479,12 +479,14 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     const int tiles_t = (int)((M + MD_TILE - 1) / MD_TILE);              // one tile where the tokens fit a smaller one
     const int64_t ntiles = npanels * tiles_t;
     // Ring depth: with more workgroups than compute units, as deep as lets two of them share a compute unit's LDS and cover
-    // each other's waits; otherwise what fits (three units and more measure the same).
+    // each other's waits.  A workgroup alone: the whole ring is requested at once, so that a deeper one delays the first
+    // unit (3584 -> 4608 at M = 256, 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
+    // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9; bf16 18944 -> 3584 at M = 16: 32.1 with eight, 34.8 with four).
     const bool shared = ntiles * S > cu_count();
 #define SS_MID(TM, RING) launch_sparse_mid_ring<DT, TM, RING, FUSED>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
     if (M <= 32) return shared ? SS_MID(32, 4) : SS_MID(32, 8);
-    if (M <= 64) return shared ? SS_MID(64, 3) : SS_MID(64, 6);
-    return shared ? SS_MID(128, 2) : SS_MID(128, 5);
+    if (M <= 64) return shared ? SS_MID(64, 3) : SS_MID(64, 4);
+    return shared ? SS_MID(128, 2) : SS_MID(128, (FUSED ? 3 : 4));
 #undef SS_MID
 }
 
