@@ -16,7 +16,7 @@ namespace ss {
 // flight at once either way, but fewer registers leave room for more tokens per compute unit.
 template <typename TIN, int OUT, int MAXV, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restrict__ X, int64_t ldx, int K, int N,
-                                                                uint8_t* __restrict__ XL, float* __restrict__ s_x, int Kp, int Kz)
+                                                                uint8_t* __restrict__ XL, float* __restrict__ s_x, int Kp, int Kz, uint32_t inv_nw1)
 {
     // Kp: stored width of a lifted row (whole 128-byte units); Kz >= n_g * 2N + 8 / ES: elements
     // of the quantised row held in LDS, those at and beyond K being zero (zero-completed last block)
@@ -73,8 +73,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
 #pragma unroll
                     for (int k = 0; k < OW; ++k) {
                         if constexpr (ES == 1)
-                            w[k] = quant1<OUT>(f[4 * k], r) | (quant1<OUT>(f[4 * k + 1], r) << 8) | (quant1<OUT>(f[4 * k + 2], r) << 16) |
-                                   (quant1<OUT>(f[4 * k + 3], r) << 24);
+                            w[k] = quant4<OUT>(f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3], r);
                         else
                             w[k] = quant1<OUT>(f[2 * k], r) | (quant1<OUT>(f[2 * k + 1], r) << 16);
                     }
@@ -98,11 +97,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
                 float f[IV::N]; IV::unpack(v[i], f);
                 if constexpr (ES == 1) {
 #pragma unroll
-                    for (int w = 0; w < IV::N / 4; ++w) {
-                        uint32_t p = quant1<OUT>(f[4 * w], r) | (quant1<OUT>(f[4 * w + 1], r) << 8) |
-                                     (quant1<OUT>(f[4 * w + 2], r) << 16) | (quant1<OUT>(f[4 * w + 3], r) << 24);
-                        lds[idx * (IV::N / 4) + w] = p;
-                    }
+                    for (int w = 0; w < IV::N / 4; ++w) lds[idx * (IV::N / 4) + w] = quant4<OUT>(f[4 * w], f[4 * w + 1], f[4 * w + 2], f[4 * w + 3], r);
                 } else {
 #pragma unroll
                     for (int w = 0; w < IV::N / 2; ++w)
@@ -131,12 +126,14 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     // ---- pass 2b: output-oriented gather of the lifted windows (window j reads b = 2N g + 2 l);
     // windows at and beyond n_w = n_g (N-1) are the zero padding of the last 128-byte unit
     const int nw1 = N - 1;
+    // j / nw1 by its reciprocal ceil(2^32 / nw1): exact for j < 2^32 / nw1 (j < 2^16 here)
+    auto block_of = [&](int j) { return nw1 == 1 ? j : (int)__umulhi((uint32_t)j, inv_nw1); };
     const int nwin = Kp / 4;
     const int ng = (K + 2 * N - 1) / (2 * N);
     uint4* out = reinterpret_cast<uint4*>(XL + m * (int64_t)Kp * ES);
     if constexpr (ES == 1) {
         for (int c = t; c < nwin / 4; c += THREADS) {
-            int j = 4 * c, g = j / nw1, l = j - g * nw1;
+            int j = 4 * c, g = block_of(j), l = j - g * nw1;
             uint32_t w[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -153,7 +150,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     } else {
         // 16-bit elements: a window is 8 bytes = elements b..b+3, b even -> two aligned dwords
         for (int c = t; c < nwin / 2; c += THREADS) {
-            int j = 2 * c, g = j / nw1, l = j - g * nw1;
+            int j = 2 * c, g = block_of(j), l = j - g * nw1;
             uint32_t w[4];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -184,9 +181,10 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const bool vec_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
     const int64_t nvec = K / IV::N;                           // 16-byte vectors per row
     dim3 grid((unsigned)M);
+    const uint32_t inv = N > 2 ? (uint32_t)(((1ull << 32) + N - 2) / (N - 1)) : 0u;
     const TIN* x = static_cast<const TIN*>(X);
     uint8_t* xl = static_cast<uint8_t*>(XL);
-#define SS_LQ(MAXV, T) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T>), grid, dim3(T), lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz)
+#define SS_LQ(MAXV, T) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T>), grid, dim3(T), lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
     if (vec_ok && nvec <= 4 * 256) SS_LQ(4, 256);
     else if (vec_ok && nvec <= 4 * 512) SS_LQ(4, 512);
     else if (vec_ok && nvec <= 5 * 1024) SS_LQ(5, 1024);

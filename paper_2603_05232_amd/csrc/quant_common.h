@@ -55,15 +55,28 @@ template <int OUT> __device__ inline uint32_t quant1(float x, float r)
 // The same codes with fewer instructions, for kernels where the conversion counts: only the low byte (OUT < 2) or half
 // of the result is meaningful.  INT8: adding 1.5 * 2^23 to the clamped product rounds it to nearest even and leaves its
 // two's complement in the low mantissa bits (clamping before or after the rounding is the same, 127 being an integer).
+// FP8: the conversion instruction (e4m3fn, nearest even) agrees with f32_to_e4m3 on every float of [-448, 448].
 template <int OUT> __device__ inline uint32_t quant_bits(float x, float r)
 {
     if constexpr (OUT == 0) return __float_as_uint(fminf(fmaxf(x * r, -127.0f), 127.0f) + 12582912.0f);
+    else if constexpr (OUT == 1) return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(fmaxf(x * r, -448.0f), 448.0f), 0.0f, 0, false);
     else return quant1<OUT>(x, r);
 }
 // the low bytes of four words
 __device__ inline uint32_t pack_bytes(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3)
 {
     return __builtin_amdgcn_perm(b1, b0, 0x0C0C0400u) | __builtin_amdgcn_perm(b3, b2, 0x04000C0Cu);
+}
+
+// four codes in a word (8-bit types)
+// (rates: bf16 in, fp8 out, 2048 x 4096 without lifting 10.9 -> 7.6 us, 2048 x 14336 28.2 -> 19.5)
+template <int OUT> __device__ inline uint32_t quant4(float x0, float x1, float x2, float x3, float r)
+{
+    if constexpr (OUT == 1) {
+        auto c = [r](float x) { return fminf(fmaxf(x * r, -448.0f), 448.0f); };
+        const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(c(x0), c(x1), 0, false);
+        return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c(x2), c(x3), lo, true);
+    } else return pack_bytes(quant_bits<OUT>(x0, r), quant_bits<OUT>(x1, r), quant_bits<OUT>(x2, r), quant_bits<OUT>(x3, r));
 }
 
 }  // namespace ss
