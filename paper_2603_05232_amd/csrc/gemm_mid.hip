@@ -144,18 +144,28 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
     store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, panel * PANEL + 16 * MS::FW * wo + 64 * (lane >> 5) + 16 * f + 4 * r4, t0 + wt * (32 * TB) + tb * 32 + (lane & 31));
 }
 
-// Work item of this workgroup: a tile of a k range.  Workgroup ids go round-robin over the 8 XCDs, so item numbers are
-// dealt out in one contiguous run per XCD, whatever their count; items are numbered range by range, a range in bands of
-// 8 token tiles, a band panel by panel.  The workgroups of an XCD then read few k ranges, few weight panels and few token
-// tiles, and share them in its L2.
+// Work item of this workgroup: a tile of a k range.  Workgroup ids go round-robin over the 8 XCDs, and what the workgroups
+// of an XCD share (weight panels, token tiles) is read into its L2 once, so tiles are dealt out in one contiguous run per
+// XCD, panel by panel in bands of token tiles.  Bands are of equal width, at most 8: a narrow last band gives one XCD few
+// token tiles of many panels, and the launch waits for it (bf16 lifted 4096 -> 4096 at M = 1280, bands of 8 and 2: 76 us, 5
+// and 5: 69; M = 1152, INT8: 42 and 38).
+// Split k: by_range false deals out a run of tiles in every range, so that the workgroups of an XCD stand in all ranges of
+// their tiles; true one run over all (range, tile) pairs, which keeps an XCD in one range or two.  The second loses where the
+// rows of those few columns meet in the same memory channels (4096 -> 4096 INT8 lifted at M = 256 in 4 ranges: 20.8 against
+// 17.3 us; the dense kernel, 8192 -> 2048 at M = 192 in 8: 21.3 against 17.5) and gains where a run of tiles reads more
+// token bytes than an XCD's L2 holds (18944 -> 3584 fused INT8 at M = 256 in 4 ranges: 29 against 35).  Over 1182 calls
+// (five operand forms, 12 layers, M = 192 .. 640, three cards) the line that loses least lies at about 19 units of k per
+// compute unit, MD_BY_RANGE tiles x units.
+constexpr int64_t MD_BY_RANGE = 19 * 256;
 struct MidItem { int64_t panel; int tt, range; int64_t tile; };
-__device__ inline MidItem mid_item(int tiles_t)
+__device__ inline MidItem mid_item(int tiles_t, bool by_range)
 {
-    const int nt = gridDim.x, total = nt * gridDim.y, id = blockIdx.y * nt + blockIdx.x;
-    const int item = xcd_run(id, total);
+    const int nt = gridDim.x;
+    const int item = by_range ? xcd_run(blockIdx.y * nt + blockIdx.x, nt * gridDim.y) : blockIdx.y * nt + xcd_run(blockIdx.x, nt);
     const int range = item / nt, k = item - range * nt;
-    const int per_band = 8 * (nt / tiles_t), band = k / per_band, within = k - band * per_band;
-    const int bw = min(8, tiles_t - band * 8), panel = within / bw, tt = band * 8 + (within - panel * bw);
+    const int bands = (tiles_t + 7) / 8, width = (tiles_t + bands - 1) / bands;
+    const int per_band = width * (nt / tiles_t), band = k / per_band, within = k - band * per_band;
+    const int bw = min(width, tiles_t - band * width), panel = within / bw, tt = band * width + (within - panel * bw);
     return {panel, tt, range, (int64_t)panel * tiles_t + tt};
 }
 
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
-    const MidItem it = mid_item(tiles_t);
+    const MidItem it = mid_item(tiles_t, tiles_t == 1 || (int64_t)gridDim.x * U_all > MD_BY_RANGE);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
     const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
@@ -230,8 +240,12 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
     // The k loop of XCD x starts x / 8 of the way into the range and wraps around: otherwise all XCDs ask the memory side
     // for the same token lines, and for few channels' worth of weights, at the same time (the loads alone, weights from
-    // HBM: 75 -> 61 us on 5003 -> 4099 fp16 8:10 at M = 777; the kernel 78 -> 73).
-    const int rot = (int)((blockIdx.y * gridDim.x + blockIdx.x) & 7) * U >> 3;
+    // HBM: 75 -> 61 us on 5003 -> 4099 fp16 8:10 at M = 777; the kernel 78 -> 73).  In a split range of one token tile, where an
+    // XCD's workgroups share nothing but the token rows of a range, so do the workgroups of an XCD: in step they all ask
+    // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 5 % less time; unsplit or with several token
+    // tiles, where they share weights or more rows than the L2 holds, up to 60 % more).
+    const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int rot = (tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3;
     auto direct_load = [&](int v, uint32_t slot, int d) __attribute__((always_inline)) {
         const uint32_t st = lds0 + slot;
         const int u = v + rot < U ? v + rot : v + rot - U;
@@ -380,7 +394,7 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
     const int wo = wave & 1, wt = wave >> 1;
     const int row = lane & 31, q = lane >> 5;
     const int U_all = (int)(Kb / ROWB);
-    const MidItem it = mid_item(tiles_t);
+    const MidItem it = mid_item(tiles_t, false);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * MD_TILE;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
     const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
