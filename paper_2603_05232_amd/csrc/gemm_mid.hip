@@ -535,10 +535,17 @@ namespace ss {
 // bytes of a tile's partial sums: the tile the launchers take for M tokens
 static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE * 4 * (kind == SS_KIND_DENSE || M > 64 ? 128 : M > 32 ? 64 : 32); }
 
-// Number of k ranges for the tiles of this shape over `units` 128-byte k units with a workspace of ws_bytes: about one
-// workgroup per compute unit (three quarters of that for tiles of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us
-// in 5 ranges, 19.1 in 7, 19.3 in 9), at least eight units per range, no more than the workspace holds (bf16 3584 -> 4608
-// at M = 64, 56 units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7).  Up to 64 tokens, short rows are not split.
+// Number of k ranges for the tiles of this shape over `units` 128-byte k units with a workspace of ws_bytes: at most one
+// workgroup per compute unit, at least eight units per range, no more than the workspace holds.
+// Dense kernel: as many as that allows.  Sparse, M <= 64: the same (three quarters of a workgroup per compute unit for tiles
+// of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us in 5 ranges, 19.1 in 7, 19.3 in 9; bf16 3584 -> 4608 at M = 64, 56
+// units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7), but short rows are not split at 33..64 tokens.
+// Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 2 + a
+// 14th of the tiles x ranges written and read back.  The unsplit kernel is fast enough that a few ranges more than that cost
+// more than they save: 3584 -> 4608 at M = 256 (28 units, 72 tiles) 15.9 us unsplit, 19.1 in 3 ranges; 4096 -> 4096 lifted at
+// M = 256 (48 units, 64 tiles) 16.3 unsplit, 16.5 in 3, 17.3 in 4; 18944 -> 3584 at M = 256 (148 units, 56 tiles) 54 unsplit, 28.7 in 4.
+// Over 2080 calls (five operand forms, 13 layers, M = 65 .. 640, weights hot and from HBM, two cards) the choice lies 2.3 % above
+// the best S, as many ranges as fit 4.4 %.
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     const int64_t ntiles = mid_tiles(M, O);
@@ -548,7 +555,14 @@ int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_byte
     if (S > units / 8) S = units / 8;
     const int64_t fit = (int64_t)(ws_bytes / ((size_t)ntiles * mid_tile_bytes(kind, M)));
     if (S > fit) S = fit;
-    return S < 2 ? 1 : (int)S;
+    if (S < 2) return 1;
+    if (!sparse || M <= 64) return (int)S;
+    int64_t best = 1, least = 14 * units;                               // 14ths of a unit
+    for (int64_t s = 2; s <= S; ++s) {
+        const int64_t t = 14 * ((units + s - 1) / s + 2) + s * ntiles;
+        if (t < least) { least = t; best = s; }
+    }
+    return (int)best;
 }
 
 size_t mid_workspace_bytes(ss_kind kind, int64_t M, int64_t O, int S)
