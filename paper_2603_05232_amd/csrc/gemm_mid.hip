@@ -152,11 +152,16 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
 // Split k: by_range false deals out a run of tiles in every range, so that the workgroups of an XCD stand in all ranges of
 // their tiles; true one run over all (range, tile) pairs, which keeps an XCD in one range or two.  The second loses where the
 // rows of those few columns meet in the same memory channels (4096 -> 4096 INT8 lifted at M = 256 in 4 ranges: 20.8 against
-// 17.3 us; the dense kernel, 8192 -> 2048 at M = 192 in 8: 21.3 against 17.5) and gains where a run of tiles reads more
-// token bytes than an XCD's L2 holds (18944 -> 3584 fused INT8 at M = 256 in 4 ranges: 29 against 35).  Over 1182 calls
-// (five operand forms, 12 layers, M = 192 .. 640, three cards) the line that loses least lies at about 19 units of k per
-// compute unit, MD_BY_RANGE tiles x units.
-constexpr int64_t MD_BY_RANGE = 19 * 256;
+// 17.3 us; the dense kernel, 8192 -> 2048 at M = 192 in 8: 21.3 against 17.5) and gains where the loop is long and a run of
+// tiles reads more token bytes than an XCD's L2 holds (18944 -> 3584 fused INT8 at M = 256 in 4 ranges: 29 against 35).
+// The lines are those that lose least over 1646 calls (five operand forms, 12 layers, M = 65 .. 640, two and three cards): 19
+// units of k per compute unit, 10 with one token tile, or 4.5 MB of tokens (12288 -> 1536 bf16 at M = 256, hot: 19.7 against 23.9).
+// Tiles of 64 and 32 tokens, where the weights are nearly all that is read, take the second throughout.  The dense kernel
+// takes the first: by the same lines 60 of 504 calls were more than 3 % slower than with the first, 21 so.
+__device__ inline bool mid_by_range(int tile_tokens, int64_t M, int tiles_t, int units)
+{
+    return tile_tokens < MD_TILE || (int64_t)gridDim.x * units > (tiles_t == 1 ? 10 : 19) * 256 || M * units > (36 << 10);
+}
 struct MidItem { int64_t panel; int tt, range; int64_t tile; };
 __device__ inline MidItem mid_item(int tiles_t, bool by_range)
 {
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
-    const MidItem it = mid_item(tiles_t, tiles_t == 1 || (int64_t)gridDim.x * U_all > MD_BY_RANGE);
+    const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all));
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
     const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
