@@ -508,8 +508,8 @@ extern "C" size_t slide_gemm_workspace_bytes(int64_t M, int64_t O, int64_t K, ss
 {
     if (!valid_dtype(dtype) || M <= 0 || O <= 0 || K <= 0 || (K * elem_size(dtype)) % KSTEP != 0) return 0;
     const int64_t units = K * elem_size(dtype) / KSTEP;
-    size_t need = 0;                                  // one size for both GEMMs of the shape
-    for (ss_kind kind : {SS_KIND_SPARSE, SS_KIND_DENSE}) {
+    size_t need = 0;                                  // one size for all GEMMs of the shape
+    for (ss_kind kind : {SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE}) {
         const ss_plan p = plan_gemm(kind, M, O, units, (size_t)-1);
         const size_t n = p.path == SS_PATH_MID ? mid_workspace_bytes(kind, M, O, p.S) : p.path == SS_PATH_SKINNY ? skinny_workspace_bytes(M, O, p.S) : 0;
         need = n > need ? n : need;
@@ -558,7 +558,7 @@ extern "C" ss_status slide_sparse_gemm_ws(const void* X_lifted, const float* s_x
     if ((uintptr_t)w_meta & 15) return SS_ERR_SHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int64_t Kpb = K_lifted * elem_size(dtype);
-    const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, Kpb / KSTEP, workspace_bytes);
+    const ss_plan p = plan_gemm(SS_KIND_LIFTED, M, O, Kpb / KSTEP, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, workspace, p.S, hs);
     return sparse_tile_and_rest(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, p.tile_o, hs);
@@ -607,7 +607,7 @@ extern "C" ss_status slide_sparse_gemm_static(const void* X_lifted, const float*
     if (st != SS_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int64_t Kpb = K_lifted * elem_size(dtype);
-    const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, Kpb / KSTEP, SS_STATIC_SCRATCH_BYTES);
+    const ss_plan p = plan_gemm(SS_KIND_LIFTED, M, O, Kpb / KSTEP, SS_STATIC_SCRATCH_BYTES);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, ws, p.S, hs);
     return sparse_tile_and_rest(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, p.tile_o, hs);

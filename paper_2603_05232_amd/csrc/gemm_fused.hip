@@ -8,7 +8,7 @@
 // 16 registers; the first eight are the B operand of step 0 as they are (windows l = 0 and l = 2 of four blocks are
 // the blocks' two halves), the second eight of step 1, and step 2 takes the eight middle windows (l = 1), each built
 // with one v_alignbyte (8-bit types) or two register copies (16-bit types).  slide_decompose_fused packs the weights
-// in the matching window order (fused_window in packed_layout.h).
+// in the matching window order (fused order of packed_layout.h).
 //
 // Tile engine.  Persistent workgroups, 256 channels x 256 tokens per tile, 2 x WT wavefronts of 128 channels x
 // (256 / WT) tokens = 4 x NBF accumulator blocks of the 32x32 instruction.  WT = 4 (eight wavefronts, two per SIMD) is
@@ -382,7 +382,7 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     const int U = (int)(K * es / KSTEP);
     const int64_t ldxb = ldx * es;
     // kernel family by shape, as for the other two GEMMs; the k loop counts super-units of 128 unlifted bytes
-    const ss_plan p = plan_gemm(SS_KIND_SPARSE, M, O, U, workspace_bytes);
+    const ss_plan p = plan_gemm(SS_KIND_FUSED, M, O, U, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_fused_mid(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
     // channels [0, p.tile_o) on 256 x 256 tiles, the others on 128 x 128 tiles

@@ -146,7 +146,7 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
 
 // Work item of this workgroup: a tile of a k range.  Workgroup ids go round-robin over the 8 XCDs, and what the workgroups
 // of an XCD share (weight panels, token tiles) is read into its L2 once, so tiles are dealt out in one contiguous run per
-// XCD, panel by panel in bands of token tiles.  Bands are of equal width, at most 8: a narrow last band gives one XCD few
+// XCD, panel by panel in bands of token tiles.  Bands are of equal width, at most `widest`: a narrow last band gives one XCD few
 // token tiles of many panels, and the launch waits for it (bf16 lifted 4096 -> 4096 at M = 1280, bands of 8 and 2: 76 us, 5
 // and 5: 69; M = 1152, INT8: 42 and 38).
 // Split k: by_range false deals out a run of tiles in every range, so that the workgroups of an XCD stand in all ranges of
@@ -163,12 +163,12 @@ __device__ inline bool mid_by_range(int tile_tokens, int64_t M, int tiles_t, int
     return tile_tokens < MD_TILE || (int64_t)gridDim.x * units > (tiles_t == 1 ? 10 : 19) * 256 || M * units > (36 << 10);
 }
 struct MidItem { int64_t panel; int tt, range; int64_t tile; };
-__device__ inline MidItem mid_item(int tiles_t, bool by_range)
+__device__ inline MidItem mid_item(int tiles_t, bool by_range, int widest = 8)
 {
     const int nt = gridDim.x;
     const int item = by_range ? xcd_run(blockIdx.y * nt + blockIdx.x, nt * gridDim.y) : blockIdx.y * nt + xcd_run(blockIdx.x, nt);
     const int range = item / nt, k = item - range * nt;
-    const int bands = (tiles_t + 7) / 8, width = (tiles_t + bands - 1) / bands;
+    const int bands = (tiles_t + widest - 1) / widest, width = (tiles_t + bands - 1) / bands;
     const int per_band = width * (nt / tiles_t), band = k / per_band, within = k - band * per_band;
     const int bw = min(width, tiles_t - band * width), panel = within / bw, tt = band * width + (within - panel * bw);
     return {panel, tt, range, (int64_t)panel * tiles_t + tt};
@@ -189,7 +189,7 @@ template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&ac
 // deep; B lane (n, qb) takes the 32 bytes [32 qb, 32 qb + 32) of each 64-byte step.  FUSED (6:8, weights packed by
 // slide_decompose_fused): a piece of an unlifted row, a super-unit of three steps; B lane (n, qb) takes the 64 bytes
 // [64 qb, 64 qb + 64), uses the first half in step 0, the second in step 1 and builds the eight middle windows of step 2
-// in registers (packed_layout.h, fused_window): the k loop is as long as the dense kernel's, with three sparse
+// in registers (packed_layout.h, fused order): the k loop is as long as the dense kernel's, with three sparse
 // instructions where that one issues four dense ones.
 //
 // A workgroup is one wavefront per SIMD, and a wavefront issues in order, so nothing overlaps by itself: requesting a
@@ -200,6 +200,11 @@ template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&ac
 // load path (a build with the loads alone takes 61 of the 73 us of 5003 -> 4099 fp16 8:10 at M = 777, one with everything
 // else 48).  Loop by loop against one that left the overlap to the compiler: that shape 81 -> 73 us, 14336 -> 4096 fp8 at
 // M = 1024 87 -> 73.
+// Without PIPE the overlap is left to a second workgroup on the compute unit and to the compiler, every XCD starts at unit 0
+// and bands are wider.  With lifted rows and up to a quarter more tiles than compute units, where most compute units hold one
+// workgroup and the launch waits for those with two, that is the faster loop (lifted INT8 / bf16 against the pipeline, weights
+// from HBM: 4096 -> 4096 at M = 1152, 288 tiles, 35 against 38 us / 59 against 68; 4096 -> 6144 at M = 768 35 against 37 / 58 against 64);
+// with more tiles than that, or unlifted rows, the pipeline is (384 tiles, 4096 -> 4096 at M = 1536: 39 against 45 us; fused 288: 33 against 35).
 template <int TM, bool FUSED> struct MidUnit {
     typedef MidShape<TM> MS;
     static constexpr int NS = FUSED ? 3 : 2;                              // steps
@@ -214,7 +219,7 @@ template <int TM, bool FUSED> struct MidUnit {
 };
 template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
 
-template <int DT, int TM, int RING, bool FUSED>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE>
 __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
@@ -231,7 +236,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
-    const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all));
+    const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all), PIPE ? 8 : 16);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
     const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
@@ -250,7 +255,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 5 % less time; unsplit or with several token
     // tiles, where they share weights or more rows than the L2 holds, up to 60 % more).
     const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int rot = (tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3;
+    const int rot = PIPE ? (tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
     auto direct_load = [&](int v, uint32_t slot, int d) __attribute__((always_inline)) {
         const uint32_t st = lds0 + slot;
         const int u = v + rot < U ? v + rot : v + rot - U;
@@ -343,44 +348,74 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
 
+    if constexpr (!PIPE) {                                               // RING - 1 units in flight, the rest is the compiler's
+        uint32_t lslot = (RING - 1) * MU::BYTES;
 #pragma unroll
-    for (int i = 0; i < RING; ++i)
-        if (i < U) {
+        for (int i = 0; i < RING - 1; ++i)
+            if (i < U) {
 #pragma unroll
-            for (int d = 0; d < LPU; ++d) direct_load(i, i * MU::BYTES, d);
+                for (int d = 0; d < LPU; ++d) direct_load(i, i * MU::BYTES, d);
+            }
+        for (int u = 0; u < U; ++u) {
+            if (u + RING - 1 <= U) wait_vmcnt<(RING - 2) * LPU>(); else wait_vmcnt<0>();
+            wg_barrier();                                                // unit u has landed, unit u - 1 is read
+            if (u + RING - 1 < U) {
+#pragma unroll
+                for (int d = 0; d < LPU; ++d) direct_load(u + RING - 1, lslot, d);
+            }
+            Ops R;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) operand_read(R, slot, r);
+            v8i al[TB];
+            if constexpr (FUSED) {
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) middle(R, al[tb], tb);
+            }
+#pragma unroll
+            for (int i = 0; i < NM; ++i) mma(R, al, i);
+            slot = slot == (RING - 1) * MU::BYTES ? 0u : slot + MU::BYTES;
+            lslot = lslot == (RING - 1) * MU::BYTES ? 0u : lslot + MU::BYTES;
         }
-    Ops A, B;
-    meet(U < RING ? U - 1 : RING - 1);                                   // unit 0
+    } else {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) operand_read(A, 0, r);
-    // Ahead of unit u: unit u + 1 has landed, and every wavefront holds unit u in registers (its slot is free).  The
-    // loops are unrolled by two, so that the two operand sets trade places, and hold no branch between matrix
-    // instructions: where paths meet, the compiler copies the accumulators (each copy waits for the instruction before).
-    int u = 0;
-    for (; u + RING + 1 < U; u += 2) {
-        meet(RING - 2);
-        unit(yes, yes, A, B, u);
-        meet(RING - 2);
-        unit(yes, yes, B, A, u + 1);
-    }
-    auto late = [&](int v) __attribute__((always_inline)) {
-        meet(v + RING <= U ? RING - 2 : U - 2 - v);
-        if (v + RING < U) {                                              // the odd unit the loop above left
+        for (int i = 0; i < RING; ++i)
+            if (i < U) {
 #pragma unroll
-            for (int d = 0; d < LPU; ++d) direct_load(v + RING, slot, d);
+                for (int d = 0; d < LPU; ++d) direct_load(i, i * MU::BYTES, d);
+            }
+        Ops A, B;
+        meet(U < RING ? U - 1 : RING - 1);                                   // unit 0
+#pragma unroll
+        for (int r = 0; r < NR; ++r) operand_read(A, 0, r);
+        // Ahead of unit u: unit u + 1 has landed, and every wavefront holds unit u in registers (its slot is free).  The
+        // loops are unrolled by two, so that the two operand sets trade places, and hold no branch between matrix
+        // instructions: where paths meet, the compiler copies the accumulators (each copy waits for the instruction before).
+        int u = 0;
+        for (; u + RING + 1 < U; u += 2) {
+            meet(RING - 2);
+            unit(yes, yes, A, B, u);
+            meet(RING - 2);
+            unit(yes, yes, B, A, u + 1);
         }
-    };
-    for (; u + 2 < U; u += 2) {
-        late(u);
-        unit(yes, no, A, B, u);
-        late(u + 1);
-        unit(yes, no, B, A, u + 1);
+        auto late = [&](int v) __attribute__((always_inline)) {
+            meet(v + RING <= U ? RING - 2 : U - 2 - v);
+            if (v + RING < U) {                                              // the odd unit the loop above left
+#pragma unroll
+                for (int d = 0; d < LPU; ++d) direct_load(v + RING, slot, d);
+            }
+        };
+        for (; u + 2 < U; u += 2) {
+            late(u);
+            unit(yes, no, A, B, u);
+            late(u + 1);
+            unit(yes, no, B, A, u + 1);
+        }
+        if (u + 1 < U) {
+            late(u);
+            unit(yes, no, A, B, u);
+            unit(no, no, B, A, u + 1);
+        } else unit(no, no, A, B, u);
     }
-    if (u + 1 < U) {
-        late(u);
-        unit(yes, no, A, B, u);
-        unit(no, no, B, A, u + 1);
-    } else unit(no, no, A, B, u);
     if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane);
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 16 * FW * wo, t0 + wt * (32 * TB), lane);
 }
@@ -475,14 +510,14 @@ static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const 
     return launch_status();
 }
 
-template <int DT, int TM, int RING, bool FUSED>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE = true>
 static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
                                         int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
                                         hipStream_t stream)
 {
     constexpr int lds = RING * MidUnit<TM, FUSED>::BYTES;
-    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
+    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
                        ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
     if (launch_status() != SS_OK) return SS_ERR_HIP;
@@ -502,10 +537,12 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     // unit (3584 -> 4608 at M = 256, 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
     // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9; bf16 18944 -> 3584 at M = 16: 32.1 with eight, 34.8 with four).
     const bool shared = ntiles * S > cu_count();
-#define SS_MID(TM, RING) launch_sparse_mid_ring<DT, TM, RING, FUSED>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
-    if (M <= 32) return shared ? SS_MID(32, 4) : SS_MID(32, 8);
-    if (M <= 64) return shared ? SS_MID(64, 3) : SS_MID(64, 4);
-    return shared ? SS_MID(128, (FUSED ? 2 : 3)) : SS_MID(128, (FUSED ? 3 : 4));
+#define SS_MID(TM, ...) launch_sparse_mid_ring<DT, TM, __VA_ARGS__>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
+    if (M <= 32) return shared ? SS_MID(32, 4, FUSED) : SS_MID(32, 8, FUSED);
+    if (M <= 64) return shared ? SS_MID(64, 3, FUSED) : SS_MID(64, 4, FUSED);
+    if constexpr (!FUSED)
+        if (shared && 4 * ntiles <= 5 * cu_count()) return SS_MID(128, 3, FUSED, false);
+    return shared ? SS_MID(128, (FUSED ? 2 : 3), FUSED) : SS_MID(128, (FUSED ? 3 : 4), FUSED);
 #undef SS_MID
 }
 
@@ -554,7 +591,7 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     const int64_t ntiles = mid_tiles(M, O);
-    const bool sparse = kind == SS_KIND_SPARSE;
+    const bool sparse = kind != SS_KIND_DENSE;
     if (sparse && M > 32 && M <= 64 && units < 48) return 1;
     int64_t S = (sparse && M <= 32 ? 3 * cu_count() / 4 : cu_count()) / ntiles;
     if (S > units / 8) S = units / 8;

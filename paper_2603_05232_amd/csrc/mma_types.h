@@ -125,7 +125,7 @@ __device__ inline void store_quad4(const QUAD& a, const float* __restrict__ s_x,
     }
 }
 
-// Kernels for few tokens (gemm_skinny.hip): one workgroup per 32..128 output channels streams their weights once.
+// Kernels for few tokens (gemm_skinny.hip): one workgroup per 32 or 64 output channels streams their weights once.
 // The dense kernel splits its k range over S workgroups per fragment where there are fewer 32-channel fragments than
 // compute units; partial sums go through `ws` (skinny_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a
 // fixed order.  (Sparse shapes that gain from a split run on the tiles of gemm_mid.hip.)
@@ -148,7 +148,7 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
-enum ss_kind { SS_KIND_SPARSE, SS_KIND_DENSE };
+enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 
 // Kernels with tiles of 128 channels x 128 tokens, sparse ones also x 64 and x 32 where the tokens fit (gemm_mid.hip),
 // for shapes that give the 256 x 256 tile kernels too few tiles to occupy the compute units.
@@ -168,9 +168,14 @@ inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M 
 
 // Which kernel family a GEMM of M tokens x O channels over `units` 128-byte k units runs on, and in how many k
 // ranges (S > 1 only with a workspace).  Measured, INT8 6:8 unless said, weights from HBM, us:
-//   M > 64    up to two tiles of 128 x 128 per compute unit those tiles (two workgroups share a compute unit), beyond the
-//             256 x 256 tiles.  448 tiles, 18944 -> 3584 at M = 2048: 141 against 182; 512, 14336 -> 4096: 117 against 140;
-//             384, 4096 -> 4096 at M = 1536: 37 against 45; 592, 3584 -> 37888 at M = 256: 76 against 51.
+//   M > 64    up to 1.25 tiles of 128 x 128 per compute unit those tiles, beyond two of them the 256 x 256 tiles (592, 3584 -> 37888 at
+//             M = 256: 76 against 51).  Between, 128 x 128 tiles (two workgroups share a compute unit) where the rows are long
+//             enough: their stores go out in shorter pieces, and they read more of their operands from L2.  Time over that of
+//             256 x 256 tiles, weights from HBM / hot, by units per row, means over one to fourteen shapes: 321 .. 448 tiles, fused 8-bit 4
+//             units 1.07 / 1.01, 8 0.99 / 1.00, 12 0.88 / 0.99, 32 0.82 / 0.93, 16-bit 8 1.02 / 1.02, 12 0.93 / 0.98; lifted 8-bit 12 1.01 / 1.07, 24
+//             0.89 / 1.07, 32 0.90 / 1.03, 16-bit 12 1.00 / 1.09, 24 0.94 / 1.03, 32 0.80 / 1.03.  449 .. 512 tiles, fused 8-bit 16 0.96 / 1.07, 24 0.92 /
+//             1.08, 32 0.88 / 1.05, 16-bit 24 0.97 / 1.05; lifted 8-bit 32 0.97 / 1.13, 48 0.95 / 1.09, 16-bit 48 0.92 / 1.07.  The lines go by
+//             the first figure, a layer's weights coming from HBM in a model of many.
 //   M 33..64  tiles of 64 tokens where the panels alone fill the chip (3584 -> 37888: 37 against 50) or the rows are long
 //             and can be split (bf16 3584 -> 4608: 13.9 against 23.6; fp8 lifted 4096 -> 6144: 13.9 against 19.9; unsplit
 //             18944 -> 3584: 64 against 31), few-token kernels otherwise (3584 -> 4608 unsplit: 15.9 against 14.4).
@@ -203,8 +208,12 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
-    if (M > 64 && tiles > 2 * cus) return {SS_PATH_TILE, 1, tile_channels(M, O, cus)};
-    if (M > 64) return {SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
+    if (M > 64) {
+        const bool many = 4 * tiles > 7 * cus;                          // more than 448
+        const int64_t long_row = kind == SS_KIND_FUSED ? (many ? 24 : 12) : (many ? 48 : 24);
+        if (tiles > 2 * cus || (4 * tiles > 5 * cus && units < long_row)) return {SS_PATH_TILE, 1, tile_channels(M, O, cus)};
+        return {SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
+    }
     const int S = mid_splits(kind, M, O, units, ws_bytes);
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
     const bool mid = wide || (S > 1 && (M > 32 || 2 * units + M >= 128));
