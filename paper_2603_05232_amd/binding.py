@@ -118,7 +118,7 @@ def slide_lifted_k(K: int, N: int) -> int:
     return int(load().slide_lifted_k(K, N))
 
 
-@functools.lru_cache(maxsize=4096)
+@functools.lru_cache(maxsize=4096, typed=True)       # typed: 512.0 equals 512 but is refused
 def slide_lifted_ld(K: int, N: int, dtype: str) -> int:
     return int(load().slide_lifted_ld(K, N, DTYPE_CODE[dtype]))
 

@@ -146,3 +146,10 @@ def test_header_is_plain_c(tmp_path):
     r = subprocess.run([gcc, "-std=c99", "-Wall", "-Werror", "-pedantic", "-fsyntax-only", "-I", inc, str(src)],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_lifted_ld_takes_integers_only(lib):
+    # the sizes are kept per argument: a float that equals an earlier integer is still no element count
+    assert binding.slide_lifted_ld(7168, 4, "i8") == 10752
+    with pytest.raises(ctypes.ArgumentError):
+        binding.slide_lifted_ld(7168.0, 4, "i8")
