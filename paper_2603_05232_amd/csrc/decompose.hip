@@ -111,8 +111,8 @@ template <int ES> __device__ inline uint2 pack_entry(uint32_t av)
     return make_uint2(lo, hi);
 }
 
-// where window l of block b of a group goes: step of the group, lane half qa, window slot w (inverse of step_window /
-// fused_window in packed_layout.h)
+// where window l of block b of a group goes: step of the group, lane half qa, window slot w (the two orders of
+// packed_layout.h)
 struct PackSlot { int step, qa, w; };
 template <int ES, int N, bool FUSED> __device__ constexpr PackSlot pack_slot(int b, int l)
 {

@@ -1,8 +1,8 @@
 // slide_sparse_gemm and dense_gemm for few tokens (M <= 64): the decode regime, bound by streaming the
 // weights from HBM once, not by the matrix cores.
 //
-// A workgroup of four wavefronts owns FPW x 32 output channels (FPW matrix-instruction fragments, FPW = 1, 2
-// or 4: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (4,
+// A workgroup of four wavefronts owns FPW x 32 output channels (FPW matrix-instruction fragments, one or, for at most
+// 32 tokens, two: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (4,
 // or 8 when there are fewer workgroups than compute units) split the k range by units of 128 bytes of a row
 // (unit u goes to wavefront u mod the number of wavefronts), so every workgroup is
 // four independent load streams, enough of them in flight on every compute unit to keep the memory system
@@ -122,7 +122,7 @@ __device__ inline void sk_store_partial(const ACC (&acc)[NACC], void* ws, int co
 // FUSED (6:8, unlifted input, weights packed by slide_decompose_fused): a unit is a super-unit of 128 unlifted bytes
 // = NS = 3 steps; B lane (n, qb) loads the 64 bytes [64 qb, 64 qb + 64) of its token's super-unit, uses the first
 // 32 in step 0, the second 32 in step 1 and builds the eight middle windows of step 2 in registers
-// (packed_layout.h, fused_window): the k loop is as long as the dense kernel's and the token rows are read once,
+// (packed_layout.h, fused order): the k loop is as long as the dense kernel's and the token rows are read once,
 // not 1.5 times.
 template <int TB, int FPW, int NS> struct SkSparseUnit { v4i a[NS][FPW]; int idx[NS][FPW]; v4i b[TB][4]; };
 
@@ -437,15 +437,6 @@ __global__ __launch_bounds__(256 * TB) void k_skinny_reduce(const v4i* __restric
 
 using namespace ss;
 
-// Fragments per workgroup: as many (4, 2 or 1) as leave every compute unit at least one workgroup.
-static int pick_fpw(int64_t frags)
-{
-    const int cus = cu_count();
-    int fpw = 4;
-    while (fpw > 1 && frags / fpw < cus) fpw >>= 1;
-    return fpw;
-}
-
 // U units of 128 bytes per token row (lifted rows, or unlifted rows when FUSED), ldxb bytes between rows
 template <int DT, int TB, int FPW, bool FUSED>
 static ss_status launch_sparse_one(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
@@ -480,10 +471,9 @@ static ss_status launch_dense_one(const void* Xq, const float* s_x, const void* 
     return launch_status();
 }
 
-// k ranges when workgroups are single 32-channel fragments (fewer fragments, counted in whole panels, than compute
-// units; eight wavefronts each): every wavefront keeps at least eight units, at most `cap` ranges.  Measured on
-// 18944 -> 3584 (112 fragments, INT8 6:8): M = 16 28 -> 20 us, M = 32 37 -> 24 us; at M = 1 the second kernel costs
-// what the split saves, so fewer than 8 tokens are not split.
+// k ranges of the dense kernel when workgroups are single 32-channel fragments (fewer fragments, counted in whole panels,
+// than compute units; eight wavefronts each): every wavefront keeps at least eight units, at most `cap` ranges; fewer than 8
+// tokens are not split.
 static int frag_splits(int64_t M, int64_t O, int64_t units, int cap)
 {
     const int64_t nfrag = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
@@ -500,12 +490,13 @@ template <int DT, bool FUSED>
 static ss_status launch_sparse_dt(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                                   int U, int64_t ldxb, void* Y, int64_t ldy, hipStream_t st)
 {
-    const int fpw = pick_fpw((O + PANEL - 1) / PANEL * FRAGS_PER_PANEL);
+    // Two fragments per workgroup where that leaves every compute unit one.  (Layers of more panels, and more tokens on as
+    // many, run on the tiles of gemm_mid.hip.)
+    const bool two = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL >= 2 * cu_count();
 #define SS_GO(TB, FPW) return launch_sparse_one<DT, TB, FPW, FUSED>(XL, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, st)
-    if (M <= 32) { if (fpw == 4) SS_GO(1, 4); if (fpw == 2) SS_GO(1, 2); SS_GO(1, 1); }
-    if (fpw == 4) SS_GO(2, 4);
-    if (fpw == 2) SS_GO(2, 2);
-    SS_GO(2, 1);
+    if (M > 32) SS_GO(2, 1);
+    if (two) SS_GO(1, 2);
+    SS_GO(1, 1);
 #undef SS_GO
 }
 

@@ -34,13 +34,8 @@ constexpr int FRAGS_PER_PANEL = 4;
 
 // output-channel offset inside a 128-row panel of row i (0..31) of fragment f (0..3)
 __host__ __device__ inline int panel_row(int f, int i) { return 64 * ((i >> 2) & 1) + 16 * f + 4 * (i >> 3) + (i & 3); }
-// window inside a step held by lane half qa at window slot w of the lane; a lane holds HW = 4 / ES
-// windows of each half of the step (ES = bytes per element: 8 slots of 16 windows, or 4 of 8)
-template <int ES> __host__ __device__ inline int step_window(int qa, int w)
-{
-    constexpr int HW = 4 / ES;
-    return 2 * HW * (w / HW) + HW * qa + (w % HW);
-}
+// Order of the lifted row: a lane holds HW = 4 / ES windows of each half of the step (ES = bytes per element: 8 slots of 16
+// windows, or 4 of 8); slot w of lane half qa is window 2 HW (w / HW) + HW qa + w % HW of the step, the wi above.
 
 // Fused order of the 6:8 pattern (N = 4), for the GEMM that takes unlifted activations and applies the lifting
 // operator on the way from LDS to the operand registers.  A super-unit is 128 unlifted bytes of a row = BL = 8 / ES
@@ -51,22 +46,10 @@ template <int ES> __host__ __device__ inline int step_window(int qa, int w)
 // So window slot wsl (0..BL-1) of B lane half qb in step 3s+J is
 //     J = 0, 1:  block (2s + qb) BL + J BL/2 + (wsl >> 1),  window l = 2 (wsl & 1)
 //     J = 2:     block (2s + qb) BL + wsl,                  window l = 1
-// and the A lane (qa, slot w) meets B lane half qb = w / HW, window slot wsl = HW qa + (w % HW) as in step_window.
-template <int ES> __host__ __device__ inline void fused_window(int step, int qa, int w, int& g, int& l)
-{
-    constexpr int HW = 4 / ES, BL = 8 / ES;
-    const int qb = w / HW, wsl = HW * qa + (w % HW);
-    const int s = step / 3, J = step - 3 * s;
-    l = J == 2 ? 1 : 2 * (wsl & 1);
-    g = (2 * s + qb) * BL + (J == 2 ? wsl : J * (BL / 2) + (wsl >> 1));
-}
+// and the A lane (qa, slot w) meets B lane half qb = w / HW, window slot wsl = HW qa + (w % HW) as above.
 
-// slot of the 16-byte value group of (panel, step, fragment, lane); values are stored [panel][step][fragment][lane],
-// index words (4 bytes each, the upper half unused for bf16) [panel][step][lane][fragment], so that one 16-byte
-// read hands a lane the words of all four fragments
-__host__ __device__ inline int64_t frag_slot(int64_t panel, int64_t nsteps, int64_t step, int f, int lane)
-{
-    return ((panel * nsteps + step) * FRAGS_PER_PANEL + f) * 64 + lane;
-}
+// Values, 16 bytes per lane and step, are stored [panel][step][fragment][lane], index words (4 bytes each, the upper half
+// unused for 16-bit types) [panel][step][lane][fragment], so that one 16-byte read hands a lane the words of all four
+// fragments.  decompose.hip (pack_slot) is the one place that computes the order.
 
 }  // namespace ss
