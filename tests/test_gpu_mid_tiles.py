@@ -12,18 +12,19 @@ def _linear(M, O, K, N, dtype, fused, with_ws, seed):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     X = torch.randint(-3, 4, (M, K), generator=gen, device="cuda")
     W = torch.randint(-3, 4, (O, K), generator=gen, device="cuda")
-    X[:, 0] = 3                                                         # full scale present in every row: the codes are the integers times a constant
     if dtype in ("i8", "fp8"):
-        td = torch.int8
-        Wq = torch.where(torch.arange(K, device="cuda") % (2 * N) < 2 * N - 2, W, 0).to(td)
-        Xq = X.to(td)
+        def enc(a):                                                     # -3 .. 3 are e4m3 values
+            return a.to(torch.int8) if dtype == "i8" else a.float().to(torch.float8_e4m3fn).view(torch.uint8)
+        td = torch.int8 if dtype == "i8" else torch.uint8
+        W = torch.where(torch.arange(K, device="cuda") % (2 * N) < 2 * N - 2, W, 0)
+        Xq, Wq = enc(X), enc(W)
         s_x = torch.rand(M, generator=gen, device="cuda") + 0.5
         s_w = torch.rand(O, generator=gen, device="cuda") + 0.5
     else:
         td = torch.bfloat16 if dtype == "bf16" else torch.float16
-        Wq = torch.where(torch.arange(K, device="cuda") % (2 * N) < 2 * N - 2, W, 0).to(td)
-        Xq, s_x, s_w = X.to(td), None, None
-    acc = (Xq.double() @ Wq.double().T).float()
+        W = torch.where(torch.arange(K, device="cuda") % (2 * N) < 2 * N - 2, W, 0)
+        Xq, Wq, s_x, s_w = X.to(td), W.to(td), None, None
+    acc = (X.double() @ W.double().T).float()
     ref = (acc if s_x is None else (acc * s_x[:, None]) * s_w[None, :]).bfloat16()
     es = Xq.element_size()
     if fused:
@@ -49,11 +50,52 @@ def _linear(M, O, K, N, dtype, fused, with_ws, seed):
     assert bool((out[M] == 7.0).all())                                 # nothing beyond the last token
 
 
-# panels alone fill the chip: 192 panels and more, unsplit; 1 .. 18 units cover every state of the rings
+# 192 panels, unsplit: one workgroup per compute unit (256 of them), rings of eight (32 tokens) and four units (64)
 @pytest.mark.parametrize("M", [1, 32, 33, 64])
 @pytest.mark.parametrize("units", [1, 2, 3, 4, 5, 7, 8, 9, 10, 18])
 def test_wide_layers_of_few_tokens(M, units):
     _linear(M, 192 * 128 - 5, 128 * units, 4, "i8", True, False, units)
+
+
+def _rows(units, N, dtype, fused):
+    """The longest row of `units` units of 128 bytes, less three elements where the form takes any length."""
+    es = 1 if dtype in ("i8", "fp8") else 2
+    return 128 * units // es if fused else 128 * units // es * N // (2 * (N - 1)) - 3
+
+
+# 257 panels: workgroups share compute units.  Rings of four (32 tokens), three (64) and, for 128 tokens, two units in the
+# pipeline (fused) and three without it (lifted), over row lengths from one unit to two rings and more
+@pytest.mark.parametrize("dtype,N", [("i8", 4), ("bf16", 4), ("fp8", 3), ("fp16", 5)])
+@pytest.mark.parametrize("M", [1, 32, 33, 64, 65, 128])
+@pytest.mark.parametrize("units", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10])
+def test_rings_of_shared_compute_units(dtype, N, M, units):
+    for fused in ([True, False] if N == 4 else [False]):
+        _linear(M, 257 * 128 - 5, _rows(units, N, dtype, fused), N, dtype, fused, False, units)
+
+
+# the same with more than a quarter of the compute units shared and rows long enough for the pipeline of three (lifted) or
+# two units (fused); nine and ten token tiles: two bands
+@pytest.mark.parametrize("dtype,M,O,units,N,fused", [("i8", 100, 321 * 128 - 3, 32, 4, False), ("bf16", 100, 322 * 128, 33, 4, False), ("fp8", 128, 330 * 128, 34, 3, False),
+                                                     ("fp16", 1100, 4700, 35, 5, False), ("i8", 1250, 4200, 12, 4, True), ("bf16", 1100, 4700, 13, 4, True),
+                                                     ("i8", 1250, 3900, 9, 4, False), ("bf16", 1100, 3700, 7, 4, False)])
+def test_shared_pipelines_and_bands(dtype, M, O, units, N, fused):
+    _linear(M, O, _rows(units, N, dtype, fused), N, dtype, fused, False, units)
+
+
+# Both sides of every line of the kernel choice for sparse calls, for 256 compute units: tiles (320, 448, 512) and units
+# per row (12 and 24 fused, 24 and 48 lifted) between 128 x 128 and 256 x 256 tiles; panels (128 and 192) and rows (48 units;
+# 2 units + tokens = 128) between few-token kernels and tiles of 32 and 64 tokens, with the workspace the rows are split
+# in; a rest of a round of exactly one tile per compute unit and of one panel more.
+@pytest.mark.parametrize("M,O,units,ws", [(65, 128 * 320, 3, False), (65, 128 * 321, 11, False), (65, 128 * 321, 12, False), (65, 128 * 321, 23, False),
+                                          (65, 128 * 321, 24, False), (65, 128 * 448, 12, False), (65, 128 * 449, 23, False), (65, 128 * 449, 24, False),
+                                          (65, 128 * 449, 47, False), (65, 128 * 449, 48, False), (65, 128 * 512, 48, False), (65, 128 * 513, 48, False),
+                                          (15, 128 * 191, 3, False), (15, 128 * 192, 3, False), (16, 128 * 127, 3, False), (16, 128 * 128, 3, False),
+                                          (64, 128 * 127, 3, False), (64, 128 * 128, 3, False), (1, 500, 63, True), (1, 500, 64, True), (32, 500, 47, True),
+                                          (32, 500, 48, True), (33, 500, 47, True), (33, 500, 48, True), (64, 500, 47, True), (64, 500, 48, True),
+                                          (1000, 16384 + 4096, 3, False), (1000, 16384 + 4097, 3, False)])
+@pytest.mark.parametrize("fused", [True, False])
+def test_lines_of_the_kernel_choice(M, O, units, ws, fused):
+    _linear(M, O, _rows(units, 4, "i8", fused), 4, "i8", fused, ws, units)
 
 
 # one workgroup per compute unit or several, split or not, tokens at the edges of the tiles, 16-bit and lifted forms

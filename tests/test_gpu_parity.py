@@ -314,8 +314,9 @@ def test_sparse_and_dense_gemm_float(dtype, N, M, O, K):
 @pytest.mark.parametrize("M,O", [(32, 128), (33, 160), (64, 8192), (65, 8192), (65, 128 * 320), (65, 128 * 321), (128, 512), (129, 512),
                                  (128, 128 * 320), (129, 128 * 161), (256, 128 * 160), (257, 128 * 107)])
 def test_gemm_kernel_selection_boundaries_int8(M, O):
-    """Shapes around the switches between the few-token kernels (M <= 64), the 128 x 128-tile kernels (up to 320
-    such tiles) and the 256 x 256 tile kernels: the result must not depend on which one runs."""
+    """Shapes around the dense GEMM's switches between the few-token kernels (M <= 64), the 128 x 128-tile kernels (up to
+    320 such tiles) and the 256 x 256 tile kernels, which short sparse rows share at 320 tiles: the result must not depend on
+    which one runs.  (The sparse lines that depend on the row length: test_gpu_mid_tiles.py.)"""
     N, K = 4, 256
     rng = np.random.default_rng(M * 7 + O)
     Wq = rng.integers(-127, 128, size=(O, K)).astype(np.int8)
@@ -345,10 +346,10 @@ def _workspace(M, O, Kp, dtype, fill, scale=1.0):
                                      (3, 300, 130, 3072),       # ragged tokens and channels, K' = 4096
                                      (2, 129, 257, 4096),       # native 2:4
                                      (5, 64, 128, 10240),       # K' = 16384
-                                     (5, 16, 200, 10240),       # few-token kernels, k range split in two
-                                     (4, 24, 130, 16384)])      # ... in three (K' = 24576)
+                                     (5, 16, 200, 10240),       # long rows of few tokens: tiles of 32 tokens (sparse), few-token kernel (dense)
+                                     (4, 24, 130, 16384)])      # ... (K' = 24576)
 def test_gemm_split_k_with_workspace(dtype, N, M, O, K):
-    """The 128 x 128-tile kernels (and, for few tokens on long rows, the few-token kernels) with the k range split
+    """The 128-channel tile kernels (and, for few tokens on long rows, the dense few-token kernel) with the k range split
     over several workgroups: partial sums go through the caller's workspace and are added in a fixed order.  INT8 must equal the oracle bit for bit (and
     so the call without workspace); floats stay within the GEMM tolerance and are reproducible bit for bit."""
     X = synth.activations(M, K, seed=M + K, n_outliers=2)
