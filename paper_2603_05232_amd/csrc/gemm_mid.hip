@@ -253,9 +253,9 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     // HBM: 75 -> 61 us on 5003 -> 4099 fp16 8:10 at M = 777; the kernel 78 -> 73).  In a split range of one token tile, where an
     // XCD's workgroups share nothing but the token rows of a range, so do the workgroups of an XCD: in step they all ask
     // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 5 % less time; unsplit or with several token
-    // tiles, where they share weights or more rows than the L2 holds, up to 60 % more).
+    // tiles, where they share weights or more rows than the L2 holds, up to 60 % more; tiles of 64 and 32 tokens, level).
     const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int rot = PIPE ? (tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
+    const int rot = PIPE ? (TM == 128 && tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
     auto direct_load = [&](int v, uint32_t slot, int d) __attribute__((always_inline)) {
         const uint32_t st = lds0 + slot;
         const int u = v + rot < U ? v + rot : v + rot - U;
@@ -582,12 +582,13 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 // Dense kernel: as many as that allows.  Sparse, M <= 64: the same (three quarters of a workgroup per compute unit for tiles
 // of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us in 5 ranges, 19.1 in 7, 19.3 in 9; bf16 3584 -> 4608 at M = 64, 56
 // units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7), but short rows are not split at 33..64 tokens.
-// Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 2 + a
-// 14th of the tiles x ranges written and read back.  The unsplit kernel is fast enough that a few ranges more than that cost
-// more than they save: 3584 -> 4608 at M = 256 (28 units, 72 tiles) 15.9 us unsplit, 19.1 in 3 ranges; 4096 -> 4096 lifted at
-// M = 256 (48 units, 64 tiles) 16.3 unsplit, 16.5 in 3, 17.3 in 4; 18944 -> 3584 at M = 256 (148 units, 56 tiles) 54 unsplit, 28.7 in 4.
-// Over 2080 calls (five operand forms, 13 layers, M = 65 .. 640, weights hot and from HBM, two cards) the choice lies 2.3 % above
-// the best S, as many ranges as fit 4.4 %.
+// Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 4 + a
+// 20th of the tiles x ranges written and read back.  The unsplit kernel is fast enough that a few ranges more than
+// that cost more than they save: 3584 -> 4608 at M = 384 (28 units, 108 tiles) 20.7 us unsplit, 22.5 in 2 ranges; 4096 -> 4096 at M = 384
+// (32 units, 96 tiles) 16.9 unsplit, 22.7 in 2, both sides hot; 18944 -> 3584 at M = 256 (148 units, 56 tiles) 54 unsplit, 26.7 in 4.
+// Over 2080 calls (five operand forms, 13 layers, M = 65 .. 640, two cards) 0.954 of the time before the pipeline with weights from HBM
+// and 0.869 hot, as many ranges as fit 0.962 and 0.882; a 14th of the partial sums instead of a 20th 0.952 and 0.855, but more
+// calls with weights from HBM then lose.
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     const int64_t ntiles = mid_tiles(M, O);
@@ -599,9 +600,9 @@ int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_byte
     if (S > fit) S = fit;
     if (S < 2) return 1;
     if (!sparse || M <= 64) return (int)S;
-    int64_t best = 1, least = 14 * units;                               // 14ths of a unit
+    int64_t best = 1, least = 20 * units;                               // 20ths of a unit
     for (int64_t s = 2; s <= S; ++s) {
-        const int64_t t = 14 * ((units + s - 1) / s + 2) + s * ntiles;
+        const int64_t t = 20 * ((units + s - 1) / s + 4) + s * ntiles;
         if (t < least) { least = t; best = s; }
     }
     return (int)best;
