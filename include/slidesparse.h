@@ -134,7 +134,8 @@ ss_status act_lift_quant(const void* X, ss_act_dtype in_dtype, int64_t M, int64_
  * aligned operand pointers.  Three kernel families are chosen from M, O and K_lifted: kernels that
  * stream the weights once (few tokens), 128 x 128 tiles (shapes too small to fill the chip with
  * large tiles) and persistent 256 x 256 tiles; results are the same (INT8) or differ in fp32
- * summation order only.  Every call with the same arguments gives the same bits. */
+ * summation order only.  Every call with the same arguments gives the same bits; the order may differ between the token
+ * tiles of a call, so equal token rows may differ in the last bit of a floating-point result. */
 ss_status slide_sparse_gemm(const void* X_lifted, const float* s_x, const void* w_vals,
                             const void* w_meta, const float* s_w, int64_t M, int64_t O,
                             int64_t K_lifted, ss_dtype dtype, void* Y, int64_t ldy, void* stream);
@@ -148,7 +149,7 @@ ss_status dense_gemm(const void* Xq, const float* s_x, const void* Wq, const flo
 
 /* The same two GEMMs with a caller-owned scratch buffer (Sec. 5 measures from decode, M = 64, to
  * prefill; small M leaves most of the chip idle unless the k range is split).  With a workspace of
- * at least slide_gemm_workspace_bytes() the 128 x 128-tile kernels (and the few-token kernels on
+ * at least slide_gemm_workspace_bytes() the 128-channel tile kernels (and the dense few-token kernel on
  * long rows) split the k range of a tile over several workgroups, write fp32 / int32 partial
  * sums to the workspace and add them in a fixed order in a second kernel (bit-reproducible; INT8 results are identical to the calls
  * without workspace).  workspace: device memory, 16-byte aligned (SS_ERR_WORKSPACE otherwise),

@@ -204,7 +204,7 @@ template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&ac
 // and bands are wider.  With lifted rows and up to a quarter more tiles than compute units, where most compute units hold one
 // workgroup and the launch waits for those with two, that is the faster loop (lifted INT8 / bf16 against the pipeline, weights
 // from HBM: 4096 -> 4096 at M = 1152, 288 tiles, 35 against 38 us / 59 against 68; 4096 -> 6144 at M = 768 35 against 37 / 58 against 64);
-// with more tiles than that, or unlifted rows, the pipeline is (384 tiles, 4096 -> 4096 at M = 1536: 39 against 45 us; fused 288: 33 against 35).
+// with more tiles than that, or unlifted rows, the pipeline is (384 tiles, 4096 -> 4096 at M = 1536, same order: 39.5 against 41.1 us; fused, 288 tiles: 33 against 35).
 template <int TM, bool FUSED> struct MidUnit {
     typedef MidShape<TM> MS;
     static constexpr int NS = FUSED ? 3 : 2;                              // steps
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     // for the same token lines, and for few channels' worth of weights, at the same time (the loads alone, weights from
     // HBM: 75 -> 61 us on 5003 -> 4099 fp16 8:10 at M = 777; the kernel 78 -> 73).  In a split range of one token tile, where an
     // XCD's workgroups share nothing but the token rows of a range, so do the workgroups of an XCD: in step they all ask
-    // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 5 % less time; unsplit or with several token
+    // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 4 % less time; unsplit or with several token
     // tiles, where they share weights or more rows than the L2 holds, up to 60 % more; tiles of 64 and 32 tokens, level).
     const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     const int rot = PIPE ? (TM == 128 && tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
             if constexpr (LOAD) {
 #pragma unroll
                 for (int d = 0; d < LPU; ++d)
-                    if ((d * (RING == 2 ? NM / 2 : NM)) / LPU == i) direct_load(u + RING, slot, d);      // a ring of two: early (47.8 -> 46.9 us, 3584 -> 37888 INT8 at M = 128)
+                    if ((d * (RING == 2 ? NM / 2 : NM)) / LPU == i) direct_load(u + RING, slot, d);      // a ring of two: early (3584 -> 37888 fused INT8 at M = 128: 46.9 us, spread out 47.8)
             }
             if (FUSED && (i == 1 || (TB == 2 && i == 4))) middle(C, al[i / 4], i / 4);       // before step 2 starts at instruction 2 ACC
             __builtin_amdgcn_sched_barrier(0);
@@ -584,8 +584,9 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 // units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7), but short rows are not split at 33..64 tokens.
 // Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 4 + a
 // 20th of the tiles x ranges written and read back.  The unsplit kernel is fast enough that a few ranges more than
-// that cost more than they save: 3584 -> 4608 at M = 384 (28 units, 108 tiles) 20.7 us unsplit, 22.5 in 2 ranges; 4096 -> 4096 at M = 384
-// (32 units, 96 tiles) 16.9 unsplit, 22.7 in 2, both sides hot; 18944 -> 3584 at M = 256 (148 units, 56 tiles) 54 unsplit, 26.7 in 4.
+// that cost more than they save (fused INT8, weights from HBM): 2048 -> 8192 at M = 256 (16 units, 128 tiles) 15.1 us unsplit, 21.0 in 2
+// ranges; 2048 -> 2048 at M = 640 (16 units, 80 tiles) 11.3 unsplit, 16.1 in 2; 4096 -> 4096 at M = 512 (32 units, 128 tiles) 22.4 unsplit, 22.0
+// in 2 (hot 17.4 and 20.4); 18944 -> 3584 at M = 256 (148 units, 56 tiles) 83 unsplit, 33.0 in 4.
 // Over 2080 calls (five operand forms, 13 layers, M = 65 .. 640, two cards) 0.954 of the time before the pipeline with weights from HBM
 // and 0.869 hot, as many ranges as fit 0.962 and 0.882; a 14th of the partial sums instead of a 20th 0.952 and 0.855, but more
 // calls with weights from HBM then lose.
