@@ -15,15 +15,17 @@ constexpr int BT = 256;   // tokens per workgroup tile
 // tiles b, b + grid, b + 2 grid, ...  Workgroup ids go round-robin to the 8 XCDs, so within a full
 // round each XCD is given one contiguous run of tiles, and tiles are ordered in bands of 8 token
 // tiles so that the 32 workgroups resident on an XCD share weight panels and token tiles in its L2.
-// A partial last round keeps the plain order: dealt out in runs as well, layers of 72 and more tiles of channels with
-// weights from HBM take 2 % longer (fused INT8 and bf16, 27 shapes each; at worst 4.8 %: 3584 -> 37888 bf16 at M = 1024,
-// 226 -> 233 us), back to back 0.4 % less.  Runs in a single partial round (fewer tiles than compute units) are 1 to 4 % faster.
+// A partial last round is dealt out in runs as well where the layer has few tiles of channels and keeps the plain order where
+// it has many (time of runs over plain, fused INT8 / fp8 / bf16, weights from HBM / hot, M = 640 .. 8192: 14 .. 32 tiles of channels, 33
+// calls, 0.989 / 0.998; 54 .. 148 tiles, 93 calls, 1.015 / 0.997, at worst 1.066; lifted rows 1.000 / 0.996 and 1.003 / 0.995).
+// Runs in a single partial round (fewer tiles than compute units) are 1 to 4 % faster.
+constexpr int RUNS_MAX_TILES_O = 40;
 __device__ inline bool tile_of_round(int round, int tiles_o, int tiles_t, int& to, int& tt)
 {
     const int nb = gridDim.x, bid = blockIdx.x, total = tiles_o * tiles_t;
     const int base = round * nb;
     if (base + bid >= total) return false;
-    const int tile = base + (base + nb <= total ? xcd_run(bid, nb) : bid);
+    const int tile = base + (base + nb <= total || tiles_o <= RUNS_MAX_TILES_O ? xcd_run(bid, min(nb, total - base)) : bid);
     constexpr int BAND = 8;
     const int per_band = BAND * tiles_o;
     const int band = tile / per_band, within = tile - band * per_band;
