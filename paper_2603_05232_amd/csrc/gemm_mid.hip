@@ -154,13 +154,16 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
 // rows of those few columns meet in the same memory channels (4096 -> 4096 INT8 lifted at M = 256 in 4 ranges: 20.8 against
 // 17.3 us; the dense kernel, 8192 -> 2048 at M = 192 in 8: 21.3 against 17.5) and gains where the loop is long and a run of
 // tiles reads more token bytes than an XCD's L2 holds (18944 -> 3584 fused INT8 at M = 256 in 4 ranges: 29 against 35).
-// The lines are those that lose least over 1646 calls (five operand forms, 12 layers, M = 65 .. 640, two and three cards): 19
-// units of k per compute unit, 10 with one token tile, or 4.5 MB of tokens (12288 -> 1536 bf16 at M = 256, hot: 19.7 against 23.9).
+// By units of k per compute unit (tiles x units / 256), time of the second over the first, means over five operand forms, 12
+// layers, M = 192 .. 640, three cards: up to 6 0.989, 8 to 12 1.07, 17 1.015, 19 and more 0.98.  So the first is taken from 7 to 19, with one
+// token tile to 10 (calls more than 3 % slower than before the pipeline, of 464: 15, with the second throughout 27), and not beyond
+// 4.5 MB of tokens (12288 -> 1536 bf16 at M = 256, hot: 19.7 against 23.9).
 // Tiles of 64 and 32 tokens, where the weights are nearly all that is read, take the second throughout.  The dense kernel
 // takes the first: by the same lines 60 of 504 calls were more than 3 % slower than with the first, 21 so.
 __device__ inline bool mid_by_range(int tile_tokens, int64_t M, int tiles_t, int units)
 {
-    return tile_tokens < MD_TILE || (int64_t)gridDim.x * units > (tiles_t == 1 ? 10 : 19) * 256 || M * units > (36 << 10);
+    const int64_t work = (int64_t)gridDim.x * units;
+    return tile_tokens < MD_TILE || work < 7 * 256 || work > (tiles_t == 1 ? 10 : 19) * 256 || M * units > (36 << 10);
 }
 struct MidItem { int64_t panel; int tt, range; int64_t tile; };
 __device__ inline MidItem mid_item(int tiles_t, bool by_range, int widest = 8)
