@@ -586,13 +586,14 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 // of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us in 5 ranges, 19.1 in 7, 19.3 in 9; bf16 3584 -> 4608 at M = 64, 56
 // units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7), but short rows are not split at 33..64 tokens.
 // Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 4 + a
-// 20th of the tiles x ranges written and read back.  The unsplit kernel is fast enough that a few ranges more than
+// 16th of the tiles x ranges written and read back, and 2 more where the ranges take over 7/8 of the compute units: on two of
+// three cards a split launch of that many workgroups ends 3 to 4 us late (8192 -> 2048 lifted INT8 at M = 192: 16.4 us in 6 ranges of
+// 32 tiles, 16.4 in 8 on one card, 21.3 on others).  The unsplit kernel is fast enough that a few ranges more than
 // that cost more than they save (fused INT8, weights from HBM): 2048 -> 8192 at M = 256 (16 units, 128 tiles) 15.1 us unsplit, 21.0 in 2
 // ranges; 2048 -> 2048 at M = 640 (16 units, 80 tiles) 11.3 unsplit, 16.1 in 2; 4096 -> 4096 at M = 512 (32 units, 128 tiles) 22.4 unsplit, 22.0
 // in 2 (hot 17.4 and 20.4); 18944 -> 3584 at M = 256 (148 units, 56 tiles) 83 unsplit, 33.0 in 4.
-// Over 2080 calls (five operand forms, 13 layers, M = 65 .. 640, two cards) 0.954 of the time before the pipeline with weights from HBM
-// and 0.869 hot, as many ranges as fit 0.962 and 0.882; a 14th of the partial sums instead of a 20th 0.952 and 0.855, but more
-// calls with weights from HBM then lose.
+// Over 2520 calls (five operand forms, 12 layers, M = 65 .. 512, three cards) 0.960 of the time before the pipeline with weights from
+// HBM (77 more than 3 % slower) and 0.865 hot (none); a 20th and nothing for the last workgroups 0.974 (188) and 0.891 (49).
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     const int64_t ntiles = mid_tiles(M, O);
@@ -604,9 +605,9 @@ int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_byte
     if (S > fit) S = fit;
     if (S < 2) return 1;
     if (!sparse || M <= 64) return (int)S;
-    int64_t best = 1, least = 20 * units;                               // 20ths of a unit
+    int64_t best = 1, least = 16 * units;                               // 16ths of a unit
     for (int64_t s = 2; s <= S; ++s) {
-        const int64_t t = 20 * ((units + s - 1) / s + 4) + s * ntiles;
+        const int64_t t = 16 * ((units + s - 1) / s + (8 * s * ntiles > 7 * cu_count() ? 6 : 4)) + s * ntiles;
         if (t < least) { least = t; best = s; }
     }
     return (int)best;
