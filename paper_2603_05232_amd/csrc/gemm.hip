@@ -237,7 +237,7 @@ __global__ __launch_bounds__(G_THREADS) void k_dense(const uint8_t* __restrict__
         settle(sx);                                   // the token scales have arrived: no wait for them behind the loads requested next
         have = tile_of_round(round + 1, tiles_o, tiles_t, to, tt);
         if (have) { setup_tile(to, tt); issue(0); issue_scales((round + 1) & 1); }
-        store_tile<MM::SCALED, 32, false>(acc, sx, reinterpret_cast<const float*>(smem + D_SW_OFF + (round & 1) * SW_BYTES) + wo * 128, Y_sub,
+        store_tile<MM::SCALED>(acc, sx, reinterpret_cast<const float*>(smem + D_SW_OFF + (round & 1) * SW_BYTES) + wo * 128, Y_sub,
                                    (uint32_t)ldy, rows_left, cols_left, stage);
     }
 }
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(G_THREADS) void k_sparse(const uint8_t* __restrict_
         settle(sx);                                   // the token scales have arrived: no wait for them behind the loads requested next
         have = tile_of_round(round + 1, tiles_o, tiles_t, to, tt);
         if (have) { setup_tile(to, tt); issue(0, 2); issue_scales((round + 1) & 1); }
-        store_tile<MM::SCALED, 32, false>(acc, sx, reinterpret_cast<const float*>(smem + S_SW_OFF + (round & 1) * SW_BYTES) + wo * 128, Y_sub,
+        store_tile<MM::SCALED>(acc, sx, reinterpret_cast<const float*>(smem + S_SW_OFF + (round & 1) * SW_BYTES) + wo * 128, Y_sub,
                                    (uint32_t)ldy, rows_left, cols_left, smem + wave * EP_WAVE_BYTES);
     }
 }

@@ -36,6 +36,23 @@ __device__ inline void lds_dma16_lanes_at(const uint8_t* uniform_base, uint32_t 
     asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds_wave_addr),
                  "v"(lane_off), "s"(uniform_base), "s"(lanes) : "memory", "m0");
 }
+// The same with the scalar address arithmetic inside the statement, for kernels whose many load sources would otherwise be
+// computed ahead of time and held in scalar registers: from base + off to LDS lds_wave_addr + DST, all lanes or those
+// of `lanes`.
+template <uint32_t DST> __device__ inline void lds_dma16_from(const uint8_t* uniform_base, uint32_t off, uint32_t lane_off, uint32_t lds_wave_addr)
+{
+    const uint32_t lo = (uint32_t)(uintptr_t)uniform_base, hi = (uint32_t)((uintptr_t)uniform_base >> 32);
+    asm volatile("s_add_u32 m0, %0, %5\n\ts_add_u32 vcc_lo, %3, %1\n\ts_addc_u32 vcc_hi, %2, 0\n\tglobal_load_lds_dwordx4 %4, vcc"
+                 ::"s"(lds_wave_addr), "s"(lo), "s"(hi), "s"(off), "v"(lane_off), "n"(DST) : "memory", "m0", "vcc", "scc");
+}
+template <uint32_t DST>
+__device__ inline void lds_dma16_lanes_from(const uint8_t* uniform_base, uint32_t off, uint32_t lane_off, uint32_t lds_wave_addr, uint64_t lanes)
+{
+    const uint32_t lo = (uint32_t)(uintptr_t)uniform_base, hi = (uint32_t)((uintptr_t)uniform_base >> 32);
+    asm volatile("s_add_u32 m0, %0, %5\n\ts_mov_b64 exec, %6\n\ts_add_u32 vcc_lo, %3, %1\n\ts_addc_u32 vcc_hi, %2, 0\n\t"
+                 "global_load_lds_dwordx4 %4, vcc\n\ts_mov_b64 exec, -1"
+                 ::"s"(lds_wave_addr), "s"(lo), "s"(hi), "s"(off), "v"(lane_off), "n"(DST), "s"(lanes) : "memory", "m0", "vcc", "scc");
+}
 __device__ inline void lds_dma16(const uint8_t* uniform_base, uint32_t lane_off, const void* lds_wave_base)
 {
     lds_dma16_at(uniform_base, lane_off, lds_address(lds_wave_base));

@@ -13,25 +13,30 @@ namespace ss {
 template <int DT> struct Mma;
 template <> struct Mma<SS_I8> {
     typedef v16i acc_t;
+    typedef v4i acc16_t;
     typedef v4i dfrag_t;
     static constexpr int ES = 1;                       // bytes per element
     static constexpr int DENSE_SUB = 32;
     static constexpr bool SCALED = true;
     __device__ static acc_t sparse(v4i a, v8i b, acc_t c, int idx) { return __builtin_amdgcn_smfmac_i32_32x32x64_i8(a, b, c, idx, 0, 0); }
+    __device__ static acc16_t sparse16(v4i a, v8i b, acc16_t c, int idx) { return __builtin_amdgcn_smfmac_i32_16x16x128_i8(a, b, c, idx, 0, 0); }
     __device__ static acc_t dense(dfrag_t a, dfrag_t b, acc_t c) { return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0); }
 };
 template <> struct Mma<SS_FP8_E4M3> {
     typedef v16f acc_t;
+    typedef v4f acc16_t;
     typedef v8i dfrag_t;
     static constexpr int ES = 1;
     static constexpr int DENSE_SUB = 64;
     static constexpr bool SCALED = true;
     __device__ static acc_t sparse(v4i a, v8i b, acc_t c, int idx) { return __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(a, b, c, idx, 0, 0); }
     // format selectors 0 = e4m3 for both operands; block scales 0 = the unscaled form of the instruction
+    __device__ static acc16_t sparse16(v4i a, v8i b, acc16_t c, int idx) { return __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(a, b, c, idx, 0, 0); }
     __device__ static acc_t dense(dfrag_t a, dfrag_t b, acc_t c) { return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0); }
 };
 template <> struct Mma<SS_BF16> {
     typedef v16f acc_t;
+    typedef v4f acc16_t;
     typedef v4i dfrag_t;
     static constexpr int ES = 2;
     static constexpr int DENSE_SUB = 32;
@@ -40,6 +45,7 @@ template <> struct Mma<SS_BF16> {
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v16bf, b), c, idx, 0, 0);
     }
+    __device__ static acc16_t sparse16(v4i a, v8i b, acc16_t c, int idx) { return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v16bf, b), c, idx, 0, 0); }
     __device__ static acc_t dense(dfrag_t a, dfrag_t b, acc_t c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
@@ -48,6 +54,7 @@ template <> struct Mma<SS_BF16> {
 
 template <> struct Mma<SS_FP16> {
     typedef v16f acc_t;
+    typedef v4f acc16_t;
     typedef v4i dfrag_t;
     static constexpr int ES = 2;
     static constexpr int DENSE_SUB = 32;
@@ -57,6 +64,7 @@ template <> struct Mma<SS_FP16> {
     {
         return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v16h, b), c, idx, 0, 0);
     }
+    __device__ static acc16_t sparse16(v4i a, v8i b, acc16_t c, int idx) { return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v16h, b), c, idx, 0, 0); }
     __device__ static acc_t dense(dfrag_t a, dfrag_t b, acc_t c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <utility>
 #include "slidesparse.h"
 
 #define SS_FORMAT_VERSION 2
@@ -39,6 +40,10 @@ inline ss_status launch_status()
 {
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_HIP;
 }
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <typename F, int... I> __device__ __forceinline__ void unroll_list(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void unroll(F&& f) { unroll_list(static_cast<F&&>(f), std::make_integer_sequence<int, N>{}); }
 
 // Workgroup ids go round-robin over the 8 XCDs (id mod 8).  Renumbers `total` workgroups so that each XCD's share is one
 // contiguous run of items: a bijection of [0, total) for any total.
