@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libslidesparse.so: argument marshalling only.
+"""Thin binding of libslidesparse.so: argument marshalling only, by ctypes and, for the calls of a forward pass, by the
+extension module _calls (csrc/py_calls.cpp).
 
 Every function has the name and argument order of its C entry point in
 include/slidesparse.h; tensors are torch CUDA tensors used purely as device
@@ -14,6 +15,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libslidesparse.so")
+CALLS_PATH = os.path.join(_PKG, "_calls.so")
 
 SS_I8, SS_FP8_E4M3, SS_BF16, SS_FP16 = 0, 1, 2, 3
 SS_IN_F32, SS_IN_BF16 = 0, 1
@@ -26,6 +28,7 @@ EXPORTS = ("slide_lifted_k", "slide_lifted_ld", "slide_packed_sizes", "slide_pru
            "ss_status_string", "slide_format_version")
 
 _lib = None
+_calls = None
 
 
 class SlideSparseError(RuntimeError):
@@ -36,11 +39,12 @@ class SlideSparseError(RuntimeError):
 
 def load():
     """Load the shared library (raises if it has not been built)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError(f"{LIB_PATH} not found: build it first (python -m paper_2603_05232_amd.build)")
+    for path in (LIB_PATH, CALLS_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} not found: build it first (python -m paper_2603_05232_amd.build)")
     lib = ctypes.CDLL(LIB_PATH)
     i64, i32, vp, sz = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t
     lib.slide_lifted_k.argtypes = [i64, i32]
@@ -73,7 +77,8 @@ def load():
     lib.ss_status_string.argtypes = [i32]
     lib.ss_status_string.restype = ctypes.c_char_p
     lib.slide_format_version.restype = i32
-    _lib = lib
+    from . import _calls as calls                     # linked against the library just loaded
+    _lib, _calls = lib, calls
     return lib
 
 
@@ -86,10 +91,12 @@ def _check(code: int, where: str) -> None:
         raise SlideSparseError(code, where)
 
 
-# Few-token calls are bound by the time between launches, most of which is spent here, so the helpers below do no more
-# than the call needs: addresses go to ctypes as plain integers (None is NULL), and the stream handle is read without
-# building a torch.cuda.Stream object (0.2 instead of 2.8 us; a launch itself is 2.8 us).
-# Quantisation + GEMM of 16 x 512 x 512: 21.7 -> 15.2 us on the host.
+# Few-token calls are bound by the time between launches, most of which is spent here.  The calls of a forward pass
+# (act_lift_quant and the sparse GEMMs) therefore go to the extension module first, which does plain calls (exact torch
+# tensors on the GPU, no active mode, no error) and answers None to any other; what follows is the general path, which also
+# raises the errors.  It does no more than the call needs either: addresses go to ctypes as plain integers (None is NULL), and
+# the stream handle is read without building a torch.cuda.Stream object (0.2 instead of 2.8 us; a launch itself is 2.8 us).
+# Quantisation + GEMM of 16 x 512 x 512 on the host: 15.3 us by the general path, 9.1 by the module.
 _STORAGE_DTYPE = {"i8": torch.int8, "fp8": torch.uint8, "bf16": torch.bfloat16, "fp16": torch.float16}
 _IN_CODE = {torch.float32: SS_IN_F32, torch.bfloat16: SS_IN_BF16}
 _UNSCALED = ("bf16", "fp16")
@@ -170,6 +177,11 @@ def slide_decompose_canonical(Wq: torch.Tensor, N: int, dtype: str):
 
 def act_lift_quant(X: torch.Tensor, N: int, dtype: str, out=None, s_x=None):
     """X[M,K] fp32/bf16 (row stride allowed) -> (X_lifted[M,Kld], s_x[M] or None)."""
+    if _calls is None:
+        load()
+    done = _calls.act_lift_quant(X, N, dtype, out, s_x)
+    if done is not None:
+        return done
     M, K = X.shape
     ldx, inner = X.stride()
     assert X.is_cuda and inner == 1
@@ -192,6 +204,11 @@ def slide_gemm_workspace_bytes(M: int, O: int, K: int, dtype: str) -> int:
 
 def slide_sparse_gemm(X_lifted, s_x, w_vals, w_meta, s_w, O: int, dtype: str, out=None, workspace=None):
     """Y[M,O] bf16 = epilogue(X_lifted[M,Kld] . W'^T); workspace: optional uint8 device tensor (slide_sparse_gemm_ws)."""
+    if _calls is None:
+        load()
+    done = _calls.slide_sparse_gemm(X_lifted, s_x, w_vals, w_meta, s_w, O, dtype, out, workspace)
+    if done is not None:
+        return done
     M, Kp = X_lifted.shape
     assert X_lifted.is_contiguous()
     if out is None:
@@ -246,6 +263,11 @@ def slide_sparse_gemm_fused(Xq, s_x, w_vals, w_meta, s_w, O: int, K: int, N: int
     """Y[M,O] bf16 = epilogue(Psi(Xq[M, :K]) . W'^T) from unlifted quantised activations (row stride = Xq.stride(0)).
     workspace: optional uint8 device tensor (slide_gemm_workspace_bytes(M, O, K, dtype) bytes) that lets the kernels for
     small and medium M split the k range."""
+    if _calls is None:
+        load()
+    done = _calls.slide_sparse_gemm_fused(Xq, s_x, w_vals, w_meta, s_w, O, K, N, dtype, out, workspace)
+    if done is not None:
+        return done
     M, width = Xq.shape
     ldx, inner = Xq.stride()
     assert Xq.is_cuda and inner == 1 and width >= K
