@@ -7,14 +7,19 @@
 // the algorithmic minimum: K input elements in, K' output elements + one scale out.
 #include "ss_common.h"
 #include "quant_common.h"
+#include <type_traits>
 
 namespace ss {
 
-// MAXV > 0: vector loads, row kept in registers (needs K <= MAXV * THREADS * VecN, 16-byte
-// aligned rows).  MAXV == 0: scalar loads, second pass re-reads the row.  Long rows take more
+// MAXV > 0: vector loads, row kept in registers.  MAXV == 0: scalar loads, second pass re-reads the
+// row (rows too long for the registers of a workgroup).  Long rows take more
 // threads per token rather than more registers per thread: the loads of a token are all in
 // flight at once either way, but fewer registers leave room for more tokens per compute unit.
-template <typename TIN, int OUT, int MAXV, int THREADS>
+// RAGGED: the rows start off a 16-byte line or end within one.  The 16-byte lines that hold the row are
+// loaded as they lie, those at its two ends element by element; element k has its code in LDS at
+// off + k, off being the row's offset from its first line, and the gather shifts accordingly.  (777 x 5003 fp32 to fp16,
+// 8:10, with the GEMM behind it: 68.6 us a pass with scalar loads in two passes, 65.9 like this.)
+template <typename TIN, int OUT, int MAXV, int THREADS, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restrict__ X, int64_t ldx, int K, int N,
                                                                 uint8_t* __restrict__ XL, float* __restrict__ s_x, int Kp, int Kz, uint32_t inv_nw1)
 {
@@ -28,17 +33,28 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     const int t = threadIdx.x;
     typedef InVec<TIN> IV;
     typename IV::V v[MAXV > 0 ? MAXV : 1];
-    const int nvec = K / IV::N;
+    const int off = RAGGED ? (int)(((uintptr_t)x / sizeof(TIN)) % IV::N) : 0;
+    const int nvec = RAGGED ? (off + K + IV::N - 1) / IV::N : K / IV::N;
+    auto whole = [&](int idx) { return !RAGGED || (idx * IV::N >= off && (idx + 1) * IV::N <= off + K); };      // all of the line belongs to the row
 
     // ---- pass 1: absmax (Alg. 1, dynamic quantisation scale)
     float amax = 0.0f;
     if constexpr (MAXV > 0) {
-        const typename IV::V* xv = reinterpret_cast<const typename IV::V*>(x);
+        const typename IV::V* xv = reinterpret_cast<const typename IV::V*>(x - off);
 #pragma unroll
         for (int i = 0; i < MAXV; ++i) {
             const int idx = t + i * THREADS;
             if (idx < nvec) {
-                v[i] = xv[idx];
+                if (whole(idx)) v[i] = xv[idx];
+                else {
+                    TIN part[IV::N];
+#pragma unroll
+                    for (int e = 0; e < IV::N; ++e) {
+                        const int k = idx * IV::N + e - off;
+                        part[e] = k >= 0 && k < K ? x[k] : (TIN)0;
+                    }
+                    v[i] = __builtin_bit_cast(typename IV::V, part);
+                }
                 if constexpr (OUT < 2) {
                     float f[IV::N]; IV::unpack(v[i], f);
 #pragma unroll
@@ -60,7 +76,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
 
     // ---- N = 2 from registers: plain quantisation has no windows to gather, so the quantised vectors go straight to
     // global memory (4 or 8 bytes per lane, contiguous across the wavefront) without the round trip through LDS
-    if constexpr (MAXV > 0) {
+    if constexpr (MAXV > 0 && !RAGGED) {
         if (N == 2) {
             constexpr int OW = IV::N * ES / 4;           // output dwords per input vector: 1 (fp32 -> 8 bit), 2, 2 or 4
             uint32_t* out32 = reinterpret_cast<uint32_t*>(XL + m * (int64_t)Kp * ES);
@@ -89,12 +105,22 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     }
 
     // ---- pass 2a: quantise every source element once, into LDS
+    typedef std::conditional_t<ES == 1, uint8_t, uint16_t> code_t;
+    code_t* const codes = reinterpret_cast<code_t*>(lds);
     if constexpr (MAXV > 0) {
 #pragma unroll
         for (int i = 0; i < MAXV; ++i) {
             const int idx = t + i * THREADS;
             if (idx < nvec) {
                 float f[IV::N]; IV::unpack(v[i], f);
+                if (!whole(idx)) {                       // only what belongs to the row: the zeros behind it are another thread's
+#pragma unroll
+                    for (int e = 0; e < IV::N; ++e) {
+                        const int k = idx * IV::N + e - off;
+                        if (k >= 0 && k < K) codes[off + k] = (code_t)quant1<OUT>(f[e], r);
+                    }
+                    continue;
+                }
                 if constexpr (ES == 1) {
 #pragma unroll
                     for (int w = 0; w < IV::N / 4; ++w) lds[idx * (IV::N / 4) + w] = quant4<OUT>(f[4 * w], f[4 * w + 1], f[4 * w + 2], f[4 * w + 3], r);
@@ -106,21 +132,9 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
             }
         }
     } else {
-        if constexpr (ES == 1) {
-            uint8_t* l8 = reinterpret_cast<uint8_t*>(lds);
-            for (int k = t; k < K; k += THREADS) l8[k] = (uint8_t)quant1<OUT>(load_scalar(x + k), r);
-        } else {
-            uint16_t* l16 = reinterpret_cast<uint16_t*>(lds);
-            for (int k = t; k < K; k += THREADS) l16[k] = (uint16_t)quant1<OUT>(load_scalar(x + k), r);
-        }
+        for (int k = t; k < K; k += THREADS) codes[k] = (code_t)quant1<OUT>(load_scalar(x + k), r);
     }
-    if constexpr (ES == 1) {
-        uint8_t* l8 = reinterpret_cast<uint8_t*>(lds);
-        for (int k = K + t; k < Kz; k += THREADS) l8[k] = 0;
-    } else {
-        uint16_t* l16 = reinterpret_cast<uint16_t*>(lds);
-        for (int k = K + t; k < Kz; k += THREADS) l16[k] = 0;
-    }
+    for (int k = K + t; k < Kz; k += THREADS) codes[off + k] = 0;
     __syncthreads();
 
     // ---- pass 2b: output-oriented gather of the lifted windows (window j reads b = 2N g + 2 l);
@@ -139,16 +153,17 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
             for (int i = 0; i < 4; ++i) {
                 w[i] = 0;
                 if (g < ng) {
-                    const int b = 2 * N * g + 2 * l;
+                    const int b = 2 * N * g + 2 * l + off;
                     const uint32_t lo = lds[b >> 2], hi = lds[(b >> 2) + 1];
-                    w[i] = (b & 2) ? ((lo >> 16) | (hi << 16)) : lo;
+                    if constexpr (RAGGED) w[i] = __builtin_amdgcn_alignbyte(hi, lo, (uint32_t)b & 3);
+                    else w[i] = (b & 2) ? ((lo >> 16) | (hi << 16)) : lo;
                 }
                 if (++l == nw1) { l = 0; ++g; }
             }
             out[c] = make_uint4(w[0], w[1], w[2], w[3]);
         }
     } else {
-        // 16-bit elements: a window is 8 bytes = elements b..b+3, b even -> two aligned dwords
+        // 16-bit elements: a window is 8 bytes = elements b..b+3: two aligned dwords, or, b odd (RAGGED only), parts of three
         for (int c = t; c < nwin / 2; c += THREADS) {
             int j = 2 * c, g = block_of(j), l = j - g * nw1;
             uint32_t w[4];
@@ -156,8 +171,13 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
             for (int i = 0; i < 2; ++i) {
                 w[2 * i] = 0; w[2 * i + 1] = 0;
                 if (g < ng) {
-                    const int b = 2 * N * g + 2 * l;
+                    const int b = 2 * N * g + 2 * l + off;
                     w[2 * i] = lds[b >> 1]; w[2 * i + 1] = lds[(b >> 1) + 1];
+                    if constexpr (RAGGED) {
+                        const uint32_t sh = 2 * ((uint32_t)b & 1), w2 = lds[(b >> 1) + 2];
+                        w[2 * i] = __builtin_amdgcn_alignbyte(w[2 * i + 1], w[2 * i], sh);
+                        w[2 * i + 1] = __builtin_amdgcn_alignbyte(w2, w[2 * i + 1], sh);
+                    }
                 }
                 if (++l == nw1) { l = 0; ++g; }
             }
@@ -177,20 +197,27 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const int ES = OUT >= 2 ? 2 : 1;
     const int Kp = (int)lifted_ld(K, N, ES);
     const int Kz = (int)lift_lds_elems(K, N, ES);
-    const size_t lds_bytes = (size_t)Kz * ES;
-    const bool vec_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
-    const int64_t nvec = K / IV::N;                           // 16-byte vectors per row
+    const bool line_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
+    const bool element_ok = (uintptr_t)X % sizeof(TIN) == 0;
+    // a ragged row: up to IV::N - 1 elements ahead of it in its first line, and as many codes more in LDS
+    const int64_t nvec = line_ok ? K / IV::N : (K + 2 * IV::N - 2) / IV::N;      // 16-byte vectors per row, at most
+    const size_t lds_bytes = (size_t)Kz * ES, ragged_bytes = lds_bytes + IV::N * ES;
     dim3 grid((unsigned)M);
     const uint32_t inv = N > 2 ? (uint32_t)(((1ull << 32) + N - 2) / (N - 1)) : 0u;
     const TIN* x = static_cast<const TIN*>(X);
     uint8_t* xl = static_cast<uint8_t*>(XL);
-#define SS_LQ(MAXV, T) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T>), grid, dim3(T), lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
-    if (vec_ok && nvec <= 4 * 256) SS_LQ(4, 256);
-    else if (vec_ok && nvec <= 4 * 512) SS_LQ(4, 512);
-    else if (vec_ok && nvec <= 5 * 1024) SS_LQ(5, 1024);
-    else if (vec_ok && nvec <= 10 * 1024) SS_LQ(10, 1024);
-    else if (vec_ok && nvec <= 20 * 1024) SS_LQ(20, 1024);
-    else SS_LQ(0, 256);
+#define SS_LQ(MAXV, T, RAGGED) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED>), grid, dim3(T), RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
+#define SS_LQ_ROWS(RAGGED)                             \
+    if (nvec <= 4 * 256) SS_LQ(4, 256, RAGGED);        \
+    else if (nvec <= 4 * 512) SS_LQ(4, 512, RAGGED);   \
+    else if (nvec <= 5 * 1024) SS_LQ(5, 1024, RAGGED); \
+    else if (nvec <= 10 * 1024) SS_LQ(10, 1024, RAGGED); \
+    else SS_LQ(20, 1024, RAGGED);
+    // 64: the kernel's small reduction buffer
+    if (!element_ok || nvec > 20 * 1024 || (!line_ok && ragged_bytes + 64 > 64 * 1024)) SS_LQ(0, 256, false);
+    else if (line_ok) { SS_LQ_ROWS(false) }
+    else { SS_LQ_ROWS(true) }
+#undef SS_LQ_ROWS
 #undef SS_LQ
     return launch_status();
 }
