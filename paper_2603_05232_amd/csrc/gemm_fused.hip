@@ -63,17 +63,6 @@ constexpr int F_SX_OFF = F_SW_OFF + BO * 4;
 constexpr int F_LDS = F_SX_OFF + BT * 4;              // 158 KB
 static_assert(F_LDS <= 160 * 1024, "LDS budget");
 
-// Waits for this wavefront's loads: mode 0 not at all, 1 until at most N are in flight, 2 for all.  The scalar branch is
-// inside the statement, so that the code around it stays one block.
-template <int N> __device__ inline void wait_vm_mode(int mode)
-{
-    asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 2f\n\ts_cmp_eq_u32 %0, 1\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(0)\n1:\n\ts_waitcnt vmcnt(%1)\n2:"
-                 ::"s"(mode), "n"(N) : "memory", "scc");
-}
-
-__device__ inline int place(int chunk) { return chunk ^ ((chunk >> 2) << 1); }      // its own inverse
-__device__ const uint4 no_values[64] = {};            // 1 KB of stored values for the super-unit that an odd row lacks
-
 template <int DT>
 __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
                                                       const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U,
@@ -338,7 +327,8 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     const ss_plan p = plan_gemm(SS_KIND_FUSED, M, O, U, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_fused_mid(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
-    // channels [0, p.tile_o) on 256 x 256 tiles, the others on 128 x 128 tiles
+    if (p.path == SS_PATH_NARROW) return launch_sparse_fused_narrow(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
+    // channels [0, p.tile_o) on 256 x 256 tiles, the others on 128 x 128 or 128 x 256 tiles
     ss_status st = SS_ERR_DTYPE;
 #define SS_F(DT) launch_fused<DT>(Xq, s_x, w_vals, w_meta, s_w, M, p.tile_o, U, ldxb, Y, ldy, hs)
     switch (dtype) {
@@ -350,8 +340,12 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
 #undef SS_F
     if (st != SS_OK || p.tile_o == O) return st;
     const int64_t row = (int64_t)U * 3 * FRAG_KB;        // lifted bytes of a weight row
-    return launch_sparse_fused_mid(Xq, s_x, static_cast<const uint8_t*>(w_vals) + p.tile_o * (row / 2), static_cast<const uint8_t*>(w_meta) + p.tile_o * (row / 8),
-                                   s_w ? s_w + p.tile_o : s_w, M, O - p.tile_o, U, ldxb, dtype, static_cast<uint16_t*>(Y) + p.tile_o, ldy, nullptr, 1, hs);
+    const uint8_t *const rest_vals = static_cast<const uint8_t*>(w_vals) + p.tile_o * (row / 2), *const rest_meta = static_cast<const uint8_t*>(w_meta) + p.tile_o * (row / 8);
+    const float* const rest_s_w = s_w ? s_w + p.tile_o : s_w;
+    uint16_t* const rest_Y = static_cast<uint16_t*>(Y) + p.tile_o;
+    const int64_t rest = O - p.tile_o;
+    if (narrow_pays(M, rest, cu_count())) return launch_sparse_fused_narrow(Xq, s_x, rest_vals, rest_meta, rest_s_w, M, rest, U, ldxb, dtype, rest_Y, ldy, hs);
+    return launch_sparse_fused_mid(Xq, s_x, rest_vals, rest_meta, rest_s_w, M, rest, U, ldxb, dtype, rest_Y, ldy, nullptr, 1, hs);
 }
 
 extern "C" ss_status slide_sparse_gemm_fused(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,

@@ -81,6 +81,14 @@ template <int N> __device__ inline void wait_vmcnt()
     asm volatile("" ::: "memory");
 }
 
+// Waits for this wavefront's loads: mode 0 not at all, 1 until at most N are in flight, 2 for all.  The scalar branch is
+// inside the statement, so that the code around it stays one block.
+template <int N> __device__ inline void wait_vm_mode(int mode)
+{
+    asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 2f\n\ts_cmp_eq_u32 %0, 1\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(0)\n1:\n\ts_waitcnt vmcnt(%1)\n2:"
+                 ::"s"(mode), "n"(N) : "memory", "scc");
+}
+
 // all LDS reads of this wave have returned (loads in flight are left alone)
 __device__ inline void wait_lgkm0()
 {

@@ -149,6 +149,9 @@ ss_status launch_sparse_fused_skinny(const void* Xq, const float* s_x, const voi
 ss_status launch_dense_skinny(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                               void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
 
+// Tiles of 128 channels x 256 tokens for unlifted activations (gemm_fused_narrow.hip), operands as for the fused kernels below.
+ss_status launch_sparse_fused_narrow(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                                     int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 
 // The 256 x 256 tile kernels (gemm.hip).
 ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
@@ -173,6 +176,7 @@ ss_status launch_dense_mid(const void* Xq, const float* s_x, const void* Wq, con
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes);
 size_t mid_workspace_bytes(ss_kind kind, int64_t M, int64_t O, int S);
 inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M + 127) / 128); }
+inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M + 255) / 256); }
 
 // Which kernel family a GEMM of M tokens x O channels over `units` 128-byte k units runs on, and in how many k
 // ranges (S > 1 only with a workspace).  Measured, INT8 6:8 unless said, weights from HBM, us:
@@ -192,20 +196,29 @@ inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M 
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
 //             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
+// Fused, more 128 x 128 tiles than compute units and at most one tile of 128 channels x 256 tokens for each: those
+//             (gemm_fused_narrow.hip).  Time over that of the paths above, INT8 and bf16, 4 to 64 units, M = 200 .. 4096,
+//             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  With as many 128 x 128 tiles as compute units or
+//             fewer, those (4096 -> 4096 at M = 1024: 23.2 against 26.2); with more than one 128 x 256 tile per compute unit 256 x 256 tiles
+//             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
-enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_TILE };
+enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE };
 struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 tiles
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
 // unit, the rest goes to those (M = 8192, 3584 -> 4608, 2.25 rounds: bf16 210 -> 194 us, INT8 120 -> 116).  With two of them per
-// compute unit (half a round) the two sides are level or worse: half a round runs at a higher clock (INT8 3584 -> 37888, 18.5
-// rounds: 797 against 835 us; 4096 -> 6144 at M = 4096: 97 against 102).
-inline int64_t tile_channels(int64_t M, int64_t O, int64_t cus)
+// compute unit (half a round) the two sides are level or worse: half a round runs at a higher clock (lifted INT8 4096 -> 6144 at M =
+// 4096: 97 against 102).  Unlifted rows have tiles of 128 x 256 for that: one per compute unit, 16 units
+// and more (time over 256 x 256 tiles throughout, INT8 and bf16, M = 777 .. 8192, rests of 0.3 to 0.5 round: 28 units 0.94 .. 1.00, 64 units 0.92 .. 0.97;
+// 8 units, where the second launch costs more than the rest, 1.01 .. 1.05).
+inline int64_t tile_channels(ss_kind kind, int64_t M, int64_t O, int64_t units, int64_t cus)
 {
     const int64_t tiles_o = (O + 255) / 256, tiles_t = (M + 255) / 256, rounds = tiles_o * tiles_t / cus, c = rounds * cus / tiles_t;
-    return c > 0 && c < tiles_o && mid_tiles(M, O - c * 256) <= cus ? c * 256 : O;
+    const int64_t rest = O - c * 256;
+    return c > 0 && c < tiles_o && (mid_tiles(M, rest) <= cus || (kind == SS_KIND_FUSED && units >= 16 && narrow_tiles(M, rest) <= cus)) ? c * 256 : O;
 }
+inline bool narrow_pays(int64_t M, int64_t O, int64_t cus) { return mid_tiles(M, O) > cus && narrow_tiles(M, O) <= cus; }
 inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)
 {
     if (kind == SS_KIND_DENSE) {
@@ -217,9 +230,10 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
     if (M > 64) {
+        if (kind == SS_KIND_FUSED && narrow_pays(M, O, cus)) return {SS_PATH_NARROW, 1};
         const bool many = 4 * tiles > 7 * cus;                          // more than 448
         const int64_t long_row = kind == SS_KIND_FUSED ? (many ? 24 : 12) : (many ? 48 : 24);
-        if (tiles > 2 * cus || (4 * tiles > 5 * cus && units < long_row)) return {SS_PATH_TILE, 1, tile_channels(M, O, cus)};
+        if (tiles > 2 * cus || (4 * tiles > 5 * cus && units < long_row)) return {SS_PATH_TILE, 1, tile_channels(kind, M, O, units, cus)};
         return {SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
     }
     const int S = mid_splits(kind, M, O, units, ws_bytes);

@@ -35,6 +35,10 @@ __device__ inline bool tile_of_round(int round, int tiles_o, int tiles_t, int& t
     return true;
 }
 
+// The fused-lifting kernels (gemm_fused.hip, gemm_fused_narrow.hip) store chunk c of a token row at place(c) ^ swz(row), see there.
+__device__ inline int place(int chunk) { return chunk ^ ((chunk >> 2) << 1); }      // its own inverse
+__device__ const uint4 no_values[64] = {};            // 1 KB of stored values for the super-unit that an odd row lacks
+
 // ---- epilogue: Y = bf16((float(acc) * s_x) * s_w), staged through LDS for coalesced stores ------
 
 // Staging holds 32 tokens x 128 channels of bf16 per wavefront at a time: rows of 256 bytes, 8 KB per wavefront.  No row
