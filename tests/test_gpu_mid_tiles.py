@@ -117,3 +117,16 @@ def test_rest_of_a_round(dtype, N, fused):
     es = 1 if dtype == "i8" else 2
     K = 3 * 128 // es
     _linear(1100, 13556, K if fused else K * N // (2 * (N - 1)) - 3, N, dtype, fused, False, N)
+
+
+# tiles of 32 tokens with two groups of wavefronts (at least two units in a range): ranges of odd and even length, one range
+# (192 panels) and several (few panels and long rows)
+@pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("M,O,units,with_ws", [(1, 192 * 128 - 5, 2, False), (32, 192 * 128, 3, False), (17, 130 * 128, 9, False),
+                                               (1, 300, 131, True), (32, 1000, 160, True), (9, 512, 97, True)])
+def test_two_groups_of_wavefronts(dtype, fused, M, O, units, with_ws):
+    N = 4
+    es = 1 if dtype in ("i8", "fp8") else 2
+    K = 128 * units // es if fused else 128 * units // es * N // (2 * (N - 1)) // (2 * N) * (2 * N)
+    _linear(M, O, max(K, 2 * N), N, dtype, fused, with_ws, units)
