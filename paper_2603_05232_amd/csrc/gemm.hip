@@ -1,20 +1,20 @@
-// slide_sparse_gemm and dense_gemm for gfx950.
+// dense_gemm's 256 x 256 tile kernel for gfx950, and the entry points of slide_sparse_gemm (tiles in gemm_lifted.hip) and
+// dense_gemm.
 //
-// Tile engine shared by both kernels: a persistent 512-thread workgroup (8 wavefronts, two per SIMD)
+// Tile engine: a persistent 512-thread workgroup (8 wavefronts, two per SIMD)
 // owns a 256 (output channels) x 256 (tokens) tile of Y at a time; wavefront (wo, wt) accumulates the
 // 128 x 64 sub-tile [wo*128, +128) x [wt*64, +64) as 4 x 2 blocks of a 32x32 matrix instruction.  The
-// weights are the A operand (sparse for slide_sparse_gemm: the 32x32 sparse instructions take 16 bytes
-// of stored values + one index word per lane), tokens are the B operand.  All k extents are counted in
-// bytes of a row, so INT8, FP8 (e4m3) and BF16 share the kernels and differ in the matrix instruction,
+// weights are the A operand, tokens are the B operand.  All k extents are counted in
+// bytes of a row, so INT8, FP8 (e4m3) and BF16 share the kernel and differ in the matrix instruction,
 // the accumulator type and the epilogue.
 //
 // Data movement.  Operand tiles go HBM/L2 -> LDS with direct-to-LDS loads (no registers hold data in
-// flight) into rings of units; token rows are fetched as whole 128-byte lines and XOR-swizzled at
+// flight) into rings of units; rows are fetched as whole 128-byte lines and XOR-swizzled at
 // 16-byte granularity (applied on the global-address side, because a direct load writes
 // lane-contiguous LDS) so the 32 lanes of an operand read hit all 64 banks.
 //
-// Schedule.  The k loop advances in sub-steps of one matrix-instruction depth (64 lifted columns
-// sparse, 32 columns dense): eight matrix instructions per wavefront, with the LDS reads of the next
+// Schedule.  The k loop advances in sub-steps of one matrix-instruction depth (32 columns, fp8 64):
+// eight matrix instructions per wavefront, with the LDS reads of the next
 // sub-step's operands (double-buffered registers) and a share of the direct loads of a later unit
 // placed one by one between them -- a wavefront issues in order, and an LDS read or a load that has to
 // wait for room in its queue keeps the matrix instructions behind it from issuing, so neither kind is
@@ -242,181 +242,6 @@ __global__ __launch_bounds__(G_THREADS) void k_dense(const uint8_t* __restrict__
     }
 }
 
-// ---- sparse over the lifted width: Y = X' . W'^T, W' packed 2:4 -------------------------------------
-// Sub-step = 64 lifted bytes (one sparse matrix instruction deep); unit = two sub-steps = 128 lifted
-// bytes.  Ring of three units; a unit is a 32 KB token tile (128-byte rows), 16 KB of weight values
-// [panel 2][sub-step 2][fragment 4][lane 64][16 B] and 4 KB of index words
-// [panel 2][sub-step 2][lane 64][fragment 4][4 B], both in the order slide_decompose stores them.
-// Kpb = bytes per lifted row.
-constexpr int S_RING = 3;
-constexpr int S_B_UNIT = BT * ROWB;                 // 32 KB
-constexpr int S_AV_UNIT = BO * 64;                  // 16 KB
-constexpr int S_AM_UNIT = BO * 16;                  // 4 KB
-constexpr int S_AV_OFF = S_RING * S_B_UNIT;
-constexpr int S_AM_OFF = S_AV_OFF + S_RING * S_AV_UNIT;
-constexpr int S_SW_OFF = S_AM_OFF + S_RING * S_AM_UNIT;
-constexpr int S_LDS = S_SW_OFF + 2 * SW_BYTES;      // 158 KB
-constexpr int EP_BYTES = G_WAVES * EP_WAVE_BYTES;   // 64 KB of staging
-static_assert(S_LDS <= 160 * 1024 && EP_BYTES <= 2 * S_B_UNIT && EP_WAVE_BYTES * 4 <= D_UNIT, "LDS budget");
-constexpr int S_LPU = ROW_LOADS + 2 + 2;            // direct loads per wavefront and unit: token rows, values, index words
-
-// weight values single-buffered; index words and token fragments double-buffered by sub-step parity
-struct SparseFrags { v4i a[4]; v4i idx[2]; v8i b[2][NBF]; };
-
-template <int DT>
-__global__ __launch_bounds__(G_THREADS) void k_sparse(const uint8_t* __restrict__ XL, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
-                                                      const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O,
-                                                      int64_t Kpb, uint16_t* __restrict__ Y, int64_t ldy, int tiles_o, int tiles_t)
-{
-    typedef Mma<DT> MM;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave id in an SGPR
-    const int wo = wave & 1, wt = wave >> 1;
-    const int n = lane & 31, qb = lane >> 5;
-    const int U = (int)(Kpb / (2 * FRAG_KB));         // units
-    const int64_t npanels = (O + PANEL - 1) / PANEL;
-    int brow[NBF];
-#pragma unroll
-    for (int bb = 0; bb < NBF; ++bb) brow[bb] = wt * (32 * NBF) + bb * 32 + n;
-
-    // Per-tile state of the loaders.  It is set up for the next tile before the current tile's epilogue, so that
-    // the first unit of the next tile is already in flight while the results are written out.
-    RowTileLoader lb;
-    const uint8_t *av_src = nullptr, *am_src = nullptr;
-    int64_t o_blk = 0, t_blk = 0;
-    const int piece = (wave & 3) * 2;
-    uint8_t* const av_dst = smem + S_AV_OFF + (wave >> 2) * 8192 + piece * 1024;
-    uint8_t* const am_dst = smem + S_AM_OFF + (wave >> 2) * 2048 + piece * 256;
-    const uint32_t lane16 = lane * 16, lane4 = lane * 4;
-    // Packed weights: per 128-channel panel the two sub-steps of a unit are contiguous, 8 KB of values
-    // and 2 KB of index words.  Waves 0..3 fetch panel 2*to, waves 4..7 panel 2*to+1 (clamped to the last
-    // panel; a clamped panel only feeds rows that are never stored): two 1 KB pieces of values (16 bytes
-    // a lane) and two 256-byte pieces of index words (4 bytes a lane) each.
-    auto setup_tile = [&](int to, int tt) {
-        o_blk = (int64_t)to * BO;
-        t_blk = (int64_t)tt * BT;
-        lb.init(XL, Kpb, t_blk, M, wave);
-        int64_t panel = (int64_t)to * 2 + (wave >> 2);
-        panel = panel < npanels ? panel : npanels - 1;
-        av_src = w_vals + panel * U * 8192 + piece * 1024;     // wave-uniform
-        am_src = w_meta + panel * U * 2048 + piece * 256;
-    };
-    // direct load number j (0..7) of this wavefront for unit u: token rows, values, token rows, index words, twice
-    auto issue_part = [&](int u, int slot, int j) {
-        const int half = j >> 2;
-        if (!(j & 1)) lb.issue_one(j >> 1, (int64_t)u * ROWB, smem + slot * S_B_UNIT, wave);
-        else if ((j & 3) == 1) lds_dma16(av_src + (int64_t)u * 8192 + half * 1024, lane16, av_dst + slot * S_AV_UNIT + half * 1024);
-        else lds_dma4(am_src + (int64_t)u * 2048 + half * 256, lane4, am_dst + slot * S_AM_UNIT + half * 256);
-    };
-    auto issue = [&](int u, int slot) {
-#pragma unroll
-        for (int j = 0; j < S_LPU; ++j) issue_part(u, slot, j);
-    };
-    // one more direct load per wavefront with unit 0 of a tile: its channel scales (4 bytes a lane; waves 4..7
-    // repeat what waves 0..3 fetch, so that every wavefront has the same number of loads in flight)
-    auto issue_scales = [&](int parity) {
-        if constexpr (MM::SCALED) {
-            const int64_t o_first = o_blk + (wave & 3) * 64, left = O - 1 - o_first;     // clamp to the last channel
-            const int left32 = left > 63 ? 63 : (int)left, ln = fresh_lane();
-            const uint32_t oc = left32 < 0 ? 0u : (uint32_t)(ln < left32 ? ln : left32);
-            lds_dma4(reinterpret_cast<const uint8_t*>(s_w + (left < 0 ? O - 1 : o_first)), oc * 4, smem + S_SW_OFF + parity * SW_BYTES + (wave & 3) * 256);
-        }
-    };
-
-    // Unit u of a tile lives in ring slot (u + 2) % 3: the epilogue's staging area is the token part of
-    // slots 0 and 1, so slot 2 (and the weight parts of all slots) can take the next tile's first unit
-    // while the epilogue runs.
-    int to, tt;
-    bool have = tile_of_round(0, tiles_o, tiles_t, to, tt);
-    if (have) { setup_tile(to, tt); issue(0, 2); issue_scales(0); }
-    for (int round = 0; have; ++round) {
-        typename MM::acc_t acc[4][NBF];
-        zero_acc(acc);
-        SparseFrags R;
-        // one operand read of half h of the unit in ring slot `slot`: parts 0..3 weight values, 4 their
-        // index words, 5..8 the two halves of the two token fragments
-        auto read_part = [&](int slot, int h, int part) {
-            if (part < 4) R.a[part] = *reinterpret_cast<const v4i*>(smem + S_AV_OFF + slot * S_AV_UNIT + ((wo * 2 + h) * 4 + part) * 1024 + lane16);
-            else if (part == 4) R.idx[h] = *reinterpret_cast<const v4i*>(smem + S_AM_OFF + slot * S_AM_UNIT + (wo * 2 + h) * 1024 + lane16);
-            else {
-                const int bb = (part - 5) >> 1, hh = (part - 5) & 1;
-                const v4i v = *tile_chunk(smem + slot * S_B_UNIT, brow[bb], 4 * h + 2 * qb + hh);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) R.b[h][bb][4 * hh + e] = v[e];
-            }
-        };
-        // Sub-step h^1 of a unit: eight matrix instructions, with the nine operand reads of the following
-        // sub-step (half h of the unit in `slot`) and, for loads = 1 / 2, the first / second four direct
-        // loads of unit `lunit` (into ring slot lslot) placed one by one behind them.  A weight fragment is
-        // used by two consecutive instructions and refilled right behind the second; index words and token
-        // fragments of the following sub-step go to the other buffer.
-        auto sub_step = [&](int slot, int h, auto prefetch, auto loads, int lunit, int lslot) {
-            const int c = h ^ 1;                      // buffers of the sub-step being computed
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 4 * NBF; ++i) {
-                acc[i / NBF][i % NBF] = MM::sparse(R.a[i / NBF], R.b[c][i % NBF], acc[i / NBF][i % NBF], R.idx[c][i / NBF]);
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (decltype(loads)::value > 0) {
-                    if (i & 1) { issue_part(lunit, lslot, 4 * (decltype(loads)::value - 1) + (i >> 1)); __builtin_amdgcn_sched_barrier(0); }
-                }
-                if constexpr (decltype(prefetch)::value) {
-                    if (i & 1) read_part(slot, h, i >> 1); else read_part(slot, h, 5 + (i >> 1));
-                    if (i == 1) read_part(slot, h, 4);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        };
-
-        // The two wavefronts of a SIMD run freely against each other; the workgroup meets once per unit.
-        // Before that barrier a wavefront holds the operands of the unit's second sub-step in registers and
-        // has seen its own loads of the next unit land; after it nobody reads the unit's ring slot any more,
-        // so the unit three ahead is requested into it, and the next unit is visible to everybody.
-        if (round > 0) wg_barrier();                  // epilogue staging of the previous tile has been read out
-        if (U > 1) issue(1, 0);
-        if (U > 2) issue(2, 1);
-        // unit 0 was requested before the previous epilogue, whose stores sit between it and units 1 and 2
-        if (U > 2) wait_vmcnt<2 * S_LPU>(); else if (U > 1) wait_vmcnt<S_LPU>(); else wait_vmcnt<0>();
-        wg_barrier();                                 // unit 0 (and the channel scales) are published
-#pragma unroll
-        for (int part = 0; part < 9; ++part) read_part(2, 0, part);
-        constexpr std::true_type prefetch{};
-        int u = 0, slot = 2;
-        sub_step(slot, 1, prefetch, no_loads, 0, 0);
-        for (; u + 3 < U; ++u) {                      // units u+1 and u+2 are in flight, unit u+3 gets requested
-            const int nslot = slot == S_RING - 1 ? 0 : slot + 1;
-            wait_vmcnt<S_LPU>();                      // own loads of unit u+1 have landed, own reads of unit u have returned
-            wg_barrier();
-            sub_step(nslot, 0, prefetch, first_half, u + 3, slot);
-            sub_step(nslot, 1, prefetch, second_half, u + 3, slot);
-            slot = nslot;
-        }
-        for (; u + 1 < U; ++u) {                      // nothing left to request
-            const int nslot = slot == S_RING - 1 ? 0 : slot + 1;
-            wait_vmcnt<0>();
-            wg_barrier();
-            sub_step(nslot, 0, prefetch, no_loads, 0, 0);
-            sub_step(nslot, 1, prefetch, no_loads, 0, 0);
-            slot = nslot;
-        }
-        // this sub-tile of Y and its token scales (requested here: they arrive behind the last matrix instructions)
-        const int64_t o_sub = o_blk + wo * 128, t_sub = t_blk + wt * (32 * NBF);
-        const int64_t rows = M - t_sub, cols = O - o_sub;          // <= 0: nothing of this sub-tile exists
-        const bool any = rows > 0 && cols > 0;
-        const int rows_left = any ? (int)(rows > 64 ? 64 : rows) : 0, cols_left = any ? (int)(cols > 128 ? 128 : cols) : 0;
-        float sx[NBF];
-        load_token_scales<MM::SCALED>(sx, MM::SCALED && any ? s_x + t_sub : s_x, rows_left);
-        sub_step(slot, 0, std::false_type{}, no_loads, 0, 0);
-        wg_barrier();                                 // every wave is done with the operand tiles: LDS becomes staging
-        uint16_t* const Y_sub = any ? Y + t_sub * ldy + o_sub : Y;
-        settle(sx);                                   // the token scales have arrived: no wait for them behind the loads requested next
-        have = tile_of_round(round + 1, tiles_o, tiles_t, to, tt);
-        if (have) { setup_tile(to, tt); issue(0, 2); issue_scales((round + 1) & 1); }
-        store_tile<MM::SCALED>(acc, sx, reinterpret_cast<const float*>(smem + S_SW_OFF + (round & 1) * SW_BYTES) + wo * 128, Y_sub,
-                                   (uint32_t)ldy, rows_left, cols_left, smem + wave * EP_WAVE_BYTES);
-    }
-}
-
 }  // namespace ss
 
 using namespace ss;
@@ -451,18 +276,7 @@ static ss_status launch_dense(const void* Xq, const float* s_x, const void* Wq, 
     return launch_status();
 }
 
-template <int DT>
-static ss_status launch_sparse(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                               int64_t Kpb, void* Y, int64_t ldy, int tiles_o, int tiles_t, int grid, hipStream_t stream)
-{
-    if (allow_dynamic_lds<k_sparse<DT>>(S_LDS) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse<DT>), dim3(grid), dim3(G_THREADS), S_LDS, stream, static_cast<const uint8_t*>(XL), s_x,
-                       static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, Kpb, static_cast<uint16_t*>(Y), ldy,
-                       tiles_o, tiles_t);
-    return launch_status();
-}
-
-// 256 x 256 tile kernels (arguments already validated)
+// the dense 256 x 256 tile kernel (arguments already validated)
 namespace ss {
 
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
@@ -476,21 +290,6 @@ ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, co
     case SS_FP8_E4M3: return launch_dense<SS_FP8_E4M3>(Xq, s_x, Wq, s_w, M, O, Kb, Y, ldy, tiles_o, tiles_t, grid, hs);
     case SS_BF16: return launch_dense<SS_BF16>(Xq, s_x, Wq, s_w, M, O, Kb, Y, ldy, tiles_o, tiles_t, grid, hs);
     case SS_FP16: return launch_dense<SS_FP16>(Xq, s_x, Wq, s_w, M, O, Kb, Y, ldy, tiles_o, tiles_t, grid, hs);
-    }
-    return SS_ERR_DTYPE;
-}
-
-ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                             int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t hs)
-{
-    const int tiles_o = (int)((O + BO - 1) / BO), tiles_t = (int)((M + BT - 1) / BT);
-    const int grid = persistent_grid(tiles_o * tiles_t);
-    if (grid <= 0) return SS_ERR_HIP;
-    switch (dtype) {
-    case SS_I8: return launch_sparse<SS_I8>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, tiles_o, tiles_t, grid, hs);
-    case SS_FP8_E4M3: return launch_sparse<SS_FP8_E4M3>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, tiles_o, tiles_t, grid, hs);
-    case SS_BF16: return launch_sparse<SS_BF16>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, tiles_o, tiles_t, grid, hs);
-    case SS_FP16: return launch_sparse<SS_FP16>(XL, s_x, w_vals, w_meta, s_w, M, O, Kpb, Y, ldy, tiles_o, tiles_t, grid, hs);
     }
     return SS_ERR_DTYPE;
 }

@@ -136,14 +136,6 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
             else lds_dma16_from<P * 8192>(b_src, off, boff[P], b_wave + tslot);
         }
     };
-    // the channel scales (wavefronts 0 .. 3) and token scales of a tile, 64 each; rows and channels beyond the last repeat it
-    auto load_scales = [&](int64_t o_blk, int64_t t_blk) {
-        const int64_t first = (wave < 4 ? o_blk : t_blk) + (wave & 3) * 64, end = wave < 4 ? O : M, left = end - 1 - first;
-        const int left32 = left > 63 ? 63 : (int)left, ln = fresh_lane();
-        const uint32_t e = left32 < 0 ? 0u : (uint32_t)(ln < left32 ? ln : left32);
-        lds_dma4_at(reinterpret_cast<const uint8_t*>((wave < 4 ? s_w : s_x) + (left < 0 ? end - 1 : first)), e * 4, lds0 + F_SW_OFF + wave * 256);
-    };
-
     constexpr std::false_type all_lanes{};
     uint32_t t0 = 0, t1 = F_BSLOT, tz = 2 * F_BSLOT;   // token slots of u0 and u1, and the one that is free for the next pair's u0
     int to, tt;
@@ -231,7 +223,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
                     else wait_vm_mode<6>(LAST ? (1 & (int)more) | rest : 1);
                     wait_lgkm0();
                     wg_barrier();
-                    if constexpr (S == 0 && LAST && MM::SCALED) load_scales(o_blk, t_blk);
+                    if constexpr (S == 0 && LAST && MM::SCALED) load_tile_scales(s_w, s_x, O, M, o_blk, t_blk, wave, lds0 + F_SW_OFF);
                 }
                 if (S == 1 && LAST && (i == 9 || i == 11)) mask_raw(2 + ((i - 9) >> 1));
                 if (S == 1 && i >= 9 && i < 13) make_mid(1, 2 + ((i - 9) >> 1), (i - 9) & 1);

@@ -153,7 +153,7 @@ ss_status launch_dense_skinny(const void* Xq, const float* s_x, const void* Wq, 
 ss_status launch_sparse_fused_narrow(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                                      int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 
-// The 256 x 256 tile kernels (gemm.hip).
+// The 256 x 256 tile kernels: lifted rows (gemm_lifted.hip), dense (gemm.hip).
 ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                              int64_t Kpb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,

@@ -1,4 +1,4 @@
-// Pieces shared by the 256 x 256 tile kernels (gemm.hip, gemm_fused.hip): the order in which persistent
+// Pieces shared by the tile kernels of 256 tokens (gemm.hip, gemm_lifted.hip, gemm_fused.hip, gemm_fused_narrow.hip): the order in which persistent
 // workgroups walk the output tiles, and the epilogue that stages a wavefront's accumulators through LDS so
 // that every global store writes whole 256-byte row segments of Y.
 #pragma once
@@ -38,6 +38,16 @@ __device__ inline bool tile_of_round(int round, int tiles_o, int tiles_t, int& t
 // The fused-lifting kernels (gemm_fused.hip, gemm_fused_narrow.hip) store chunk c of a token row at place(c) ^ swz(row), see there.
 __device__ inline int place(int chunk) { return chunk ^ ((chunk >> 2) << 1); }      // its own inverse
 __device__ const uint4 no_values[64] = {};            // 1 KB of stored values for the super-unit that an odd row lacks
+
+// Direct loads of a tile's 256 channel scales and 256 token scales into LDS, by eight wavefronts: 0 .. 3 the channels', 4 .. 7 the
+// tokens', 64 each; those beyond the last repeat it.
+__device__ inline void load_tile_scales(const float* s_w, const float* s_x, int64_t O, int64_t M, int64_t o_blk, int64_t t_blk, int wave, uint32_t lds)
+{
+    const int64_t first = (wave < 4 ? o_blk : t_blk) + (wave & 3) * 64, end = wave < 4 ? O : M, left = end - 1 - first;
+    const int left32 = left > 63 ? 63 : (int)left, ln = fresh_lane();
+    const uint32_t e = left32 < 0 ? 0u : (uint32_t)(ln < left32 ? ln : left32);
+    lds_dma4_at(reinterpret_cast<const uint8_t*>((wave < 4 ? s_w : s_x) + (left < 0 ? end - 1 : first)), e * 4, lds + wave * 256);
+}
 
 // ---- epilogue: Y = bf16((float(acc) * s_x) * s_w), staged through LDS for coalesced stores ------
 
@@ -146,7 +156,8 @@ __device__ inline void store_tile(const ACC (&acc)[4][NB], const float (&sx)[NB]
 // All loads this wavefront has in flight (the next tile's first operands) are waited for right before the first store.  The
 // wait counter counts loads and stores alike, so a later wait for those loads would also wait for the stores to be
 // acknowledged; here the loads have had the first block's conversion to arrive and the stores are never waited for.
-template <bool SCALED, typename ACC>
+// SPLIT: the block's four groups of four rows lie 8 KB apart, which is where a wavefront's own direct loads of a token tile go.
+template <bool SCALED, bool SPLIT = false, typename ACC>
 __device__ inline void store_tile16(const ACC (&acc)[4][2][4], const float* sx_lds, const float* sw_lds, uint16_t* __restrict__ Y_sub, uint32_t ldy,
                                     int rows_left, int cols_left, uint8_t* stage)
 {
@@ -162,7 +173,7 @@ __device__ inline void store_tile16(const ACC (&acc)[4][2][4], const float* sx_l
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const float sx = SCALED ? sx_lds[16 * b + n] : 1.0f;
-        uint8_t* const row = stage + n * EP_ROWB + 8 * (q >> 1);
+        uint8_t* const row = stage + (SPLIT ? (n >> 2) * 8192 + (n & 3) * EP_ROWB : n * EP_ROWB) + 8 * (q >> 1);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const ACC& v = acc[e >> 1][e & 1][b];
@@ -178,7 +189,7 @@ __device__ inline void store_tile16(const ACC (&acc)[4][2][4], const float* sx_l
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * i + q;
-            const uint4 v = *reinterpret_cast<const uint4*>(stage + r * EP_ROWB + ((n ^ r) << 4));
+            const uint4 v = *reinterpret_cast<const uint4*>(stage + (SPLIT ? i * 8192 + q * EP_ROWB : r * EP_ROWB) + ((n ^ r) << 4));
             if (16 * b + r < rows_left) {
                 uint16_t* dst = Y_sub + (lane_elem + (uint32_t)(16 * b + 4 * i) * ldy);
                 if (vec_ok && oc + 8 <= cols_left) {
