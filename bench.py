@@ -421,7 +421,7 @@ def main():
                                 "prune_quant_GBps_of_weight_bytes": sum(b for _, b, _, _ in offline) / sum(p for _, _, p, _ in offline) * 1e-6},
         "roofline": {"bound": "mfma", "achieved": executed_tops, "peak": PEAK_INT8_DENSE_TOPS, "unit": "TOP/s",
                      "frac": executed_tops / PEAK_INT8_DENSE_TOPS, "traffic": RECORDED_TRAFFIC["fused"],
-                     "kernel": "ss::k_sparse_fused<0, 4> (slide_sparse_gemm_fused, INT8), mean over the four layer launches of a step",
+                     "kernel": "ss::k_sparse_fused<0> (slide_sparse_gemm_fused, INT8), mean over the four layer launches of a step",
                      "note": "INT8 ops; achieved = executed MACs x 2 = M*O*K_lifted per launch / HIP-event duration; "
                              "identical to hardware-counted 2*M*O*K_lifted against the 2x sparse peak; traffic is a recorded "
                              "constant from an earlier rocprofv3 --pmc run of this script (null until recorded)"},
