@@ -26,6 +26,8 @@ EXPORTS = ("slide_lifted_k", "slide_lifted_ld", "slide_packed_sizes", "slide_pru
            "slide_packed_sizes_fused", "slide_decompose_fused", "slide_sparse_gemm_fused", "slide_sparse_gemm_fused_ws",
            "slide_static_scratch_bytes", "slide_sparse_gemm_static",
            "ss_status_string", "slide_format_version")
+# entry points that the extension module calls, at the addresses of the library loaded here (order of its bind())
+_CALLED = ("slide_lifted_ld", "act_lift_quant", "slide_sparse_gemm_ws", "slide_sparse_gemm_fused_ws")
 
 _lib = None
 _calls = None
@@ -77,7 +79,8 @@ def load():
     lib.ss_status_string.argtypes = [i32]
     lib.ss_status_string.restype = ctypes.c_char_p
     lib.slide_format_version.restype = i32
-    from . import _calls as calls                     # linked against the library just loaded
+    from . import _calls as calls
+    calls.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in _CALLED))
     _lib, _calls = lib, calls
     return lib
 

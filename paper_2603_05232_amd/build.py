@@ -50,8 +50,7 @@ def build(verbose: bool = False) -> str:
         outs = list(ex.map(_run, commands))
     outs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]))
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    outs.append(_run([os.environ.get("CXX", "g++"), "-shared", "-o", CALLS, calls_obj, "-L" + PKG, "-lslidesparse", "-Wl,-rpath,$ORIGIN",
-                      "-L" + torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]))
+    outs.append(_run([os.environ.get("CXX", "g++"), "-shared", "-o", CALLS, calls_obj, "-L" + torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]))
     if verbose:
         print("\n".join(o for o in outs if o.strip()))
     return LIB

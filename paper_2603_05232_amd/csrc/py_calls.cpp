@@ -5,6 +5,9 @@
 // Each function does plain calls only: exact torch.Tensor arguments on the GPU, exact ints, no active function or dispatch
 // mode, and a status of SS_OK.  For anything else it returns None and the caller's general path does the call over, which is
 // where arguments are refused and errors raised.  The C entry points check their arguments before they launch anything.
+//
+// The module is not linked against libslidesparse.so: the binding hands it the addresses of the library that it has loaded by path.
+// By name, the loader would give a second copy of the package in the process the first copy's library.
 #include <Python.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
@@ -18,6 +21,13 @@
 #include "slidesparse.h"
 
 namespace {
+
+struct Library {
+    decltype(&::slide_lifted_ld) lifted_ld;
+    decltype(&::act_lift_quant) lift_quant;
+    decltype(&::slide_sparse_gemm_ws) sparse_gemm;
+    decltype(&::slide_sparse_gemm_fused_ws) sparse_gemm_fused;
+} lib;                                                // zeros until bind()
 
 // the interpreter lock is given up while memory is allocated and kernels are launched (either may wait for the GPU)
 struct Unlocked {
@@ -68,10 +78,10 @@ PyObject* py_act_lift_quant(PyObject*, PyObject* const* a, Py_ssize_t n)
     HANDLE_TH_ERRORS
     int64_t N;
     Type t;
-    if (n != 5 || !plain(a[0]) || !integer(a[1], INT_MIN, INT_MAX, N) || !operand_type(a[2], t) || !plain_or_none(a[3]) || !plain_or_none(a[4]) || modes_active()) Py_RETURN_NONE;
+    if (!lib.lift_quant || n != 5 || !plain(a[0]) || !integer(a[1], INT_MIN, INT_MAX, N) || !operand_type(a[2], t) || !plain_or_none(a[3]) || !plain_or_none(a[4]) || modes_active()) Py_RETURN_NONE;
     const at::Tensor& X = THPVariable_Unpack(a[0]);
     if (!X.is_cuda() || X.dim() != 2 || X.stride(1) != 1 || (X.scalar_type() != at::kFloat && X.scalar_type() != at::kBFloat16)) Py_RETURN_NONE;
-    const int64_t M = X.size(0), K = X.size(1), width = slide_lifted_ld(K, (int)N, t.code);
+    const int64_t M = X.size(0), K = X.size(1), width = lib.lifted_ld(K, (int)N, t.code);
     if (width < 0) Py_RETURN_NONE;
     at::Tensor out, s_x;
     void *out_ptr = address(a[3]), *s_x_ptr = address(a[4]);
@@ -80,7 +90,7 @@ PyObject* py_act_lift_quant(PyObject*, PyObject* const* a, Py_ssize_t n)
         Unlocked u;
         if (a[3] == Py_None) { out = at::empty({M, width}, X.options().dtype(t.storage)); out_ptr = out.data_ptr(); }
         if (a[4] == Py_None && t.scaled) { s_x = at::empty({M}, X.options().dtype(at::kFloat)); s_x_ptr = s_x.data_ptr(); }
-        st = act_lift_quant(X.data_ptr(), X.scalar_type() == at::kFloat ? SS_IN_F32 : SS_IN_BF16, M, K, M > 1 ? X.stride(0) : K, (int)N, t.code, out_ptr,
+        st = lib.lift_quant(X.data_ptr(), X.scalar_type() == at::kFloat ? SS_IN_F32 : SS_IN_BF16, M, K, M > 1 ? X.stride(0) : K, (int)N, t.code, out_ptr,
                             static_cast<float*>(s_x_ptr), current_stream());
     }
     if (st != SS_OK) Py_RETURN_NONE;
@@ -116,7 +126,7 @@ PyObject* py_slide_sparse_gemm(PyObject*, PyObject* const* a, Py_ssize_t n)
     HANDLE_TH_ERRORS
     int64_t O;
     Type t;
-    if (n != 9 || !gemm_operands(a, a[7], a[8]) || !integer(a[5], 0, INT64_MAX, O) || !operand_type(a[6], t)) Py_RETURN_NONE;
+    if (!lib.sparse_gemm || n != 9 || !gemm_operands(a, a[7], a[8]) || !integer(a[5], 0, INT64_MAX, O) || !operand_type(a[6], t)) Py_RETURN_NONE;
     const at::Tensor& X = THPVariable_Unpack(a[0]);
     if (!X.is_cuda() || X.dim() != 2 || !X.is_contiguous()) Py_RETURN_NONE;
     void* const ws = address(a[8]);
@@ -127,7 +137,7 @@ PyObject* py_slide_sparse_gemm(PyObject*, PyObject* const* a, Py_ssize_t n)
     {
         Unlocked u;
         y = output(a[7], X, X.size(0), O);
-        st = slide_sparse_gemm_ws(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), X.size(0), O, X.size(1), t.code, y.ptr, y.ld, ws, ws_bytes,
+        st = lib.sparse_gemm(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), X.size(0), O, X.size(1), t.code, y.ptr, y.ld, ws, ws_bytes,
                                   current_stream());
     }
     if (st != SS_OK) Py_RETURN_NONE;
@@ -141,7 +151,7 @@ PyObject* py_slide_sparse_gemm_fused(PyObject*, PyObject* const* a, Py_ssize_t n
     HANDLE_TH_ERRORS
     int64_t O, K, N;
     Type t;
-    if (n != 11 || !gemm_operands(a, a[9], a[10]) || !integer(a[5], 0, INT64_MAX, O) || !integer(a[6], 0, INT64_MAX, K) || !integer(a[7], INT_MIN, INT_MAX, N) ||
+    if (!lib.sparse_gemm_fused || n != 11 || !gemm_operands(a, a[9], a[10]) || !integer(a[5], 0, INT64_MAX, O) || !integer(a[6], 0, INT64_MAX, K) || !integer(a[7], INT_MIN, INT_MAX, N) ||
         !operand_type(a[8], t))
         Py_RETURN_NONE;
     const at::Tensor& X = THPVariable_Unpack(a[0]);
@@ -155,7 +165,7 @@ PyObject* py_slide_sparse_gemm_fused(PyObject*, PyObject* const* a, Py_ssize_t n
     {
         Unlocked u;
         y = output(a[9], X, M, O);
-        st = slide_sparse_gemm_fused_ws(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), M, O, K, M > 1 ? X.stride(0) : X.size(1), (int)N,
+        st = lib.sparse_gemm_fused(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), M, O, K, M > 1 ? X.stride(0) : X.size(1), (int)N,
                                         t.code, y.ptr, y.ld, ws, ws_bytes, current_stream());
     }
     if (st != SS_OK) Py_RETURN_NONE;
@@ -163,10 +173,27 @@ PyObject* py_slide_sparse_gemm_fused(PyObject*, PyObject* const* a, Py_ssize_t n
     END_HANDLE_TH_ERRORS
 }
 
+// bind(slide_lifted_ld, act_lift_quant, slide_sparse_gemm_ws, slide_sparse_gemm_fused_ws): their addresses; library() tells them
+PyObject* py_bind(PyObject*, PyObject* args)
+{
+    unsigned long long f[4];
+    if (!PyArg_ParseTuple(args, "KKKK", &f[0], &f[1], &f[2], &f[3])) return nullptr;
+    lib = {reinterpret_cast<decltype(lib.lifted_ld)>(f[0]), reinterpret_cast<decltype(lib.lift_quant)>(f[1]), reinterpret_cast<decltype(lib.sparse_gemm)>(f[2]),
+           reinterpret_cast<decltype(lib.sparse_gemm_fused)>(f[3])};
+    Py_RETURN_NONE;
+}
+PyObject* py_library(PyObject*, PyObject*)
+{
+    return Py_BuildValue("KKKK", reinterpret_cast<unsigned long long>(lib.lifted_ld), reinterpret_cast<unsigned long long>(lib.lift_quant),
+                         reinterpret_cast<unsigned long long>(lib.sparse_gemm), reinterpret_cast<unsigned long long>(lib.sparse_gemm_fused));
+}
+
 #define SS_PY(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL
 PyMethodDef methods[] = {{"act_lift_quant", SS_PY(py_act_lift_quant), nullptr},
                          {"slide_sparse_gemm", SS_PY(py_slide_sparse_gemm), nullptr},
                          {"slide_sparse_gemm_fused", SS_PY(py_slide_sparse_gemm_fused), nullptr},
+                         {"bind", py_bind, METH_VARARGS, nullptr},
+                         {"library", py_library, METH_NOARGS, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -153,3 +153,26 @@ def test_lifted_ld_takes_integers_only(lib):
     assert binding.slide_lifted_ld(7168, 4, "i8") == 10752
     with pytest.raises(ctypes.ArgumentError):
         binding.slide_lifted_ld(7168.0, 4, "i8")
+
+
+def test_copies_of_the_package_keep_their_own_library(lib, tmp_path):
+    """Two copies of the package in one process: no extension module calls into the other copy's library (their builds and packed
+    formats may differ).  Seen in what the loader binds, and in the addresses that the module calls."""
+    import shutil
+    import subprocess
+    import sys
+    src = os.path.dirname(binding.LIB_PATH)
+    for name in ("first_copy", "second_copy"):
+        shutil.copytree(src, tmp_path / name, ignore=shutil.ignore_patterns("csrc", "__pycache__"))
+    code = ("import ctypes, first_copy.binding as a, second_copy.binding as b\n"
+            "for m in (a, b):\n"
+            "    m.load()\n"
+            "    print('CALLS', m._calls.__file__)\n"
+            "    own = tuple(ctypes.cast(getattr(m._lib, n), ctypes.c_void_p).value for n in m._CALLED)\n"
+            "    assert m._calls.library() == own, m\n"
+            "assert a._calls.library() != b._calls.library()\n")
+    env = dict(os.environ, PYTHONPATH=str(tmp_path), LD_DEBUG="bindings", LD_BIND_NOW="1")
+    r = subprocess.run([sys.executable, "-c", code], env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, errors="replace")
+    crossed = [line for line in r.stderr.splitlines() if "second_copy/_calls" in line and "first_copy/libslidesparse" in line]
+    assert not crossed, crossed[0]
+    assert r.returncode == 0 and r.stdout.count("CALLS") == 2, r.stderr[-2000:]
