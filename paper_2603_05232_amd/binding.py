@@ -80,7 +80,7 @@ def load():
     lib.ss_status_string.restype = ctypes.c_char_p
     lib.slide_format_version.restype = i32
     from . import _calls as calls
-    calls.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in _CALLED))
+    calls.bind(SlideSparseError, *(ctypes.cast(getattr(lib, name), vp).value for name in _CALLED))
     _lib, _calls = lib, calls
     return lib
 
@@ -96,8 +96,8 @@ def _check(code: int, where: str) -> None:
 
 # Few-token calls are bound by the time between launches, most of which is spent here.  The calls of a forward pass
 # (act_lift_quant and the sparse GEMMs) therefore go to the extension module first, which does plain calls (exact torch
-# tensors on the GPU, no active mode, no error) and answers None to any other; what follows is the general path, which also
-# raises the errors.  It does no more than the call needs either: addresses go to ctypes as plain integers (None is NULL), and
+# tensors on the GPU, no active mode, nothing to refuse) and answers None to any other; what follows is the general path,
+# which refuses what has to be.  It does no more than the call needs either: addresses go to ctypes as plain integers (None is NULL), and
 # the stream handle is read without building a torch.cuda.Stream object (0.2 instead of 2.8 us; a launch itself is 2.8 us).
 # Quantisation + GEMM of 16 x 512 x 512 on the host: 15.3 us by the general path, 9.1 by the module.
 _STORAGE_DTYPE = {"i8": torch.int8, "fp8": torch.uint8, "bf16": torch.bfloat16, "fp16": torch.float16}

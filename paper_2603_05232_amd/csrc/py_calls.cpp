@@ -3,8 +3,10 @@
 // between launches, most of which was spent there (quantisation + GEMM of 16 x 512 x 512: see binding.py).
 //
 // Each function does plain calls only: exact torch.Tensor arguments on the GPU, exact ints, no active function or dispatch
-// mode, and a status of SS_OK.  For anything else it returns None and the caller's general path does the call over, which is
-// where arguments are refused and errors raised.  The C entry points check their arguments before they launch anything.
+// mode, and arguments that the C entry point accepts.  For anything else it returns None and the caller's general path does the
+// call over, which is where arguments are refused and errors raised: the C entry points check their arguments before they launch
+// anything.  A launch that failed is no argument to refuse: SS_ERR_HIP raises here, since a second attempt would launch
+// again and find the runtime's error cleared.
 //
 // The module is not linked against libslidesparse.so: the binding hands it the addresses of the library that it has loaded by path.
 // By name, the loader would give a second copy of the package in the process the first copy's library.
@@ -28,6 +30,7 @@ struct Library {
     decltype(&::slide_sparse_gemm_ws) sparse_gemm;
     decltype(&::slide_sparse_gemm_fused_ws) sparse_gemm_fused;
 } lib;                                                // zeros until bind()
+PyObject* error_type = nullptr;                       // SlideSparseError(status, where)
 
 // the interpreter lock is given up while memory is allocated and kernels are launched (either may wait for the GPU)
 struct Unlocked {
@@ -72,6 +75,17 @@ bool operand_type(PyObject* o, Type& t)
 bool modes_active() { return c10::impl::TorchDispatchModeTLS::any_modes_set() || at::impl::torch_function_mode_enabled(); }
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// what a function returns for a status other than SS_OK
+PyObject* refused(ss_status st, const char* where)
+{
+    if (st != SS_ERR_HIP) Py_RETURN_NONE;
+    if (PyObject* e = PyObject_CallFunction(error_type, "is", (int)st, where)) {
+        PyErr_SetObject(error_type, e);
+        Py_DECREF(e);
+    }
+    return nullptr;
+}
+
 // act_lift_quant(X, N, dtype, out, s_x)
 PyObject* py_act_lift_quant(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
@@ -93,7 +107,7 @@ PyObject* py_act_lift_quant(PyObject*, PyObject* const* a, Py_ssize_t n)
         st = lib.lift_quant(X.data_ptr(), X.scalar_type() == at::kFloat ? SS_IN_F32 : SS_IN_BF16, M, K, M > 1 ? X.stride(0) : K, (int)N, t.code, out_ptr,
                             static_cast<float*>(s_x_ptr), current_stream());
     }
-    if (st != SS_OK) Py_RETURN_NONE;
+    if (st != SS_OK) return refused(st, "act_lift_quant");
     PyObject* po = out.defined() ? THPVariable_Wrap(std::move(out)) : Py_NewRef(a[3]);
     PyObject* ps = s_x.defined() ? THPVariable_Wrap(std::move(s_x)) : Py_NewRef(a[4]);
     PyObject* r = po && ps ? PyTuple_Pack(2, po, ps) : nullptr;
@@ -140,7 +154,7 @@ PyObject* py_slide_sparse_gemm(PyObject*, PyObject* const* a, Py_ssize_t n)
         st = lib.sparse_gemm(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), X.size(0), O, X.size(1), t.code, y.ptr, y.ld, ws, ws_bytes,
                                   current_stream());
     }
-    if (st != SS_OK) Py_RETURN_NONE;
+    if (st != SS_OK) return refused(st, a[8] == Py_None ? "slide_sparse_gemm" : "slide_sparse_gemm_ws");
     return result(y, a[7]);
     END_HANDLE_TH_ERRORS
 }
@@ -168,18 +182,23 @@ PyObject* py_slide_sparse_gemm_fused(PyObject*, PyObject* const* a, Py_ssize_t n
         st = lib.sparse_gemm_fused(X.data_ptr(), static_cast<const float*>(s_x), wv, wm, static_cast<const float*>(s_w), M, O, K, M > 1 ? X.stride(0) : X.size(1), (int)N,
                                         t.code, y.ptr, y.ld, ws, ws_bytes, current_stream());
     }
-    if (st != SS_OK) Py_RETURN_NONE;
+    if (st != SS_OK) return refused(st, a[10] == Py_None ? "slide_sparse_gemm_fused" : "slide_sparse_gemm_fused_ws");
     return result(y, a[9]);
     END_HANDLE_TH_ERRORS
 }
 
-// bind(slide_lifted_ld, act_lift_quant, slide_sparse_gemm_ws, slide_sparse_gemm_fused_ws): their addresses; library() tells them
+// bind(SlideSparseError, slide_lifted_ld, act_lift_quant, slide_sparse_gemm_ws, slide_sparse_gemm_fused_ws), the last four as
+// addresses; library() tells these
 PyObject* py_bind(PyObject*, PyObject* args)
 {
+    PyObject* error;
     unsigned long long f[4];
-    if (!PyArg_ParseTuple(args, "KKKK", &f[0], &f[1], &f[2], &f[3])) return nullptr;
+    if (!PyArg_ParseTuple(args, "OKKKK", &error, &f[0], &f[1], &f[2], &f[3])) return nullptr;
     lib = {reinterpret_cast<decltype(lib.lifted_ld)>(f[0]), reinterpret_cast<decltype(lib.lift_quant)>(f[1]), reinterpret_cast<decltype(lib.sparse_gemm)>(f[2]),
            reinterpret_cast<decltype(lib.sparse_gemm_fused)>(f[3])};
+    Py_INCREF(error);
+    Py_XDECREF(error_type);
+    error_type = error;
     Py_RETURN_NONE;
 }
 PyObject* py_library(PyObject*, PyObject*)

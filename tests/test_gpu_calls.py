@@ -1,5 +1,11 @@
 """The extension module's calls against the general path of the binding: same results over the forms of arguments that
 both take, same errors for those that neither does."""
+import ctypes
+import importlib
+import os
+import shutil
+import subprocess
+import sys
 import types
 
 import pytest
@@ -105,3 +111,48 @@ def test_refused_calls_raise_as_before():
                      (lambda: binding.slide_sparse_gemm_fused(Xq, s_x, w, w, s_w, 128, 256, 4, "i8", workspace=w[1:]), binding.SlideSparseError)):
         with pytest.raises(error):
             f()
+
+
+STUB = """
+#include <stdint.h>
+extern "C" {{
+int calls = 0;
+{}
+int64_t slide_lifted_ld(int64_t, int, int) {{ return 128; }}
+const char* ss_status_string(int) {{ return "stub"; }}
+int act_lift_quant() {{ return ++calls == 1 ? 6 : 0; }}
+int slide_sparse_gemm_ws() {{ return ++calls == 1 ? 6 : 0; }}
+int slide_sparse_gemm_fused_ws() {{ return ++calls == 1 ? 6 : 0; }}
+}}
+"""
+
+
+@pytest.fixture(scope="module")
+def failing_copy(tmp_path_factory):
+    """The binding of a copy of the package whose library reports a HIP error (6) for the first launch and none for the next."""
+    root = tmp_path_factory.mktemp("copy")
+    shutil.copytree(os.path.dirname(binding.LIB_PATH), root / "failing_copy", ignore=shutil.ignore_patterns("csrc", "__pycache__", "lib*.so"))
+    own = ("slide_lifted_ld", "ss_status_string", "act_lift_quant", "slide_sparse_gemm_ws", "slide_sparse_gemm_fused_ws")
+    (root / "stub.cpp").write_text(STUB.format("\n".join(f"int {n}() {{ return 0; }}" for n in binding.EXPORTS if n not in own)))
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(root / "failing_copy" / "libslidesparse.so"), str(root / "stub.cpp")], check=True)
+    sys.path.insert(0, str(root))
+    try:
+        yield importlib.import_module("failing_copy.binding")
+    finally:
+        sys.path.remove(str(root))
+
+
+@pytest.mark.parametrize("call", ["act_lift_quant", "slide_sparse_gemm_ws", "slide_sparse_gemm_fused_ws"])
+def test_a_launch_error_raises_and_is_not_tried_again(failing_copy, call):
+    calls = ctypes.c_int.in_dll(failing_copy.load(), "calls")
+    calls.value = 0
+    X = torch.zeros((4, 128), device=DEV)
+    q, s, w = X.to(torch.int8), X[:, 0].contiguous(), torch.zeros((64,), dtype=torch.uint8, device=DEV)
+    f = {"act_lift_quant": lambda: failing_copy.act_lift_quant(X, 2, "i8"),
+         "slide_sparse_gemm_ws": lambda: failing_copy.slide_sparse_gemm(q, s, w, w, s, 4, "i8", workspace=w),
+         "slide_sparse_gemm_fused_ws": lambda: failing_copy.slide_sparse_gemm_fused(q, s, w, w, s, 4, 128, 4, "i8", workspace=w)}[call]
+    with pytest.raises(failing_copy.SlideSparseError, match=call) as e:
+        f()
+    assert e.value.code == 6 and calls.value == 1
+    f()
+    assert calls.value == 2
