@@ -10,12 +10,15 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+import sysconfig
+import types
+import warnings
 
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libslidesparse.so")
-CALLS_PATH = os.path.join(_PKG, "_calls.so")
+CALLS_PATH = os.path.join(_PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SS_I8, SS_FP8_E4M3, SS_BF16, SS_FP16 = 0, 1, 2, 3
 SS_IN_F32, SS_IN_BF16 = 0, 1
@@ -44,9 +47,8 @@ def load():
     global _lib, _calls
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, CALLS_PATH):
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} not found: build it first (python -m paper_2603_05232_amd.build)")
+    if not os.path.exists(LIB_PATH):
+        raise RuntimeError(f"{LIB_PATH} not found: build it first (python -m paper_2603_05232_amd.build)")
     lib = ctypes.CDLL(LIB_PATH)
     i64, i32, vp, sz = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t
     lib.slide_lifted_k.argtypes = [i64, i32]
@@ -79,10 +81,22 @@ def load():
     lib.ss_status_string.argtypes = [i32]
     lib.ss_status_string.restype = ctypes.c_char_p
     lib.slide_format_version.restype = i32
-    from . import _calls as calls
-    calls.bind(SlideSparseError, *(ctypes.cast(getattr(lib, name), vp).value for name in _CALLED))
-    _lib, _calls = lib, calls
+    _lib, _calls = lib, _load_calls(lib)
     return lib
+
+
+def _load_calls(lib):
+    """The extension module, told which library to call; without one that was built for this torch, a stand-in that leaves every
+    call to the general path, which needs the library alone."""
+    try:
+        from . import _calls as calls
+        if calls.torch_version != str(torch.__version__):
+            raise ImportError(f"built for torch {calls.torch_version}, not {torch.__version__}")
+    except (ImportError, AttributeError) as e:
+        warnings.warn(f"{CALLS_PATH} cannot be used ({e}): calls go through ctypes, 6 us more on the host for each layer", RuntimeWarning, stacklevel=3)
+        return types.SimpleNamespace(**dict.fromkeys(("act_lift_quant", "slide_sparse_gemm", "slide_sparse_gemm_fused"), lambda *args: None))
+    calls.bind(SlideSparseError, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _CALLED))
+    return calls
 
 
 def status_string(code: int) -> str:

@@ -1,4 +1,4 @@
-"""Builds libslidesparse.so (HIP kernels + C ABI, hipcc for gfx950) and the extension module _calls.so (host C++), in-tree."""
+"""Builds libslidesparse.so (HIP kernels + C ABI, hipcc for gfx950) and the extension module _calls (host C++), in-tree."""
 from __future__ import annotations
 
 import os
@@ -12,7 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libslidesparse.so")
-CALLS = os.path.join(PKG, "_calls.so")
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ("lift_quant.hip", "prune_quant.hip", "decompose.hip", "gemm.hip", "gemm_skinny.hip", "gemm_mid.hip", "gemm_lifted.hip", "gemm_fused.hip", "gemm_fused_narrow.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -33,7 +33,7 @@ def _calls_command(obj: str):
     import torch
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"), "-I" + inc,
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSS_TORCH_VERSION="{torch.__version__}"', "-I" + os.path.join(ROOT, "include"), "-I" + inc,
             "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"],
             "-c", os.path.join(CSRC, "py_calls.cpp"), "-o", obj]
 

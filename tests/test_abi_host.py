@@ -176,3 +176,36 @@ def test_copies_of_the_package_keep_their_own_library(lib, tmp_path):
     crossed = [line for line in r.stderr.splitlines() if "second_copy/_calls" in line and "first_copy/libslidesparse" in line]
     assert not crossed, crossed[0]
     assert r.returncode == 0 and r.stdout.count("CALLS") == 2, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("module", ["absent", "unloadable", "of another torch"])
+def test_binding_loads_without_the_extension_module(lib, tmp_path, module):
+    """The extension module only saves host time: without one that fits the running torch, all calls go through ctypes."""
+    import shutil
+    import subprocess
+    import sys
+    pkg = tmp_path / "plain_copy"
+    shutil.copytree(os.path.dirname(binding.LIB_PATH), pkg, ignore=shutil.ignore_patterns("csrc", "__pycache__", *([] if module == "of another torch" else ["_calls*"])))
+    if module == "unloadable":
+        (pkg / os.path.basename(binding.CALLS_PATH)).write_bytes(b"not a shared library")
+    code = ("import warnings, torch\n"
+            + ("torch.__version__ = '1.0'\n" if module == "of another torch" else "")
+            + "from plain_copy import binding as b\n"
+            "with warnings.catch_warnings(record=True) as seen:\n"
+            "    warnings.simplefilter('always')\n"
+            "    assert b.slide_lifted_ld(512, 4, 'i8') == 768 and b.slide_packed_sizes(512, 512, 4, 'i8') == (512 * 384, 512 * 96)\n"
+            "assert [w.category for w in seen] == [RuntimeWarning], seen\n"
+            "for call in (lambda: b.act_lift_quant(torch.zeros(2, 64), 9, 'i8'), lambda: b.act_lift_quant(torch.zeros(64, 2).T, 4, 'i8')):\n"
+            "    try:\n"
+            "        call()\n"
+            "    except AssertionError:\n"
+            "        continue\n"
+            "    raise SystemExit('accepted')\n")
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, PYTHONPATH=str(tmp_path)), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+
+
+def test_extension_module_carries_its_abi_in_its_name(lib):
+    import sysconfig
+    assert binding.CALLS_PATH.endswith("_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
+    assert os.path.samefile(binding._calls.__file__, binding.CALLS_PATH)
