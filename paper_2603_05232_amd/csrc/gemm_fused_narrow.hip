@@ -67,11 +67,9 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
         }
     }
     const uint32_t v_wave = lds0 + wave * 1024, m_wave = lds0 + FN_IDX_OFF + wave * 768, b_wave = lds0 + FN_B_OFF + wave * 1024;
-    auto load_tokens = [&](auto i_c, int u, uint32_t slot, uint64_t lanes, auto masked_c) __attribute__((always_inline)) {
+    auto load_tokens = [&](auto i_c, int u, uint32_t slot) __attribute__((always_inline)) {
         constexpr int I = decltype(i_c)::value;
-        const uint32_t off = (uint32_t)min(u, U - 1) * ROWB;
-        if constexpr (decltype(masked_c)::value) lds_dma16_lanes_from<I * 8192>(b_src, off, boff[I], b_wave + slot, lanes);
-        else lds_dma16_from<I * 8192>(b_src, off, boff[I], b_wave + slot);
+        lds_dma16_from<I * 8192>(b_src, (uint32_t)min(u, U - 1) * ROWB, boff[I], b_wave + slot);
     };
     auto load_values = [&](auto group_c, int p, uint32_t area) __attribute__((always_inline)) {
         constexpr int G = decltype(group_c)::value;
@@ -98,10 +96,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     constexpr std::integral_constant<int, 1> c1{};
     constexpr std::integral_constant<int, 2> c2{};
     constexpr std::integral_constant<int, 3> c3{};
-    constexpr std::false_type all{};
-    auto tokens4 = [&](int u, uint32_t slot) __attribute__((always_inline)) {
-        load_tokens(c0, u, slot, 0, all); load_tokens(c1, u, slot, 0, all); load_tokens(c2, u, slot, 0, all); load_tokens(c3, u, slot, 0, all);
-    };
+    auto tokens4 = [&](int u, uint32_t slot) __attribute__((always_inline)) { load_tokens(c0, u, slot); load_tokens(c1, u, slot); load_tokens(c2, u, slot); load_tokens(c3, u, slot); };
     uint32_t t0 = 0, t1 = FN_BSLOT, tz = 2 * FN_BSLOT;         // token slots of u0 and u1, and that of the next pair's u0
     load_values(c0, 0, 0); load_values(c1, 0, 0); load_values(c2, 0, 0); load_index(0, 0);
     tokens4(0, t0);
@@ -146,18 +141,17 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
         }
     };
 
-    // Step S of pair p, whose weights lie in `area`.  TAIL: the last two pairs; they request no weights and only tokens of the last u1.
-    auto step = [&](auto step_c, auto tail_c, int p, uint32_t area) __attribute__((always_inline)) {
-        constexpr int S = decltype(step_c)::value, NS = S == 2 ? 0 : S + 1, MEET = 3;
-        constexpr bool TAIL = decltype(tail_c)::value;
-        const uint32_t last_u1 = __builtin_amdgcn_readfirstlane(p + 2 == P ? ~0u : 0u);
-        const uint64_t lanes = ((uint64_t)last_u1 << 32) | last_u1;
-        const int keep = TAIL && odd && p + 1 == P ? 0 : -1;
+    // Step S of pair p, whose weights lie in `area`, by the pairs that follow: of the next but one the weights and u0's tokens are
+    // requested, of the next u1's tokens; the last step reads no operands (the token slots are the epilogue's by then).
+    enum { MIDDLE, LAST2, LAST1 };
+    auto step = [&](auto step_c, auto pos_c, int p, uint32_t area) __attribute__((always_inline)) {
+        constexpr int S = decltype(step_c)::value, NS = S == 2 ? 0 : S + 1, MEET = 3, POS = decltype(pos_c)::value;
+        const int keep = POS == LAST1 && odd ? 0 : -1;
         __builtin_amdgcn_sched_barrier(0);
         unroll<16>([&](auto i_c) __attribute__((always_inline)) {
             constexpr int i = decltype(i_c)::value;
             constexpr int a = (i >> 1) & 3, b = 2 * (i >> 3) + (i & 1);
-            if constexpr (TAIL && S == 1 && (i == 0 || i == 8)) {
+            if constexpr (POS == LAST1 && S == 1 && (i == 0 || i == 8)) {
 #pragma unroll
                 for (int k = 0; k < 2; ++k) R[1].raw[(i >> 2) + k] = R[1].raw[(i >> 2) + k] & keep;
                 __builtin_amdgcn_sched_barrier(0);
@@ -172,9 +166,8 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
                 else asm("v_mov_b32 %0, %1" : "=v"(mid[mb][4 * S + j]) : "v"(R[S].raw[mb][4 * (j >> 1) + 1 + (j & 1)]));      // opaque: see gemm_fused.hip
             }
             if constexpr (i == MEET) {
-                if constexpr (S == 0 && TAIL) wait_vm_mode<8>(p + 1 == P ? 2 : 1);
-                else if constexpr (S == 0 || (S == 2 && !TAIL)) wait_vmcnt<8>();
-                else if constexpr (S == 2) wait_vmcnt<0>();
+                if constexpr (POS == LAST1 ? S == 0 : POS == LAST2 && S == 2) wait_vmcnt<0>();
+                else if constexpr (POS != LAST1 && S != 1) wait_vmcnt<8>();
                 wait_lgkm0();
                 wg_barrier();
             }
@@ -184,16 +177,16 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
             // requests, four a step: u1 tokens of the next pair; values and the next but one's u0 tokens; rest of those
             if constexpr (i == 5 || i == 8 || i == 11 || i == 14) {
                 constexpr int d = (i - 5) / 3;
-                if constexpr (S == 0) load_tokens(std::integral_constant<int, d>{}, 2 * p + 3, t0, lanes, tail_c);
-                else if constexpr (!TAIL) {
+                if constexpr (S == 0 && POS != LAST1) load_tokens(std::integral_constant<int, d>{}, 2 * p + 3, t0);
+                else if constexpr (POS == MIDDLE) {
                     if constexpr (S == 1 && d < 2) load_values(std::integral_constant<int, d>{}, p + 2, area);
-                    else if constexpr (S == 1) load_tokens(std::integral_constant<int, d - 2>{}, 2 * p + 4, t1, 0, all);
-                    else if constexpr (d < 2) load_tokens(std::integral_constant<int, d + 2>{}, 2 * p + 4, t1, 0, all);
+                    else if constexpr (S == 1) load_tokens(std::integral_constant<int, d - 2>{}, 2 * p + 4, t1);
+                    else if constexpr (d < 2) load_tokens(std::integral_constant<int, d + 2>{}, 2 * p + 4, t1);
                     else if constexpr (d == 2) load_values(c2, p + 2, area);
                     else load_index(p + 2, area);
                 }
             }
-            if constexpr (i > MEET) {                          // fourteen reads behind twelve instructions
+            if constexpr (i > MEET && !(POS == LAST1 && S == 2)) {       // fourteen reads behind twelve instructions
                 constexpr std::integral_constant<int, NS> ns{};
                 const uint32_t next_area = S == 2 ? area ^ 1 : area, next_tok = S == 0 ? t1 : tz;
                 constexpr int k = i - MEET - 1;
@@ -210,20 +203,20 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
         });
     };
     unroll<14>([&](auto r_c) __attribute__((always_inline)) { read(c0, r_c, 0, t0); });
-    auto pair = [&](auto tail_c, int p) __attribute__((always_inline)) {
+    auto pair = [&](auto pos_c, int p) __attribute__((always_inline)) {
         const uint32_t area = p & 1;
-        step(c0, tail_c, p, area);
-        step(c1, tail_c, p, area);
-        step(c2, tail_c, p, area);
+        step(c0, pos_c, p, area);
+        step(c1, pos_c, p, area);
+        step(c2, pos_c, p, area);
         const uint32_t was0 = t0, was1 = t1;
         t0 = tz; t1 = was0; tz = was1;
     };
-    int p = 0;
-    for (; p + 2 < P; ++p) pair(std::false_type{}, p);
-    for (; p < P; ++p) pair(std::true_type{}, p);
+    for (int p = 0; p + 2 < P; ++p) pair(std::integral_constant<int, MIDDLE>{}, p);
+    if (P > 1) pair(std::integral_constant<int, LAST2>{}, P - 2);
+    pair(std::integral_constant<int, LAST1>{}, P - 1);
 
-    // Epilogue: Y = bf16((float(acc) * s_x) * s_w), the whole tile staged in the token slots (nobody reads tokens behind the
-    // last meeting): rows of 256 bytes, chunk c of row r at c ^ (r & 15).
+    // Epilogue: Y = bf16((float(acc) * s_x) * s_w), the whole tile staged in the token slots (the last operand reads, of step 2's
+    // weights, returned before the last meeting; all requests had landed at the first meeting of the last pair): rows of 256 bytes, chunk c of row r at c ^ (r & 15).
     uint8_t* const stage = smem + FN_B_OFF;
     const int q = g;
     float4 sw[4];
