@@ -12,13 +12,13 @@
 namespace ss {
 
 // MAXV > 0: vector loads, row kept in registers.  MAXV == 0: scalar loads, second pass re-reads the
-// row (rows too long for the registers of a workgroup).  Long rows take more
+// row (rows too long for the registers of a workgroup, short ones off a line: launch_lift).  Long rows take more
 // threads per token rather than more registers per thread: the loads of a token are all in
 // flight at once either way, but fewer registers leave room for more tokens per compute unit.
-// RAGGED: the rows start off a 16-byte line or end within one.  The 16-byte lines that hold the row are
-// loaded as they lie, those at its two ends element by element; element k has its code in LDS at
-// off + k, off being the row's offset from its first line, and the gather shifts accordingly.  (777 x 5003 fp32 to fp16,
-// 8:10, with the GEMM behind it: 68.6 us a pass with scalar loads in two passes, 65.9 like this.)
+// RAGGED: the rows start off a 16-byte line or end within one.  The 16-byte lines that are the row's alone are
+// loaded as they lie, the up to 2 (IV::N - 1) elements ahead of and behind them by one thread each, the last of the
+// workgroup; element k has its code in LDS at off + k, off being the row's offset from its first line, and the gather shifts
+// accordingly.  (One thread for all that a line has of the row, element by element: bf16 to fp16, 8192 x 2051 17.7 us, like this 12.8; 2048 x 8195 14.4 and 10.6.)
 template <typename TIN, int OUT, int MAXV, int THREADS, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restrict__ X, int64_t ldx, int K, int N,
                                                                 uint8_t* __restrict__ XL, float* __restrict__ s_x, int Kp, int Kz, uint32_t inv_nw1)
@@ -34,34 +34,30 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     typedef InVec<TIN> IV;
     typename IV::V v[MAXV > 0 ? MAXV : 1];
     const int off = RAGGED ? (int)(((uintptr_t)x / sizeof(TIN)) % IV::N) : 0;
-    const int nvec = RAGGED ? (off + K + IV::N - 1) / IV::N : K / IV::N;
-    auto whole = [&](int idx) { return !RAGGED || (idx * IV::N >= off && (idx + 1) * IV::N <= off + K); };      // all of the line belongs to the row
+    const int head = RAGGED ? (IV::N - off) % IV::N : 0;      // elements ahead of the first whole line (the rows are longer)
+    const int nvec = (K - head) / IV::N, body = head + nvec * IV::N;  // whole lines, and the first element behind them
+    // the element at one of the row's two ends that this thread takes, if any
+    const int e = THREADS - 1 - t, edge = !RAGGED ? K : e < head ? e : body + e - head;
+    float at_edge = 0.0f;
 
     // ---- pass 1: absmax (Alg. 1, dynamic quantisation scale)
     float amax = 0.0f;
     if constexpr (MAXV > 0) {
-        const typename IV::V* xv = reinterpret_cast<const typename IV::V*>(x - off);
+        if (edge < K) at_edge = load_scalar(x + edge);
+        const typename IV::V* xv = reinterpret_cast<const typename IV::V*>(x + head);
 #pragma unroll
         for (int i = 0; i < MAXV; ++i) {
             const int idx = t + i * THREADS;
             if (idx < nvec) {
-                if (whole(idx)) v[i] = xv[idx];
-                else {
-                    TIN part[IV::N];
-#pragma unroll
-                    for (int e = 0; e < IV::N; ++e) {
-                        const int k = idx * IV::N + e - off;
-                        part[e] = k >= 0 && k < K ? x[k] : (TIN)0;
-                    }
-                    v[i] = __builtin_bit_cast(typename IV::V, part);
-                }
+                v[i] = xv[idx];
                 if constexpr (OUT < 2) {
                     float f[IV::N]; IV::unpack(v[i], f);
 #pragma unroll
-                    for (int e = 0; e < IV::N; ++e) amax = fmaxf(amax, fabsf(f[e]));
+                    for (int k = 0; k < IV::N; ++k) amax = fmaxf(amax, fabsf(f[k]));
                 }
             }
         }
+        if constexpr (RAGGED) amax = fmaxf(amax, fabsf(at_edge));
     } else if constexpr (OUT < 2) {
         for (int k = t; k < K; k += THREADS) amax = fmaxf(amax, fabsf(load_scalar(x + k)));
     }
@@ -108,26 +104,19 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     typedef std::conditional_t<ES == 1, uint8_t, uint16_t> code_t;
     code_t* const codes = reinterpret_cast<code_t*>(lds);
     if constexpr (MAXV > 0) {
+        if (edge < K) codes[off + edge] = (code_t)quant1<OUT>(at_edge, r);
 #pragma unroll
         for (int i = 0; i < MAXV; ++i) {
-            const int idx = t + i * THREADS;
+            const int idx = t + i * THREADS, line = idx + (head > 0);
             if (idx < nvec) {
                 float f[IV::N]; IV::unpack(v[i], f);
-                if (!whole(idx)) {                       // only what belongs to the row: the zeros behind it are another thread's
-#pragma unroll
-                    for (int e = 0; e < IV::N; ++e) {
-                        const int k = idx * IV::N + e - off;
-                        if (k >= 0 && k < K) codes[off + k] = (code_t)quant1<OUT>(f[e], r);
-                    }
-                    continue;
-                }
                 if constexpr (ES == 1) {
 #pragma unroll
-                    for (int w = 0; w < IV::N / 4; ++w) lds[idx * (IV::N / 4) + w] = quant4<OUT>(f[4 * w], f[4 * w + 1], f[4 * w + 2], f[4 * w + 3], r);
+                    for (int w = 0; w < IV::N / 4; ++w) lds[line * (IV::N / 4) + w] = quant4<OUT>(f[4 * w], f[4 * w + 1], f[4 * w + 2], f[4 * w + 3], r);
                 } else {
 #pragma unroll
                     for (int w = 0; w < IV::N / 2; ++w)
-                        lds[idx * (IV::N / 2) + w] = quant1<OUT>(f[2 * w], r) | (quant1<OUT>(f[2 * w + 1], r) << 16);
+                        lds[line * (IV::N / 2) + w] = quant1<OUT>(f[2 * w], r) | (quant1<OUT>(f[2 * w + 1], r) << 16);
                 }
             }
         }
@@ -199,8 +188,8 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const int Kz = (int)lift_lds_elems(K, N, ES);
     const bool line_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
     const bool element_ok = (uintptr_t)X % sizeof(TIN) == 0;
-    // a ragged row: up to IV::N - 1 elements ahead of it in its first line, and as many codes more in LDS
-    const int64_t nvec = line_ok ? K / IV::N : (K + 2 * IV::N - 2) / IV::N;      // 16-byte vectors per row, at most
+    // a ragged row: up to IV::N - 1 codes more in LDS, ahead of it in its first line
+    const int64_t nvec = K / IV::N;                           // whole 16-byte vectors per row, at most
     const size_t lds_bytes = (size_t)Kz * ES, ragged_bytes = lds_bytes + IV::N * ES;
     dim3 grid((unsigned)M);
     const uint32_t inv = N > 2 ? (uint32_t)(((1ull << 32) + N - 2) / (N - 1)) : 0u;
@@ -213,8 +202,12 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     else if (nvec <= 5 * 1024) SS_LQ(5, 1024, RAGGED); \
     else if (nvec <= 10 * 1024) SS_LQ(10, 1024, RAGGED); \
     else SS_LQ(20, 1024, RAGGED);
+    // Rows off a line: whole lines against scalar loads, time, M = 1 .. 30000, N = 2 .. 8: 8-bit codes (two passes over the row) of 37 to 195
+    // elements 0.91 .. 1.22, 257 to 771 0.55 .. 1.07, 1003 and more 0.18 .. 1.06 (8192 x 4099 fp32 to fp8 0.46); 16-bit codes (one pass) of 37 to
+    // 385 elements 0.92 .. 1.76, 515 to 771 0.73 .. 1.13, 1003 and more 0.37 .. 1.10.  Where the rows are short, a thread has an element or two.
+    const bool few = !line_ok && K <= (OUT < 2 ? 256 : 512);
     // 64: the kernel's small reduction buffer
-    if (!element_ok || nvec > 20 * 1024 || (!line_ok && ragged_bytes + 64 > 64 * 1024)) SS_LQ(0, 256, false);
+    if (!element_ok || few || nvec > 20 * 1024 || (!line_ok && ragged_bytes + 64 > 64 * 1024)) SS_LQ(0, 256, false);
     else if (line_ok) { SS_LQ_ROWS(false) }
     else { SS_LQ_ROWS(true) }
 #undef SS_LQ_ROWS

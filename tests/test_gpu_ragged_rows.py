@@ -12,11 +12,11 @@ from test_gpu_parity import check_lifted, dev, host
 pytestmark = pytest.mark.gpu
 
 
-# K: less than one vector, around the widths of the launch choices (4 x 256, 4 x 512, 5 x 1024 vectors of 4 or 8 elements; the
+# K: less than one vector, around the lengths up to which rows are loaded by elements (256, 512), around the widths of the launch choices (4 x 256, 4 x 512, 5 x 1024 vectors of 4 or 8 elements; the
 # longest 8-bit rows that LDS holds), ends at every place within a line
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
 @pytest.mark.parametrize("act", ["fp32", "bf16"])
-@pytest.mark.parametrize("N,M,K,first,pad", [(4, 3, 1, 0, 2), (2, 4, 3, 1, 1), (4, 9, 7, 3, 0), (5, 9, 64, 5, 3), (3, 9, 1003, 2, 1), (2, 9, 1021, 7, 0),
+@pytest.mark.parametrize("N,M,K,first,pad", [(4, 3, 1, 0, 2), (2, 4, 3, 1, 1), (4, 9, 7, 3, 0), (5, 9, 64, 5, 3), (3, 9, 256, 2, 1), (4, 9, 257, 1, 0), (2, 9, 258, 7, 3), (5, 9, 512, 3, 1), (3, 9, 513, 6, 0), (4, 9, 519, 0, 2), (3, 9, 1003, 2, 1), (2, 9, 1021, 7, 0),
                                              (8, 5, 4093, 6, 2), (4, 5, 4097, 1, 0), (7, 3, 8190, 3, 3), (6, 3, 8195, 4, 1), (4, 2, 16385, 0, 1),
                                              (3, 2, 20479, 2, 0), (5, 2, 32000, 3, 2), (4, 2, 65430, 1, 1)])
 def test_rows_off_a_line(dtype, act, N, M, K, first, pad):
