@@ -19,8 +19,9 @@
 // instruction) serve the 16x16 one as they are: weight lane (r, g) takes, for rows 16 hh + r of a fragment, the 16 bytes
 // of lane 16 hh + r + 32 (g >> 1) of packed step g & 1 of the super-unit in steps 0 and 1, and those of lane
 // 16 hh + r + 32 (g & 1) of packed step 2 of super-unit u(g >> 1) in step 2 (measured: value half h of weight lane group g
-// meets 16-byte half g >> 1 of token lane group 2 (g & 1) + h).  With an odd number of super-units the last pair has zeros
-// in u1's place.
+// meets 16-byte half g >> 1 of token lane group 2 (g & 1) + h).  With an odd number of super-units the last pair has no step
+// 1, and zeros in u1's place in step 2 (time over that with a whole pair, u1 all zeros: 1 to 5 super-units 0.95 .. 0.97, 7 to 13 0.96 .. 0.98, 21
+// to 57 0.98 .. 0.99; against the 32x32 kernel before it 3 and 5 super-units in a single round of tiles are 1.00 .. 1.05, more of either 0.90 .. 1.02).
 //
 // Tile engine.  Persistent workgroups, 256 channels x 256 tokens per tile, eight wavefronts (two per SIMD) of 128
 // channels x 64 tokens = 8 x 4 accumulator blocks.  Operands go L2 -> LDS with direct loads into two rings: token tiles
@@ -34,7 +35,8 @@
 // next tile's first pair, and between two tiles there is only the epilogue, without a meeting (wavefronts may be in
 // different tiles until the next one).  The epilogue stages in the token slot that is free then; it waits for the wavefront's
 // own requests before its first store, because the wait counter counts stores too, and the first two meetings of a tile
-// then wait for no load at all.
+// behind another then wait for no load at all.  A workgroup's first tile starts when the operands of step 0 have landed (time over waiting for
+// the whole pair: rows of 2 to 8 super-units 0.93 .. 0.99, 28 and 32 0.95 .. 1.00).
 //
 // Token tile in LDS: 256 rows x 128 bytes, the 16-byte chunk c of row r stored at chunk place(c) ^ ((r >> 1) & 7) (the
 // permutation is applied on the global-address side: a direct load writes 64 lanes x 16 bytes contiguously, i.e. eight
@@ -63,7 +65,8 @@ constexpr int F_SX_OFF = F_SW_OFF + BO * 4;
 constexpr int F_LDS = F_SX_OFF + BT * 4;              // 158 KB
 static_assert(F_LDS <= 160 * 1024, "LDS budget");
 
-template <int DT>
+// ODD: an odd number of super-units
+template <int DT, bool ODD>
 __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
                                                       const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U,
                                                       int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, int tiles_o, int tiles_t)
@@ -113,18 +116,18 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
     };
     // Load number d of group g of the pair whose first super-unit is u0.  Group 0: packed steps 0, 1 of u0 and u0's token tile;
     // 1: those of u1; 2: packed step 2 of both.  d: 0, 1 values, 2 index words, 3 .. 6 tokens (to ring slot tslot).
-    // Where the row ends with u0, the values of u1 are zeros, its tokens (u0's again) are masked out when they are read.
+    // Where the row ends with u0, the values of u1 are zeros and its tokens (u0's again) are not read.
     auto load = [&](auto group_c, auto d_c, int u0, uint32_t tslot, uint64_t lanes, auto masked_c) __attribute__((always_inline)) {
         constexpr int G = decltype(group_c)::value, D = decltype(d_c)::value;
         constexpr bool MASKED = decltype(masked_c)::value;
-        const int u1 = u0 + 1 < U ? u0 + 1 : u0;
+        const int u1 = !ODD || u0 + 1 < U ? u0 + 1 : u0;
         if constexpr (D == 2) {
             const int u = G == 0 ? u0 : G == 1 ? u1 : mj ? u1 : u0;
-            lds_dma16_lanes_from<(G == 0 ? 0 : G == 1 ? 3 : 2) * F_ASTEP>(am_src, u * 3072 + (G == 2 ? 2048 : mj * 1024), lane16, m_wave + (G == 2 ? 3 : 1) * mj * F_ASTEP, lanes & 0xffffffffull);
+            lds_dma16_lanes_from<(G == 0 ? 0 : G == 1 ? 3 : 2) * F_ASTEP>(am_src, __builtin_amdgcn_readfirstlane(u * 3072 + (G == 2 ? 2048 : mj * 1024)), lane16, m_wave + (G == 2 ? 3 : 1) * mj * F_ASTEP, lanes & 0xffffffffull);
         } else if constexpr (D < 2) {
             constexpr bool OF_U1 = G == 1 || (G == 2 && D == 1);
             constexpr int SLOT = G == 2 ? 2 + 3 * D : 3 * G + D;         // ring slot; packed step SLOT % 3 of its super-unit
-            const bool none = OF_U1 && u1 == u0;
+            const bool none = ODD && OF_U1 && u1 == u0;
             const uint8_t* src = none ? reinterpret_cast<const uint8_t*>(no_values) : av_src;
             const uint32_t off = none ? 0 : (OF_U1 ? u1 : u0) * 12288 + (SLOT % 3) * 4096;
             if constexpr (MASKED) lds_dma16_lanes_from<SLOT * F_ASTEP>(src, off, lane16, a_wave, lanes);
@@ -146,7 +149,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
         constexpr int d = decltype(d_c)::value, G = d / 7;
         load(std::integral_constant<int, G>{}, std::integral_constant<int, d - 7 * G>{}, 0, G ? t1 : t0, ~0ull, all_lanes);
     });
-    wait_vmcnt<0>();
+    wait_vmcnt<10>();                                 // group 0
     wg_barrier();
 
     struct Regs { v4i a[8], ix[2]; v8i raw[4], mid[4]; };
@@ -175,8 +178,6 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
         };
 
         const uint32_t more = __builtin_amdgcn_readfirstlane(have ? ~0u : 0u);       // the last pair requests the next tile's first one, if there is one
-        const int keep = U & 1 ? 0 : -1;              // the last pair's u1: nothing if the row has an odd number of super-units
-        auto mask_raw = [&](int b) __attribute__((always_inline)) { R.raw[b] = R.raw[b] & keep; };
 
         // The direct loads behind instruction i of step S, as group * 8 + number, -1 none.  They are spread evenly: the compute
         // unit takes 17 cycles for each, and a wavefront that has to wait for room in the queue issues no matrix instruction.
@@ -184,10 +185,14 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
         // group 1 from step 1 to step 2, the three of group 2.  Cycles of a pair, INT8 / bf16, 3584 -> 37888 (matrix
         // instructions 3072): 3750 / 3850 like this, 3937 / 4040 with the meeting four instructions earlier, weights first and
         // even priorities (below), 4020 / 4500 with the loads in bunches.
-        constexpr auto load_at = [](int S, int i) constexpr {
+        // SHORT: the last pair has no u1, so no step 1; its requests go to steps 0 and 2.
+        constexpr auto load_at = [](bool SHORT, int S, int i) constexpr {
             constexpr int at[3][6] = {{15, 19, 23, 27, 31, -1}, {4, 9, 15, 20, 25, 30}, {4, 9, 15, 20, 25, 30}};
             constexpr int what[3][6] = {{3, 4, 5, 6, 0, -1}, {1, 2, 8, 9, 10, 11}, {12, 13, 14, 16, 17, 18}};
-            for (int d = 0; d < 6; ++d) if (at[S][d] == i) return what[S][d];
+            constexpr int at_short[2][10] = {{15, 17, 19, 22, 25, 28, 31, -1, -1, -1}, {1, 4, 7, 10, 13, 17, 20, 23, 26, 29}};
+            constexpr int what_short[2][10] = {{3, 4, 5, 6, 0, 1, 2, -1, -1, -1}, {8, 9, 10, 11, 12, 13, 14, 16, 17, 18}};
+            for (int d = 0; d < (SHORT ? 10 : 6); ++d)
+                if ((SHORT ? at_short[S / 2][d] : at[S][d]) == i) return SHORT ? what_short[S / 2][d] : what[S][d];
             return -1;
         };
 
@@ -195,14 +200,19 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
         // so that everything has fourteen or more instructions between its last use and its next.
         auto step = [&](auto step_c, auto last_c, int p) __attribute__((always_inline)) {
             constexpr int S = decltype(step_c)::value;
-            constexpr bool LAST = decltype(last_c)::value, NEXT = S < 2 || !LAST;       // the next step's operands are read
-            constexpr int NS = S == 2 ? 0 : S + 1;
+            constexpr bool LAST = decltype(last_c)::value, SHORT = ODD && LAST, NEXT = S < 2 || !LAST;       // NEXT: the next step's operands are read
+            constexpr int NS = S == 2 ? 0 : SHORT ? 2 : S + 1;
             constexpr int MEET = 14;
             const int u_ld = LAST ? 0 : 2 * p + 2;                       // first super-unit of the pair being requested
             const uint64_t lanes = LAST ? ((uint64_t)more << 32) | more : ~0ull;
             const uint32_t vb_now = vb + t1, vb_next = vb + (S == 0 ? t1 : tz);
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (S == 1 && LAST) { mask_raw(0); mask_raw(1); __builtin_amdgcn_sched_barrier(0); }
+            if constexpr (SHORT && S == 0) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int j = 4; j < 8; ++j) asm("v_mov_b32 %0, 0" : "=v"(R.mid[b][j]));      // opaque, as in make_mid
+            }
             unroll<32>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value;
                 constexpr int a = (i >> 1) & 7, b = 2 * (i >> 4) + (i & 1);
@@ -217,22 +227,23 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
                 if (i == 16) __builtin_amdgcn_s_setprio(1);
                 if (S == 0 && LAST && i == 4) setup_tile(to, tt);          // the next tile's, or this one's again
                 if (i == MEET) {
-                    const int later = min(p, 1), rest = LAST ? (2 & ~(int)more) : 0;      // a tile's first pair; nothing requested by the last one
-                    if constexpr (S == 0) wait_vm_mode<3>(later);
+                    // 0 for the first pair of a tile that follows another: it landed before the epilogue's stores.  rest: nothing is requested by the last pair
+                    const int later = min(p + 1 - min(round, 1), 1), rest = LAST ? (2 & ~(int)more) : 0;
+                    if constexpr (SHORT && S == 0) wait_vm_mode<0>(later);
+                    else if constexpr (S == 0) wait_vm_mode<3>(later);
                     else if constexpr (S == 1) wait_vm_mode<(LAST && MM::SCALED ? 8 : 7)>(LAST ? (later & (int)more) | rest : later);
-                    else wait_vm_mode<6>(LAST ? (1 & (int)more) | rest : 1);
+                    else wait_vm_mode<(SHORT ? 5 : 6)>(LAST ? (1 & (int)more) | rest : 1);
                     wait_lgkm0();
                     wg_barrier();
                     if constexpr (S == 0 && LAST && MM::SCALED) load_tile_scales(s_w, s_x, O, M, o_blk, t_blk, wave, lds0 + F_SW_OFF);
                 }
-                if (S == 1 && LAST && (i == 9 || i == 11)) mask_raw(2 + ((i - 9) >> 1));
                 if (S == 1 && i >= 9 && i < 13) make_mid(1, 2 + ((i - 9) >> 1), (i - 9) & 1);
-                if constexpr (constexpr int l = load_at(S, i); l >= 0)
+                if constexpr (constexpr int l = load_at(SHORT, S, i); l >= 0)
                     load(std::integral_constant<int, (l >> 3)>{}, std::integral_constant<int, (l & 7)>{}, u_ld, l < 8 ? tz : t0, lanes, std::integral_constant<bool, LAST>{});
                 if constexpr (NEXT) {
                     if (i >= 17 && (i & 1)) read_a(NS, (i - 17) >> 1);
                     if (i == 24) read_ix(NS, 0);
-                    if (S == 0 && i >= 16 && !(i & 1) && i < 24) read_raw((i - 16) >> 2, (i >> 1) & 1, vb_next);
+                    if (S == 0 && !SHORT && i >= 16 && !(i & 1) && i < 24) read_raw((i - 16) >> 2, (i >> 1) & 1, vb_next);
                     if (S == 2 && i >= 16 && !(i & 1)) read_raw((i - 16) >> 2, (i >> 1) & 1, vb_next);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -265,7 +276,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
             t0 = tz; t1 = was0; tz = was1;
         }
         step(s0, std::true_type{}, p);
-        step(s1, std::true_type{}, p);
+        if constexpr (!ODD) step(s1, std::true_type{}, p);
         step(s2, std::true_type{}, p);
         const uint32_t was0 = t0, was1 = t1;
         t0 = tz; t1 = was0; tz = was1;                 // tz: nobody reads it any more, nothing is requested into it before the next meeting
@@ -282,7 +293,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused(const uint8_t* __restrict_
 
 using namespace ss;
 
-template <int DT>
+template <int DT, bool ODD>
 static ss_status launch_fused(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
                               int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
 {
@@ -290,8 +301,8 @@ static ss_status launch_fused(const void* Xq, const float* s_x, const void* w_va
     const int cus = cu_count(), ntiles = tiles_o * tiles_t;
     const int grid = ntiles < cus ? ntiles : cus;
     if (grid <= 0) return SS_ERR_HIP;
-    if (allow_dynamic_lds<k_sparse_fused<DT>>(F_LDS) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_fused<DT>), dim3(grid), dim3(512), F_LDS, stream, static_cast<const uint8_t*>(Xq), s_x,
+    if (allow_dynamic_lds<k_sparse_fused<DT, ODD>>(F_LDS) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_fused<DT, ODD>), dim3(grid), dim3(512), F_LDS, stream, static_cast<const uint8_t*>(Xq), s_x,
                        static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy,
                        tiles_o, tiles_t);
     return launch_status();
@@ -322,7 +333,7 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     if (p.path == SS_PATH_NARROW) return launch_sparse_fused_narrow(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     // channels [0, p.tile_o) on 256 x 256 tiles, the others on 128 x 128 or 128 x 256 tiles
     ss_status st = SS_ERR_DTYPE;
-#define SS_F(DT) launch_fused<DT>(Xq, s_x, w_vals, w_meta, s_w, M, p.tile_o, U, ldxb, Y, ldy, hs)
+#define SS_F(DT) (U & 1 ? launch_fused<DT, true> : launch_fused<DT, false>)(Xq, s_x, w_vals, w_meta, s_w, M, p.tile_o, U, ldxb, Y, ldy, hs)
     switch (dtype) {
     case SS_I8: st = SS_F(SS_I8); break;
     case SS_FP8_E4M3: st = SS_F(SS_FP8_E4M3); break;

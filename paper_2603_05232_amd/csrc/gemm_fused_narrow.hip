@@ -13,7 +13,8 @@
 // direct loads (1570 cycles at 60 bytes a clock) beside 1536 cycles of matrix instructions; starting each XCD
 // elsewhere in the k range, or bands of four token tiles instead of eight, changed nothing (10 shapes, 0.95 .. 1.06).
 // Against the 128 x 128 tiles, time with weights from HBM: fp8 4096 -> 4096 at M = 2048 41.3 -> 31.7 us, 14336 -> 4096 110 ->
-// 91.5, INT8 4096 -> 8192 at M = 1024 41.0 -> 31.6, bf16 3584 -> 3584 at M = 2048 54.1 -> 44.7.
+// 91.5, INT8 4096 -> 8192 at M = 1024 41.0 -> 31.6, bf16 3584 -> 3584 at M = 2048 54.1 -> 44.7.  Rows of an odd number of super-units
+// (70 shapes of 1 to 57): 0.88 .. 0.99 of the time with a whole last pair (mean 0.95).
 #include "ss_common.h"
 #include "packed_layout.h"
 #include "mma_types.h"
@@ -33,7 +34,8 @@ constexpr int FN_SX_OFF = FN_SW_OFF + PANEL * 4;
 constexpr int FN_LDS = FN_SX_OFF + BT * 4;
 static_assert(FN_LDS <= 160 * 1024, "LDS budget");
 
-template <int DT>
+// ODD: an odd number of super-units; the last pair has no u1, so no step 1, and zeros in u1's place in step 2
+template <int DT, bool ODD>
 __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
                                                              const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U,
                                                              int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, int panels, int tiles_t)
@@ -46,7 +48,6 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     const int n = lane & 15, g = lane >> 4;
     const uint32_t lds0 = lds_address(smem), lane16 = lane * 16;
     const int P = (U + 1) >> 1;                       // pairs
-    const bool odd = U & 1;                           // the last pair's u1 does not exist: zeros in its values' place, its tokens masked out
     int to, tt;
     if (!tile_of_round(0, panels, tiles_t, to, tt)) return;
     const int64_t o_blk = (int64_t)to * PANEL, t_blk = (int64_t)tt * BT;
@@ -74,12 +75,12 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     auto load_values = [&](auto group_c, int p, uint32_t area) __attribute__((always_inline)) {
         constexpr int G = decltype(group_c)::value;
         const uint32_t at = G == 0 ? 0u : G == 1 ? 12288u : 8192u + (wave >> 2) * 8192u;
-        const bool none = odd && p + 1 == P && (G == 1 || (G == 2 && wave >= 4));
+        const bool none = ODD && p + 1 == P && (G == 1 || (G == 2 && wave >= 4));
         lds_dma16_from<0>(none ? reinterpret_cast<const uint8_t*>(no_values) : av_src, none ? 0u : (uint32_t)p * 24576u + at, lane16, v_wave + area * FN_VALS + at);
     };
     // the index words of a u1 that does not exist stay as they are: they choose among tokens that are zero
     auto load_index = [&](int p, uint32_t area) __attribute__((always_inline)) {
-        const uint64_t lanes = odd && p + 1 == P && wave >= 4 ? 0 : (1ull << 48) - 1;
+        const uint64_t lanes = ODD && p + 1 == P && wave >= 4 ? 0 : (1ull << 48) - 1;
         lds_dma16_lanes_from<0>(am_src, (uint32_t)p * 6144u, lane16, m_wave + area * FN_IDX, lanes);
     };
 
@@ -145,16 +146,16 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     // requested, of the next u1's tokens; the last step reads no operands (the token slots are the epilogue's by then).
     enum { MIDDLE, LAST2, LAST1 };
     auto step = [&](auto step_c, auto pos_c, int p, uint32_t area) __attribute__((always_inline)) {
-        constexpr int S = decltype(step_c)::value, NS = S == 2 ? 0 : S + 1, MEET = 3, POS = decltype(pos_c)::value;
-        const int keep = POS == LAST1 && odd ? 0 : -1;
+        constexpr int S = decltype(step_c)::value, MEET = 3, POS = decltype(pos_c)::value;
+        constexpr bool SHORT = ODD && POS == LAST1;
+        constexpr int NS = S == 2 ? 0 : SHORT ? 2 : S + 1;
         __builtin_amdgcn_sched_barrier(0);
         unroll<16>([&](auto i_c) __attribute__((always_inline)) {
             constexpr int i = decltype(i_c)::value;
             constexpr int a = (i >> 1) & 3, b = 2 * (i >> 3) + (i & 1);
-            if constexpr (POS == LAST1 && S == 1 && (i == 0 || i == 8)) {
+            if constexpr (SHORT && S == 0 && i < 4) {
 #pragma unroll
-                for (int k = 0; k < 2; ++k) R[1].raw[(i >> 2) + k] = R[1].raw[(i >> 2) + k] & keep;
-                __builtin_amdgcn_sched_barrier(0);
+                for (int j = 4; j < 8; ++j) asm("v_mov_b32 %0, 0" : "=v"(mid[i][j]));      // opaque: see gemm_fused.hip
             }
             if constexpr (S == 2) acc[a][b] = MM::sparse16(R[2].a[a], mid[b], acc[a][b], R[2].ix[a & 1][a >> 1]);
             else acc[a][b] = MM::sparse16(R[S].a[a], R[S].raw[b], acc[a][b], R[S].ix[a & 1][a >> 1]);
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     auto pair = [&](auto pos_c, int p) __attribute__((always_inline)) {
         const uint32_t area = p & 1;
         step(c0, pos_c, p, area);
-        step(c1, pos_c, p, area);
+        if constexpr (!(ODD && decltype(pos_c)::value == LAST1)) step(c1, pos_c, p, area);
         step(c2, pos_c, p, area);
         const uint32_t was0 = t0, was1 = t1;
         t0 = tz; t1 = was0; tz = was1;
@@ -262,13 +263,13 @@ __global__ __launch_bounds__(512) void k_sparse_fused_narrow(const uint8_t* __re
     }
 }
 
-template <int DT>
+template <int DT, bool ODD>
 static ss_status launch_narrow(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
                                int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
 {
     const int panels = (int)((O + PANEL - 1) / PANEL), tiles_t = (int)((M + BT - 1) / BT);
-    if (allow_dynamic_lds<k_sparse_fused_narrow<DT>>(FN_LDS) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_fused_narrow<DT>), dim3(panels * tiles_t), dim3(512), FN_LDS, stream, static_cast<const uint8_t*>(Xq), s_x,
+    if (allow_dynamic_lds<k_sparse_fused_narrow<DT, ODD>>(FN_LDS) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_fused_narrow<DT, ODD>), dim3(panels * tiles_t), dim3(512), FN_LDS, stream, static_cast<const uint8_t*>(Xq), s_x,
                        static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy,
                        panels, tiles_t);
     return launch_status();
@@ -277,12 +278,14 @@ static ss_status launch_narrow(const void* Xq, const float* s_x, const void* w_v
 ss_status launch_sparse_fused_narrow(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                                      int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
 {
+#define SS_N(DT) (U & 1 ? launch_narrow<DT, true> : launch_narrow<DT, false>)(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
     switch (dtype) {
-    case SS_I8: return launch_narrow<SS_I8>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
-    case SS_FP8_E4M3: return launch_narrow<SS_FP8_E4M3>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
-    case SS_BF16: return launch_narrow<SS_BF16>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
-    case SS_FP16: return launch_narrow<SS_FP16>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream);
+    case SS_I8: return SS_N(SS_I8);
+    case SS_FP8_E4M3: return SS_N(SS_FP8_E4M3);
+    case SS_BF16: return SS_N(SS_BF16);
+    case SS_FP16: return SS_N(SS_FP16);
     }
+#undef SS_N
     return SS_ERR_DTYPE;
 }
 

@@ -18,11 +18,13 @@ def test_pairs_of_super_units(dtype, units):
 
 
 # more tiles than compute units (256): tiles that follow one another in a workgroup, with tokens and channels that end
-# inside a tile, and rows of one pair, where every load of the next tile is requested by the first pair of the one before
-@pytest.mark.parametrize("dtype", ["i8", "bf16"])
-@pytest.mark.parametrize("M,O,units", [(4300, 4400, 1), (4300, 4400, 2), (4300, 4400, 3), (8100, 9000, 4), (257, 66000, 5)])
+# inside a tile, and rows of one pair, where every load of the next tile is requested by the first pair of the one before.
+# 32 x 36 tiles: four rounds and a half; 2 x 256 and 17 x 15 tiles: two rounds and one, the channels behind them go to other tiles.
+@pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16"])
+@pytest.mark.parametrize("M,O,units", [(4300, 4400, 1), (4300, 4400, 2), (4300, 4400, 3), (8100, 9000, 1), (8100, 9000, 2), (8100, 9000, 3), (8100, 9000, 4),
+                                       (8100, 9000, 5), (257, 66000, 5), (257, 66000, 6)])
 def test_rounds(dtype, M, O, units):
-    _linear(M, O, 128 * units // (1 if dtype == "i8" else 2), 4, dtype, True, False, units)
+    _linear(M, O, 128 * units // (1 if dtype in ("i8", "fp8") else 2), 4, dtype, True, False, units)
 
 
 # an infinite activation in the last super-unit, alone in its pair or not: the products that the row has, and no others
