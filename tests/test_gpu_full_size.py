@@ -182,9 +182,9 @@ def test_output_offsets_beyond_32_bits(M, ldy_log2):
 
 @pytest.mark.parametrize("dtype", ["i8", "fp8"])
 def test_two_persistent_rounds_full_output(dtype):
-    """More 256 x 256 tiles than compute units (17 x 18 = 306: a second persistent round with its tile renumbering, the
-    next tile's first unit requested before the epilogue, scale parity) with ragged edges and a short K, so that the
-    CPU oracle can check EVERY output element of the sparse and of the dense kernel (not one against the other)."""
+    """More 256 x 256 tiles than compute units (17 x 18 = 306; dense: a second persistent round with its tile renumbering, the
+    next tile's first unit requested before the epilogue, scale parity; sparse: one round of 17 x 15, the channels behind it on 128 x
+    128 tiles) with ragged edges and a short K, so that the CPU oracle can check EVERY output element of the sparse and of the dense kernel (not one against the other)."""
     from oracle import gemm_ref
     N, M, O, K = 4, 4300, 4400, 256
     rng = np.random.default_rng(11)

@@ -77,8 +77,8 @@ def test_fused_gemm_small_and_mid_float(dtype, M, O, K):
 
 
 def test_fused_gemm_two_rounds_full_output_and_strides():
-    """More tiles than compute units (17 x 18 = 306 tiles of 256 x 256: two persistent rounds), ragged edges, random
-    sparse supports (windows with 0, 1 and 2 stored values), strided X and Y; every output element against the C oracle."""
+    """More tiles of 256 x 256 than compute units (17 x 18: one round of 17 x 15, the channels behind it on 128 x 128 tiles), ragged
+    edges, random sparse supports (windows with 0, 1 and 2 stored values), strided X and Y; every output element against the C oracle."""
     rng = np.random.default_rng(5)
     M, O, K = 4300, 4400, 256
     Wq = rng.integers(-127, 128, size=(O, K)).astype(np.int8)
@@ -190,7 +190,7 @@ def test_fused_random_shapes_float_end_to_end(dtype, M, O, K, with_ws):
 
 @pytest.mark.parametrize("M", [16, 128, 600])
 def test_fused_hip_graph_replay(M):
-    """Quantisation + fused GEMM (few-token kernel; 128 x 128 tiles with split k and their reduction; persistent tiles)
+    """Quantisation + fused GEMM (few-token kernel; 128 x 128 tiles with split k and their reduction, one and five token tiles)
     recorded into a HIP graph: nothing is allocated and nothing synchronises.  Every replay is checked against the oracle,
     with new activations written into the captured input buffer between replays."""
     K, O = 2048, 640

@@ -20,9 +20,12 @@ def test_pairs_of_super_units(dtype, units):
 # more tiles than compute units (256): tiles that follow one another in a workgroup, with tokens and channels that end
 # inside a tile, and rows of one pair, where every load of the next tile is requested by the first pair of the one before.
 # 32 x 36 tiles: four rounds and a half; 2 x 256 and 17 x 15 tiles: two rounds and one, the channels behind them go to other tiles.
+ROUNDS = [(8100, 9000, 1), (8100, 9000, 2), (8100, 9000, 3), (8100, 9000, 4), (8100, 9000, 5), (257, 66000, 5), (257, 66000, 6)]
+ONE_ROUND_AND_REST = [(4300, 4400, 1), (4300, 4400, 2), (4300, 4400, 3)]
+
+
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16"])
-@pytest.mark.parametrize("M,O,units", [(4300, 4400, 1), (4300, 4400, 2), (4300, 4400, 3), (8100, 9000, 1), (8100, 9000, 2), (8100, 9000, 3), (8100, 9000, 4),
-                                       (8100, 9000, 5), (257, 66000, 5), (257, 66000, 6)])
+@pytest.mark.parametrize("M,O,units", ROUNDS + ONE_ROUND_AND_REST)
 def test_rounds(dtype, M, O, units):
     _linear(M, O, 128 * units // (1 if dtype in ("i8", "fp8") else 2), 4, dtype, True, False, units)
 

@@ -50,7 +50,8 @@ def _linear(M, O, K, N, dtype, fused, with_ws, seed):
     assert bool((out[M] == 7.0).all())                                 # nothing beyond the last token
 
 
-# 192 panels, unsplit: one workgroup per compute unit (256 of them), rings of eight (32 tokens) and four units (64)
+# 192 panels, unsplit: one workgroup per compute unit (256 of them), two groups of wavefronts with rings of four units each (32 tokens, from two
+# units up) and a ring of four units (64)
 @pytest.mark.parametrize("M", [1, 32, 33, 64])
 @pytest.mark.parametrize("units", [1, 2, 3, 4, 5, 7, 8, 9, 10, 18])
 def test_wide_layers_of_few_tokens(M, units):
@@ -74,10 +75,15 @@ def test_rings_of_shared_compute_units(dtype, N, M, units):
 
 
 # the same with more than a quarter of the compute units shared and rows long enough for the pipeline of three (lifted) or
-# two units (fused); nine and ten token tiles: two bands
-@pytest.mark.parametrize("dtype,M,O,units,N,fused", [("i8", 100, 321 * 128 - 3, 32, 4, False), ("bf16", 100, 322 * 128, 33, 4, False), ("fp8", 128, 330 * 128, 34, 3, False),
-                                                     ("fp16", 1100, 4700, 35, 5, False), ("i8", 1250, 4200, 12, 4, True), ("bf16", 1100, 4700, 13, 4, True),
-                                                     ("i8", 1250, 3900, 9, 4, False), ("bf16", 1100, 3700, 7, 4, False)])
+# two units (fused); three, nine and ten token tiles, the last two in two bands
+SHARED = [("i8", 100, 321 * 128 - 3, 32, 4, False), ("bf16", 100, 322 * 128, 33, 4, False), ("fp8", 128, 330 * 128, 34, 3, False), ("fp16", 1100, 4700, 35, 5, False),
+          ("i8", 1250, 3900, 9, 4, False), ("bf16", 1100, 3700, 7, 4, False), ("i8", 300, 130 * 128 - 3, 12, 4, True), ("bf16", 300, 130 * 128, 13, 4, True),
+          ("i8", 1100, 52 * 128, 24, 4, True), ("fp16", 1100, 52 * 128 - 5, 25, 4, True), ("fp8", 1100, 55 * 128, 26, 4, True)]
+# at most one tile of 128 channels x 256 tokens per compute unit: those
+SHARED_NARROW = [("i8", 1250, 4200, 12, 4, True), ("bf16", 1100, 4700, 13, 4, True)]
+
+
+@pytest.mark.parametrize("dtype,M,O,units,N,fused", SHARED + SHARED_NARROW)
 def test_shared_pipelines_and_bands(dtype, M, O, units, N, fused):
     _linear(M, O, _rows(units, N, dtype, fused), N, dtype, fused, False, units)
 
@@ -85,14 +91,16 @@ def test_shared_pipelines_and_bands(dtype, M, O, units, N, fused):
 # Both sides of every line of the kernel choice for sparse calls, for 256 compute units: tiles (320, 448, 512) and units
 # per row (12 and 24 fused, 24 and 48 lifted) between 128 x 128 and 256 x 256 tiles; panels (128 and 192) and rows (48 units;
 # 2 units + tokens = 128) between few-token kernels and tiles of 32 and 64 tokens, with the workspace the rows are split
-# in; a rest of a round of exactly one tile per compute unit and of one panel more.
+# in; a rest of a round of exactly one tile per compute unit and of one panel more, and, fused, of up to one 128 x 256 tile (16 units and
+# more).
 @pytest.mark.parametrize("M,O,units,ws", [(65, 128 * 320, 3, False), (65, 128 * 321, 11, False), (65, 128 * 321, 12, False), (65, 128 * 321, 23, False),
                                           (65, 128 * 321, 24, False), (65, 128 * 448, 12, False), (65, 128 * 449, 23, False), (65, 128 * 449, 24, False),
                                           (65, 128 * 449, 47, False), (65, 128 * 449, 48, False), (65, 128 * 512, 48, False), (65, 128 * 513, 48, False),
                                           (15, 128 * 191, 3, False), (15, 128 * 192, 3, False), (16, 128 * 127, 3, False), (16, 128 * 128, 3, False),
                                           (64, 128 * 127, 3, False), (64, 128 * 128, 3, False), (1, 500, 63, True), (1, 500, 64, True), (32, 500, 47, True),
                                           (32, 500, 48, True), (33, 500, 47, True), (33, 500, 48, True), (64, 500, 47, True), (64, 500, 48, True),
-                                          (1000, 16384 + 4096, 3, False), (1000, 16384 + 4097, 3, False)])
+                                          (1000, 16384 + 4096, 3, False), (1000, 16384 + 4097, 3, False),
+                                          (8100, 2048 + 1000, 15, False), (8100, 2048 + 1000, 16, False), (8100, 2048 + 1100, 16, False)])
 @pytest.mark.parametrize("fused", [True, False])
 def test_lines_of_the_kernel_choice(M, O, units, ws, fused):
     _linear(M, O, _rows(units, 4, "i8", fused), 4, "i8", fused, ws, units)

@@ -21,17 +21,23 @@ def test_pairs_of_super_units(dtype, units):
     _linear(1100, 4224 - (units & 1) * 3, _k(units, dtype), 4, dtype, True, bool(units & 2), units)
 
 
+EDGES = [(129, 129 * 128), (255, 140 * 128 - 1), (256, 256 * 128), (257, 86 * 128 + 8), (4097, 1000), (16300, 500)]
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
-@pytest.mark.parametrize("M,O", [(129, 129 * 128), (255, 140 * 128 - 1), (256, 256 * 128), (257, 86 * 128 + 8), (4097, 1000), (16300, 500)])
+@pytest.mark.parametrize("M,O", EDGES)
 def test_edges_of_tiles(dtype, M, O):
     _linear(M, O, _k(5, dtype), 4, dtype, True, False, M)
 
 
 # 8 token tiles: one round of 32 x 8 tiles of 256 x 256, the rest 25 panels x 8
+REST = (2048, 32 * 256 + 3142)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
 @pytest.mark.parametrize("units", [16, 17])
 def test_rest_behind_whole_rounds(dtype, units):
-    _linear(2048, 32 * 256 + 3142, _k(units, dtype), 4, dtype, True, False, units)
+    _linear(*REST, _k(units, dtype), 4, dtype, True, False, units)
 
 
 @pytest.mark.parametrize("dtype", ["i8", "fp16"])

@@ -1,0 +1,95 @@
+"""The shapes that the GPU tests name for a kernel are the ones that the dispatch sends there (on 256 compute units): the rule of
+mma_types.h, compiled for the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_large_tiles
+import test_gpu_lifted_tiles
+import test_gpu_mid_tiles
+import test_gpu_narrow_tiles
+import test_gpu_replay
+from paper_2603_05232_amd import binding, build
+
+SOURCE = """
+#include "mma_types.h"
+#include <stdio.h>
+using namespace ss;
+int main()
+{
+    int kind; long long M, O, units; unsigned long long ws;
+    while (scanf("%d %lld %lld %lld %llu", &kind, &M, &O, &units, &ws) == 5) {
+        const ss_plan p = plan_gemm((ss_kind)kind, M, O, units, (size_t)ws);
+        const long long cut = p.path == SS_PATH_TILE ? (long long)p.tile_o : 0;
+        const int rest = cut == 0 || cut == O ? -1 : kind == SS_KIND_FUSED && narrow_pays(M, O - cut, cu_count()) ? SS_PATH_NARROW : SS_PATH_MID;
+        printf("%d %d %lld %d %d\\n", (int)p.path, p.S, cut, rest, cu_count());
+    }
+}
+"""
+MID, NARROW, TILE = 1, 2, 3
+LIFTED, FUSED = 0, 1
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if shutil.which(hipcc) is None:
+        pytest.skip("no hipcc")
+    binding.load()
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(build.ROOT, "include"), "-I" + build.CSRC,
+                    "-c", str(d / "plan.cpp"), "-o", str(d / "plan.o")], check=True)
+    subprocess.run([hipcc, str(d / "plan.o"), "-L" + build.PKG, "-lslidesparse", "-Wl,-rpath," + build.PKG, "-o", str(d / "plan")], check=True)
+
+    def ask(kind, M, O, units, ws=0):
+        out = subprocess.run([str(d / "plan")], input=f"{kind} {M} {O} {units} {ws}\n", stdout=subprocess.PIPE, text=True, check=True).stdout
+        path, S, cut, rest, cus = map(int, out.split())
+        if cus != 256:
+            pytest.skip("the shapes are chosen for 256 compute units")
+        return {"path": path, "S": S, "cut": cut, "rest": rest, "large_tiles": -(-cut // 256) * -(-M // 256)}
+    return ask
+
+
+@pytest.mark.parametrize("kind,module", [(FUSED, test_gpu_large_tiles), (LIFTED, test_gpu_lifted_tiles)])
+def test_rounds_of_large_tiles(plan, kind, module):
+    for M, O, units in module.ROUNDS:
+        p = plan(kind, M, O, units)
+        assert p["path"] == TILE and p["large_tiles"] > 256, (M, O, units, p)
+    assert {u for M, O, u in module.ROUNDS if M == 8100} >= {1, 2, 3, 4, 5}
+    for M, O, units in module.ONE_ROUND_AND_REST:
+        p = plan(kind, M, O, units)
+        assert p["path"] == TILE and p["large_tiles"] <= 256 and p["rest"] == MID, (M, O, units, p)
+
+
+def test_narrow_tiles(plan):
+    for M, O in test_gpu_narrow_tiles.EDGES + [(1100, 4224), (1100, 4221), (700, 50 * 128 - 5)]:
+        assert plan(FUSED, M, O, 5)["path"] == NARROW, (M, O)
+    M, O = test_gpu_narrow_tiles.REST
+    assert plan(FUSED, M, O, 16)["rest"] == NARROW and plan(FUSED, M, O, 15)["cut"] == O
+
+
+def test_shared_compute_units(plan):
+    for dtype, M, O, units, N, fused in test_gpu_mid_tiles.SHARED:
+        p = plan(FUSED if fused else LIFTED, M, O, units)
+        assert p["path"] == MID and -(-M // 128) * -(-O // 128) > 256, (dtype, M, O, units, N, fused, p)
+    for dtype, M, O, units, N, fused in test_gpu_mid_tiles.SHARED_NARROW:
+        assert plan(FUSED, M, O, units)["path"] == NARROW
+
+
+def test_replayed_routes(plan):
+    for name, (fused, M, O, K, with_ws) in test_gpu_replay.ROUTES.items():
+        units = (K if fused else binding.slide_lifted_ld(K, 4, "i8")) // 128
+        p = plan(FUSED if fused else LIFTED, M, O, units, 1 << 30 if with_ws else 0)
+        if "groups" in name:
+            assert p["path"] == MID and M <= 32 and (p["S"] > 1) == with_ws and units // p["S"] >= 2 and -(-O // 128) * p["S"] <= 256, name
+        elif name == "narrow tiles":
+            assert p["path"] == NARROW, name
+        else:
+            assert p["path"] == TILE and (p["rest"] == NARROW) == ("rest" in name) and (p["large_tiles"] > 256) == ("rounds" in name), name
+        if "odd" in name or "even" in name:
+            assert units % 2 == ("odd" in name), name
+        if "short" in name:
+            assert units < 4, name
