@@ -25,14 +25,14 @@ sys.path.insert(0, ROOT)
 PEAK_INT8_DENSE_TOPS = 5033.0      # MI355X published dense INT8; v_smfmac runs at the same MAC rate with 2x the K
 PEAK_INT8_SPARSE_TOPS = 2 * PEAK_INT8_DENSE_TOPS
 PEAK_HBM_GBS = 8000.0
-# Fabric-side traffic of the sparse GEMM kernels per launch (mean over the four layer launches of a step): a RECORDED
+# Fabric-side traffic of the sparse GEMMs per layer (mean over the four layers of a step, the rests on smaller tiles counted in): a RECORDED
 # constant, not measured by the run that prints it.  It comes from the FETCH_SIZE and WRITE_SIZE counters of two
 # rocprofv3 --pmc runs of this script, each scaled by what the same counter reads for the 256 MiB elementwise copy of
 # --copy-calibration; summary and commands in profiles/gemm_qwen7b_m8192_int8_hbm_traffic.txt.
 # Untimed load before every measurement, in seconds (ahead of the --warmup steps): the device needs about 50 ms under
 # load to reach steady clocks after the idle set-up phase.
 SETTLE_SECONDS = 0.15
-RECORDED_TRAFFIC = {"fused": 1.0443e9, "lifted": 1.2932e9}
+RECORDED_TRAFFIC = {"fused": 9.565e8, "lifted": 1.2410e9}
 N_PATTERN = 4                      # 6:8
 M_TOKENS = 8192
 
@@ -421,7 +421,7 @@ def main():
                                 "prune_quant_GBps_of_weight_bytes": sum(b for _, b, _, _ in offline) / sum(p for _, _, p, _ in offline) * 1e-6},
         "roofline": {"bound": "mfma", "achieved": executed_tops, "peak": PEAK_INT8_DENSE_TOPS, "unit": "TOP/s",
                      "frac": executed_tops / PEAK_INT8_DENSE_TOPS, "traffic": RECORDED_TRAFFIC["fused"],
-                     "kernel": "ss::k_sparse_fused<0> (slide_sparse_gemm_fused, INT8), mean over the four layer launches of a step",
+                     "kernel": "ss::k_sparse_fused<0, false> (slide_sparse_gemm_fused, INT8; rests on ss::k_sparse_mid and ss::k_sparse_fused_narrow), mean over the four layers of a step",
                      "note": "INT8 ops; achieved = executed MACs x 2 = M*O*K_lifted per launch / HIP-event duration; "
                              "identical to hardware-counted 2*M*O*K_lifted against the 2x sparse peak; traffic is a recorded "
                              "constant from an earlier rocprofv3 --pmc run of this script (null until recorded)"},

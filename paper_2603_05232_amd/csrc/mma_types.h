@@ -5,8 +5,8 @@
 
 namespace ss {
 
-// Sparse: one instruction is 32 channels x 32 tokens x 64 lifted bytes (A = 16 bytes of stored values + an
-// index word per lane, B = 32 bytes per lane).  Dense: DENSE_SUB k-bytes per instruction, A and B
+// Sparse: one instruction is 32 channels x 32 tokens x 64 lifted bytes (sparse) or 16 x 16 x 128 (sparse16), A = 16 bytes of
+// stored values + an index word per lane, B = 32 bytes per lane in both.  Dense: DENSE_SUB k-bytes per instruction, A and B
 // DENSE_SUB / 2 bytes per lane; lane (row, q) holds the bytes [q DENSE_SUB / 2, (q + 1) DENSE_SUB / 2) of
 // its row within the instruction's k range, for both operands (measured: element e of A lane (i, q)
 // meets element e of B lane (n, q)).
@@ -30,8 +30,8 @@ template <> struct Mma<SS_FP8_E4M3> {
     static constexpr int DENSE_SUB = 64;
     static constexpr bool SCALED = true;
     __device__ static acc_t sparse(v4i a, v8i b, acc_t c, int idx) { return __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(a, b, c, idx, 0, 0); }
-    // format selectors 0 = e4m3 for both operands; block scales 0 = the unscaled form of the instruction
     __device__ static acc16_t sparse16(v4i a, v8i b, acc16_t c, int idx) { return __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(a, b, c, idx, 0, 0); }
+    // format selectors 0 = e4m3 for both operands; block scales 0 = the unscaled form of the instruction
     __device__ static acc_t dense(dfrag_t a, dfrag_t b, acc_t c) { return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0); }
 };
 template <> struct Mma<SS_BF16> {
@@ -198,20 +198,23 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
 // Fused, more 128 x 128 tiles than compute units and at most one tile of 128 channels x 256 tokens for each: those
 //             (gemm_fused_narrow.hip).  Time over that of the paths above, INT8 and bf16, 4 to 64 units, M = 200 .. 4096,
-//             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  With as many 128 x 128 tiles as compute units or
+//             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  At the fewest, a middle and the most panels for M = 129 .. 8192, 4
+//             to 112 units, all types, 118 shapes: 0.69 .. 0.94 (mean 0.79) and 0.70 .. 1.04; the worst, M = 257 on 128 panels, where half of the tiles
+//             hold one token: 0.83 and 1.04.  With as many 128 x 128 tiles as compute units or
 //             fewer, those (4096 -> 4096 at M = 1024: 23.2 against 26.2); with more than one 128 x 256 tile per compute unit 256 x 256 tiles
 //             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
 enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE };
-struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 tiles
+struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
 // unit, the rest goes to those (M = 8192, 3584 -> 4608, 2.25 rounds: bf16 210 -> 194 us, INT8 120 -> 116).  With two of them per
 // compute unit (half a round) the two sides are level or worse: half a round runs at a higher clock (lifted INT8 4096 -> 6144 at M =
 // 4096: 97 against 102).  Unlifted rows have tiles of 128 x 256 for that: one per compute unit, 16 units
-// and more (time over 256 x 256 tiles throughout, INT8 and bf16, M = 777 .. 8192, rests of 0.3 to 0.5 round: 28 units 0.94 .. 1.00, 64 units 0.92 .. 0.97;
-// 8 units, where the second launch costs more than the rest, 1.01 .. 1.05).
+// and more (time over 256 x 256 tiles throughout, INT8, fp8 and bf16, M = 513 .. 8192, weights from HBM, 240 shapes: 4 to 6 units 1.01 .. 1.09 (mean 1.04),
+// 8 to 13 0.96 .. 1.09 (1.00), 14 and 15 0.96 .. 1.02 (0.99), 16 to 20 0.93 .. 1.01 (0.985), 24 to 48 0.91 .. 1.01 (0.96): in short rows the second
+// launch costs what the rest saves).
 inline int64_t tile_channels(ss_kind kind, int64_t M, int64_t O, int64_t units, int64_t cus)
 {
     const int64_t tiles_o = (O + 255) / 256, tiles_t = (M + 255) / 256, rounds = tiles_o * tiles_t / cus, c = rounds * cus / tiles_t;
