@@ -200,7 +200,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             (gemm_fused_narrow.hip).  Time over that of the paths above, INT8 and bf16, 4 to 64 units, M = 200 .. 4096,
 //             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  At the fewest, a middle and the most panels for M = 129 .. 8192, 4
 //             to 112 units, all types, 118 shapes: 0.69 .. 0.94 (mean 0.79) and 0.70 .. 1.04; the worst, M = 257 on 128 panels, where half of the tiles
-//             hold one token: 0.83 and 1.04.  With as many 128 x 128 tiles as compute units or
+//             hold one token: 0.83 and 1.04.  M = 11000 .. 65536 on four panels to one, 140 shapes, two cards: 0.68 .. 1.06, but on one panel with 50000 tokens and more, rows
+//             of 8 and 12 KB (whose lines meet in the same memory channels) 1.00 .. 1.23.  With as many 128 x 128 tiles as compute units or
 //             fewer, those (4096 -> 4096 at M = 1024: 23.2 against 26.2); with more than one 128 x 256 tile per compute unit 256 x 256 tiles
 //             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
