@@ -225,7 +225,7 @@ template <int TM, bool FUSED> struct MidUnit {
 };
 template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE, int KG>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE, int KG, bool ONCE>
 __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
@@ -272,8 +272,8 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
         if (d < RL) lds_dma16_at(lb.base + (int64_t)u * ROWB, lb.off[d % RL], st + (d * MD_WAVES + wave) * 8 * ROWB);
         else if (d < RL + NS) {
             const int i = d - RL;
-            lds_dma16_at(av_src + (int64_t)u * MU::AV + i * 1024, lane16, st + TOK + wave * (NS * 1024) + i * 1024);
-        } else lds_dma16_lanes_at(am_src + (int64_t)u * MU::AM, lane16, st + TOK + MU::AV + wave * (NS * 256), (1ull << (16 * NS)) - 1);
+            lds_dma16_at<ONCE>(av_src + (int64_t)u * MU::AV + i * 1024, lane16, st + TOK + wave * (NS * 1024) + i * 1024);
+        } else lds_dma16_lanes_at<ONCE>(am_src + (int64_t)u * MU::AM, lane16, st + TOK + MU::AV + wave * (NS * 256), (1ull << (16 * NS)) - 1);
     };
     // LDS reads of a unit's operands, in the order of their first use
     const uint32_t va = lane16 + wo * (FW * 1024) + TOK, vi = lane16 + wo * (FW * 4) + TOK + MU::AV;
@@ -544,15 +544,15 @@ static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const 
     return launch_status();
 }
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, int KG = 1>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, int KG = 1, bool ONCE = false>
 static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
                                         int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
                                         hipStream_t stream)
 {
     constexpr int lds = KG * RING * MidUnit<TM, FUSED>::BYTES;
     static_assert(lds <= 160 * 1024 && (KG == 1 || lds >= TM * 512), "the rings, then the sums that are handed over");
-    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
+    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG, ONCE>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
                        ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
     if (launch_status() != SS_OK) return SS_ERR_HIP;
@@ -576,8 +576,15 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     // tiles of 64 and 128 tokens, whose rings would be two or three deep, 0.98 .. 1.24.
     const bool shared = ntiles * S > cu_count();
 #define SS_MID(TM, ...) launch_sparse_mid_ring<DT, TM, __VA_ARGS__>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
-    if (M <= 32) return !shared && U / S >= 2 ? SS_MID(32, 4, FUSED, true, 2) : SS_MID(32, 4, FUSED);
-    if (M <= 64) return shared ? SS_MID(64, 3, FUSED) : SS_MID(64, 4, FUSED);
+    const bool once = weights_stream(O, (int64_t)U * MidUnit<32, FUSED>::NS * FRAG_KB);
+    if (M <= 32) {
+        if (!shared && U / S >= 2) return once ? SS_MID(32, 4, FUSED, true, 2, true) : SS_MID(32, 4, FUSED, true, 2);
+        return once ? SS_MID(32, 4, FUSED, true, 1, true) : SS_MID(32, 4, FUSED);
+    }
+    if (M <= 64) {
+        if (shared) return once ? SS_MID(64, 3, FUSED, true, 1, true) : SS_MID(64, 3, FUSED);
+        return once ? SS_MID(64, 4, FUSED, true, 1, true) : SS_MID(64, 4, FUSED);
+    }
     if constexpr (!FUSED)
         if (shared && 4 * ntiles <= 5 * cu_count()) return SS_MID(128, 3, FUSED, false);
     return shared ? SS_MID(128, (FUSED ? 2 : 3), FUSED) : SS_MID(128, (FUSED ? 3 : 4), FUSED);

@@ -21,9 +21,11 @@ __device__ inline uint32_t lds_address(const void* lds_ptr)
 {
     return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_void*)lds_ptr);
 }
-__device__ inline void lds_dma16_at(const uint8_t* uniform_base, uint32_t lane_off, uint32_t lds_wave_addr)
+// ONCE: a non-temporal load, for data that one workgroup reads and nobody after it
+template <bool ONCE = false> __device__ inline void lds_dma16_at(const uint8_t* uniform_base, uint32_t lane_off, uint32_t lds_wave_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_wave_addr), "v"(lane_off), "s"(uniform_base) : "memory", "m0");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_wave_addr), "v"(lane_off), "s"(uniform_base) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_wave_addr), "v"(lane_off), "s"(uniform_base) : "memory", "m0");
 }
 __device__ inline void lds_dma4_at(const uint8_t* uniform_base, uint32_t lane_off, uint32_t lds_wave_addr)
 {
@@ -31,9 +33,13 @@ __device__ inline void lds_dma4_at(const uint8_t* uniform_base, uint32_t lane_of
 }
 // the same by the lanes of `lanes` only, in a wavefront whose lanes are all active: the execution mask is changed and put
 // back inside the statement, so that the caller's code stays one straight block
+template <bool ONCE = false>
 __device__ inline void lds_dma16_lanes_at(const uint8_t* uniform_base, uint32_t lane_off, uint32_t lds_wave_addr, uint64_t lanes)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds_wave_addr),
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\ts_mov_b64 exec, -1" ::"s"(lds_wave_addr),
+                     "v"(lane_off), "s"(uniform_base), "s"(lanes) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds_wave_addr),
                  "v"(lane_off), "s"(uniform_base), "s"(lanes) : "memory", "m0");
 }
 // The same with the scalar address arithmetic inside the statement, for kernels whose many load sources would otherwise be

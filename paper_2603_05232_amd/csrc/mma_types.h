@@ -159,6 +159,12 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
+// Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are more than a
+// third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise;
+// calls of M = 1 .. 64 with weights from HBM, 96 to 254 MB, 0.88 .. 0.98 of the time.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose where
+// the cache holds them (1.0 .. 1.27); tiles of 128 tokens 0.98 .. 1.02.
+inline bool weights_stream(int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= (80ll << 20); }
+
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 
 // Kernels with tiles of 128 channels x 128 tokens, sparse ones also x 64 and x 32 where the tokens fit (gemm_mid.hip),

@@ -138,3 +138,11 @@ def test_two_groups_of_wavefronts(dtype, fused, M, O, units, with_ws):
     es = 1 if dtype in ("i8", "fp8") else 2
     K = 128 * units // es if fused else 128 * units // es * N // (2 * (N - 1)) // (2 * N) * (2 * N)
     _linear(M, O, max(K, 2 * N), N, dtype, fused, with_ws, units)
+
+
+# packed weights of 80 MB and more, which are loaded non-temporally: unsplit panels and split rows, tiles of 32 and 64 tokens
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("M", [3, 50])
+@pytest.mark.parametrize("O,units", [(192 * 128 + 4, 29), (24 * 128, 230)])
+def test_weights_larger_than_the_cache_keeps(dtype, M, O, units):
+    _linear(M, O, _rows(units, 4, dtype, True), 4, dtype, True, True, M)
