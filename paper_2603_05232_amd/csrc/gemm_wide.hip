@@ -1,0 +1,180 @@
+// Sparse GEMMs of few tokens on layers of more panels than compute units: M <= 128, one tile of tokens.
+//
+// The call is a stream of weights, bound by HBM.  A workgroup per panel (gemm_mid.hip) gives some compute units two streams where
+// the others have one, and a compute unit has about a hundred cache lines in flight whatever its workgroups ask for, so the launch waits
+// for those with two: 128 MB streamed into LDS by 256 workgroups take 20.3 us, by 296 26.1.  Here a workgroup owns NF = 5, 6 or 8
+// fragments of 32 channels, as many as leave at most one workgroup for each compute unit, a wavefront for each fragment.  3584 -> 37888 at
+// M = 1, weights from HBM: INT8 29.3 -> 22.1 us (5.8 TB/s), bf16 53.5 -> 37.9 (6.7 TB/s).
+// The loop is left to the compiler's scheduler: a unit takes a compute unit 1500 cycles to stream and its operand reads and
+// matrix instructions a third of that.
+#include "ss_common.h"
+#include "packed_layout.h"
+#include "mma_types.h"
+#include "lds_pipe.h"
+#include "device_info.h"
+
+namespace ss {
+
+// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [fragment][step][lane][16 B], index words of the two
+// panels the fragments lie in [panel][step][lane][fragment of the panel][4 B]
+template <int NF, int TB, bool FUSED> struct WideUnit {
+    static constexpr int NS = FUSED ? 3 : 2;
+    static constexpr int TOK = TB * 32 * ROWB, AV = NF * NS * 1024, AM = 2 * NS * 1024, BYTES = TOK + AV + AM;
+    static constexpr int SHARED = TB * 4 + 2 * NS;                        // 1 KB pieces of tokens and index words
+    static constexpr int E = (SHARED + NF - 1) / NF, LPU = NS + E;        // direct loads per wavefront: its values, its share of those
+    static constexpr int FIT = 160 * 1024 / BYTES, RING = FIT < 5 ? FIT : 5;
+};
+
+template <int DT, int NF, int TB, bool FUSED, bool ONCE>
+__global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
+                                                         const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U,
+                                                         int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy)
+{
+    typedef Mma<DT> MM;
+    typedef WideUnit<NF, TB, FUSED> WU;
+    constexpr int NS = WU::NS, RING = WU::RING;
+    static_assert(RING >= 3 && (RING - 2) * WU::LPU < 64, "loads in flight");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 31, qb = lane >> 5;
+    const int npanels = (int)((O + PANEL - 1) / PANEL), nfrags = npanels * FRAGS_PER_PANEL;
+    const int f_first = xcd_run(blockIdx.x, gridDim.x) * NF, p_first = f_first / FRAGS_PER_PANEL;
+    const int frag = min(f_first + wave, nfrags - 1), panel = frag / FRAGS_PER_PANEL, f = frag % FRAGS_PER_PANEL;     // beyond the last: that one again, not stored
+    const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
+
+    // Sources of this wavefront's loads.  Lanes of tokens that do not exist load nothing (their products are never stored).
+    const uint8_t* const av_src = w_vals + ((int64_t)panel * NS * U * FRAGS_PER_PANEL + f) * 1024;
+    const uint8_t* e_src[WU::E];
+    uint32_t e_off[WU::E], e_step[WU::E], e_dst[WU::E];
+    uint64_t e_lanes[WU::E];
+    auto uniform = [](uint64_t v) { return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v); };
+#pragma unroll
+    for (int e = 0; e < WU::E; ++e) {
+        const int piece = wave + e * NF;
+        const bool tokens = piece < TB * 4;
+        const int rows = max(0, min(8, (int)M - piece * 8)), row = piece * 8 + (lane >> 3);
+        const int k = max(0, piece - TB * 4), p = min(p_first + k / NS, npanels - 1);
+        const uint64_t some = rows == 8 ? ~0ull : (1ull << (8 * rows)) - 1;
+        e_src[e] = reinterpret_cast<const uint8_t*>(uniform((uint64_t)(uintptr_t)(tokens ? Xq : w_meta + ((int64_t)p * NS * U + k % NS) * 1024)));
+        e_off[e] = tokens ? (uint32_t)row * (uint32_t)ldxb + (((lane & 7) ^ swz(row)) << 4) : lane16;
+        e_step[e] = __builtin_amdgcn_readfirstlane(tokens ? ROWB : NS * 1024);
+        e_dst[e] = __builtin_amdgcn_readfirstlane(tokens ? piece * 1024 : WU::TOK + WU::AV + k * 1024);
+        e_lanes[e] = uniform(tokens ? some : piece < WU::SHARED ? ~0ull : 0ull);
+    }
+    // as in gemm_mid.hip the XCDs start at different places of the row
+    const int rot = (blockIdx.x & 7) * U >> 3;
+    auto issue = [&](int v, uint32_t slot) __attribute__((always_inline)) {
+        const int u = v + rot < U ? v + rot : v + rot - U;
+#pragma unroll
+        for (int h = 0; h < NS; ++h)
+            lds_dma16_at<ONCE>(av_src + ((int64_t)u * NS + h) * (FRAGS_PER_PANEL * 1024), lane16, lds0 + slot + WU::TOK + (wave * NS + h) * 1024);
+#pragma unroll
+        for (int e = 0; e < WU::E; ++e) lds_dma16_lanes_at(e_src[e] + (int64_t)u * e_step[e], e_off[e], lds0 + slot + e_dst[e], e_lanes[e]);
+    };
+    uint32_t vb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) vb[c] = n * ROWB + (((FUSED ? 4 * qb + c : 4 * (c >> 1) + 2 * qb + (c & 1)) ^ swz(n)) << 4);
+    const uint32_t va = WU::TOK + wave * (NS * 1024) + lane16, vi = WU::TOK + WU::AV + (panel - p_first) * (NS * 1024) + lane16 + 4 * f;
+
+    typename MM::acc_t acc[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[tb][r] = 0;
+#pragma unroll
+    for (int i = 0; i < RING - 1; ++i)
+        if (i < U) issue(i, i * WU::BYTES);
+    uint32_t slot = 0, lslot = (RING - 1) * WU::BYTES;
+    for (int u = 0; u < U; ++u) {
+        if (u + RING - 1 <= U) wait_vmcnt<(RING - 2) * WU::LPU>(); else wait_vmcnt<0>();
+        wg_barrier();                                                    // unit u has landed, unit u - 1 is read
+        if (u + RING - 1 < U) issue(u + RING - 1, lslot);
+        const uint8_t* st = smem + slot;
+        v4i a[NS];
+        int idx[NS];
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            a[h] = *reinterpret_cast<const v4i*>(st + va + h * 1024);
+            idx[h] = *reinterpret_cast<const int*>(st + vi + h * 1024);
+        }
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+            v4i x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = *reinterpret_cast<const v4i*>(st + vb[c] + tb * (32 * ROWB));
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                acc[tb] = MM::sparse(a[h], v8i{x[2 * h][0], x[2 * h][1], x[2 * h][2], x[2 * h][3], x[2 * h + 1][0], x[2 * h + 1][1], x[2 * h + 1][2], x[2 * h + 1][3]}, acc[tb], idx[h]);
+            if constexpr (FUSED) {                                       // middle windows: see gemm_mid.hip
+                v8i m;
+#pragma unroll
+                for (int jd = 0; jd < 8; ++jd) {
+                    auto w = [&](int k) { return (uint32_t)x[k >> 2][k & 3]; };
+                    if constexpr (MM::ES == 1) m[jd] = (int)__builtin_amdgcn_alignbyte(w(2 * jd + 1), w(2 * jd), 2);
+                    else m[jd] = (int)w(4 * (jd >> 1) + 1 + (jd & 1));
+                }
+                acc[tb] = MM::sparse(a[2], m, acc[tb], idx[2]);
+            }
+        }
+        slot = slot == (RING - 1) * WU::BYTES ? 0u : slot + WU::BYTES;
+        lslot = lslot == (RING - 1) * WU::BYTES ? 0u : lslot + WU::BYTES;
+    }
+    if (f_first + wave >= nfrags) return;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+        store_block16<MM::SCALED>(acc[tb], s_x, s_w, Y, ldy, M, O, (int64_t)panel * PANEL + 64 * qb + 16 * f, tb * 32 + n);
+}
+
+}  // namespace ss
+
+using namespace ss;
+
+template <int DT, int NF, int TB, bool FUSED, bool ONCE>
+static ss_status launch_wide_one(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
+                                 int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
+{
+    typedef WideUnit<NF, TB, FUSED> WU;
+    constexpr int lds = WU::RING * WU::BYTES;
+    static_assert(lds <= 160 * 1024, "LDS budget");
+    const int64_t nfrags = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
+    if (allow_dynamic_lds<k_sparse_wide<DT, NF, TB, FUSED, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_wide<DT, NF, TB, FUSED, ONCE>), dim3((unsigned)((nfrags + NF - 1) / NF)), dim3(64 * NF), lds, stream,
+                       static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb,
+                       static_cast<uint16_t*>(Y), ldy);
+    return launch_status();
+}
+
+template <int DT, bool FUSED>
+static ss_status launch_wide_dt(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
+                                int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
+{
+    const int nf = wide_fragments(O, cu_count());
+    const bool once = weights_stream(O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB);
+#define SS_W(NF, TB) return once ? launch_wide_one<DT, NF, TB, FUSED, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream) \
+                                 : launch_wide_one<DT, NF, TB, FUSED, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
+#define SS_WN(NF) { if (M <= 32) SS_W(NF, 1); if (M <= 64) SS_W(NF, 2); SS_W(NF, 4); }
+    if (nf == 5) SS_WN(5)
+    if (nf == 6) SS_WN(6)
+    SS_WN(8)
+#undef SS_WN
+#undef SS_W
+}
+
+namespace ss {
+
+ss_status launch_sparse_wide(bool fused, const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
+{
+#define SS_WD(DT) return fused ? launch_wide_dt<DT, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream) \
+                               : launch_wide_dt<DT, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
+    switch (dtype) {
+    case SS_I8: SS_WD(SS_I8);
+    case SS_FP8_E4M3: SS_WD(SS_FP8_E4M3);
+    case SS_BF16: SS_WD(SS_BF16);
+    case SS_FP16: SS_WD(SS_FP16);
+    }
+#undef SS_WD
+    return SS_ERR_DTYPE;
+}
+
+}  // namespace ss

@@ -159,6 +159,16 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
+// Few tokens on more panels than compute units (gemm_wide.hip), up to two of them for each.  X: lifted rows, or unlifted ones and weights of
+// slide_decompose_fused; U units of 128 bytes per row, ldxb bytes between rows.
+ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
+// fragments of 32 channels that a workgroup of theirs takes, 0 where they are not used
+inline int wide_fragments(int64_t O, int64_t cus)
+{
+    const int64_t frags = (O + 127) / 128 * 4, f = (frags + cus - 1) / cus;
+    return f <= 4 || f > 8 ? 0 : f == 7 ? 8 : (int)f;
+}
 // Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are more than a
 // third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise;
 // calls of M = 1 .. 64 with weights from HBM, 96 to 254 MB, 0.88 .. 0.98 of the time.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose where
@@ -202,6 +212,9 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
 //             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
+// M <= 64, fused 128, and 257 .. 512 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each compute unit.  Time over
+//             that of a panel for each workgroup, weights from HBM, 96 calls, INT8, bf16 and fp8 lifted: 16 units and more 0.62 .. 0.95 (3584 -> 37888 at
+//             M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9), 4 to 12 units 0.91 .. 1.07.  Lifted rows of 65 .. 128 tokens keep the 128 x 128 tiles.
 // Fused, more 128 x 128 tiles than compute units and at most one tile of 128 channels x 256 tokens for each: those
 //             (gemm_fused_narrow.hip).  Time over that of the paths above, INT8 and bf16, 4 to 64 units, M = 200 .. 4096,
 //             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  At the fewest, a middle and the most panels for M = 129 .. 8192, 4
@@ -212,7 +225,7 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
-enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE };
+enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE };
 struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
@@ -239,6 +252,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
+    if (M <= (kind == SS_KIND_FUSED ? 128 : 64) && units >= 16 && wide_fragments(O, cus)) return {SS_PATH_WIDE, 1};
     if (M > 64) {
         if (kind == SS_KIND_FUSED && narrow_pays(M, O, cus)) return {SS_PATH_NARROW, 1};
         const bool many = 4 * tiles > 7 * cus;                          // more than 448

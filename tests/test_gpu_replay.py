@@ -13,6 +13,7 @@ ROUTES = {"narrow tiles": (True, 1100, 4224, 640, False),
           "large tiles and a rest on narrow ones": (True, 2048, 32 * 256 + 3142, 2048, False),
           "large tiles in rounds, odd rows": (True, 8100, 9000, 384, False),
           "large tiles in rounds, even rows": (True, 8100, 9000, 512, False),
+          "five fragments a workgroup": (True, 17, 257 * 128, 2048, False),
           "two groups of wavefronts": (True, 17, 192 * 128, 1152, False),
           "two groups of wavefronts, split rows": (True, 9, 300, 16768, True),
           "lifted tiles in rounds": (False, 8100, 9000, 411, False),

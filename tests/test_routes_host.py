@@ -11,6 +11,7 @@ import test_gpu_lifted_tiles
 import test_gpu_mid_tiles
 import test_gpu_narrow_tiles
 import test_gpu_replay
+import test_gpu_wide_layers
 from paper_2603_05232_amd import binding, build
 
 SOURCE = """
@@ -28,7 +29,7 @@ int main()
     }
 }
 """
-MID, NARROW, TILE = 1, 2, 3
+MID, NARROW, TILE, WIDE = 1, 2, 3, 4
 LIFTED, FUSED = 0, 1
 
 
@@ -79,12 +80,21 @@ def test_shared_compute_units(plan):
         assert plan(FUSED, M, O, units)["path"] == NARROW
 
 
+def test_wide_layers(plan):
+    for M, O, units, fused in test_gpu_wide_layers.SHAPES:
+        assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
+        assert plan(FUSED if fused else LIFTED, M, O, 15)["path"] != WIDE
+    assert plan(FUSED, 5, 256 * 128, 16)["path"] == MID and plan(FUSED, 5, 513 * 128, 16)["path"] == MID
+
+
 def test_replayed_routes(plan):
     for name, (fused, M, O, K, with_ws) in test_gpu_replay.ROUTES.items():
         units = (K if fused else binding.slide_lifted_ld(K, 4, "i8")) // 128
         p = plan(FUSED if fused else LIFTED, M, O, units, 1 << 30 if with_ws else 0)
         if "groups" in name:
             assert p["path"] == MID and M <= 32 and (p["S"] > 1) == with_ws and units // p["S"] >= 2 and -(-O // 128) * p["S"] <= 256, name
+        elif name == "five fragments a workgroup":
+            assert p["path"] == WIDE, name
         elif name == "narrow tiles":
             assert p["path"] == NARROW, name
         else:
