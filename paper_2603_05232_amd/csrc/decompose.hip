@@ -4,6 +4,7 @@
 // the few earlier windows of its 2N block to recover what they took).
 #include "ss_common.h"
 #include "packed_layout.h"
+#include <type_traits>
 
 namespace ss {
 
@@ -80,9 +81,9 @@ __global__ __launch_bounds__(256) void k_decompose_canonical(const typename Elem
 // that depends on the four availability bits (positions, byte selectors that fetch the values and write zeros where
 // nothing is stored, the hand-over) is one entry of a 16-entry LDS table, so a window costs one table read, one byte
 // permute and a few bit operations.
-// Measured, 37888 x 3584 INT8 6:8, window order of the fused GEMM: 221 -> 58 us (4.5 TB/s) (a thread per lane of
+// Measured, 37888 x 3584 INT8 6:8, window order of the fused GEMM: 221 -> 58 us (a thread per lane of
 // the packed form, which loads its two to four blocks straight from rows K bytes apart and runs the greedy bit by bit,
-// before).
+// before), with non-temporal loads (of lines that one workgroup reads) and stores 44 us (5.9 TB/s).
 template <int ES, int N> struct PackGroup {
     static constexpr int BLOCKS = 16 / ES;
     static constexpr int BYTES = 32 * N;
@@ -162,14 +163,22 @@ __global__ __launch_bounds__(PANEL) void k_decompose_packed(const uint8_t* __res
     if (t < 16) table[t] = pack_entry<ES>(t);
     if (aligned) {
         uint4 in[CHUNKS];
+        auto load_rows = [&](auto once_c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < CHUNKS; ++c) {
-            const int id = c * PANEL + t, slot = id / CHUNKS, part = id - slot * CHUNKS;
-            const int64_t o = (int64_t)panel * PANEL + panel_row(slot >> 5, slot & 31);
-            const int k0 = group * PG::BYTES + part * 16;
-            in[c] = make_uint4(0, 0, 0, 0);
-            if (o < O && k0 < row_bytes) in[c] = *reinterpret_cast<const uint4*>(Wq + o * row_bytes + k0);
-        }
+            for (int c = 0; c < CHUNKS; ++c) {
+                const int id = c * PANEL + t, slot = id / CHUNKS, part = id - slot * CHUNKS;
+                const int64_t o = (int64_t)panel * PANEL + panel_row(slot >> 5, slot & 31);
+                const int k0 = group * PG::BYTES + part * 16;
+                in[c] = make_uint4(0, 0, 0, 0);
+                if (o < O && k0 < row_bytes) {
+                    const uint4* p = reinterpret_cast<const uint4*>(Wq + o * row_bytes + k0);
+                    in[c] = decltype(once_c)::value ? load_once(p) : *p;
+                }
+            }
+        };
+        // lines that no other workgroup reads are loaded non-temporally
+        if (PG::BYTES % 128 == 0 && ((row_bytes | (uintptr_t)Wq) & 127) == 0) load_rows(std::true_type{});
+        else load_rows(std::false_type{});
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c) {
             const int id = c * PANEL + t, slot = id / CHUNKS, part = id - slot * CHUNKS;
@@ -253,17 +262,19 @@ __global__ __launch_bounds__(PANEL) void k_decompose_packed(const uint8_t* __res
     }
     // ---- out: values straight, index words through LDS
     const int64_t ps0 = (int64_t)panel * nsteps + group * PG::STEPS;
+    // non-temporal, but for a single step of the pattern's shortest group (2:4: 1.02 to 1.06 of the time with them)
+    auto put = [](uint4* p, uint4 x) { if constexpr (N > 2) store_once(p, x); else *p = x; };
     const int left = nsteps - group * PG::STEPS;          // steps of this group that exist (the last group may stick out)
 #pragma unroll
     for (int s = 0; s < PG::STEPS; ++s)
 #pragma unroll
         for (int qa = 0; qa < 2; ++qa) {
-            if (s < left) vals[((ps0 + s) * FRAGS_PER_PANEL + f) * 64 + qa * 32 + i] = make_uint4(v[s][qa][0], v[s][qa][1], v[s][qa][2], v[s][qa][3]);
+            if (s < left) put(vals + ((ps0 + s) * FRAGS_PER_PANEL + f) * 64 + qa * 32 + i, make_uint4(v[s][qa][0], v[s][qa][1], v[s][qa][2], v[s][qa][3]));
             words[(s * 64 + qa * 32 + i) * FRAGS_PER_PANEL + f] = meta_w[s][qa];
         }
     __syncthreads();
     for (int k = t; k < (PG::STEPS < left ? PG::STEPS : left) * 64; k += PANEL)
-        reinterpret_cast<uint4*>(meta)[ps0 * 64 + k] = reinterpret_cast<const uint4*>(words)[k];
+        put(reinterpret_cast<uint4*>(meta) + ps0 * 64 + k, reinterpret_cast<const uint4*>(words)[k]);
 }
 
 }  // namespace ss

@@ -173,7 +173,7 @@ inline int wide_fragments(int64_t O, int64_t cus)
 // third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise;
 // calls of M = 1 .. 64 with weights from HBM, 96 to 254 MB, 0.88 .. 0.98 of the time.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose where
 // the cache holds them (1.0 .. 1.27); tiles of 128 tokens 0.98 .. 1.02.
-inline bool weights_stream(int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= (80ll << 20); }
+inline bool weights_stream(int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= CACHED_BYTES; }
 
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 

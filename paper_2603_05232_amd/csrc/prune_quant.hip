@@ -1,6 +1,7 @@
 // slide_prune_quant: offline (2N-2):2N magnitude pruning + per-channel quantisation (Sec. 4.1, App. E; Alg. 1 pass 1).
 #include "ss_common.h"
 #include "quant_common.h"
+#include <type_traits>
 
 namespace ss {
 
@@ -36,7 +37,10 @@ __device__ inline void prune_block(const TIN* __restrict__ w, int K, int L, int 
 // (6:8 from bf16: one block = one vector), so a block is never shared between threads, every load is a vector and a
 // wavefront reads contiguous memory; the row stays in registers between the absmax and the pruning.  A unit per
 // thread and load instead of a block per thread with one load per element (the kernel below): 37888 x 3584 bf16 -> INT8
-// 398 -> 82 us (5.0 TB/s).
+// 398 -> 82 us.  Matrices that the memory-side cache does not hold are loaded non-temporally, since nobody reads
+// them again: the codes, which the decomposition reads next, then find room there (82 -> 63 us, 6.5 TB/s; a matrix that it may hold 1.05 of
+// the time).  Not where units are several vectors: they take several loads for a cache line, which would not be there any more for
+// the second (fp32 14:16 of 8539 x 2048 with its decomposition 54 -> 78 us); nor for 2:4 (8192 x 4096 fp32 -> bf16 59.1 -> 60.9).
 template <typename TIN, int N> struct PruneUnit {
     static constexpr int ESI = (int)sizeof(TIN);
     static constexpr int BLOCK = 2 * N * ESI;                                  // bytes of a block
@@ -52,7 +56,7 @@ __device__ inline void unpack_word(uint32_t w, float* f, uint16_t) { f[0] = __ui
 
 template <typename TIN, int OUT, int N>
 __global__ __launch_bounds__((PruneUnit<TIN, N>::MAX_THREADS)) void k_prune_rows(const TIN* __restrict__ W, int K, int nunits, uint8_t* __restrict__ Wq, float* __restrict__ s_w,
-                                                     int vec_out)
+                                                     int vec_out, bool once)
 {
     typedef PruneUnit<TIN, N> PU;
     constexpr int ES = OUT >= 2 ? 2 : 1, ESI = PU::ESI, CH = PU::CH, EPW = 4 / ESI, L = 2 * N;
@@ -64,16 +68,20 @@ __global__ __launch_bounds__((PruneUnit<TIN, N>::MAX_THREADS)) void k_prune_rows
     const uint4* w = reinterpret_cast<const uint4*>(W + o * (int64_t)K);
     const int nvec = K / (16 / ESI);
     uint32_t v[PU::MAXU][CH * 4];
+    auto load_row = [&](auto once_c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < PU::MAXU; ++i) {
-        const int u = t + i * T;
+        for (int i = 0; i < PU::MAXU; ++i) {
+            const int u = t + i * T;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            uint4 x = make_uint4(0, 0, 0, 0);             // beyond the row: zeros complete the last block
-            if (u < nunits && u * CH + c < nvec) x = w[u * CH + c];
-            v[i][4 * c] = x.x; v[i][4 * c + 1] = x.y; v[i][4 * c + 2] = x.z; v[i][4 * c + 3] = x.w;
+            for (int c = 0; c < CH; ++c) {
+                uint4 x = make_uint4(0, 0, 0, 0);         // beyond the row: zeros complete the last block
+                if (u < nunits && u * CH + c < nvec) x = decltype(once_c)::value ? load_once(w + u * CH + c) : w[u * CH + c];
+                v[i][4 * c] = x.x; v[i][4 * c + 1] = x.y; v[i][4 * c + 2] = x.z; v[i][4 * c + 3] = x.w;
+            }
         }
-    }
+    };
+    if (CH == 1 && N > 2 && once) load_row(std::true_type{});
+    else load_row(std::false_type{});
     float r = 0.0f;
     if constexpr (OUT < 2) {
         float amax = 0.0f;
@@ -219,7 +227,8 @@ static bool launch_prune_rows(const TIN* W, int64_t O, int64_t K, uint8_t* Wq, f
     constexpr int OW = PU::CH * (4 / PU::ESI) * ES;
     constexpr int VB = OW % 4 == 0 ? 16 : OW % 2 == 0 ? 8 : 4;           // bytes of one output store
     const int vec_out = (K * ES) % VB == 0 && ((uintptr_t)Wq % VB) == 0;
-    hipLaunchKernelGGL((k_prune_rows<TIN, OUT, N>), dim3((unsigned)O), dim3(T), 0, st, W, (int)K, (int)nunits, Wq, s_w, vec_out);
+    hipLaunchKernelGGL((k_prune_rows<TIN, OUT, N>), dim3((unsigned)O), dim3(T), 0, st, W, (int)K, (int)nunits, Wq, s_w, vec_out,
+                       O * K * PU::ESI >= CACHED_BYTES);
     return true;
 }
 

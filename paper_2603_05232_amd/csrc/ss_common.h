@@ -53,6 +53,22 @@ __device__ inline int xcd_run(int id, int total)
     return x * (total >> 3) + (x < rest ? x : rest) + (id >> 3);
 }
 
+// What a program passes over in turn and comes to more than this is hardly found in the memory-side cache again: a third of its 256 MB.
+constexpr int64_t CACHED_BYTES = 80ll << 20;
+// non-temporal load and store, for data that is read once or written and not read soon
+__device__ inline uint4 load_once(const uint4* p)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+__device__ inline void store_once(uint4* p, uint4 v)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store((u32x4){v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(p));
+}
+
 // ---- scalar format conversions (device) --------------------------------------------------
 __device__ inline float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
