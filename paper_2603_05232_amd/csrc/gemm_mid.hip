@@ -79,15 +79,17 @@ __device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* __restri
 }
 
 // Split k: the raw accumulators of k-range s of tile `tile` go to the workspace as
-// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (512 TM bytes per tile and range, coalesced).
+// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (512 TM bytes per tile and range, coalesced).  `tokens` of
+// this wavefront's exist (may be <= 0); nothing is written for the others.
 template <typename ACC, int FW, int TB>
-__device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int64_t item, int wave, int lane)
+__device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int64_t item, int wave, int lane, int tokens)
 {
     v4i* dst = static_cast<v4i*>(ws) + ((item * MD_WAVES + wave) * (4 * FW * TB)) * 64 + lane;
 #pragma unroll
     for (int f = 0; f < FW; ++f)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb)
+            if (tb * 32 + (lane & 31) < tokens)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
@@ -98,8 +100,9 @@ __device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int
 
 // Sum of the S partial accumulators of every tile in range order (bit-reproducible also for fp32) and the
 // scale epilogue.  One workgroup per (tile, wavefront of the GEMM kernel); thread (f, tb, register quad, lane) owns four
-// consecutive channels of one token, so a range costs it one 16-byte load and up to eight ranges are in flight at once.
-template <int DT, int TM>
+// consecutive channels of one token.  The kernel is a memory round trip between two launches, so everything is asked for at once:
+// the scales, and B ranges in flight (B the least of 2, 4 and 8 that covers S; loads beyond the last range repeat it and are not added).
+template <int DT, int TM, int B>
 __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const v4i* __restrict__ ws, int S, int64_t ntiles, const float* __restrict__ s_x,
                                                                const float* __restrict__ s_w, int64_t M, int64_t O, uint16_t* __restrict__ Y,
                                                                int64_t ldy, int tiles_t)
@@ -110,38 +113,30 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
     typedef typename MM::acc_t acc_t;
     typedef decltype(acc_t{}[0] + acc_t{}[0]) elem_t;
     typedef elem_t quad_t __attribute__((ext_vector_type(4)));
-    const int64_t tile = blockIdx.x / MD_WAVES;
+    const int tile = blockIdx.x / MD_WAVES;
     const int wave = blockIdx.x % MD_WAVES, wo = MS::wo(wave), wt = MS::wt(wave);
     const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3, ft = threadIdx.x >> 8, f = ft / TB, tb = ft % TB;
+    const int panel = tile / tiles_t;
+    const int64_t tok = (int64_t)(tile - panel * tiles_t) * TM + wt * (32 * TB) + tb * 32 + (lane & 31);
+    const int64_t o = (int64_t)panel * PANEL + 16 * MS::FW * wo + 64 * (lane >> 5) + 16 * f + 4 * r4;
+    if (tok >= M || o >= O) return;
+    float sx = 1.0f, sw[4];
+    if constexpr (MM::SCALED) {
+        sx = s_x[tok];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sw[e] = s_w[o + e < O ? o + e : O - 1];
+    }
     quad_t a = {0, 0, 0, 0};
-    const v4i* src = ws + ((tile * MD_WAVES + wave) * (4 * ACC) + ft * 4 + r4) * 64 + lane;
+    const v4i* src = ws + (((int64_t)tile * MD_WAVES + wave) * (4 * ACC) + ft * 4 + r4) * 64 + lane;
     const int64_t range_stride = ntiles * MD_WAVES * (4 * ACC) * 64;             // 16-byte groups between consecutive k ranges
-    int s = 0;
-    for (; s + 8 <= S; s += 8) {
-        quad_t q[8];
+    for (int s = 0; s < S; s += B) {
+        quad_t q[B];
 #pragma unroll
-        for (int d = 0; d < 8; ++d) q[d] = __builtin_bit_cast(quad_t, src[(s + d) * range_stride]);
+        for (int d = 0; d < B; ++d) q[d] = __builtin_bit_cast(quad_t, src[min(s + d, S - 1) * range_stride]);
 #pragma unroll
-        for (int d = 0; d < 8; ++d) a += q[d];
+        for (int d = 0; d < B; ++d) a = s + d < S ? a + q[d] : a;
     }
-    if (s + 4 <= S) {
-        quad_t q[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) q[d] = __builtin_bit_cast(quad_t, src[(s + d) * range_stride]);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) a += q[d];
-        s += 4;
-    }
-    {
-        quad_t q[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) q[d] = s + d < S ? __builtin_bit_cast(quad_t, src[(s + d) * range_stride]) : quad_t{0, 0, 0, 0};
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-            if (s + d < S) a += q[d];
-    }
-    const int64_t panel = tile / tiles_t, t0 = (tile - panel * tiles_t) * TM;
-    store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, panel * PANEL + 16 * MS::FW * wo + 64 * (lane >> 5) + 16 * f + 4 * r4, t0 + wt * (32 * TB) + tb * 32 + (lane & 31));
+    store_quad4<MM::SCALED>(a, sx, sw, Y, ldy, O, o, tok);
 }
 
 // Work item of this workgroup: a tile of a k range.  Workgroup ids go round-robin over the 8 XCDs, and what the workgroups
@@ -450,7 +445,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
             for (int e = 0; e < 4; ++e) v[4 * r4 + e] += q[e];
         }
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, item, wave, lane);
+    if (gridDim.y > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, o_wave, t_wave, lane);
 }
 
@@ -527,7 +522,7 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
         slot = slot == RING - 1 ? 0 : slot + 1;
         lslot = lslot == RING - 1 ? 0 : lslot + 1;
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane);
+    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane, (int)(M - t0) - wt * 64);
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
 }
 
@@ -539,8 +534,12 @@ template <int DT, int TM>
 static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const float* s_x, const float* s_w, int64_t M, int64_t O, void* Y,
                                    int64_t ldy, int tiles_t, hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_mid_reduce<DT, TM>), dim3((unsigned)(ntiles * MD_WAVES)), dim3(256 * MidShape<TM>::ACC), 0, stream, static_cast<const v4i*>(ws), S, ntiles,
-                       s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy, tiles_t);
+#define SS_RD(B) hipLaunchKernelGGL((k_mid_reduce<DT, TM, B>), dim3((unsigned)(ntiles * MD_WAVES)), dim3(256 * MidShape<TM>::ACC), 0, stream, static_cast<const v4i*>(ws), S, ntiles, \
+                       s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy, tiles_t)
+    if (S <= 2) SS_RD(2);
+    else if (S <= 4) SS_RD(4);
+    else SS_RD(8);
+#undef SS_RD
     return launch_status();
 }
 

@@ -402,6 +402,14 @@ __global__ __launch_bounds__(256 * TB) void k_skinny_reduce(const v4i* __restric
     typedef elem_t quad_t __attribute__((ext_vector_type(4)));
     const int64_t F = blockIdx.x, nfrag = gridDim.x;
     const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3, tb = threadIdx.x >> 8, h = lane >> 5;
+    const int64_t o = F * 32 + 16 * h + 4 * r4, tok = tb * 32 + (lane & 31);
+    if (tok >= M || o >= O) return;
+    float sx = 1.0f, sw[4];
+    if constexpr (MM::SCALED) {
+        sx = s_x[tok];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sw[e] = s_w[o + e < O ? o + e : O - 1];
+    }
     quad_t a = {0, 0, 0, 0};
     const v4i* src = ws + ((F * TB + tb) * 4 + r4) * 64 + lane;
     const int64_t range_stride = nfrag * TB * 4 * 64;
@@ -429,8 +437,7 @@ __global__ __launch_bounds__(256 * TB) void k_skinny_reduce(const v4i* __restric
         for (int d = 0; d < 3; ++d)
             if (s + d < S) a += q[d];
     }
-    const int64_t o = F * 32 + 16 * h + 4 * r4;
-    store_quad4<MM::SCALED>(a, s_x, s_w, Y, ldy, M, O, o, tb * 32 + (lane & 31));
+    store_quad4<MM::SCALED>(a, sx, sw, Y, ldy, O, o, tok);
 }
 
 }  // namespace ss

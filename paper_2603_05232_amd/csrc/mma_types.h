@@ -110,18 +110,16 @@ __device__ inline void store_block16(const ACC& a, const float* __restrict__ s_x
     }
 }
 
-// Epilogue of four consecutive channels o .. o + 3 of token tok held by one thread (the split-k reduce kernels):
-// Y = bf16((float(a) * s_x[tok]) * s_w[o]) (SCALED) or bf16(a).  Out-of-range tokens and channels are skipped.
+// Epilogue of four consecutive channels o .. o + 3 (o < O) of an existing token tok held by one thread (the split-k reduce kernels):
+// Y = bf16((float(a) * sx) * sw[e]) (SCALED) or bf16(a).  Out-of-range channels are skipped.
 template <bool SCALED, typename QUAD>
-__device__ inline void store_quad4(const QUAD& a, const float* __restrict__ s_x, const float* __restrict__ s_w, uint16_t* __restrict__ Y,
-                                   int64_t ldy, int64_t M, int64_t O, int64_t o, int64_t tok)
+__device__ inline void store_quad4(const QUAD& a, float sx, const float (&sw)[4], uint16_t* __restrict__ Y, int64_t ldy, int64_t O, int64_t o, int64_t tok)
 {
-    if (tok >= M || o >= O) return;
     float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         v[e] = (float)a[e];
-        if constexpr (SCALED) v[e] = (v[e] * s_x[tok]) * s_w[o + e < O ? o + e : O - 1];
+        if constexpr (SCALED) v[e] = (v[e] * sx) * sw[e];
     }
     const uint32_t w[2] = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     uint16_t* dst = Y + tok * ldy + o;
