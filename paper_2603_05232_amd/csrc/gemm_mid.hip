@@ -4,8 +4,8 @@
 // There the large-tile kernels leave most compute units idle (M = 256 on a 3584-channel layer is 14
 // tiles for 256 units), so these kernels use 128 (one weight panel) x 128 (tokens) tiles, one tile per
 // workgroup of four wavefronts, each wavefront accumulating 64 channels x 64 tokens (2 x 2 blocks of a
-// 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 and 32 tokens for calls that
-// have no more: a call of few tokens is a stream of weights, and every token row that does not exist would
+// 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 tokens and, where workgroups share compute
+// units (gemm_wide.hip has the other calls of up to 32 tokens), 32 tokens for calls that have no more: a call of few tokens is a stream of weights, and every token row that does not exist would
 // be loaded, read and, with a split k range, written as partial sums all the same.  Operands go HBM/L2 -> LDS
 // with direct-to-LDS loads into a ring of units of 128 k-bytes, one barrier per unit.
 //   sparse: a unit is the token tile plus the panel's stored values and index words, which are already in
@@ -76,26 +76,6 @@ __device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* __restri
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb)
             store_block16<SCALED>(acc[f][tb], s_x, s_w, Y, ldy, M, O, o_wave + 64 * h + 16 * f, t_wave + tb * 32 + n);
-}
-
-// Split k: the raw accumulators of k-range s of tile `tile` go to the workspace as
-// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (512 TM bytes per tile and range, coalesced).  `tokens` of
-// this wavefront's exist (may be <= 0); nothing is written for the others.
-template <typename ACC, int FW, int TB>
-__device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int64_t item, int wave, int lane, int tokens)
-{
-    v4i* dst = static_cast<v4i*>(ws) + ((item * MD_WAVES + wave) * (4 * FW * TB)) * 64 + lane;
-#pragma unroll
-    for (int f = 0; f < FW; ++f)
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb)
-            if (tb * 32 + (lane & 31) < tokens)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
-                const elem_t q[4] = {acc[f][tb][4 * r4], acc[f][tb][4 * r4 + 1], acc[f][tb][4 * r4 + 2], acc[f][tb][4 * r4 + 3]};
-                dst[((f * TB + tb) * 4 + r4) * 64] = __builtin_bit_cast(v4i, q);
-            }
 }
 
 // Sum of the S partial accumulators of every tile in range order (bit-reproducible also for fp32) and the
@@ -203,9 +183,6 @@ template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&ac
 // workgroup and the launch waits for those with two, that is the faster loop (lifted INT8 / bf16 against the pipeline, weights
 // from HBM: 4096 -> 4096 at M = 1152, 288 tiles, 35 against 38 us / 59 against 68; 4096 -> 6144 at M = 768 35 against 37 / 58 against 64);
 // with more tiles than that, or unlifted rows, the pipeline is (384 tiles, 4096 -> 4096 at M = 1536, same order: 39.5 against 41.1 us; fused, 288 tiles: 33 against 35).
-// KG = 2: two groups of four wavefronts, each with half of the workgroup's k range and a ring of its own, meet at the same
-// barriers; the second hands its sums to the first in LDS.  Two wavefronts per SIMD then cover each other's waits, which a
-// deeper ring for one does less well, and no partial sums more are written.
 template <int TM, bool FUSED> struct MidUnit {
     typedef MidShape<TM> MS;
     static constexpr int NS = FUSED ? 3 : 2;                              // steps
@@ -220,8 +197,8 @@ template <int TM, bool FUSED> struct MidUnit {
 };
 template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE, int KG, bool ONCE>
-__global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
+template <int DT, int TM, int RING, bool FUSED, bool PIPE, bool ONCE>
+__global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
                                                               uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
@@ -233,18 +210,14 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
     constexpr int FW = MU::MS::FW, TB = MU::MS::TB;
     typedef MidOps<NS, FW, TB> Ops;
     typedef int idx_t __attribute__((ext_vector_type(FW)));
-    static_assert(KG == 1 || PIPE, "groups of wavefronts run the pipeline");
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];      // RING units for each of the KG groups
-    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % MD_WAVES, kg = wave_all / MD_WAVES, lane = threadIdx.x & 63;
-    uint8_t* const smem = lds + kg * (RING * MU::BYTES);
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];     // RING units
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
     const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all), PIPE ? 8 : 16);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
-    const int first = (int)((int64_t)it.range * U_all / gridDim.y), count = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - first;
-    // units [u0, u0 + U) of it are this group's; the host takes KG groups only for ranges of at least KG units
-    const int u0 = first + kg * (count / KG), U = kg + 1 < KG ? count / KG : count - kg * (count / KG);
+    const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
 
     // Direct loads of a unit, by wavefront: TM / 32 of token rows, NS of values ([step][fragment 4][lane 64][16 B]) and one of
     // NS * 256 bytes of index words ([step][lane 64][fragment 4][4 B]; lanes 0 .. 16 NS - 1)
@@ -422,29 +395,6 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
         } else unit(no, no, A, B, u);
     }
     const int64_t o_wave = panel * PANEL + 16 * FW * wo, t_wave = t0 + wt * (32 * TB), item = (int64_t)it.range * gridDim.x + it.tile;
-    if constexpr (KG == 2) {                                             // the second group hands its sums to the first in LDS
-        static_assert(FW * TB == 1, "one accumulator block per wavefront");
-        if (kg == 0 && count & 1) wg_barrier();                          // it has one unit, and one meeting, more
-        wait_lgkm0();
-        wg_barrier();                                                    // nobody reads operands any more
-        v4i* const x = reinterpret_cast<v4i*>(lds) + wave * 256 + lane;
-        typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
-        typedef elem_t quad_t __attribute__((ext_vector_type(4)));
-        auto& v = acc[0][0];
-        if (kg == 1) {
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) x[r4 * 64] = __builtin_bit_cast(v4i, (quad_t){v[4 * r4], v[4 * r4 + 1], v[4 * r4 + 2], v[4 * r4 + 3]});
-            wait_lgkm0();
-        }
-        wg_barrier();
-        if (kg == 1) return;
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const quad_t q = __builtin_bit_cast(quad_t, x[r4 * 64]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * r4 + e] += q[e];
-        }
-    }
     if (gridDim.y > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, o_wave, t_wave, lane);
 }
@@ -543,15 +493,15 @@ static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const 
     return launch_status();
 }
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, int KG = 1, bool ONCE = false>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, bool ONCE = false>
 static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
                                         int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
                                         hipStream_t stream)
 {
-    constexpr int lds = KG * RING * MidUnit<TM, FUSED>::BYTES;
-    static_assert(lds <= 160 * 1024 && (KG == 1 || lds >= TM * 512), "the rings, then the sums that are handed over");
-    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, KG, ONCE>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
+    constexpr int lds = RING * MidUnit<TM, FUSED>::BYTES;
+    static_assert(lds <= 160 * 1024, "LDS budget");
+    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
                        ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
     if (launch_status() != SS_OK) return SS_ERR_HIP;
@@ -569,20 +519,18 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     // Ring depth: with more workgroups than compute units, as deep as lets two of them share a compute unit's LDS and cover
     // each other's waits.  A workgroup alone: the whole ring is requested at once, so that a deeper one delays the first
     // unit (3584 -> 4608 at M = 256, 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
-    // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9).  Tiles of 32 tokens: two groups of wavefronts with a ring of four each
-    // (KG = 2, see k_sparse_mid) against one with a ring of eight, weights from HBM: 63 calls of M = 1 .. 32 in three operand
-    // forms 0.93 .. 1.03 of the time, those whose rows are split 0.93 .. 0.99 (18944 -> 3584 INT8 at M = 1 18.3 -> 17.5 us, bf16 28.2 -> 26.8);
-    // tiles of 64 and 128 tokens, whose rings would be two or three deep, 0.98 .. 1.24.
+    // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9).  32 tokens at most and no more workgroups than compute units:
+    // the weight stream of gemm_wide.hip (both sides there).
     const bool shared = ntiles * S > cu_count();
 #define SS_MID(TM, ...) launch_sparse_mid_ring<DT, TM, __VA_ARGS__>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
     const bool once = weights_stream(O, (int64_t)U * MidUnit<32, FUSED>::NS * FRAG_KB);
     if (M <= 32) {
-        if (!shared && U / S >= 2) return once ? SS_MID(32, 4, FUSED, true, 2, true) : SS_MID(32, 4, FUSED, true, 2);
-        return once ? SS_MID(32, 4, FUSED, true, 1, true) : SS_MID(32, 4, FUSED);
+        if (!shared) return launch_sparse_wide(FUSED, Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, (ss_dtype)DT, Y, ldy, ws, S, stream);
+        return once ? SS_MID(32, 4, FUSED, true, true) : SS_MID(32, 4, FUSED);
     }
     if (M <= 64) {
-        if (shared) return once ? SS_MID(64, 3, FUSED, true, 1, true) : SS_MID(64, 3, FUSED);
-        return once ? SS_MID(64, 4, FUSED, true, 1, true) : SS_MID(64, 4, FUSED);
+        if (shared) return once ? SS_MID(64, 3, FUSED, true, true) : SS_MID(64, 3, FUSED);
+        return once ? SS_MID(64, 4, FUSED, true, true) : SS_MID(64, 4, FUSED);
     }
     if constexpr (!FUSED)
         if (shared && 4 * ntiles <= 5 * cu_count()) return SS_MID(128, 3, FUSED, false);
@@ -617,6 +565,18 @@ static ss_status launch_dense_mid_dt(const void* Xq, const float* s_x, const voi
 
 // Host side, called by the C entry points.  Arguments are already validated.
 namespace ss {
+
+ss_status launch_mid_reduce32(const void* ws, int S, const float* s_x, const float* s_w, int64_t M, int64_t O, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
+{
+    const int64_t ntiles = (O + PANEL - 1) / PANEL;
+    switch (dtype) {
+    case SS_I8: return launch_mid_reduce<SS_I8, 32>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, 1, stream);
+    case SS_FP8_E4M3: return launch_mid_reduce<SS_FP8_E4M3, 32>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, 1, stream);
+    case SS_BF16: return launch_mid_reduce<SS_BF16, 32>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, 1, stream);
+    case SS_FP16: return launch_mid_reduce<SS_FP16, 32>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, 1, stream);
+    }
+    return SS_ERR_DTYPE;
+}
 
 // bytes of a tile's partial sums: the tile the launchers take for M tokens
 static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE * 4 * (kind == SS_KIND_DENSE || M > 64 ? 128 : M > 32 ? 64 : 32); }

@@ -1,12 +1,17 @@
-// Sparse GEMMs of few tokens on layers of more panels than compute units: M <= 128, one tile of tokens.
+// Sparse GEMMs of one tile of tokens as a stream of weights, bound by HBM: up to 32 tokens with a workgroup for each panel (NF = 4
+// fragments of 32 channels) and k range, and up to 128 tokens on layers of more panels than compute units (NF = 5, 6 or 8).
 //
-// The call is a stream of weights, bound by HBM.  A workgroup per panel (gemm_mid.hip) gives some compute units two streams where
-// the others have one, and a compute unit has about a hundred cache lines in flight whatever its workgroups ask for, so the launch waits
-// for those with two: 128 MB streamed into LDS by 256 workgroups take 20.3 us, by 296 26.1.  Here a workgroup owns NF = 5, 6 or 8
-// fragments of 32 channels, as many as leave at most one workgroup for each compute unit, a wavefront for each fragment.  3584 -> 37888 at
-// M = 1, weights from HBM: INT8 29.3 -> 22.1 us (5.8 TB/s), bf16 53.5 -> 37.9 (6.7 TB/s).
-// The loop is left to the compiler's scheduler: a unit takes a compute unit 1500 cycles to stream and its operand reads and
-// matrix instructions a third of that.
+// A wavefront owns one fragment and all tokens.  The loop is plain: wait for a unit, meet, request a later one, read the operands,
+// multiply; the order is left to the compiler.  A unit takes a compute unit 1500 cycles to stream and its operand reads and
+// matrix instructions a third of that, so a software pipeline or a second group of wavefronts with half of the k range (both in the
+// kernel for 32 tokens before) only costs: NF = 4 against it, M = 1 .. 32, weights from HBM / hot, 63 calls of rows of 16 units and more in
+// fused INT8, bf16 and lifted fp8, bf16: 0.88 .. 1.03 (mean 0.96) / 0.88 .. 1.02; 24 calls of 1 to 15 units 0.88 .. 0.98 / 0.81 .. 1.10 (18944 -> 3584 bf16 at M = 1 26.7 -> 23.4 us).
+//
+// More panels than compute units: a workgroup per panel gives some compute units two streams where the others have one, and a
+// compute unit has about a hundred cache lines in flight whatever its workgroups ask for, so the launch waits for those with two:
+// 128 MB streamed into LDS by 256 workgroups take 20.3 us, by 296 26.1.  There a workgroup owns as many fragments as leave at most one
+// workgroup for each compute unit, without a k split.  3584 -> 37888 at M = 1, weights from HBM: INT8 29.3 -> 22.1 us (5.8 TB/s),
+// bf16 53.5 -> 37.9 (6.7 TB/s).
 #include "ss_common.h"
 #include "packed_layout.h"
 #include "mma_types.h"
@@ -15,20 +20,22 @@
 
 namespace ss {
 
-// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [fragment][step][lane][16 B], index words of the two
-// panels the fragments lie in [panel][step][lane][fragment of the panel][4 B]
+// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [fragment][step][lane][16 B], index words of the panel or
+// the two panels the fragments lie in [panel][step][lane][fragment of the panel][4 B].  NF = 4: a ring of four (fused) or five units; one more, for
+// which a compute unit has room where it holds one workgroup, 1.01 to 1.02 of the time.
 template <int NF, int TB, bool FUSED> struct WideUnit {
     static constexpr int NS = FUSED ? 3 : 2;
-    static constexpr int TOK = TB * 32 * ROWB, AV = NF * NS * 1024, AM = 2 * NS * 1024, BYTES = TOK + AV + AM;
-    static constexpr int SHARED = TB * 4 + 2 * NS;                        // 1 KB pieces of tokens and index words
+    static constexpr int PANELS = NF == 4 ? 1 : 2;
+    static constexpr int TOK = TB * 32 * ROWB, AV = NF * NS * 1024, AM = PANELS * NS * 1024, BYTES = TOK + AV + AM;
+    static constexpr int SHARED = TB * 4 + PANELS * NS;                        // 1 KB pieces of tokens and index words
     static constexpr int E = (SHARED + NF - 1) / NF, LPU = NS + E;        // direct loads per wavefront: its values, its share of those
-    static constexpr int FIT = 160 * 1024 / BYTES, RING = FIT < 5 ? FIT : 5;
+    static constexpr int FIT = (NF == 4 ? 80 : 160) * 1024 / BYTES, RING = FIT < 5 ? FIT : 5;
 };
 
 template <int DT, int NF, int TB, bool FUSED, bool ONCE>
 __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
-                                                         const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U,
-                                                         int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy)
+                                                         const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U_all,
+                                                         int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, void* __restrict__ ws)
 {
     typedef Mma<DT> MM;
     typedef WideUnit<NF, TB, FUSED> WU;
@@ -38,12 +45,15 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 31, qb = lane >> 5;
     const int npanels = (int)((O + PANEL - 1) / PANEL), nfrags = npanels * FRAGS_PER_PANEL;
-    const int f_first = xcd_run(blockIdx.x, gridDim.x) * NF, p_first = f_first / FRAGS_PER_PANEL;
+    // work item: fragments of a k range, one run over all (range, fragments) pairs for each XCD
+    const int item = xcd_run(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y), range = item / (int)gridDim.x, col = item - range * gridDim.x;
+    const int u_first = (int)((int64_t)range * U_all / gridDim.y), U = (int)((int64_t)(range + 1) * U_all / gridDim.y) - u_first;
+    const int f_first = col * NF, p_first = f_first / FRAGS_PER_PANEL;
     const int frag = min(f_first + wave, nfrags - 1), panel = frag / FRAGS_PER_PANEL, f = frag % FRAGS_PER_PANEL;     // beyond the last: that one again, not stored
     const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
 
     // Sources of this wavefront's loads.  Lanes of tokens that do not exist load nothing (their products are never stored).
-    const uint8_t* const av_src = w_vals + ((int64_t)panel * NS * U * FRAGS_PER_PANEL + f) * 1024;
+    const uint8_t* const av_src = w_vals + (((int64_t)panel * U_all + u_first) * NS * FRAGS_PER_PANEL + f) * 1024;
     const uint8_t* e_src[WU::E];
     uint32_t e_off[WU::E], e_step[WU::E], e_dst[WU::E];
     uint64_t e_lanes[WU::E];
@@ -55,14 +65,14 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
         const int rows = max(0, min(8, (int)M - piece * 8)), row = piece * 8 + (lane >> 3);
         const int k = max(0, piece - TB * 4), p = min(p_first + k / NS, npanels - 1);
         const uint64_t some = rows == 8 ? ~0ull : (1ull << (8 * rows)) - 1;
-        e_src[e] = reinterpret_cast<const uint8_t*>(uniform((uint64_t)(uintptr_t)(tokens ? Xq : w_meta + ((int64_t)p * NS * U + k % NS) * 1024)));
+        e_src[e] = reinterpret_cast<const uint8_t*>(uniform((uint64_t)(uintptr_t)(tokens ? Xq + (int64_t)u_first * ROWB : w_meta + (((int64_t)p * U_all + u_first) * NS + k % NS) * 1024)));
         e_off[e] = tokens ? (uint32_t)row * (uint32_t)ldxb + (((lane & 7) ^ swz(row)) << 4) : lane16;
         e_step[e] = __builtin_amdgcn_readfirstlane(tokens ? ROWB : NS * 1024);
         e_dst[e] = __builtin_amdgcn_readfirstlane(tokens ? piece * 1024 : WU::TOK + WU::AV + k * 1024);
         e_lanes[e] = uniform(tokens ? some : piece < WU::SHARED ? ~0ull : 0ull);
     }
     // as in gemm_mid.hip the XCDs start at different places of the row
-    const int rot = (blockIdx.x & 7) * U >> 3;
+    const int rot = ((blockIdx.y * gridDim.x + blockIdx.x) & 7) * U >> 3;
     auto issue = [&](int v, uint32_t slot) __attribute__((always_inline)) {
         const int u = v + rot < U ? v + rot : v + rot - U;
 #pragma unroll
@@ -120,6 +130,11 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
         lslot = lslot == (RING - 1) * WU::BYTES ? 0u : lslot + WU::BYTES;
     }
     if (f_first + wave >= nfrags) return;
+    if (NF == 4 && TB == 1 && gridDim.y > 1) {
+        const typename MM::acc_t part[1][1] = {{acc[0]}};
+        mid_store_partial(part, ws, item, wave, lane, (int)M);
+        return;
+    }
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
         store_block16<MM::SCALED>(acc[tb], s_x, s_w, Y, ldy, M, O, (int64_t)panel * PANEL + 64 * qb + 16 * f, tb * 32 + n);
@@ -131,28 +146,29 @@ using namespace ss;
 
 template <int DT, int NF, int TB, bool FUSED, bool ONCE>
 static ss_status launch_wide_one(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
-                                 int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
+                                 int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     typedef WideUnit<NF, TB, FUSED> WU;
     constexpr int lds = WU::RING * WU::BYTES;
     static_assert(lds <= 160 * 1024, "LDS budget");
     const int64_t nfrags = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
     if (allow_dynamic_lds<k_sparse_wide<DT, NF, TB, FUSED, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_wide<DT, NF, TB, FUSED, ONCE>), dim3((unsigned)((nfrags + NF - 1) / NF)), dim3(64 * NF), lds, stream,
+    hipLaunchKernelGGL((k_sparse_wide<DT, NF, TB, FUSED, ONCE>), dim3((unsigned)((nfrags + NF - 1) / NF), (unsigned)S), dim3(64 * NF), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb,
-                       static_cast<uint16_t*>(Y), ldy);
+                       static_cast<uint16_t*>(Y), ldy, ws);
     return launch_status();
 }
 
 template <int DT, bool FUSED>
 static ss_status launch_wide_dt(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U,
-                                int64_t ldxb, void* Y, int64_t ldy, hipStream_t stream)
+                                int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
-    const int nf = wide_fragments(O, cu_count());
+    const int nf = (O + PANEL - 1) / PANEL <= cu_count() ? 4 : wide_fragments(FUSED ? SS_KIND_FUSED : SS_KIND_LIFTED, M, O, cu_count());
     const bool once = weights_stream(O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB);
-#define SS_W(NF, TB) return once ? launch_wide_one<DT, NF, TB, FUSED, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream) \
-                                 : launch_wide_one<DT, NF, TB, FUSED, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
+#define SS_W(NF, TB) return once ? launch_wide_one<DT, NF, TB, FUSED, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream) \
+                                 : launch_wide_one<DT, NF, TB, FUSED, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream)
 #define SS_WN(NF) { if (M <= 32) SS_W(NF, 1); if (M <= 64) SS_W(NF, 2); SS_W(NF, 4); }
+    if (nf == 4) SS_W(4, 1);
     if (nf == 5) SS_WN(5)
     if (nf == 6) SS_WN(6)
     SS_WN(8)
@@ -163,10 +179,11 @@ static ss_status launch_wide_dt(const void* Xq, const float* s_x, const void* w_
 namespace ss {
 
 ss_status launch_sparse_wide(bool fused, const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream)
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
-#define SS_WD(DT) return fused ? launch_wide_dt<DT, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream) \
-                               : launch_wide_dt<DT, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
+    ss_status st = SS_ERR_DTYPE;
+#define SS_WD(DT) st = fused ? launch_wide_dt<DT, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream) \
+                             : launch_wide_dt<DT, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream); break
     switch (dtype) {
     case SS_I8: SS_WD(SS_I8);
     case SS_FP8_E4M3: SS_WD(SS_FP8_E4M3);
@@ -174,7 +191,7 @@ ss_status launch_sparse_wide(bool fused, const void* Xq, const float* s_x, const
     case SS_FP16: SS_WD(SS_FP16);
     }
 #undef SS_WD
-    return SS_ERR_DTYPE;
+    return st == SS_OK && S > 1 ? launch_mid_reduce32(ws, S, s_x, s_w, M, O, dtype, Y, ldy, stream) : st;
 }
 
 }  // namespace ss

@@ -131,6 +131,26 @@ __device__ inline void store_quad4(const QUAD& a, float sx, const float (&sw)[4]
     }
 }
 
+// Split k, tiles of 128 channels: the raw accumulators of k-range s of tile `tile` go to the workspace as
+// ws[s][tile][wave][f][tb][register quad][lane] 16-byte groups (512 TM bytes per tile and range, coalesced).  `tokens` of
+// this wavefront's exist (may be <= 0); nothing is written for the others.
+template <typename ACC, int FW, int TB>
+__device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int64_t item, int wave, int lane, int tokens)
+{
+    v4i* dst = static_cast<v4i*>(ws) + ((item * 4 + wave) * (4 * FW * TB)) * 64 + lane;
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+            if (tb * 32 + (lane & 31) < tokens)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
+                const elem_t q[4] = {acc[f][tb][4 * r4], acc[f][tb][4 * r4 + 1], acc[f][tb][4 * r4 + 2], acc[f][tb][4 * r4 + 3]};
+                dst[((f * TB + tb) * 4 + r4) * 64] = __builtin_bit_cast(v4i, q);
+            }
+}
+
 // Kernels for few tokens (gemm_skinny.hip): one workgroup per 32 or 64 output channels streams their weights once.
 // The dense kernel splits its k range over S workgroups per fragment where there are fewer 32-channel fragments than
 // compute units; partial sums go through `ws` (skinny_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a
@@ -157,16 +177,6 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
-// Few tokens on more panels than compute units (gemm_wide.hip), up to two of them for each.  X: lifted rows, or unlifted ones and weights of
-// slide_decompose_fused; U units of 128 bytes per row, ldxb bytes between rows.
-ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
-                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
-// fragments of 32 channels that a workgroup of theirs takes, 0 where they are not used
-inline int wide_fragments(int64_t O, int64_t cus)
-{
-    const int64_t frags = (O + 127) / 128 * 4, f = (frags + cus - 1) / cus;
-    return f <= 4 || f > 8 ? 0 : f == 7 ? 8 : (int)f;
-}
 // Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are more than a
 // third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise;
 // calls of M = 1 .. 64 with weights from HBM, 96 to 254 MB, 0.88 .. 0.98 of the time.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose where
@@ -174,6 +184,20 @@ inline int wide_fragments(int64_t O, int64_t cus)
 inline bool weights_stream(int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= CACHED_BYTES; }
 
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
+
+// Few tokens as a stream of weights (gemm_wide.hip): up to 32 tokens on as many panels as compute units or fewer, up to 128 on more, up to two for each.
+// X: lifted rows, or unlifted ones and weights of slide_decompose_fused; U units of 128 bytes per row, ldxb bytes between rows.
+// S > 1 (NF = 4): partial sums as of the 32-token tiles of gemm_mid.hip go through `ws`.
+ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
+// fragments of 32 channels that a workgroup of theirs takes, 0 where they are not used
+inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
+{
+    const int64_t frags = (O + 127) / 128 * 4, f = (frags + cus - 1) / cus;
+    if (M > (kind == SS_KIND_FUSED ? 128 : 64) || f > 8) return 0;
+    if (f <= 4) return M <= 32 && f >= 3 ? 4 : 0;
+    return f == 7 ? 8 : (int)f;
+}
 
 // Kernels with tiles of 128 channels x 128 tokens, sparse ones also x 64 and x 32 where the tokens fit (gemm_mid.hip),
 // for shapes that give the 256 x 256 tile kernels too few tiles to occupy the compute units.
@@ -187,6 +211,8 @@ ss_status launch_sparse_fused_mid(const void* Xq, const float* s_x, const void* 
                                   int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
 ss_status launch_dense_mid(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                            void* Y, int64_t ldy, void* ws, int S, hipStream_t stream);
+// the second kernel alone, for the partial sums of 32-token tiles
+ss_status launch_mid_reduce32(const void* ws, int S, const float* s_x, const float* s_w, int64_t M, int64_t O, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes);
 size_t mid_workspace_bytes(ss_kind kind, int64_t M, int64_t O, int S);
 inline int64_t mid_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * ((M + 127) / 128); }
@@ -205,8 +231,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //   M 33..64  tiles of 64 tokens where the panels alone fill the chip (3584 -> 37888: 37 against 50) or the rows are long
 //             and can be split (bf16 3584 -> 4608: 13.9 against 23.6; fp8 lifted 4096 -> 6144: 13.9 against 19.9; unsplit
 //             18944 -> 3584: 64 against 31), few-token kernels otherwise (3584 -> 4608 unsplit: 15.9 against 14.4).
-//   M <= 32   tiles of 32 tokens where the panels alone fill the chip (3584 -> 37888, M = 1: 32 against 34; M = 32: 34
-//             against 37; 18944 channels, M = 32: 19 against 23; 16384, M = 1: 18.5 against 17.2) or the rows are long
+//   M <= 32   a workgroup per panel (and k range; gemm_wide.hip) where there are more panels than half of the compute units (rows of 16 units and more: 3584 -> 18944
+//             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
 //             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
@@ -250,7 +276,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
-    if (M <= (kind == SS_KIND_FUSED ? 128 : 64) && units >= 16 && wide_fragments(O, cus)) return {SS_PATH_WIDE, 1};
+    if (units >= 16 && wide_fragments(kind, M, O, cus)) return {SS_PATH_WIDE, 1};
     if (M > 64) {
         if (kind == SS_KIND_FUSED && narrow_pays(M, O, cus)) return {SS_PATH_NARROW, 1};
         const bool many = 4 * tiles > 7 * cus;                          // more than 448

@@ -1,5 +1,6 @@
-"""Few tokens on layers of more panels than compute units: workgroups of five, six and eight fragments (256 compute units: 257 to 320,
-321 to 384 and 385 to 512 panels), token tiles of 32, 64 and 128; against a product in 64 bits.  Operands are small integers, so every partial sum is exact."""
+"""Few tokens as a stream of weights: workgroups of five, six and eight fragments on layers of more panels than compute units (256 compute
+units: 257 to 320, 321 to 384 and 385 to 512 panels), token tiles of 32, 64 and 128, and of four fragments on fewer panels, with and without split
+rows; against a product in 64 bits.  Operands are small integers, so every partial sum is exact."""
 import pytest
 import torch
 
@@ -40,3 +41,12 @@ def test_rows_with_gaps(dtype, M, pad_x, pad_y):
     binding.slide_sparse_gemm_fused(X, None if one is None else one[:M], wv, wm, None if one is None else one[:O], O, K, 4, dtype, out=out[:, :O])
     assert torch.equal(out[:, :O], (X.double() @ W.double().T).bfloat16())
     assert bool((out[:, O:] == 7.0).all())
+
+
+# a workgroup per panel: fewer units than the ring holds to several rings, one range and several, ranges of unlike length
+@pytest.mark.parametrize("dtype,N", [("i8", 4), ("bf16", 4), ("fp8", 3), ("fp16", 5)])
+@pytest.mark.parametrize("M,O,units,with_ws", [(1, 129 * 128 - 5, 16, False), (31, 200 * 128, 21, False), (8, 192 * 128 + 4, 1, False), (32, 256 * 128, 3, False),
+                                               (17, 192 * 128, 6, False), (1, 300, 131, True), (9, 4096, 65, True), (32, 1000, 160, True)])
+def test_panels(dtype, N, M, O, units, with_ws):
+    for fused in ([True, False] if N == 4 else [False]):
+        _linear(M, O, _rows(units, N, dtype, fused), N, dtype, fused, with_ws, M)

@@ -84,7 +84,9 @@ def test_wide_layers(plan):
     for M, O, units, fused in test_gpu_wide_layers.SHAPES:
         assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
         assert plan(FUSED if fused else LIFTED, M, O, 15)["path"] != WIDE
-    assert plan(FUSED, 5, 256 * 128, 16)["path"] == MID and plan(FUSED, 5, 513 * 128, 16)["path"] == MID
+    for kind in (FUSED, LIFTED):
+        assert plan(kind, 32, 129 * 128, 16)["path"] == plan(kind, 1, 256 * 128, 16)["path"] == WIDE
+        assert plan(kind, 33, 256 * 128, 16)["path"] == plan(kind, 5, 513 * 128, 16)["path"] == MID
 
 
 def test_replayed_routes(plan):
