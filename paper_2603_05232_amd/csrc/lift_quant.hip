@@ -7,6 +7,7 @@
 // the algorithmic minimum: K input elements in, K' output elements + one scale out.
 #include "ss_common.h"
 #include "quant_common.h"
+#include "device_info.h"
 #include <type_traits>
 
 namespace ss {
@@ -197,7 +198,9 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     uint8_t* xl = static_cast<uint8_t*>(XL);
 #define SS_LQ(MAXV, T, RAGGED) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED>), grid, dim3(T), RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
 #define SS_LQ_ROWS(RAGGED)                             \
-    if (nvec <= 4 * 256) SS_LQ(4, 256, RAGGED);        \
+    if (spread && nvec <= 2 * 512) SS_LQ(2, 512, RAGGED);        \
+    else if (spread && nvec <= 2 * 1024) SS_LQ(2, 1024, RAGGED); \
+    else if (nvec <= 4 * 256) SS_LQ(4, 256, RAGGED);   \
     else if (nvec <= 4 * 512) SS_LQ(4, 512, RAGGED);   \
     else if (nvec <= 5 * 1024) SS_LQ(5, 1024, RAGGED); \
     else if (nvec <= 10 * 1024) SS_LQ(10, 1024, RAGGED); \
@@ -205,6 +208,11 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     // Rows off a line: whole lines against scalar loads, time, M = 1 .. 30000, N = 2 .. 8: 8-bit codes (two passes over the row) of 37 to 195
     // elements 0.91 .. 1.22, 257 to 771 0.55 .. 1.07, 1003 and more 0.18 .. 1.06 (8192 x 4099 fp32 to fp8 0.46); 16-bit codes (one pass) of 37 to
     // 385 elements 0.92 .. 1.76, 515 to 771 0.73 .. 1.13, 1003 and more 0.37 .. 1.10.  Where the rows are short, a thread has an element or two.
+    // Where every token has a compute unit to itself, a row is a chain of latencies: twice the threads, half the work of each (rows of more
+    // than 256 vectors, two for a thread; time over four for a thread, M = 1 .. 256, five type and pattern forms: K = 3584 and 4096 0.81 .. 1.00, 8192 0.81 .. 0.99,
+    // 14336 0.88 .. 1.01; four layers of a block: fp8 lifted M = 64 85.1 -> 81.2 us, INT8 M = 1 65.9 -> 64.6, M = 256 127.4 -> 125.7).
+    // With more tokens than compute units rows of more than 512 threads lose (M = 300: up to 1.06).
+    const bool spread = M <= cu_count() && nvec > 256;
     const bool few = !line_ok && K <= (OUT < 2 ? 256 : 512);
     // 64: the kernel's small reduction buffer
     if (!element_ok || few || nvec > 20 * 1024 || (!line_ok && ragged_bytes + 64 > 64 * 1024)) SS_LQ(0, 256, false);
