@@ -4,9 +4,9 @@
 // There the large-tile kernels leave most compute units idle (M = 256 on a 3584-channel layer is 14
 // tiles for 256 units), so these kernels use 128 (one weight panel) x 128 (tokens) tiles, one tile per
 // workgroup of four wavefronts, each wavefront accumulating 64 channels x 64 tokens (2 x 2 blocks of a
-// 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 tokens and, where workgroups share compute
-// units (gemm_wide.hip has the other calls of up to 32 tokens), 32 tokens for calls that have no more: a call of few tokens is a stream of weights, and every token row that does not exist would
-// be loaded, read and, with a split k range, written as partial sums all the same.  Operands go HBM/L2 -> LDS
+// 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 tokens and, where workgroups share compute units
+// (gemm_wide.hip has the other calls of up to 32 tokens), 32 tokens for calls that have no more: a call of few tokens is a
+// stream of weights, and every token row that does not exist would be loaded and read all the same.  Operands go HBM/L2 -> LDS
 // with direct-to-LDS loads into a ring of units of 128 k-bytes, one barrier per unit.
 //   sparse: a unit is the token tile plus the panel's stored values and index words, which are already in
 //           operand-register order (packed_layout.h); software pipeline, see k_sparse_mid;
@@ -584,7 +584,7 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 // Number of k ranges for the tiles of this shape over `units` 128-byte k units with a workspace of ws_bytes: at most one
 // workgroup per compute unit, at least eight units per range, no more than the workspace holds.
 // Dense kernel: as many as that allows.  Sparse, M <= 64: the same (three quarters of a workgroup per compute unit for tiles
-// of 32 tokens: 18944 -> 3584 at M = 1, 28 tiles: 20.4 us in 5 ranges, 19.1 in 7, 19.3 in 9; bf16 3584 -> 4608 at M = 64, 56
+// of up to 32 tokens, where as many as compute units are 0.94 to 1.04 of the time of that, mean 1.00; bf16 3584 -> 4608 at M = 64, 56
 // units: 17.3 us in 3 ranges, 14.4 in 5, 13.8 in 7), but short rows are not split at 33..64 tokens.
 // Sparse, M > 64: the S of the least S-th part of the units + cost of the partial sums, which is, counted in units, 4 + a
 // 16th of the tiles x ranges written and read back, and 2 more where the ranges take over 7/8 of the compute units: on two of
