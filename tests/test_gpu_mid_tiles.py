@@ -146,3 +146,14 @@ def test_two_groups_of_wavefronts(dtype, fused, M, O, units, with_ws):
 @pytest.mark.parametrize("O,units", [(192 * 128 + 4, 29), (24 * 128, 230)])
 def test_weights_larger_than_the_cache_keeps(dtype, M, O, units):
     _linear(M, O, _rows(units, 4, dtype, True), 4, dtype, True, True, M)
+
+
+# split rows by the number of ranges that the reduce kernel adds (eight at a time, the last one to four of them by four or two): a full
+# batch and 1, 2, 3, 4, 5 or 8 more, two full batches and more, many; tiles of 32, 64 and 128 tokens
+RANGES = [(M, 300, 8 * S, S) for M in (5, 40) for S in (8, 9, 10, 11, 12, 13, 16, 17, 21)] + [(33, 300, 48, 6), (100, 128, 300, 34)]
+
+
+@pytest.mark.parametrize("dtype,fused", [("i8", True), ("bf16", False)])
+@pytest.mark.parametrize("M,O,units,S", RANGES)
+def test_numbers_of_ranges(dtype, fused, M, O, units, S):
+    _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, True, S)

@@ -80,6 +80,13 @@ def test_shared_compute_units(plan):
         assert plan(FUSED, M, O, units)["path"] == NARROW
 
 
+def test_numbers_of_ranges(plan):
+    for M, O, units, S in test_gpu_mid_tiles.RANGES:
+        for kind in (FUSED, LIFTED):
+            p = plan(kind, M, O, units, 1 << 30)
+            assert (p["path"], p["S"]) == (MID, S), (M, O, units, p)
+
+
 def test_wide_layers(plan):
     for M, O, units, fused in test_gpu_wide_layers.SHAPES:
         assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
