@@ -71,8 +71,12 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
         e_dst[e] = __builtin_amdgcn_readfirstlane(tokens ? piece * 1024 : WU::TOK + WU::AV + k * 1024);
         e_lanes[e] = uniform(tokens ? some : piece < WU::SHARED ? ~0ull : 0ull);
     }
-    // as in gemm_mid.hip the XCDs start at different places of the row
-    const int rot = ((blockIdx.y * gridDim.x + blockIdx.x) & 7) * U >> 3;
+    // As in gemm_mid.hip the XCDs start at different places of the row, NF = 4 in twice as many: with eight places, panels of
+    // certain sizes (504 KB, 512 KB) meet in the same memory channels (time with 16 over 8, M = 4 and 24, 129 to 256 panels, weights from HBM: fused rows of 42 units
+    // 0.90 .. 1.00, 96 units 0.88 .. 1.00, lifted rows of 64 units 0.95 .. 1.00, 128 units 0.93 .. 1.01; all other lengths of 21 to 148 units 0.96 .. 1.04, mean 1.00;
+    // 32 and 64 places up to 1.16 and 1.22 at single lengths; NF = 5, 6 and 8 with 16 places 0.97 .. 1.15).
+    constexpr int PLACES = NF == 4 ? 16 : 8;
+    const int rot = ((blockIdx.y * gridDim.x + blockIdx.x) & (PLACES - 1)) * U / PLACES;
     auto issue = [&](int v, uint32_t slot) __attribute__((always_inline)) {
         const int u = v + rot < U ? v + rot : v + rot - U;
 #pragma unroll
