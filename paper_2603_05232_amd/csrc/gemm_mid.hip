@@ -5,8 +5,8 @@
 // tiles for 256 units), so these kernels use 128 (one weight panel) x 128 (tokens) tiles, one tile per
 // workgroup of four wavefronts, each wavefront accumulating 64 channels x 64 tokens (2 x 2 blocks of a
 // 32x32 matrix instruction).  The sparse kernel also comes with tiles of 64 tokens and, where workgroups share compute units
-// (gemm_wide.hip has the other calls of up to 32 tokens), 32 tokens for calls that have no more: a call of few tokens is a
-// stream of weights, and every token row that does not exist would be loaded and read all the same.  Operands go HBM/L2 -> LDS
+// or for some lifted rows (gemm_wide.hip has the other calls of up to 32 tokens), 32 tokens for calls that have no more: a call of few tokens
+// is a stream of weights, and every token row that does not exist would be loaded and read all the same.  Operands go HBM/L2 -> LDS
 // with direct-to-LDS loads into a ring of units of 128 k-bytes, one barrier per unit.
 //   sparse: a unit is the token tile plus the panel's stored values and index words, which are already in
 //           operand-register order (packed_layout.h); software pipeline, see k_sparse_mid;
@@ -194,6 +194,9 @@ template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&ac
 // workgroup and the launch waits for those with two, that is the faster loop (lifted INT8 / bf16 against the pipeline, weights
 // from HBM: 4096 -> 4096 at M = 1152, 288 tiles, 35 against 38 us / 59 against 68; 4096 -> 6144 at M = 768 35 against 37 / 58 against 64);
 // with more tiles than that, or unlifted rows, the pipeline is (384 tiles, 4096 -> 4096 at M = 1536, same order: 39.5 against 41.1 us; fused, 288 tiles: 33 against 35).
+// KG = 2: two groups of four wavefronts, each with half of the workgroup's k range and a ring of its own, meet at the same
+// barriers; the second hands its sums to the first in LDS.  Two wavefronts per SIMD then cover each other's waits, which a
+// deeper ring for one does less well, and no partial sums more are written.
 template <int TM, bool FUSED> struct MidUnit {
     typedef MidShape<TM> MS;
     static constexpr int NS = FUSED ? 3 : 2;                              // steps
@@ -208,8 +211,8 @@ template <int TM, bool FUSED> struct MidUnit {
 };
 template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE, bool ONCE>
-__global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
+template <int DT, int TM, int RING, bool FUSED, bool PIPE, bool ONCE, int KG>
+__global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
                                                               uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
@@ -221,14 +224,18 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
     constexpr int FW = MU::MS::FW, TB = MU::MS::TB;
     typedef MidOps<NS, FW, TB> Ops;
     typedef int idx_t __attribute__((ext_vector_type(FW)));
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];     // RING units
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    static_assert(KG == 1 || PIPE, "groups of wavefronts run the pipeline");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];      // RING units for each of the KG groups
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % MD_WAVES, kg = wave_all / MD_WAVES, lane = threadIdx.x & 63;
+    uint8_t* const smem = lds + kg * (RING * MU::BYTES);
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
     const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all), PIPE ? 8 : 16);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
     // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
-    const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
+    const int first = (int)((int64_t)it.range * U_all / gridDim.y), count = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - first;
+    // units [u0, u0 + U) of it are this group's; the host takes KG groups only for ranges of at least KG units
+    const int u0 = first + kg * (count / KG), U = kg + 1 < KG ? count / KG : count - kg * (count / KG);
 
     // Direct loads of a unit, by wavefront: TM / 32 of token rows, NS of values ([step][fragment 4][lane 64][16 B]) and one of
     // NS * 256 bytes of index words ([step][lane 64][fragment 4][4 B]; lanes 0 .. 16 NS - 1)
@@ -406,6 +413,29 @@ __global__ __launch_bounds__(MD_THREADS, (RING * MidUnit<TM, FUSED>::BYTES <= 80
         } else unit(no, no, A, B, u);
     }
     const int64_t o_wave = panel * PANEL + 16 * FW * wo, t_wave = t0 + wt * (32 * TB), item = (int64_t)it.range * gridDim.x + it.tile;
+    if constexpr (KG == 2) {                                             // the second group hands its sums to the first in LDS
+        static_assert(FW * TB == 1, "one accumulator block per wavefront");
+        if (kg == 0 && count & 1) wg_barrier();                          // it has one unit, and one meeting, more
+        wait_lgkm0();
+        wg_barrier();                                                    // nobody reads operands any more
+        v4i* const x = reinterpret_cast<v4i*>(lds) + wave * 256 + lane;
+        typedef decltype(acc[0][0][0] + acc[0][0][0]) elem_t;
+        typedef elem_t quad_t __attribute__((ext_vector_type(4)));
+        auto& v = acc[0][0];
+        if (kg == 1) {
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) x[r4 * 64] = __builtin_bit_cast(v4i, (quad_t){v[4 * r4], v[4 * r4 + 1], v[4 * r4 + 2], v[4 * r4 + 3]});
+            wait_lgkm0();
+        }
+        wg_barrier();
+        if (kg == 1) return;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const quad_t q = __builtin_bit_cast(quad_t, x[r4 * 64]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * r4 + e] += q[e];
+        }
+    }
     if (gridDim.y > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, o_wave, t_wave, lane);
 }
@@ -500,15 +530,15 @@ static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const 
     return launch_status();
 }
 
-template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, bool ONCE = false>
+template <int DT, int TM, int RING, bool FUSED, bool PIPE = true, bool ONCE = false, int KG = 1>
 static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M,
                                         int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
                                         hipStream_t stream)
 {
-    constexpr int lds = RING * MidUnit<TM, FUSED>::BYTES;
-    static_assert(lds <= 160 * 1024, "LDS budget");
-    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream,
+    constexpr int lds = KG * RING * MidUnit<TM, FUSED>::BYTES;
+    static_assert(lds <= 160 * 1024 && (KG == 1 || lds >= TM * 512), "the rings, then the sums that are handed over");
+    if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>>(lds) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
                        ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
     if (launch_status() != SS_OK) return SS_ERR_HIP;
@@ -527,11 +557,13 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     // each other's waits.  A workgroup alone: the whole ring is requested at once, so that a deeper one delays the first
     // unit (3584 -> 4608 at M = 256, 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
     // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9).  32 tokens at most and no more workgroups than compute units:
-    // the weight stream of gemm_wide.hip (both sides there).
+    // the weight stream of gemm_wide.hip (both sides there), or two groups of wavefronts with a ring of four each (two_groups).
     const bool shared = ntiles * S > cu_count();
 #define SS_MID(TM, ...) launch_sparse_mid_ring<DT, TM, __VA_ARGS__>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
     const bool once = weights_stream(O, (int64_t)U * MidUnit<32, FUSED>::NS * FRAG_KB);
     if (M <= 32) {
+        if constexpr (!FUSED)
+            if (two_groups(M, O, U, cu_count())) return once ? SS_MID(32, 4, FUSED, true, true, 2) : SS_MID(32, 4, FUSED, true, false, 2);
         if (!shared) return launch_sparse_wide(FUSED, Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, (ss_dtype)DT, Y, ldy, ws, S, stream);
         return once ? SS_MID(32, 4, FUSED, true, true) : SS_MID(32, 4, FUSED);
     }

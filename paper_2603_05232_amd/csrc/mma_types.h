@@ -199,6 +199,19 @@ inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
     return f == 7 ? 8 : (int)f;
 }
 
+// Up to 32 tokens of lifted rows on half to two thirds as many panels as compute units: tiles of 32 tokens in two groups of wavefronts (gemm_mid.hip),
+// not the weight stream.  A unit of lifted rows is two steps, and a wavefront for each SIMD waits for its operand reads longer than it
+// multiplies; with half of the compute units idle the loads do not cover that.  Time over the stream, M = 1 .. 32, 12 to 100 units, weights
+// from HBM / hot: 129 panels 0.88 .. 1.04 / 0.82 .. 1.02 (mean 0.99 / 0.90; fp8 3584 -> 16512 at M = 16 14.9 against 15.0 us, hot 11.4 against 13.9), 148 panels 0.88 .. 1.05 /
+// 0.83 .. 1.03 (1.00 / 0.93), 170 panels 0.96 .. 1.06 / 0.88 .. 1.01 (1.01 / 0.95), 191 panels 0.97 .. 1.09 / 0.88 .. 1.08 (1.02 / 1.00), 256 panels 0.95 .. 1.05 /
+// 0.95 .. 1.15 (1.00 / 1.01); ten units and fewer lose.  Unlifted rows gain from HBM by the stream (129 panels, M = 16 and 32: 0.98, hot 1.07).  M < 16 over the
+// few-token kernels, 16 to 64 units: 0.70 .. 1.00 / 0.77 .. 1.08.
+inline bool two_groups(int64_t M, int64_t O, int64_t units, int64_t cus)
+{
+    const int64_t panels = (O + 127) / 128;
+    return M <= 32 && units >= (M < 16 ? 16 : 12) && 2 * panels >= cus + (M < 16) && 3 * panels <= 2 * cus;
+}
+
 // Kernels with tiles of 128 channels x 128 tokens, sparse ones also x 64 and x 32 where the tokens fit (gemm_mid.hip),
 // for shapes that give the 256 x 256 tile kernels too few tiles to occupy the compute units.
 // S > 1 splits the k range over S workgroups per tile; their partial sums go through `ws`
@@ -235,7 +248,7 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
-//             against 12.8).  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
+//             against 12.8); lifted rows by two_groups.  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
 // M <= 64, fused 128, and 257 .. 512 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each compute unit.  Time over
 //             that of a panel for each workgroup, weights from HBM, 96 calls, INT8, bf16 and fp8 lifted: 16 units and more 0.62 .. 0.95 (3584 -> 37888 at
 //             M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9), 4 to 12 units 0.91 .. 1.07.  Lifted rows of 65 .. 128 tokens keep the 128 x 128 tiles.
@@ -276,6 +289,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
+    if (kind == SS_KIND_LIFTED && two_groups(M, O, units, cus)) return {SS_PATH_MID, 1};
     if (units >= 16 && wide_fragments(kind, M, O, cus)) return {SS_PATH_WIDE, 1};
     if (M > 64) {
         if (kind == SS_KIND_FUSED && narrow_pays(M, O, cus)) return {SS_PATH_NARROW, 1};

@@ -50,8 +50,8 @@ def _linear(M, O, K, N, dtype, fused, with_ws, seed):
     assert bool((out[M] == 7.0).all())                                 # nothing beyond the last token
 
 
-# 192 panels, unsplit: one workgroup per compute unit (256 of them), two groups of wavefronts with rings of four units each (32 tokens, from two
-# units up) and a ring of four units (64)
+# 192 panels, unsplit: one workgroup per compute unit (256 of them), the weight stream with a ring of four units (32 tokens) and tiles of 64 tokens with a
+# ring of four units
 @pytest.mark.parametrize("M", [1, 32, 33, 64])
 @pytest.mark.parametrize("units", [1, 2, 3, 4, 5, 7, 8, 9, 10, 18])
 def test_wide_layers_of_few_tokens(M, units):
@@ -127,13 +127,26 @@ def test_rest_of_a_round(dtype, N, fused):
     _linear(1100, 13556, K if fused else K * N // (2 * (N - 1)) - 3, N, dtype, fused, False, N)
 
 
-# tiles of 32 tokens with two groups of wavefronts (at least two units in a range): ranges of odd and even length, one range
-# (192 panels) and several (few panels and long rows)
+# up to 32 tokens with two groups of wavefronts (lifted rows on half to two thirds as many panels as compute units, 12 units and more, M < 16: 16):
+# ranges of odd and even length, from one ring and less for each group to several, the fewest and the most panels, weights of 80 MB and more
+TWO_GROUPS = [(16, 128 * 128, 12), (31, 129 * 128 - 5, 13), (32, 170 * 128, 14), (1, 129 * 128, 16), (9, 170 * 128 - 100, 17), (15, 140 * 128 + 4, 33),
+              (20, 150 * 128, 41), (32, 160 * 128 - 1, 54)]
+
+
+@pytest.mark.parametrize("dtype,N", [("i8", 4), ("fp8", 3), ("bf16", 4), ("fp16", 5)])
+@pytest.mark.parametrize("M,O,units", TWO_GROUPS)
+def test_two_groups_of_wavefronts(dtype, N, M, O, units):
+    _linear(M, O, _rows(units, N, dtype, False), N, dtype, False, False, units)
+
+
+# up to 32 tokens by the weight stream: odd and even rows, one range (130 and 192 panels) and several (few panels and long rows)
+STREAM = [(1, 192 * 128 - 5, 2, False), (32, 192 * 128, 3, False), (17, 130 * 128, 9, False), (1, 300, 131, True), (32, 1000, 160, True), (9, 512, 97, True)]
+
+
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
 @pytest.mark.parametrize("fused", [True, False])
-@pytest.mark.parametrize("M,O,units,with_ws", [(1, 192 * 128 - 5, 2, False), (32, 192 * 128, 3, False), (17, 130 * 128, 9, False),
-                                               (1, 300, 131, True), (32, 1000, 160, True), (9, 512, 97, True)])
-def test_two_groups_of_wavefronts(dtype, fused, M, O, units, with_ws):
+@pytest.mark.parametrize("M,O,units,with_ws", STREAM)
+def test_stream_of_a_panel(dtype, fused, M, O, units, with_ws):
     N = 4
     es = 1 if dtype in ("i8", "fp8") else 2
     K = 128 * units // es if fused else 128 * units // es * N // (2 * (N - 1)) // (2 * N) * (2 * N)

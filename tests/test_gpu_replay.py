@@ -14,8 +14,9 @@ ROUTES = {"narrow tiles": (True, 1100, 4224, 640, False),
           "large tiles in rounds, odd rows": (True, 8100, 9000, 384, False),
           "large tiles in rounds, even rows": (True, 8100, 9000, 512, False),
           "five fragments a workgroup": (True, 17, 257 * 128, 2048, False),
-          "two groups of wavefronts": (True, 17, 192 * 128, 1152, False),
-          "two groups of wavefronts, split rows": (True, 9, 300, 16768, True),
+          "stream of a panel": (True, 17, 192 * 128, 1152, False),
+          "stream of a panel, split rows": (True, 9, 300, 16768, True),
+          "two groups of wavefronts": (False, 17, 130 * 128, 1536, False),
           "lifted tiles in rounds": (False, 8100, 9000, 411, False),
           "lifted tiles in rounds, short rows": (False, 8100, 9000, 160, False),
           "lifted tiles, one round": (False, 2100, 4224, 1003, False)}

@@ -25,7 +25,9 @@ int main()
         const ss_plan p = plan_gemm((ss_kind)kind, M, O, units, (size_t)ws);
         const long long cut = p.path == SS_PATH_TILE ? (long long)p.tile_o : 0;
         const int rest = cut == 0 || cut == O ? -1 : kind == SS_KIND_FUSED && narrow_pays(M, O - cut, cu_count()) ? SS_PATH_NARROW : SS_PATH_MID;
-        printf("%d %d %lld %d %d\\n", (int)p.path, p.S, cut, rest, cu_count());
+        const bool groups = kind == SS_KIND_LIFTED && p.path == SS_PATH_MID && two_groups(M, O, units, cu_count());
+        const bool stream = p.path == SS_PATH_WIDE || (kind != SS_KIND_DENSE && p.path == SS_PATH_MID && M <= 32 && !groups && (O + 127) / 128 * p.S <= cu_count());
+        printf("%d %d %lld %d %d %d %d\\n", (int)p.path, p.S, cut, rest, cu_count(), groups, stream);
     }
 }
 """
@@ -47,10 +49,10 @@ def plan(tmp_path_factory):
 
     def ask(kind, M, O, units, ws=0):
         out = subprocess.run([str(d / "plan")], input=f"{kind} {M} {O} {units} {ws}\n", stdout=subprocess.PIPE, text=True, check=True).stdout
-        path, S, cut, rest, cus = map(int, out.split())
+        path, S, cut, rest, cus, groups, stream = map(int, out.split())
         if cus != 256:
             pytest.skip("the shapes are chosen for 256 compute units")
-        return {"path": path, "S": S, "cut": cut, "rest": rest, "large_tiles": -(-cut // 256) * -(-M // 256)}
+        return {"path": path, "S": S, "cut": cut, "rest": rest, "groups": bool(groups), "stream": bool(stream), "large_tiles": -(-cut // 256) * -(-M // 256)}
     return ask
 
 
@@ -80,6 +82,17 @@ def test_shared_compute_units(plan):
         assert plan(FUSED, M, O, units)["path"] == NARROW
 
 
+def test_up_to_32_tokens(plan):
+    for M, O, units in test_gpu_mid_tiles.TWO_GROUPS:
+        assert plan(LIFTED, M, O, units)["groups"], (M, O, units)
+        assert not plan(FUSED, M, O, units)["groups"] and not plan(LIFTED, M, O, 11)["groups"]
+    assert not plan(LIFTED, 32, 170 * 128 + 1, 40)["groups"] and not plan(LIFTED, 32, 127 * 128, 40)["groups"] and not plan(LIFTED, 15, 129 * 128, 15)["groups"]
+    for M, O, units, with_ws in test_gpu_mid_tiles.STREAM:
+        for kind in (FUSED, LIFTED):
+            p = plan(kind, M, O, units, 1 << 30 if with_ws else 0)
+            assert p["stream"] and (p["S"] > 1) == with_ws, (kind, M, O, units)
+
+
 def test_numbers_of_ranges(plan):
     for M, O, units, S in test_gpu_mid_tiles.RANGES:
         for kind in (FUSED, LIFTED):
@@ -92,7 +105,7 @@ def test_wide_layers(plan):
         assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
         assert plan(FUSED if fused else LIFTED, M, O, 15)["path"] != WIDE
     for kind in (FUSED, LIFTED):
-        assert plan(kind, 32, 129 * 128, 16)["path"] == plan(kind, 1, 256 * 128, 16)["path"] == WIDE
+        assert plan(kind, 32, 171 * 128, 16)["path"] == plan(kind, 1, 256 * 128, 16)["path"] == plan(FUSED, 32, 129 * 128, 16)["path"] == WIDE
         assert plan(kind, 33, 256 * 128, 16)["path"] == plan(kind, 5, 513 * 128, 16)["path"] == MID
 
 
@@ -101,7 +114,9 @@ def test_replayed_routes(plan):
         units = (K if fused else binding.slide_lifted_ld(K, 4, "i8")) // 128
         p = plan(FUSED if fused else LIFTED, M, O, units, 1 << 30 if with_ws else 0)
         if "groups" in name:
-            assert p["path"] == MID and M <= 32 and (p["S"] > 1) == with_ws and units // p["S"] >= 2 and -(-O // 128) * p["S"] <= 256, name
+            assert p["groups"] and not with_ws, name
+        elif "panel" in name:
+            assert p["path"] == MID and p["stream"] and (p["S"] > 1) == with_ws, name
         elif name == "five fragments a workgroup":
             assert p["path"] == WIDE, name
         elif name == "narrow tiles":
