@@ -1,5 +1,6 @@
 // Sparse GEMMs of one tile of tokens as a stream of weights, bound by HBM: up to 32 tokens with a workgroup for each panel (NF = 4
-// fragments of 32 channels) and k range, and up to 128 tokens on layers of more panels than compute units (NF = 5, 6 or 8).
+// fragments of 32 channels) and k range, and up to 64 tokens, unlifted rows of 97 to 128, on layers of
+// more panels than compute units (NF = 5, 6 or 8).
 //
 // A wavefront owns one fragment and all tokens.  The loop is plain: wait for a unit, meet, request a later one, read the operands,
 // multiply; the order is left to the compiler.  A unit takes a compute unit 1500 cycles to stream and its operand reads and
@@ -168,14 +169,19 @@ static ss_status launch_wide_dt(const void* Xq, const float* s_x, const void* w_
                                 int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     const int nf = (O + PANEL - 1) / PANEL <= cu_count() ? 4 : wide_fragments(FUSED ? SS_KIND_FUSED : SS_KIND_LIFTED, M, O, cu_count());
-    const bool once = weights_stream(O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB);
+    const bool once = weights_stream(M, O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB);
 #define SS_W(NF, TB) return once ? launch_wide_one<DT, NF, TB, FUSED, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream) \
                                  : launch_wide_one<DT, NF, TB, FUSED, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream)
-#define SS_WN(NF) { if (M <= 32) SS_W(NF, 1); if (M <= 64) SS_W(NF, 2); SS_W(NF, 4); }
+#define SS_WN(NF) { if (M <= 32) SS_W(NF, 1); if (M <= 64) SS_W(NF, 2); }
     if (nf == 4) SS_W(4, 1);
     if (nf == 5) SS_WN(5)
     if (nf == 6) SS_WN(6)
-    SS_WN(8)
+    if (nf == 8) SS_WN(8)
+    if constexpr (FUSED) {
+        if (nf == 5) SS_W(5, 4);
+        if (nf == 6) SS_W(6, 4);
+    }
+    return SS_ERR_SHAPE;                                                 // not a call that plan_gemm sends here
 #undef SS_WN
 #undef SS_W
 }

@@ -178,14 +178,17 @@ ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, co
                             void* Y, int64_t ldy, hipStream_t stream);
 
 // Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are more than a
-// third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise;
-// calls of M = 1 .. 64 with weights from HBM, 96 to 254 MB, 0.88 .. 0.98 of the time.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose where
-// the cache holds them (1.0 .. 1.27); tiles of 128 tokens 0.98 .. 1.02.
-inline bool weights_stream(int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= CACHED_BYTES; }
+// third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise.
+// Time over that of ordinary loads, packed weights of 80 to 256 MB, from HBM / hot in that cache (which a model of many layers never has them): up to
+// 32 tokens 0.84 .. 0.97 / 0.90 .. 1.23, the most at 32 tokens; 33 to 64 tokens, tiles of 64, 8-bit types 0.92 .. 0.96 / 1.02 .. 1.26, 16-bit 0.95 .. 1.00 / 1.07 .. 1.46; 33 to 64
+// tokens on 257 to 512 panels 0.83 .. 1.00 / 0.94 .. 1.25; 65 to 128 tokens there 0.83 .. 1.03 (mean 0.96) / 1.01 .. 1.33 (1.10), which is no gain to pay
+// that for: beyond 64 tokens only weights that the cache does not hold at all are loaded so (0.91 .. 0.95 either way).  Smaller layers gain
+// less from HBM (0.95 .. 1.04) and lose hot (1.0 .. 1.27); the 128 x 128 tiles 0.98 .. 1.02.
+inline bool weights_stream(int64_t M, int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= (M <= 64 ? CACHED_BYTES : CACHE_BYTES); }
 
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 
-// Few tokens as a stream of weights (gemm_wide.hip): up to 32 tokens on as many panels as compute units or fewer, up to 128 on more, up to two for each.
+// Few tokens as a stream of weights (gemm_wide.hip): up to 32 tokens on as many panels as compute units or fewer, up to 64 on up to twice, unlifted rows of 97 to 128 on up to one and a half times as many.
 // X: lifted rows, or unlifted ones and weights of slide_decompose_fused; U units of 128 bytes per row, ldxb bytes between rows.
 // S > 1 (NF = 4): partial sums as of the 32-token tiles of gemm_mid.hip go through `ws`.
 ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
@@ -194,7 +197,7 @@ ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const 
 inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
 {
     const int64_t frags = (O + 127) / 128 * 4, f = (frags + cus - 1) / cus;
-    if (M > (kind == SS_KIND_FUSED ? 128 : 64) || f > 8) return 0;
+    if (M > 64 ? kind != SS_KIND_FUSED || M <= 96 || M > 128 || f > 6 : f > 8) return 0;
     if (f <= 4) return M <= 32 && f >= 3 ? 4 : 0;
     return f == 7 ? 8 : (int)f;
 }
@@ -202,7 +205,7 @@ inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
 // Up to 32 tokens of lifted rows on half to two thirds as many panels as compute units: tiles of 32 tokens in two groups of wavefronts (gemm_mid.hip),
 // not the weight stream.  A unit of lifted rows is two steps, and a wavefront for each SIMD waits for its operand reads longer than it
 // multiplies; with half of the compute units idle the loads do not cover that.  Time over the stream, M = 1 .. 32, 12 to 100 units, weights
-// from HBM / hot: 129 panels 0.88 .. 1.04 / 0.82 .. 1.02 (mean 0.99 / 0.90; fp8 3584 -> 16512 at M = 16 14.9 against 15.0 us, hot 11.4 against 13.9), 148 panels 0.88 .. 1.05 /
+// from HBM / hot: 129 panels 0.88 .. 1.04 / 0.82 .. 1.02 (mean 0.99 / 0.90; fp8 3584 -> 16512 at M = 16 15.2 against 15.1 us, hot 11.3 against 13.8), 148 panels 0.88 .. 1.05 /
 // 0.83 .. 1.03 (1.00 / 0.93), 170 panels 0.96 .. 1.06 / 0.88 .. 1.01 (1.01 / 0.95), 191 panels 0.97 .. 1.09 / 0.88 .. 1.08 (1.02 / 1.00), 256 panels 0.95 .. 1.05 /
 // 0.95 .. 1.15 (1.00 / 1.01); ten units and fewer lose.  Unlifted rows gain from HBM by the stream (129 panels, M = 16 and 32: 0.98, hot 1.07).  M < 16 over the
 // few-token kernels, 16 to 64 units: 0.70 .. 1.00 / 0.77 .. 1.08.
@@ -249,9 +252,12 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
 //             against 12.8); lifted rows by two_groups.  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
-// M <= 64, fused 128, and 257 .. 512 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each compute unit.  Time over
-//             that of a panel for each workgroup, weights from HBM, 96 calls, INT8, bf16 and fp8 lifted: 16 units and more 0.62 .. 0.95 (3584 -> 37888 at
-//             M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9), 4 to 12 units 0.91 .. 1.07.  Lifted rows of 65 .. 128 tokens keep the 128 x 128 tiles.
+// M <= 64 and 257 .. 512 panels, fused 97 .. 128 tokens and 257 .. 384 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each
+//             compute unit.  Time over that of a panel for each workgroup, 16 units and more, weights from HBM / hot: M <= 64, INT8, bf16 and fp8 lifted, 120 calls
+//             0.64 .. 0.98 / 0.72 .. 1.11 (3584 -> 37888 at M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9).  Fused, 257 .. 384 panels, two cards, means by tokens: 65 0.94 and
+//             0.97 / 1.15 and 1.18, 80 0.91 and 0.94 / 1.13 and 1.16, 96 0.89 and 0.91 / 1.11 and 1.14, 97 0.88 and 0.90 / 1.10 and 1.14, 112 0.87 and 0.89 / 1.09 and 1.10, 128 0.84 and 0.86 / 1.05
+//             and 1.06 (3584 -> 37888 at M = 128 INT8 44.4 -> 36.0, hot 28.8 -> 30.5): where three blocks of 32 tokens will do, the loss hot is the larger one.
+//             385 .. 512 panels at 65 .. 128 tokens 0.95 .. 1.11 / 0.75 .. 1.05.  Those, lifted rows of more than 64 tokens, and 4 to 12 units (0.91 .. 1.07) keep the tiles.
 // Fused, more 128 x 128 tiles than compute units and at most one tile of 128 channels x 256 tokens for each: those
 //             (gemm_fused_narrow.hip).  Time over that of the paths above, INT8 and bf16, 4 to 64 units, M = 200 .. 4096,
 //             267 shapes: 0.69 .. 0.99 with weights from HBM (mean 0.79), 0.71 .. 1.01 hot.  At the fewest, a middle and the most panels for M = 129 .. 8192, 4

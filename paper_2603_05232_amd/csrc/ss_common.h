@@ -55,6 +55,8 @@ __device__ inline int xcd_run(int id, int total)
 
 // What a program passes over in turn and comes to more than this is hardly found in the memory-side cache again: a third of its 256 MB.
 constexpr int64_t CACHED_BYTES = 80ll << 20;
+// What that cache does not hold at all.
+constexpr int64_t CACHE_BYTES = 256ll << 20;
 // non-temporal load and store, for data that is read once or written and not read soon
 __device__ inline uint4 load_once(const uint4* p)
 {

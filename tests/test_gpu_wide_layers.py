@@ -11,20 +11,22 @@ pytestmark = pytest.mark.gpu
 
 # tokens, channels, units per row, fused
 SHAPES = [(1, 257 * 128 - 5, 16, True), (9, 320 * 128, 17, False), (32, 321 * 128 - 3, 18, True), (33, 384 * 128, 16, False), (63, 385 * 128 - 1, 19, True),
-          (64, 512 * 128, 17, True), (48, 300 * 128 - 100, 20, False), (65, 300 * 128 - 9, 16, True), (127, 330 * 128, 18, True), (128, 512 * 128, 16, True)]
+          (64, 512 * 128, 17, True), (48, 300 * 128 - 100, 20, False), (97, 300 * 128 - 9, 16, True), (127, 330 * 128, 18, True), (128, 384 * 128, 16, True)]
+# beside them: 65 to 96 tokens, more panels, and lifted rows, on tiles of 128 x 128 or 256 x 256
+BESIDE = [(65, 300 * 128 - 9, 16, True), (96, 384 * 128, 17, True), (97, 385 * 128 - 1, 17, True), (128, 512 * 128, 16, True), (100, 300 * 128, 16, False)]
 
 
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
-@pytest.mark.parametrize("M,O,units,fused", SHAPES)
+@pytest.mark.parametrize("M,O,units,fused", SHAPES + BESIDE)
 def test_fragments_and_token_tiles(dtype, M, O, units, fused):
     _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, False, M)
 
 
-# packed weights of 80 MB and more, which are loaded non-temporally
+# packed weights of 80 MB and more, which are loaded non-temporally for up to 64 tokens, and of 256 MB and more for up to 128
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
-@pytest.mark.parametrize("M", [3, 50, 100])
-def test_weights_larger_than_the_cache_keeps(dtype, M):
-    _linear(M, 257 * 128 - 5, _rows(22, 4, dtype, True), 4, dtype, True, False, M)
+@pytest.mark.parametrize("M,units", [(3, 22), (50, 22), (100, 22), (100, 70)])
+def test_weights_larger_than_the_cache_keeps(dtype, M, units):
+    _linear(M, 257 * 128 - 5, _rows(units, 4, dtype, True), 4, dtype, True, False, M)
 
 
 @pytest.mark.parametrize("dtype", ["i8", "fp16"])

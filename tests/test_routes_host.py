@@ -104,6 +104,8 @@ def test_wide_layers(plan):
     for M, O, units, fused in test_gpu_wide_layers.SHAPES:
         assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
         assert plan(FUSED if fused else LIFTED, M, O, 15)["path"] != WIDE
+    for M, O, units, fused in test_gpu_wide_layers.BESIDE:
+        assert plan(FUSED if fused else LIFTED, M, O, units)["path"] in (MID, TILE), (M, O, units, fused)
     for kind in (FUSED, LIFTED):
         assert plan(kind, 32, 171 * 128, 16)["path"] == plan(kind, 1, 256 * 128, 16)["path"] == plan(FUSED, 32, 129 * 128, 16)["path"] == WIDE
         assert plan(kind, 33, 256 * 128, 16)["path"] == plan(kind, 5, 513 * 128, 16)["path"] == MID
