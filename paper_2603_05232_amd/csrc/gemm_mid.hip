@@ -560,7 +560,7 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     // the weight stream of gemm_wide.hip (both sides there), or two groups of wavefronts with a ring of four each (two_groups).
     const bool shared = ntiles * S > cu_count();
 #define SS_MID(TM, ...) launch_sparse_mid_ring<DT, TM, __VA_ARGS__>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, tiles_t, ntiles, stream)
-    const bool once = weights_stream(M, O, (int64_t)U * MidUnit<32, FUSED>::NS * FRAG_KB);
+    const bool once = weights_stream(O, (int64_t)U * MidUnit<32, FUSED>::NS * FRAG_KB, M <= 32 || (Mma<DT>::ES == 1 && !shared) ? CACHED_BYTES : CACHE_BYTES);
     if (M <= 32) {
         if constexpr (!FUSED)
             if (two_groups(M, O, U, cu_count())) return once ? SS_MID(32, 4, FUSED, true, true, 2) : SS_MID(32, 4, FUSED, true, false, 2);

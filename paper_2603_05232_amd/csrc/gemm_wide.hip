@@ -169,7 +169,7 @@ static ss_status launch_wide_dt(const void* Xq, const float* s_x, const void* w_
                                 int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     const int nf = (O + PANEL - 1) / PANEL <= cu_count() ? 4 : wide_fragments(FUSED ? SS_KIND_FUSED : SS_KIND_LIFTED, M, O, cu_count());
-    const bool once = weights_stream(M, O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB);
+    const bool once = weights_stream(O, (int64_t)U * (FUSED ? 3 : 2) * FRAG_KB, M <= 64 ? CACHED_BYTES : CACHE_BYTES);
 #define SS_W(NF, TB) return once ? launch_wide_one<DT, NF, TB, FUSED, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream) \
                                  : launch_wide_one<DT, NF, TB, FUSED, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, ws, S, stream)
 #define SS_WN(NF) { if (M <= 32) SS_W(NF, 1); if (M <= 64) SS_W(NF, 2); }

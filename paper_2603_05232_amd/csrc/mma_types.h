@@ -177,14 +177,18 @@ ss_status launch_sparse_tile(const void* XL, const float* s_x, const void* w_val
 ss_status launch_dense_tile(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, ss_dtype dtype,
                             void* Y, int64_t ldy, hipStream_t stream);
 
-// Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are more than a
-// third of the memory-side cache, which then keeps the smaller layers and the activations.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise.
-// Time over that of ordinary loads, packed weights of 80 to 256 MB, from HBM / hot in that cache (which a model of many layers never has them): up to
-// 32 tokens 0.84 .. 0.97 / 0.90 .. 1.23, the most at 32 tokens; 33 to 64 tokens, tiles of 64, 8-bit types 0.92 .. 0.96 / 1.02 .. 1.26, 16-bit 0.95 .. 1.00 / 1.07 .. 1.46; 33 to 64
-// tokens on 257 to 512 panels 0.83 .. 1.00 / 0.94 .. 1.25; 65 to 128 tokens there 0.83 .. 1.03 (mean 0.96) / 1.01 .. 1.33 (1.10), which is no gain to pay
-// that for: beyond 64 tokens only weights that the cache does not hold at all are loaded so (0.91 .. 0.95 either way).  Smaller layers gain
-// less from HBM (0.95 .. 1.04) and lose hot (1.0 .. 1.27); the 128 x 128 tiles 0.98 .. 1.02.
-inline bool weights_stream(int64_t M, int64_t O, int64_t lifted) { return O * (lifted / 8 * 5) >= (M <= 64 ? CACHED_BYTES : CACHE_BYTES); }
+// Kernels that read every weight once load them non-temporally where the packed weights (rows of `lifted` bytes) are `limit` and more: a
+// third of the memory-side cache, which then keeps the smaller layers and the activations, or all of it.  128 MB streamed into LDS: 20.3 us non-temporal, 23.2 otherwise.
+// Time over that of ordinary loads, packed weights of 80 to 256 MB, from HBM / hot in that cache (where a model of many layers never finds them):
+//   up to 32 tokens                                                   0.84 .. 0.98 (mean 0.89) / 0.86 .. 1.23 (1.04; the most at 32 tokens)
+//   33 to 64 tokens, 257 to 512 panels (gemm_wide.hip)                0.86 .. 0.98 (0.90) / 0.94 .. 1.23 (1.05)
+//   33 to 64 tokens, tiles of 64, a compute unit each, 8-bit types    0.91 .. 0.96 (0.94) / 1.01 .. 1.26 (1.13)
+//   the same, 16-bit types                                            0.95 .. 1.00 (0.98) / 1.06 .. 1.46 (1.17)
+//   the same on shared compute units (more than 512 panels)           0.92 .. 1.06 (0.97) / 1.11 .. 1.35 (1.19)
+//   97 to 128 tokens, 257 to 384 panels (gemm_wide.hip)               0.83 .. 1.03 (0.96) / 1.01 .. 1.33 (1.10)
+// The limit is a third of the cache in the first three, all of it in the others, whose gain is not worth that loss.  Weights of 256 MB and more: 0.81 .. 0.98
+// / 0.80 .. 1.08 in all of them.  Smaller layers gain less from HBM (0.95 .. 1.04) and lose hot (1.0 .. 1.27); the 128 x 128 tiles 0.98 .. 1.02.
+inline bool weights_stream(int64_t O, int64_t lifted, int64_t limit) { return O * (lifted / 8 * 5) >= limit; }
 
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 

@@ -153,7 +153,8 @@ def test_stream_of_a_panel(dtype, fused, M, O, units, with_ws):
     _linear(M, O, max(K, 2 * N), N, dtype, fused, with_ws, units)
 
 
-# packed weights of 80 MB and more, which are loaded non-temporally: unsplit panels and split rows, tiles of 32 and 64 tokens
+# packed weights of 80 MB and more, which are loaded non-temporally: unsplit panels and split rows, the weight stream (3 tokens) and tiles of 64 tokens
+# (8-bit types; 16-bit ones from 256 MB on)
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("M", [3, 50])
 @pytest.mark.parametrize("O,units", [(192 * 128 + 4, 29), (24 * 128, 230)])
@@ -170,3 +171,14 @@ RANGES = [(M, 300, 8 * S, S) for M in (5, 40) for S in (8, 9, 10, 11, 12, 13, 16
 @pytest.mark.parametrize("M,O,units,S", RANGES)
 def test_numbers_of_ranges(dtype, fused, M, O, units, S):
     _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, True, S)
+
+
+# the same, each with its limit in MB: tiles of 32 tokens on shared compute units, tiles of 64 on shared ones, and with one each in 8-bit and in 16-bit types
+LARGE = [(3, 513 * 128, 16, True, 80), (30, 513 * 128 - 5, 17, False, 80), (50, 513 * 128, 35, True, 256), (40, 520 * 128 - 3, 52, False, 256),
+         (50, 200 * 128, 28, True, 80), (33, 224 * 128 - 4, 48, False, 80), (64, 250 * 128, 72, True, 256), (60, 256 * 128, 104, False, 256)]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("M,O,units,fused,limit", LARGE)
+def test_large_weights(dtype, M, O, units, fused, limit):
+    _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, False, M)

@@ -93,6 +93,16 @@ def test_up_to_32_tokens(plan):
             assert p["stream"] and (p["S"] > 1) == with_ws, (kind, M, O, units)
 
 
+def test_large_weights(plan):
+    for M, O, units, fused, limit in test_gpu_mid_tiles.LARGE:
+        p = plan(FUSED if fused else LIFTED, M, O, units)
+        assert (p["path"], p["S"]) == (MID, 1) and not p["stream"] and not p["groups"], (M, O, units, fused)
+        assert limit << 20 <= O * units * (120 if fused else 80) < 2 * limit << 20
+        assert (-(-O // 128) > 256) == (O > 512 * 128)                   # shared compute units
+    M, O, units = test_gpu_mid_tiles.TWO_GROUPS[-1]
+    assert O * units * 80 >= 80 << 20
+
+
 def test_numbers_of_ranges(plan):
     for M, O, units, S in test_gpu_mid_tiles.RANGES:
         for kind in (FUSED, LIFTED):
