@@ -79,13 +79,14 @@ __device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* __restri
 }
 
 // Sum of the S partial accumulators of every tile in range order (bit-reproducible also for fp32) and the
-// scale epilogue.  One workgroup per (tile, wavefront of the GEMM kernel); thread (f, tb, register quad, lane) owns four
-// consecutive channels of one token.  The kernel is a memory round trip between two launches, so much is asked for at once: the
-// scales, and eight ranges at a time, the last one to four of them four or two (loads beyond the last range repeat it and are not added).
+// scale epilogue.  A workgroup has one (PER = 1) or all (PER = ACC) of the ACC blocks of 32 channels x 32 tokens of a wavefront of the GEMM kernel in a
+// token tile of a panel (gridDim.y); thread (block, register quad, lane) owns four consecutive channels of one token.  The kernel is a memory round trip
+// between two launches, so much is asked for at once: all arguments (not some behind the first branch: 2 % of a call), the scales, and eight ranges at a
+// time, a rest of five to seven eight, of three or four four, of one or two two (loads beyond the last range repeat it and are not added).
 // Against addresses by products of 64 bits, and eight loads for any rest: calls of 1 to 8 panels, M = 1 .. 32, 10, 18 and 25 ranges
 // 0.89 .. 0.99 of the time (mean 0.94; 512 channels x 18944 bytes, bf16, M = 1: 10.2 -> 9.5 us), 8 to 14 ranges 0.93 .. 1.01 (0.97).
-template <int DT, int TM>
-__global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const v4i* __restrict__ ws, int S, int64_t ntiles, const float* __restrict__ s_x,
+template <int DT, int TM, int PER>
+__global__ __launch_bounds__((256 * PER)) void k_mid_reduce(const v4i* __restrict__ ws, int S, int64_t ntiles, const float* __restrict__ s_x,
                                                                const float* __restrict__ s_w, int64_t M, int64_t O, uint16_t* __restrict__ Y,
                                                                int64_t ldy, int tiles_t)
 {
@@ -95,11 +96,12 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
     typedef typename MM::acc_t acc_t;
     typedef decltype(acc_t{}[0] + acc_t{}[0]) elem_t;
     typedef elem_t quad_t __attribute__((ext_vector_type(4)));
-    const int tile = blockIdx.x / MD_WAVES;
-    const int wave = blockIdx.x % MD_WAVES, wo = MS::wo(wave), wt = MS::wt(wave);
-    const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3, ft = threadIdx.x >> 8, f = ft / TB, tb = ft % TB;
-    const int panel = tile / tiles_t;
-    const int64_t tok = (int64_t)(tile - panel * tiles_t) * TM + wt * (32 * TB) + tb * 32 + (lane & 31);
+    asm volatile("" ::"s"(ws), "s"(S), "s"(ntiles), "s"(s_x), "s"(s_w), "s"(M), "s"(O), "s"(Y), "s"(ldy), "s"(tiles_t));
+    const int panel = blockIdx.y, tw = blockIdx.x / (ACC / PER), tt = tw / MD_WAVES, tile = panel * tiles_t + tt;
+    const int ft = blockIdx.x % (ACC / PER) + (PER > 1 ? threadIdx.x >> 8 : 0), f = ft / TB, tb = ft % TB;
+    const int wave = tw % MD_WAVES, wo = MS::wo(wave), wt = MS::wt(wave);
+    const int lane = threadIdx.x & 63, r4 = (threadIdx.x >> 6) & 3;
+    const int64_t tok = (int64_t)tt * TM + wt * (32 * TB) + tb * 32 + (lane & 31);
     const int64_t o = (int64_t)panel * PANEL + 16 * MS::FW * wo + 64 * (lane >> 5) + 16 * f + 4 * r4;
     if (tok >= M || o >= O) return;
     float sx = 1.0f, sw[4];
@@ -112,21 +114,23 @@ __global__ __launch_bounds__((256 * MidShape<TM>::ACC)) void k_mid_reduce(const 
     const v4i* src = ws + (((int64_t)tile * MD_WAVES + wave) * (4 * ACC) + ft * 4 + r4) * 64 + lane;
     const int64_t range_stride = ntiles * MD_WAVES * (4 * ACC) * 64;             // 16-byte groups between consecutive k ranges
     int s = 0;
-    auto batch = [&](auto b_c) __attribute__((always_inline)) {
+    auto batch = [&](auto b_c, auto full_c) __attribute__((always_inline)) {
         constexpr int B = decltype(b_c)::value;
+        constexpr bool FULL = decltype(full_c)::value;
         quad_t q[B];
 #pragma unroll
         for (int d = 0; d < B; ++d) {
             q[d] = __builtin_bit_cast(quad_t, *src);
-            src += s + d + 1 < S ? range_stride : 0;                            
+            src += FULL || s + d + 1 < S ? range_stride : 0;
         }
 #pragma unroll
-        for (int d = 0; d < B; ++d) a = s + d < S ? a + q[d] : a;
+        for (int d = 0; d < B; ++d) a = FULL || s + d < S ? a + q[d] : a;
         s += B;
     };
-    while (S - s > 4) batch(std::integral_constant<int, 8>{});
-    if (S - s > 2) batch(std::integral_constant<int, 4>{});
-    else if (S - s > 0) batch(std::integral_constant<int, 2>{});
+    while (S - s >= 8) batch(std::integral_constant<int, 8>{}, std::true_type{});
+    if (S - s > 4) batch(std::integral_constant<int, 8>{}, std::false_type{});
+    else if (S - s > 2) batch(std::integral_constant<int, 4>{}, std::false_type{});
+    else if (S - s > 0) batch(std::integral_constant<int, 2>{}, std::false_type{});
     store_quad4<MM::SCALED>(a, sx, sw, Y, ldy, O, o, tok);
 }
 
@@ -525,8 +529,15 @@ template <int DT, int TM>
 static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const float* s_x, const float* s_w, int64_t M, int64_t O, void* Y,
                                    int64_t ldy, int tiles_t, hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_mid_reduce<DT, TM>), dim3((unsigned)(ntiles * MD_WAVES)), dim3(256 * MidShape<TM>::ACC), 0, stream, static_cast<const v4i*>(ws), S, ntiles,
-                       s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy, tiles_t);
+    // Workgroups of all blocks of a wavefront where half of the compute units get one, of one block otherwise: S ranges of few tiles are a matter of latency.
+    // Time of a whole call (sparse and dense) with one block over all of them, M = 40 .. 400, weights from HBM: 4 tiles 0.83 .. 0.95, 16 tiles 0.93 .. 0.99, 28 and 32 tiles 0.94 ..
+    // 1.00; 48 and 56 tiles 1.00 .. 1.05.
+    constexpr int ACC = MidShape<TM>::ACC;
+#define SS_RD(PER) hipLaunchKernelGGL((k_mid_reduce<DT, TM, PER>), dim3((unsigned)(tiles_t * MD_WAVES * (ACC / PER)), (unsigned)(ntiles / tiles_t)), dim3(256 * PER), 0, stream, \
+                       static_cast<const v4i*>(ws), S, ntiles, s_x, s_w, M, O, static_cast<uint16_t*>(Y), ldy, tiles_t)
+    if (2 * ntiles * MD_WAVES > cu_count()) SS_RD(ACC);
+    else SS_RD(1);
+#undef SS_RD
     return launch_status();
 }
 
