@@ -498,7 +498,7 @@ static ss_status launch_sparse_dt(const void* XL, const float* s_x, const void* 
                                   int U, int64_t ldxb, void* Y, int64_t ldy, hipStream_t st)
 {
     // Two fragments per workgroup where that leaves every compute unit one.  (Layers of more panels, and more tokens on as
-    // many, run on the tiles of gemm_mid.hip.)
+    // many, run on gemm_wide.hip and the tiles of gemm_mid.hip.)
     const bool two = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL >= 2 * cu_count();
 #define SS_GO(TB, FPW) return launch_sparse_one<DT, TB, FPW, FUSED>(XL, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, st)
     if (M > 32) SS_GO(2, 1);

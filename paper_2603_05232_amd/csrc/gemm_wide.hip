@@ -4,9 +4,11 @@
 //
 // A wavefront owns one fragment and all tokens.  The loop is plain: wait for a unit, meet, request a later one, read the operands,
 // multiply; the order is left to the compiler.  A unit takes a compute unit 1500 cycles to stream and its operand reads and
-// matrix instructions a third of that, so a software pipeline or a second group of wavefronts with half of the k range (both in the
-// kernel for 32 tokens before) only costs: NF = 4 against it, M = 1 .. 32, weights from HBM / hot, 63 calls of rows of 16 units and more in
-// fused INT8, bf16 and lifted fp8, bf16: 0.88 .. 1.03 (mean 0.96) / 0.88 .. 1.02; 24 calls of 1 to 15 units 0.88 .. 0.98 / 0.81 .. 1.10 (18944 -> 3584 bf16 at M = 1 26.7 -> 23.4 us).
+// matrix instructions a third of that, so a software pipeline in two groups of wavefronts, each with half of the k range (KG = 2 in gemm_mid.hip),
+// does not pay but for the lifted rows it has kept.  NF = 4 over it with the same kind of loads, INT8 and bf16 fused, fp8 and bf16 lifted, M = 1 .. 32, weights from HBM / hot:
+// rows of 64 to 200 units in ranges, 300 calls 0.91 .. 1.02 (mean 0.96) / 0.91 .. 1.12 (0.97), 129 to 256 panels in 12 to 100 units, fused, 168 calls 0.91 .. 1.02
+// (0.96) / 0.87 .. 1.15 (0.97), and in 1 to 15 units, 216 calls 0.86 .. 1.02 (0.95) / 0.81 .. 1.10 (0.95).  There is no line by the length of a row: two to ten units gain
+// most, and the calls that lose 5 % hot and more, 12 to 16 units whose weights the L2 holds (129 panels, lifted rows 192) and single longer ones, gain 1 to 5 % from HBM.
 //
 // More panels than compute units: a workgroup per panel gives some compute units two streams where the others have one, and a
 // compute unit has about a hundred cache lines in flight whatever its workgroups ask for, so the launch waits for those with two:
