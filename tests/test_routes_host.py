@@ -82,6 +82,14 @@ def test_shared_compute_units(plan):
         assert plan(FUSED, M, O, units)["path"] == NARROW
 
 
+def test_lines_of_the_kernel_choice(plan):
+    """Each line of the 65-token rows of test_gpu_mid_tiles.test_lines_of_the_kernel_choice has a row on either side."""
+    for kind, line, many in ((FUSED, 12, 24), (LIFTED, 24, 48)):
+        for panels, units in ((321, line), (449, many)):
+            assert plan(kind, 65, 128 * panels, units - 1)["path"] == TILE and plan(kind, 65, 128 * panels, units)["path"] == MID
+        assert plan(kind, 65, 128 * 320, 3)["path"] == MID and plan(kind, 65, 128 * 513, 48)["path"] == TILE
+
+
 def test_up_to_32_tokens(plan):
     for M, O, units in test_gpu_mid_tiles.TWO_GROUPS:
         assert plan(LIFTED, M, O, units)["groups"], (M, O, units)
