@@ -173,6 +173,18 @@ def test_numbers_of_ranges(dtype, fused, M, O, units, S):
     _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, True, S)
 
 
+# split rows on 32 tiles (a workgroup of the reduce kernel for each block of 32 channels x 32 tokens) and on more (one for all blocks of a wavefront), of 64 and 128
+# tokens, with tokens and channels missing in the last tile
+BLOCKS = [(64, 32 * 128, 64), (50, 33 * 128 - 5, 64), (128, 32 * 128 - 3, 48), (70, 33 * 128, 48), (200, 16 * 128, 48), (200, 17 * 128 - 4, 48)]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("M,O,units", BLOCKS)
+def test_blocks_of_the_reduce_kernel(dtype, fused, M, O, units):
+    _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, True, M)
+
+
 # the same, each with its limit in MB: tiles of 32 tokens on shared compute units, tiles of 64 on shared ones, and with one each in 8-bit and in 16-bit types
 LARGE = [(3, 513 * 128, 16, True, 80), (30, 513 * 128 - 5, 17, False, 80), (50, 513 * 128, 35, True, 256), (40, 520 * 128 - 3, 52, False, 256),
          (50, 200 * 128, 28, True, 80), (33, 224 * 128 - 4, 48, False, 80), (64, 250 * 128, 72, True, 256), (60, 256 * 128, 104, False, 256)]

@@ -118,6 +118,13 @@ def test_numbers_of_ranges(plan):
             assert (p["path"], p["S"]) == (MID, S), (M, O, units, p)
 
 
+def test_blocks_of_the_reduce_kernel(plan):
+    for i, (M, O, units) in enumerate(test_gpu_mid_tiles.BLOCKS):
+        for kind in (FUSED, LIFTED):
+            p = plan(kind, M, O, units, 1 << 30)
+            assert p["path"] == MID and p["S"] > 1 and (-(-M // 128) * -(-O // 128) > 32) == i % 2, (M, O, units, p)
+
+
 def test_wide_layers(plan):
     for M, O, units, fused in test_gpu_wide_layers.SHAPES:
         assert plan(FUSED if fused else LIFTED, M, O, units)["path"] == WIDE, (M, O, units, fused)
