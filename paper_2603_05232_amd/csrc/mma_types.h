@@ -206,6 +206,24 @@ inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
     return f == 7 ? 8 : (int)f;
 }
 
+// Up to 16 tokens with a workgroup for every 16 channels (gemm_slim.hip), unsplit; operands as above.
+ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
+// Every one of its workgroups reads all token rows, so the lines go by units and tokens.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before,
+// all types, weights from HBM / hot, M = 1 .. 16:
+//   at most one workgroup per compute unit, not split: 1 to 56 units 0.57 .. 0.83 / 0.55 .. 0.82, without a workspace 72 to 256 units 0.48 .. 0.77 / 0.44 .. 0.88
+//   the same, split, 8 panels and more, by units (M + 8): up to 1000 0.82 .. 1.01 / 0.59 .. 0.89, 1000 .. 1400 0.93 .. 1.33 / 0.66 .. 1.03, more 1.1 .. 2.0.  Fewer
+//     panels would leave most compute units idle, which their ranges do not
+//   some compute units with two of them, by units (M + 2): up to 120 0.76 .. 0.99 / 0.76 .. 1.00 (3584 -> 4608 INT8 at M = 1 7.2 -> 6.9 us, hot 5.7 -> 4.4), 120 ..
+//     170 0.88 .. 1.10 / 0.79 .. 0.98
+inline bool slim_pays(int64_t M, int64_t O, int64_t units, int64_t cus, bool split)
+{
+    const int64_t panels = (O + 127) / 128, wgs = 8 * panels;
+    if (M > 16 || wgs > 2 * cus) return false;
+    if (wgs > cus) return units * (M + 2) <= 120;
+    return !split || (panels >= 8 && units * (M + 8) <= 1000);
+}
+
 // Up to 32 tokens of lifted rows on half to two thirds as many panels as compute units: tiles of 32 tokens in two groups of wavefronts (gemm_mid.hip),
 // not the weight stream.  A unit of lifted rows is two steps, and a wavefront for each SIMD waits for its operand reads longer than it
 // multiplies; with half of the compute units idle the loads do not cover that.  Time over the stream, M = 1 .. 32, 12 to 100 units, weights
@@ -255,7 +273,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
-//             against 12.8); lifted rows by two_groups.  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4).
+//             against 12.8); lifted rows by two_groups.  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4), up to 16 tokens
+//             mostly those of 16 channels a workgroup (slim_pays).
 // M <= 64 and 257 .. 512 panels, fused 97 .. 128 tokens and 257 .. 384 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each
 //             compute unit.  Time over that of a panel for each workgroup, 16 units and more, weights from HBM / hot: M <= 64, INT8, bf16 and fp8 lifted, 120 calls
 //             0.64 .. 0.98 / 0.72 .. 1.11 (3584 -> 37888 at M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9).  Fused, 257 .. 384 panels, two cards, means by tokens: 65 0.94 and
@@ -272,7 +291,7 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
-enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE };
+enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE, SS_PATH_SLIM };
 struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
@@ -311,6 +330,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
     const int S = mid_splits(kind, M, O, units, ws_bytes);
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
     const bool mid = wide || (S > 1 && (M > 32 || 2 * units + M >= 128));
+    if (!wide && slim_pays(M, O, units, cus, mid)) return {SS_PATH_SLIM, 1};
     return mid ? ss_plan{SS_PATH_MID, S} : ss_plan{SS_PATH_SKINNY, 1};
 }
 

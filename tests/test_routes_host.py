@@ -11,6 +11,7 @@ import test_gpu_lifted_tiles
 import test_gpu_mid_tiles
 import test_gpu_narrow_tiles
 import test_gpu_replay
+import test_gpu_slim
 import test_gpu_wide_layers
 from paper_2603_05232_amd import binding, build
 
@@ -31,7 +32,7 @@ int main()
     }
 }
 """
-MID, NARROW, TILE, WIDE = 1, 2, 3, 4
+MID, NARROW, TILE, WIDE, SLIM = 1, 2, 3, 4, 5
 LIFTED, FUSED = 0, 1
 
 
@@ -154,3 +155,11 @@ def test_replayed_routes(plan):
             assert units % 2 == ("odd" in name), name
         if "short" in name:
             assert units < 4, name
+
+
+def test_sixteen_channels(plan):
+    for kind in (FUSED, LIFTED):
+        for M, O, units, with_ws in test_gpu_slim.SHAPES:
+            assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] == SLIM, (kind, M, O, units)
+        for M, O, units, with_ws in test_gpu_slim.BESIDE:
+            assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] != SLIM, (kind, M, O, units)
