@@ -150,21 +150,27 @@ __global__ __launch_bounds__((256 * PER)) void k_mid_reduce(const v4i* __restric
 // 4.5 MB of tokens (12288 -> 1536 bf16 at M = 256, hot: 19.7 against 23.9).
 // Tiles of 64 and 32 tokens, where the weights are nearly all that is read, take the second throughout.  The dense kernel
 // takes the first: by the same lines 60 of 504 calls were more than 3 % slower than with the first, 21 so.
-__device__ inline bool mid_by_range(int tile_tokens, int64_t M, int tiles_t, int units)
+static bool mid_by_range(int tile_tokens, int64_t ntiles, int64_t M, int tiles_t, int64_t units)
 {
-    const int64_t work = (int64_t)gridDim.x * units;
+    const int64_t work = ntiles * units;
     return tile_tokens < MD_TILE || work < 7 * 256 || work > (tiles_t == 1 ? 10 : 19) * 256 || M * units > (36 << 10);
 }
-struct MidItem { int64_t panel; int tt, range; int64_t tile; };
-__device__ inline MidItem mid_item(int tiles_t, bool by_range, int widest = 8)
+// What the workgroups of a launch need to find their items, prepared on the host (Div): nt tiles, tiles_t of them along the tokens, in `bands` bands of `width` token
+// tiles (the last one of last_width), S ranges of k.
+struct MidOrder {
+    int nt, S, by_range, tiles_t, bands, width, last_width, per_band;
+    Div by_nt, by_band, by_width, by_last;
+    KRanges k;
+};
+struct MidItem { int panel, tt, range, tile; };
+__device__ inline MidItem mid_item(const MidOrder& g)
 {
-    const int nt = gridDim.x;
-    const int item = by_range ? xcd_run(blockIdx.y * nt + blockIdx.x, nt * gridDim.y) : blockIdx.y * nt + xcd_run(blockIdx.x, nt);
-    const int range = item / nt, k = item - range * nt;
-    const int bands = (tiles_t + widest - 1) / widest, width = (tiles_t + bands - 1) / bands;
-    const int per_band = width * (nt / tiles_t), band = k / per_band, within = k - band * per_band;
-    const int bw = min(width, tiles_t - band * width), panel = within / bw, tt = band * width + (within - panel * bw);
-    return {panel, tt, range, (int64_t)panel * tiles_t + tt};
+    const int item = g.by_range ? xcd_run(blockIdx.y * g.nt + blockIdx.x, g.nt * g.S) : blockIdx.y * g.nt + xcd_run(blockIdx.x, g.nt);
+    const int range = quot(item, g.by_nt), k = item - range * g.nt;
+    const int band = quot(k, g.by_band), within = k - band * g.per_band;
+    const bool last = band == g.bands - 1;
+    const int panel = quot(within, last ? g.by_last : g.by_width), tt = band * g.width + within - panel * (last ? g.last_width : g.width);
+    return {panel, tt, range, panel * g.tiles_t + tt};
 }
 
 template <typename ACC, int FW, int TB> __device__ inline void mid_zero(ACC (&acc)[FW][TB])
@@ -219,7 +225,7 @@ template <int DT, int TM, int RING, bool FUSED, bool PIPE, bool ONCE, int KG>
 __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
-                                                              uint16_t* __restrict__ Y, int64_t ldy, int tiles_t, void* __restrict__ ws)
+                                                              uint16_t* __restrict__ Y, int64_t ldy, MidOrder order, void* __restrict__ ws)
 {
     static_assert(RING >= 2 && RING <= 8, "meet() covers up to seven units behind");
     typedef Mma<DT> MM;
@@ -234,10 +240,11 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
     uint8_t* const smem = lds + kg * (RING * MU::BYTES);
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
     const int n = lane & 31, qb = lane >> 5;
-    const MidItem it = mid_item(tiles_t, mid_by_range(TM, M, tiles_t, U_all), PIPE ? 8 : 16);
+    asm volatile("" ::"s"(Xq), "s"(w_vals), "s"(w_meta), "s"(M), "s"(U_all), "s"(ldxb));      // with the order all arguments that the first loads wait for, in one go
+    const MidItem it = mid_item(order);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * TM;
-    // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
-    const int first = (int)((int64_t)it.range * U_all / gridDim.y), count = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - first;
+    // k range of this workgroup, not empty (S <= U_all)
+    const int first = range_first(order.k, it.range), count = range_units(order.k, it.range);
     // units [u0, u0 + U) of it are this group's; the host takes KG groups only for ranges of at least KG units
     const int u0 = first + kg * (count / KG), U = kg + 1 < KG ? count / KG : count - kg * (count / KG);
 
@@ -254,8 +261,8 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
     // XCD's workgroups share nothing but the token rows of a range, so do the workgroups of an XCD: in step they all ask
     // for the same rows' lines (14336 -> 4096 at M = 65 and 128, ten forms: 4 % less time; unsplit or with several token
     // tiles, where they share weights or more rows than the L2 holds, up to 60 % more; tiles of 64 and 32 tokens, level).
-    const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int rot = PIPE ? (TM == 128 && tiles_t == 1 && gridDim.y > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
+    const int wg = (int)(blockIdx.y * order.nt + blockIdx.x);
+    const int rot = PIPE ? (TM == 128 && order.tiles_t == 1 && order.S > 1 ? (wg + (wg >> 3)) & 7 : wg & 7) * U >> 3 : 0;
     auto direct_load = [&](int v, uint32_t slot, int d) __attribute__((always_inline)) {
         const uint32_t st = lds0 + slot;
         const int u = v + rot < U ? v + rot : v + rot - U;
@@ -416,7 +423,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
             unit(no, no, B, A, u + 1);
         } else unit(no, no, A, B, u);
     }
-    const int64_t o_wave = panel * PANEL + 16 * FW * wo, t_wave = t0 + wt * (32 * TB), item = (int64_t)it.range * gridDim.x + it.tile;
+    const int64_t o_wave = panel * PANEL + 16 * FW * wo, t_wave = t0 + wt * (32 * TB), item = (int64_t)it.range * order.nt + it.tile;
     if constexpr (KG == 2) {                                             // the second group hands its sums to the first in LDS
         static_assert(FW * TB == 1, "one accumulator block per wavefront");
         if (kg == 0 && count & 1) wg_barrier();                          // it has one unit, and one meeting, more
@@ -440,7 +447,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
             for (int e = 0; e < 4; ++e) v[4 * r4 + e] += q[e];
         }
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
+    if (order.S > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, o_wave, t_wave, lane);
 }
 
@@ -448,7 +455,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
 template <int DT, int RING>
 __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ Wq,
                                                           const float* __restrict__ s_w, int64_t M, int64_t O, int64_t Kb, uint16_t* __restrict__ Y,
-                                                          int64_t ldy, int tiles_t, void* __restrict__ ws)
+                                                          int64_t ldy, MidOrder order, void* __restrict__ ws)
 {
     typedef Mma<DT> MM;
     typedef typename MM::dfrag_t frag_t;
@@ -457,11 +464,10 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wo = wave & 1, wt = wave >> 1;
     const int row = lane & 31, q = lane >> 5;
-    const int U_all = (int)(Kb / ROWB);
-    const MidItem it = mid_item(tiles_t, false);
+    const MidItem it = mid_item(order);
     const int64_t panel = it.panel, t0 = (int64_t)it.tt * MD_TILE;
-    // k range of this workgroup: units [u0, u0 + U); gridDim.y ranges, all non-empty (gridDim.y <= U_all)
-    const int u0 = (int)((int64_t)it.range * U_all / gridDim.y), U = (int)((int64_t)(it.range + 1) * U_all / gridDim.y) - u0;
+    // k range of this workgroup: units [u0, u0 + U), not empty
+    const int u0 = range_first(order.k, it.range), U = range_units(order.k, it.range);
 
     MidRowLoader<MD_TILE> la, lb;
     la.init(Wq + (int64_t)u0 * ROWB, Kb, panel * PANEL, O, wave, lane);
@@ -517,13 +523,20 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
         slot = slot == RING - 1 ? 0 : slot + 1;
         lslot = lslot == RING - 1 ? 0 : lslot + 1;
     }
-    if (gridDim.y > 1) mid_store_partial(acc, ws, (int64_t)it.range * gridDim.x + it.tile, wave, lane, (int)(M - t0) - wt * 64);
+    if (order.S > 1) mid_store_partial(acc, ws, (int64_t)it.range * order.nt + it.tile, wave, lane, (int)(M - t0) - wt * 64);
     else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
 }
 
 }  // namespace ss
 
 using namespace ss;
+
+static MidOrder mid_order(int64_t ntiles, int tiles_t, int S, bool by_range, int64_t units, int widest = 8)
+{
+    const int bands = (tiles_t + widest - 1) / widest, width = (tiles_t + bands - 1) / bands, last = tiles_t - (bands - 1) * width;
+    const int per_band = (int)(width * (ntiles / tiles_t));
+    return {(int)ntiles, S, by_range, tiles_t, bands, width, last, per_band, make_div(ntiles), make_div(per_band), make_div(width), make_div(last), k_ranges(units, S)};
+}
 
 template <int DT, int TM>
 static ss_status launch_mid_reduce(const void* ws, int S, int64_t ntiles, const float* s_x, const float* s_w, int64_t M, int64_t O, void* Y,
@@ -551,7 +564,7 @@ static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const 
     if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>>(lds) != SS_OK) return SS_ERR_HIP;
     hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U,
-                       ldxb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
+                       ldxb, static_cast<uint16_t*>(Y), ldy, mid_order(ntiles, tiles_t, S, mid_by_range(TM, ntiles, M, tiles_t, U), U, PIPE ? 8 : 16), ws);
     if (launch_status() != SS_OK) return SS_ERR_HIP;
     return S > 1 ? launch_mid_reduce<DT, TM>(ws, S, ntiles, s_x, s_w, M, O, Y, ldy, tiles_t, stream) : SS_OK;
 }
@@ -595,7 +608,7 @@ static ss_status launch_dense_mid_ring(const void* Xq, const float* s_x, const v
     constexpr int lds = RING * MD_D_UNIT;
     if (allow_dynamic_lds<k_dense_mid<DT, RING>>(lds) != SS_OK) return SS_ERR_HIP;
     hipLaunchKernelGGL((k_dense_mid<DT, RING>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream, static_cast<const uint8_t*>(Xq),
-                       s_x, static_cast<const uint8_t*>(Wq), s_w, M, O, Kb, static_cast<uint16_t*>(Y), ldy, tiles_t, ws);
+                       s_x, static_cast<const uint8_t*>(Wq), s_w, M, O, Kb, static_cast<uint16_t*>(Y), ldy, mid_order(ntiles, tiles_t, S, false, Kb / ROWB), ws);
     return launch_status();
 }
 

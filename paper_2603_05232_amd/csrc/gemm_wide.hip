@@ -38,7 +38,8 @@ template <int NF, int TB, bool FUSED> struct WideUnit {
 template <int DT, int NF, int TB, bool FUSED, bool ONCE>
 __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
                                                          const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U_all,
-                                                         int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, void* __restrict__ ws)
+                                                         int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, void* __restrict__ ws, int cols, int S, Div by_cols,
+                                                         KRanges ranges)
 {
     typedef Mma<DT> MM;
     typedef WideUnit<NF, TB, FUSED> WU;
@@ -47,10 +48,11 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 31, qb = lane >> 5;
+    asm volatile("" ::"s"(Xq), "s"(w_vals), "s"(w_meta), "s"(M), "s"(O), "s"(U_all), "s"(ldxb), "s"(cols), "s"(S), "s"(by_cols.mul), "s"(ranges.q));      // in one go
     const int npanels = (int)((O + PANEL - 1) / PANEL), nfrags = npanels * FRAGS_PER_PANEL;
     // work item: fragments of a k range, one run over all (range, fragments) pairs for each XCD
-    const int item = xcd_run(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y), range = item / (int)gridDim.x, col = item - range * gridDim.x;
-    const int u_first = (int)((int64_t)range * U_all / gridDim.y), U = (int)((int64_t)(range + 1) * U_all / gridDim.y) - u_first;
+    const int wg = blockIdx.y * cols + blockIdx.x, item = xcd_run(wg, cols * S), range = quot(item, by_cols), col = item - range * cols;
+    const int u_first = range_first(ranges, range), U = range_units(ranges, range);
     const int f_first = col * NF, p_first = f_first / FRAGS_PER_PANEL;
     const int frag = min(f_first + wave, nfrags - 1), panel = frag / FRAGS_PER_PANEL, f = frag % FRAGS_PER_PANEL;     // beyond the last: that one again, not stored
     const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
     // 0.90 .. 1.00, 96 units 0.88 .. 1.00, lifted rows of 64 units 0.95 .. 1.00, 128 units 0.93 .. 1.01; all other lengths of 21 to 148 units 0.96 .. 1.04, mean 1.00;
     // 32 and 64 places up to 1.16 and 1.22 at single lengths; NF = 5, 6 and 8 with 16 places 0.97 .. 1.15).
     constexpr int PLACES = NF == 4 ? 16 : 8;
-    const int rot = ((blockIdx.y * gridDim.x + blockIdx.x) & (PLACES - 1)) * U / PLACES;
+    const int rot = (wg & (PLACES - 1)) * U / PLACES;
     auto issue = [&](int v, uint32_t slot) __attribute__((always_inline)) {
         const int u = v + rot < U ? v + rot : v + rot - U;
 #pragma unroll
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
         lslot = lslot == (RING - 1) * WU::BYTES ? 0u : lslot + WU::BYTES;
     }
     if (f_first + wave >= nfrags) return;
-    if (NF == 4 && TB == 1 && gridDim.y > 1) {
+    if (NF == 4 && TB == 1 && S > 1) {
         const typename MM::acc_t part[1][1] = {{acc[0]}};
         mid_store_partial(part, ws, item, wave, lane, (int)M);
         return;
@@ -159,10 +161,11 @@ static ss_status launch_wide_one(const void* Xq, const float* s_x, const void* w
     constexpr int lds = WU::RING * WU::BYTES;
     static_assert(lds <= 160 * 1024, "LDS budget");
     const int64_t nfrags = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
+    const int cols = (int)((nfrags + NF - 1) / NF);
     if (allow_dynamic_lds<k_sparse_wide<DT, NF, TB, FUSED, ONCE>>(lds) != SS_OK) return SS_ERR_HIP;
-    hipLaunchKernelGGL((k_sparse_wide<DT, NF, TB, FUSED, ONCE>), dim3((unsigned)((nfrags + NF - 1) / NF), (unsigned)S), dim3(64 * NF), lds, stream,
+    hipLaunchKernelGGL((k_sparse_wide<DT, NF, TB, FUSED, ONCE>), dim3((unsigned)cols, (unsigned)S), dim3(64 * NF), lds, stream,
                        static_cast<const uint8_t*>(Xq), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb,
-                       static_cast<uint16_t*>(Y), ldy, ws);
+                       static_cast<uint16_t*>(Y), ldy, ws, cols, S, make_div(cols), k_ranges(U, S));
     return launch_status();
 }
 

@@ -151,6 +151,12 @@ __device__ inline void mid_store_partial(const ACC (&acc)[FW][TB], void* ws, int
             }
 }
 
+// The k ranges of a split row: U = S q + rest units, one more in the first `rest` ranges.
+struct KRanges { int q, rest; };
+inline KRanges k_ranges(int64_t U, int64_t S) { return {(int)(U / S), (int)(U % S)}; }
+__device__ inline int range_first(KRanges k, int range) { return range * k.q + min(range, k.rest); }
+__device__ inline int range_units(KRanges k, int range) { return k.q + (range < k.rest); }
+
 // Kernels for few tokens (gemm_skinny.hip): one workgroup per 32 or 64 output channels streams their weights once.
 // The dense kernel splits its k range over S workgroups per fragment where there are fewer 32-channel fragments than
 // compute units; partial sums go through `ws` (skinny_workspace_bytes(M, O, S) bytes) and a second kernel adds them in a

@@ -53,6 +53,17 @@ __device__ inline int xcd_run(int id, int total)
     return x * (total >> 3) + (x < rest ? x : rest) + (id >> 3);
 }
 
+// n / d for n < 2^31 by a multiplication, prepared on the host: a kernel that divides ahead of its first load makes all its loads wait for it (an integer division
+// is some 25 dependent instructions, one of 64 bits 100; the tile kernels of few tokens had 570 instructions there, 1.2 us of a 10 us launch).
+struct Div { uint32_t mul, shift; };
+inline Div make_div(int64_t d)                       // 1 <= d < 2^31
+{
+    uint32_t s = 0;
+    while ((1ll << s) < d) ++s;
+    return {(uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s};      // mul d - 2^(31 + s) < 2^s, so the quotient is exact
+}
+__host__ __device__ inline int quot(int n, Div d) { return (int)((uint64_t)(uint32_t)n * d.mul >> d.shift); }
+
 // What a program passes over in turn and comes to more than this is hardly found in the memory-side cache again: a third of its 256 MB.
 constexpr int64_t CACHED_BYTES = 80ll << 20;
 // What that cache does not hold at all.
