@@ -20,7 +20,7 @@ namespace ss {
 // loaded as they lie, the up to 2 (IV::N - 1) elements ahead of and behind them by one thread each, the last of the
 // workgroup; element k has its code in LDS at off + k, off being the row's offset from its first line, and the gather shifts
 // accordingly.  (One thread for all that a line has of the row, element by element: bf16 to fp16, 8192 x 2051 17.7 us, like this 12.8; 2048 x 8195 14.4 and 10.6.)
-template <typename TIN, int OUT, int MAXV, int THREADS, bool RAGGED>
+template <typename TIN, int OUT, int MAXV, int THREADS, bool RAGGED, bool THROUGH>
 __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restrict__ X, int64_t ldx, int K, int N,
                                                                 uint8_t* __restrict__ XL, float* __restrict__ s_x, int Kp, int Kz, uint32_t inv_nw1)
 {
@@ -32,6 +32,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
     const int64_t m = blockIdx.x;
     const TIN* x = X + m * ldx;
     const int t = threadIdx.x;
+    auto put = [&](auto* p, auto x) __attribute__((always_inline)) { if constexpr (THROUGH) store_through(p, x); else *p = x; };
     typedef InVec<TIN> IV;
     typename IV::V v[MAXV > 0 ? MAXV : 1];
     const int off = RAGGED ? (int)(((uintptr_t)x / sizeof(TIN)) % IV::N) : 0;
@@ -90,9 +91,9 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
                         else
                             w[k] = quant1<OUT>(f[2 * k], r) | (quant1<OUT>(f[2 * k + 1], r) << 16);
                     }
-                    if constexpr (OW == 1) out32[idx] = w[0];
-                    else if constexpr (OW == 2) reinterpret_cast<uint2*>(out32)[idx] = make_uint2(w[0], w[1]);
-                    else reinterpret_cast<uint4*>(out32)[idx] = make_uint4(w[0], w[1], w[2], w[3]);
+                    if constexpr (OW == 1) put(out32 + idx, w[0]);
+                    else if constexpr (OW == 2) put(reinterpret_cast<uint2*>(out32) + idx, make_uint2(w[0], w[1]));
+                    else put(reinterpret_cast<uint4*>(out32) + idx, make_uint4(w[0], w[1], w[2], w[3]));
                 }
             }
             // zero padding of the stored width (K is a whole number of vectors here, so of dwords too)
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
                 }
                 if (++l == nw1) { l = 0; ++g; }
             }
-            out[c] = make_uint4(w[0], w[1], w[2], w[3]);
+            put(out + c, make_uint4(w[0], w[1], w[2], w[3]));
         }
     } else {
         // 16-bit elements: a window is 8 bytes = elements b..b+3: two aligned dwords, or, b odd (RAGGED only), parts of three
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
                 }
                 if (++l == nw1) { l = 0; ++g; }
             }
-            out[c] = make_uint4(w[0], w[1], w[2], w[3]);
+            put(out + c, make_uint4(w[0], w[1], w[2], w[3]));
         }
     }
 }
@@ -188,6 +189,10 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const int Kp = (int)lifted_ld(K, N, ES);
     const int Kz = (int)lift_lds_elems(K, N, ES);
     const bool line_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
+    // Stores through the L2 (store_through): 4 to 32 MB of output, unless a lane's stores are of four bytes.  Time over plain stores, 98 calls of both input types, without and with lifting: below 1 MB
+    // 1.03 .. 1.06, 1 to 4 MB 0.86 .. 1.05, more 0.85 .. 1.04 and one 1.08 (mean 0.97; bf16 -> fp8 2048 x 4096 7.7 -> 7.0 us, with lifting 10.1 -> 8.8).  fp32 to 8 bits without
+    // lifting 0.98 .. 1.05; beyond 32 MB, which the L2s do not hold, the kernel gains 1 % and the GEMM behind it loses as much (fp32 -> INT8 4:6, 8192 x 6144, both 1.014).
+    const bool through = M * Kp * ES >= (4 << 20) && M * Kp * ES <= (32 << 20) && !(N == 2 && line_ok && IV::N * ES == 4);
     const bool element_ok = (uintptr_t)X % sizeof(TIN) == 0;
     // a ragged row: up to IV::N - 1 codes more in LDS, ahead of it in its first line
     const int64_t nvec = K / IV::N;                           // whole 16-byte vectors per row, at most
@@ -196,7 +201,7 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const uint32_t inv = N > 2 ? (uint32_t)(((1ull << 32) + N - 2) / (N - 1)) : 0u;
     const TIN* x = static_cast<const TIN*>(X);
     uint8_t* xl = static_cast<uint8_t*>(XL);
-#define SS_LQ(MAXV, T, RAGGED) hipLaunchKernelGGL((k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED>), grid, dim3(T), RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
+#define SS_LQ(MAXV, T, RAGGED) hipLaunchKernelGGL((through ? k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, true> : k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, false>), grid, dim3(T), RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
 #define SS_LQ_ROWS(RAGGED)                             \
     if (spread && nvec <= 2 * 512) SS_LQ(2, 512, RAGGED);        \
     else if (spread && nvec <= 2 * 1024) SS_LQ(2, 1024, RAGGED); \

@@ -82,6 +82,23 @@ __device__ inline void store_once(uint4* p, uint4 v)
     __builtin_nontemporal_store((u32x4){v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(p));
 }
 
+// Stores that go through the L2 at once.  What a kernel leaves in the eight L2s is written back when it ends, at 2.6 TB/s, before the next kernel starts;
+// written through, it leaves while the kernel still reads.  Where a wavefront writes whole lines and megabytes of
+// them: part of a line goes to memory as such (fp32 4:6 pruning 1.34 of the time), and a kernel of little output waits for the acknowledgement (1.03 .. 1.06).  Partial sums
+// of split rows gain nothing (four layers at M = 64 1.009, M = 256 0.997): their kernels write at their end.
+__device__ inline void store_through(uint32_t* p, uint32_t v) { asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory"); }
+__device__ inline void store_through(uint2* p, uint2 v)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" ::"v"(p), "v"((u32x2){v.x, v.y}) : "memory");
+}
+__device__ inline void store_through(uint4* p, uint4 v)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    // (a vector instruction must not overwrite the data of a store of more than 8 bytes right behind it, which the compiler does not see here)
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"((u32x4){v.x, v.y, v.z, v.w}) : "memory");
+}
+
 // ---- scalar format conversions (device) --------------------------------------------------
 __device__ inline float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 

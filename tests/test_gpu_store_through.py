@@ -1,0 +1,33 @@
+"""Quantisation, lifting and pruning on either side of the lines (4 MB of output, quantiser also 32 MB) between which they store through the L2: the rows of one call are those of calls on a few rows each."""
+import pytest
+import torch
+
+from paper_2603_05232_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("act,dtype,K,N", [("bf16", "i8", 4096, 2), ("bf16", "fp8", 4096, 4), ("fp32", "fp8", 4096, 2), ("fp32", "i8", 1003, 3), ("bf16", "bf16", 2051, 5), ("fp32", "fp16", 1024, 2)])
+@pytest.mark.parametrize("megabytes", [4, 32])
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_quantiser(act, dtype, K, N, megabytes, beyond):
+    row = binding.slide_lifted_ld(K, N, dtype) * (1 if dtype in ("i8", "fp8") else 2)
+    M = (megabytes << 20) // row + beyond
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    X = torch.randn((M, K), generator=gen, device="cuda").to(torch.float32 if act == "fp32" else torch.bfloat16)
+    q, s = binding.act_lift_quant(X, N, dtype)
+    for rows in (slice(0, 5), slice(M // 2, M // 2 + 7), slice(M - 3, M)):
+        qr, sr = binding.act_lift_quant(X[rows], N, dtype)
+        assert torch.equal(q[rows].view(torch.uint8), qr.view(torch.uint8)) and (s is None or torch.equal(s[rows], sr))
+
+
+@pytest.mark.parametrize("act,dtype,K,N", [("bf16", "i8", 4096, 4), ("bf16", "fp8", 2048, 2), ("bf16", "i8", 2048, 8), ("fp32", "i8", 2048, 3), ("bf16", "i8", 4104, 4)])
+@pytest.mark.parametrize("beyond", [-1, 1])
+def test_pruning(act, dtype, K, N, beyond):
+    O = (4 << 20) // K + beyond
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    W = torch.randn((O, K), generator=gen, device="cuda").to(torch.float32 if act == "fp32" else torch.bfloat16)
+    Wq, s_w = binding.slide_prune_quant(W, N, dtype)
+    for rows in (slice(0, 4), slice(O // 2, O // 2 + 4), slice(O - 3, O)):
+        wr, sr = binding.slide_prune_quant(W[rows].contiguous(), N, dtype)
+        assert torch.equal(Wq[rows].view(torch.uint8), wr.view(torch.uint8)) and torch.equal(s_w[rows], sr)
