@@ -66,16 +66,28 @@ template <int ROWS> struct MidRowLoader {
 };
 
 // acc[f][tb][r] of lane (n = lane & 31, h = lane >> 5) is channel o_wave + 64 h + 16 f + r of token t_wave + 32 tb + n
+// sw: the scales of the panel's channels from the wavefront's first, sx: those of the wavefront's tokens, both in LDS
 template <bool SCALED, typename ACC, int FW, int TB>
-__device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* __restrict__ s_x, const float* __restrict__ s_w, uint16_t* __restrict__ Y,
-                                 int64_t ldy, int64_t M, int64_t O, int64_t o_wave, int64_t t_wave, int lane)
+__device__ inline void mid_store(const ACC (&acc)[FW][TB], const float* sx, const float* sw, uint16_t* __restrict__ Y, int64_t ldy, int64_t M, int64_t O,
+                                 int64_t o_wave, int64_t t_wave, int lane)
 {
     const int n = lane & 31, h = lane >> 5;
 #pragma unroll
     for (int f = 0; f < FW; ++f)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb)
-            store_block16<SCALED>(acc[f][tb], s_x, s_w, Y, ldy, M, O, o_wave + 64 * h + 16 * f, t_wave + tb * 32 + n);
+            store_block16<SCALED>(acc[f][tb], SCALED ? sx[tb * 32 + n] : 1.0f, sw + 64 * h + 16 * f, Y, ldy, M, O, o_wave + 64 * h + 16 * f, t_wave + tb * 32 + n);
+}
+
+// The scales of a tile's 128 channels and TM tokens, behind its operand rings in LDS: asked for ahead of the first unit, so that the epilogue of an unsplit call does not
+// start with a trip to memory (0.4 us: 512 -> 4608 INT8 at M = 256 6.9 -> 6.4 us, 2048 -> 8192 fp8 at M = 300 13.5 -> 13.0, lifted 4096 -> 4096 INT8 at M = 1152
+// 30.1 -> 29.0).
+template <int TM> constexpr int MD_SCALES = (PANEL + TM + (TM & 32)) * 4;
+template <int TM> __device__ inline void mid_scales(const float* s_x, const float* s_w, int64_t t0, int64_t M, int64_t o0, int64_t O, int wave, int lane, uint32_t lds)
+{
+    constexpr int T = (TM + 63) / 64;
+    if (wave < 2) lds_dma_scales(s_w, o0 + wave * 64, O, lane, lds + wave * 256);
+    else if (wave - 2 < T) lds_dma_scales(s_x, t0 + (wave - 2) * 64, M, lane, lds + wave * 256);
 }
 
 // Sum of the S partial accumulators of every tile in range order (bit-reproducible also for fp32) and the
@@ -222,7 +234,7 @@ template <int TM, bool FUSED> struct MidUnit {
 template <int NS, int FW, int TB> struct MidOps { v4i a[NS][FW]; int idx[NS][FW]; v8i b[TB][2]; };      // b[token block][half of the lane's 64 bytes]
 
 template <int DT, int TM, int RING, bool FUSED, bool PIPE, bool ONCE, int KG>
-__global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
+__global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUSED>::BYTES + MD_SCALES<TM> <= 80 * 1024 ? 2 : 1)) void k_sparse_mid(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                               const float* __restrict__ s_w, int64_t M, int64_t O, int U_all, int64_t ldxb,
                                                               uint16_t* __restrict__ Y, int64_t ldy, MidOrder order, void* __restrict__ ws)
@@ -235,7 +247,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
     typedef MidOps<NS, FW, TB> Ops;
     typedef int idx_t __attribute__((ext_vector_type(FW)));
     static_assert(KG == 1 || PIPE, "groups of wavefronts run the pipeline");
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];      // RING units for each of the KG groups
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];      // RING units for each of the KG groups, the scales
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % MD_WAVES, kg = wave_all / MD_WAVES, lane = threadIdx.x & 63;
     uint8_t* const smem = lds + kg * (RING * MU::BYTES);
     const int wo = MU::MS::wo(wave), wt = MU::MS::wt(wave);
@@ -299,6 +311,8 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
         else { const int k = r - FW - 1 - NB, h = 1 + k / (FW + 1); if (k % (FW + 1) < FW) rd_a(h, k % (FW + 1)); else rd_i(h); }
     };
 
+    constexpr int SCALES = KG * RING * MU::BYTES;
+    if (MM::SCALED && order.S == 1 && kg == 0) mid_scales<TM>(s_x, s_w, t0, M, panel * PANEL, O, wave, lane, lds_address(lds) + SCALES);
     typename MM::acc_t acc[FW][TB];
     mid_zero(acc);
     auto mma = [&](const Ops& R, const v8i (&al)[TB], int i) __attribute__((always_inline)) {
@@ -448,7 +462,7 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
         }
     }
     if (order.S > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
-    else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, o_wave, t_wave, lane);
+    else mid_store<MM::SCALED>(acc, reinterpret_cast<const float*>(lds + SCALES) + PANEL + wt * (32 * TB), reinterpret_cast<const float*>(lds + SCALES) + 16 * FW * wo, Y, ldy, M, O, o_wave, t_wave, lane);
 }
 
 // ---- dense ----------------------------------------------------------------------------------------------
@@ -483,6 +497,7 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) brow[tb] = wt * 64 + tb * 32 + row;
 
+    if (MM::SCALED && order.S == 1) mid_scales<MD_TILE>(s_x, s_w, t0, M, panel * PANEL, O, wave, lane, lds_address(smem) + RING * MD_D_UNIT);
     typename MM::acc_t acc[2][2];
     mid_zero(acc);
     constexpr int AHEAD = RING - 1;
@@ -524,7 +539,7 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
         lslot = lslot == RING - 1 ? 0 : lslot + 1;
     }
     if (order.S > 1) mid_store_partial(acc, ws, (int64_t)it.range * order.nt + it.tile, wave, lane, (int)(M - t0) - wt * 64);
-    else mid_store<MM::SCALED>(acc, s_x, s_w, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
+    else mid_store<MM::SCALED>(acc, reinterpret_cast<const float*>(smem + RING * MD_D_UNIT) + PANEL + wt * 64, reinterpret_cast<const float*>(smem + RING * MD_D_UNIT) + 32 * wo, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
 }
 
 }  // namespace ss
@@ -559,7 +574,7 @@ static ss_status launch_sparse_mid_ring(const void* Xq, const float* s_x, const 
                                         int64_t O, int U, int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles,
                                         hipStream_t stream)
 {
-    constexpr int lds = KG * RING * MidUnit<TM, FUSED>::BYTES;
+    constexpr int lds = KG * RING * MidUnit<TM, FUSED>::BYTES + MD_SCALES<TM>;
     static_assert(lds <= 160 * 1024 && (KG == 1 || lds >= TM * 512), "the rings, then the sums that are handed over");
     if (allow_dynamic_lds<k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>>(lds) != SS_OK) return SS_ERR_HIP;
     hipLaunchKernelGGL((k_sparse_mid<DT, TM, RING, FUSED, PIPE, ONCE, KG>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS * KG), lds, stream,
@@ -605,7 +620,7 @@ template <int DT, int RING>
 static ss_status launch_dense_mid_ring(const void* Xq, const float* s_x, const void* Wq, const float* s_w, int64_t M, int64_t O, int64_t Kb, void* Y,
                                        int64_t ldy, void* ws, int S, int tiles_t, int64_t ntiles, hipStream_t stream)
 {
-    constexpr int lds = RING * MD_D_UNIT;
+    constexpr int lds = RING * MD_D_UNIT + MD_SCALES<MD_TILE>;
     if (allow_dynamic_lds<k_dense_mid<DT, RING>>(lds) != SS_OK) return SS_ERR_HIP;
     hipLaunchKernelGGL((k_dense_mid<DT, RING>), dim3((unsigned)ntiles, (unsigned)S), dim3(MD_THREADS), lds, stream, static_cast<const uint8_t*>(Xq),
                        s_x, static_cast<const uint8_t*>(Wq), s_w, M, O, Kb, static_cast<uint16_t*>(Y), ldy, mid_order(ntiles, tiles_t, S, false, Kb / ROWB), ws);

@@ -32,7 +32,10 @@ template <int NF, int TB, bool FUSED> struct WideUnit {
     static constexpr int TOK = TB * 32 * ROWB, AV = NF * NS * 1024, AM = PANELS * NS * 1024, BYTES = TOK + AV + AM;
     static constexpr int SHARED = TB * 4 + PANELS * NS;                        // 1 KB pieces of tokens and index words
     static constexpr int E = (SHARED + NF - 1) / NF, LPU = NS + E;        // direct loads per wavefront: its values, its share of those
+    static constexpr int SCALES = (PANELS * PANEL + (TB == 1 ? 64 : TB * 32)) * 4;          // of the channels and tokens, behind the ring
     static constexpr int FIT = (NF == 4 ? 80 : 160) * 1024 / BYTES, RING = FIT < 5 ? FIT : 5;
+    static constexpr bool SCALES_FIT = RING * BYTES + SCALES <= (NF == 4 ? 80 : 160) * 1024;
+    static constexpr int LDS = RING * BYTES + (SCALES_FIT ? SCALES : 0);
 };
 
 template <int DT, int NF, int TB, bool FUSED, bool ONCE>
@@ -56,6 +59,18 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
     const int f_first = col * NF, p_first = f_first / FRAGS_PER_PANEL;
     const int frag = min(f_first + wave, nfrags - 1), panel = frag / FRAGS_PER_PANEL, f = frag % FRAGS_PER_PANEL;     // beyond the last: that one again, not stored
     const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
+
+    // The scales, asked for ahead of the first unit (else the epilogue starts with a trip to memory: 3584 -> 37888 INT8 at M = 1 22.1 -> 21.6 us, at M = 100 33.8 -> 33.2).  NF = 6 with 128 tokens has no room for them but in the ring, when all units are read.
+    constexpr int SCALES = WU::SCALES_FIT ? RING * WU::BYTES : 0, PIECES = WU::SCALES / 256;
+    auto scales = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < (PIECES + NF - 1) / NF; ++e) {
+            const int piece = wave + e * NF;
+            if (piece < 2 * WU::PANELS) lds_dma_scales(s_w, (int64_t)p_first * PANEL + piece * 64, O, lane, lds0 + SCALES + piece * 256);
+            else if (piece < PIECES) lds_dma_scales(s_x, (piece - 2 * WU::PANELS) * 64, M, lane, lds0 + SCALES + piece * 256);
+        }
+    };
+    if (MM::SCALED && WU::SCALES_FIT && S == 1) scales();
 
     // Sources of this wavefront's loads.  Lanes of tokens that do not exist load nothing (their products are never stored).
     const uint8_t* const av_src = w_vals + (((int64_t)panel * U_all + u_first) * NS * FRAGS_PER_PANEL + f) * 1024;
@@ -138,15 +153,24 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
         slot = slot == (RING - 1) * WU::BYTES ? 0u : slot + WU::BYTES;
         lslot = lslot == (RING - 1) * WU::BYTES ? 0u : lslot + WU::BYTES;
     }
+    if constexpr (MM::SCALED && !WU::SCALES_FIT) {
+        wait_lgkm0();
+        wg_barrier();
+        scales();
+        wait_vmcnt<0>();
+        wg_barrier();
+    }
     if (f_first + wave >= nfrags) return;
     if (NF == 4 && TB == 1 && S > 1) {
         const typename MM::acc_t part[1][1] = {{acc[0]}};
         mid_store_partial(part, ws, item, wave, lane, (int)M);
         return;
     }
+    const float* const sw = reinterpret_cast<const float*>(smem + SCALES), *const sx = sw + WU::PANELS * PANEL;
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
-        store_block16<MM::SCALED>(acc[tb], s_x, s_w, Y, ldy, M, O, (int64_t)panel * PANEL + 64 * qb + 16 * f, tb * 32 + n);
+        store_block16<MM::SCALED>(acc[tb], MM::SCALED ? sx[tb * 32 + n] : 1.0f, sw + (panel - p_first) * PANEL + 64 * qb + 16 * f, Y, ldy, M, O,
+                                  (int64_t)panel * PANEL + 64 * qb + 16 * f, tb * 32 + n);
 }
 
 }  // namespace ss
@@ -158,7 +182,7 @@ static ss_status launch_wide_one(const void* Xq, const float* s_x, const void* w
                                  int64_t ldxb, void* Y, int64_t ldy, void* ws, int S, hipStream_t stream)
 {
     typedef WideUnit<NF, TB, FUSED> WU;
-    constexpr int lds = WU::RING * WU::BYTES;
+    constexpr int lds = WU::LDS;
     static_assert(lds <= 160 * 1024, "LDS budget");
     const int64_t nfrags = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL;
     const int cols = (int)((nfrags + NF - 1) / NF);

@@ -78,6 +78,15 @@ __device__ inline int fresh_lane()
     return l;
 }
 
+// Direct load of 64 scales, first .. first + 63 of `end`, by one wavefront; those beyond the last repeat it.
+__device__ inline void lds_dma_scales(const float* scales, int64_t first, int64_t end, int lane, uint32_t lds_wave_addr)
+{
+    const int64_t left = end - 1 - first;
+    const int left32 = left > 63 ? 63 : (int)left;
+    const uint32_t e = left < 0 ? 0u : (uint32_t)(lane < left32 ? lane : left32);
+    lds_dma4_at(reinterpret_cast<const uint8_t*>(scales + (left < 0 ? end - 1 : first)), e * 4, lds_wave_addr);
+}
+
 // Wait until at most N of this wave's direct loads are still in flight and all of its LDS reads
 // have returned (gfx9 s_waitcnt encoding: vmcnt = bits [3:0] and [15:14], lgkmcnt = bits [11:8]).
 template <int N> __device__ inline void wait_vmcnt()

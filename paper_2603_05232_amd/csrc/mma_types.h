@@ -81,19 +81,19 @@ __device__ inline uint32_t pack_bf16x2(float a, float b)
 }
 
 // Epilogue of one accumulator block held by one lane: a[r] is channel o_lane + r (16 consecutive channels) of token
-// tok; Y = bf16((float(a) * s_x[tok]) * s_w[o]) (SCALED) or bf16(a).  Out-of-range tokens and channels are skipped.
+// tok; Y = bf16((float(a) * sx) * sw_lds[r]) (SCALED; the channels' scales lie in LDS) or bf16(a).  Out-of-range tokens and channels are skipped.
 template <bool SCALED, typename ACC>
-__device__ inline void store_block16(const ACC& a, const float* __restrict__ s_x, const float* __restrict__ s_w, uint16_t* __restrict__ Y,
-                                     int64_t ldy, int64_t M, int64_t O, int64_t o_lane, int64_t tok)
+__device__ inline void store_block16(const ACC& a, float sx, const float* sw_lds, uint16_t* __restrict__ Y, int64_t ldy, int64_t M, int64_t O, int64_t o_lane,
+                                     int64_t tok)
 {
     if (tok >= M || o_lane >= O) return;
     uint32_t w[8];
     if constexpr (SCALED) {
-        const float sx = s_x[tok];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t o0 = o_lane + 2 * q, o1 = o0 + 1;
-            w[q] = pack_bf16x2(((float)a[2 * q] * sx) * s_w[o0 < O ? o0 : O - 1], ((float)a[2 * q + 1] * sx) * s_w[o1 < O ? o1 : O - 1]);
+        for (int q = 0; q < 4; ++q) {
+            const float4 sw = reinterpret_cast<const float4*>(sw_lds)[q];
+            w[2 * q] = pack_bf16x2(((float)a[4 * q] * sx) * sw.x, ((float)a[4 * q + 1] * sx) * sw.y);
+            w[2 * q + 1] = pack_bf16x2(((float)a[4 * q + 2] * sx) * sw.z, ((float)a[4 * q + 3] * sx) * sw.w);
         }
     } else {
 #pragma unroll
