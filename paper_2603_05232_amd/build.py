@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libslidesparse.so")
 CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
-SOURCES = ("lift_quant.hip", "prune_quant.hip", "decompose.hip", "gemm.hip", "gemm_skinny.hip", "gemm_mid.hip", "gemm_wide.hip", "gemm_slim.hip", "gemm_lifted.hip", "gemm_fused.hip", "gemm_fused_narrow.hip")
+SOURCES = ("lift_quant.hip", "prune_quant.hip", "decompose.hip", "gemm.hip", "gemm_skinny.hip", "gemm_mid.hip", "gemm_wide.hip", "gemm_slim.hip", "gemm_small.hip", "gemm_lifted.hip", "gemm_fused.hip", "gemm_fused_narrow.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-inline-asm",      # the direct-to-LDS loads name M0 as clobbered, which clang reports as a reserved register

@@ -359,6 +359,7 @@ extern "C" ss_status slide_sparse_gemm_ws(const void* X_lifted, const float* s_x
     const int64_t Kpb = K_lifted * elem_size(dtype);
     const ss_plan p = plan_gemm(SS_KIND_LIFTED, M, O, Kpb / KSTEP, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
+    if (p.path == SS_PATH_SMALL) return launch_sparse_small(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, p.small, hs);
     if (p.path == SS_PATH_SLIM) return launch_sparse_slim(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_WIDE) return launch_sparse_wide(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, nullptr, 1, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, workspace, p.S, hs);
@@ -410,6 +411,7 @@ extern "C" ss_status slide_sparse_gemm_static(const void* X_lifted, const float*
     const int64_t Kpb = K_lifted * elem_size(dtype);
     const ss_plan p = plan_gemm(SS_KIND_LIFTED, M, O, Kpb / KSTEP, SS_STATIC_SCRATCH_BYTES);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_skinny(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, hs);
+    if (p.path == SS_PATH_SMALL) return launch_sparse_small(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, p.small, hs);
     if (p.path == SS_PATH_SLIM) return launch_sparse_slim(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_WIDE) return launch_sparse_wide(false, X_lifted, s_x, w_vals, w_meta, s_w, M, O, (int)(Kpb / KSTEP), Kpb, dtype, Y, ldy, nullptr, 1, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_mid(X_lifted, s_x, w_vals, w_meta, s_w, M, O, Kpb, dtype, Y, ldy, ws, p.S, hs);

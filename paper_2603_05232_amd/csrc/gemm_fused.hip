@@ -329,6 +329,7 @@ static ss_status fused_gemm(const void* Xq, const float* s_x, const void* w_vals
     // kernel family by shape, as for the other two GEMMs; the k loop counts super-units of 128 unlifted bytes
     const ss_plan p = plan_gemm(SS_KIND_FUSED, M, O, U, workspace_bytes);
     if (p.path == SS_PATH_SKINNY) return launch_sparse_fused_skinny(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
+    if (p.path == SS_PATH_SMALL) return launch_sparse_small(true, Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, p.small, hs);
     if (p.path == SS_PATH_SLIM) return launch_sparse_slim(true, Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, hs);
     if (p.path == SS_PATH_MID) return launch_sparse_fused_mid(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, workspace, p.S, hs);
     if (p.path == SS_PATH_WIDE) return launch_sparse_wide(true, Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, dtype, Y, ldy, nullptr, 1, hs);

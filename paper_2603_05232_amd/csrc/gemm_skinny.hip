@@ -492,7 +492,7 @@ static int frag_splits(int64_t M, int64_t O, int64_t units, int cap)
     return S < 2 ? 1 : (int)S;
 }
 
-// token blocks of 32: 1 (M <= 32) or 2 (M <= 64)
+// M <= 32
 template <int DT, bool FUSED>
 static ss_status launch_sparse_dt(const void* XL, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                                   int U, int64_t ldxb, void* Y, int64_t ldy, hipStream_t st)
@@ -501,7 +501,6 @@ static ss_status launch_sparse_dt(const void* XL, const float* s_x, const void* 
     // many, run on gemm_wide.hip and the tiles of gemm_mid.hip.)
     const bool two = (O + PANEL - 1) / PANEL * FRAGS_PER_PANEL >= 2 * cu_count();
 #define SS_GO(TB, FPW) return launch_sparse_one<DT, TB, FPW, FUSED>(XL, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, st)
-    if (M > 32) SS_GO(2, 1);
     if (two) SS_GO(1, 2);
     SS_GO(1, 1);
 #undef SS_GO

@@ -1,0 +1,221 @@
+// Sparse GEMMs on small unsplit tiles: 32 or 64 channels (one or two fragments of a panel) x 32 to 128 tokens, for layers that have too few tiles of 128 channels to
+// occupy the compute units and would split their rows.
+//
+// A split row costs its partial sums twice (6 MB at M = 64 leave the L2s in 2.4 us between the two kernels, 14 MB at M = 256 in 3.2) and a second launch, 4 to 8 us of a call
+// together.  Small tiles read more: what a compute unit loads grows from 8 to 28 super-units of fewer lines each (3584 -> 3584 INT8 at M = 256 2300 -> 3800 lines), at 270 lines
+// a microsecond and compute unit with weights from HBM, 430 hot.  So they win until rows are long, the more the more tokens there are to sum up (small_pays, mma_types.h).
+// Within a workgroup the row is still split: KG groups of TB wavefronts, each with a KG-th of the row and a ring of its own, whose sums meet in LDS in the order of the groups;
+// two wavefronts on a SIMD cover each other's waits.  The loop is plain (wait for a unit, meet, request a later one, read the operands, multiply).  Four groups for one block of tokens, two for
+// more (four with two blocks, rings of two units: 1.1 .. 1.3 of the time; one, two workgroups sharing a compute unit: 1.0 .. 1.4).
+// us, weights from HBM / hot, before and now: INT8 3584 -> 4608 at M = 256 19.4 / 17.2 -> 12.9 / 11.1, 3584 -> 3584 at M = 256 16.8 / 15.4 -> 11.7 / 9.7, at M = 64 13.5 / 11.9 -> 7.7 / 5.9,
+// at M = 32 9.4 / 7.9 -> 7.7 / 5.8; fp8 lifted 4096 -> 4096 at M = 64 11.7 / 10.5 -> 9.9 / 7.1.
+#include "ss_common.h"
+#include "packed_layout.h"
+#include "mma_types.h"
+#include "lds_pipe.h"
+#include "mid_order.h"
+#include "device_info.h"
+
+namespace ss {
+
+// A workgroup has FW fragments of a panel and TB blocks of 32 tokens, in KG groups of TB wavefronts (one for each block) with a KG-th of the row and a ring of units each.
+// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [step][fragment][lane][16 B], the panel's index words [step][lane][fragment 4][4 B]
+template <int FW, int TB, int KG, bool FUSED> struct SmallUnit {
+    static constexpr int NS = FUSED ? 3 : 2;
+    static constexpr int TOK = TB * 32 * ROWB, AV = NS * FW * 1024, AM = NS * 1024, BYTES = TOK + AV + AM;
+    static constexpr int PIECES = NS * (FW + 1);                          // 1 KB pieces of values and index words
+    static constexpr int E = (PIECES + TB - 1) / TB, LPU = 4 + E;         // direct loads per wavefront: its 32 token rows, its share of those
+    static constexpr int SCALES = (64 + (TB * 32 + 63) / 64 * 64) * 4;
+    static constexpr int FIT = (160 * 1024 - SCALES) / (KG * BYTES), RING = FIT < 4 ? FIT : 4, LDS = KG * RING * BYTES + SCALES;
+};
+
+template <int DT, int FW, int TB, int KG, bool FUSED>
+__global__ __launch_bounds__(64 * TB * KG) void k_sparse_small(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x, const uint8_t* __restrict__ w_vals,
+                                                             const uint8_t* __restrict__ w_meta, const float* __restrict__ s_w, int64_t M, int64_t O, int U_all,
+                                                             int64_t ldxb, uint16_t* __restrict__ Y, int64_t ldy, MidOrder order)
+{
+    typedef Mma<DT> MM;
+    typedef SmallUnit<FW, TB, KG, FUSED> SU;
+    constexpr int NS = SU::NS, RING = SU::RING, E = SU::E, PARTS = FRAGS_PER_PANEL / FW;
+    static_assert(KG > 1 && RING >= 3 && (RING - 2) * SU::LPU < 64, "loads in flight");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];      // RING units for each of the groups, the scales
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kg = wave_all / TB, t = wave_all % TB, lane = threadIdx.x & 63;
+    const int n = lane & 31, qb = lane >> 5;
+    asm volatile("" ::"s"(Xq), "s"(w_vals), "s"(w_meta), "s"(M), "s"(U_all), "s"(ldxb));      // with the order all that the first loads wait for, in one go
+    const MidItem it = mid_item(order);                                  // its "panels" are parts of FW fragments
+    const int64_t panel = it.panel / PARTS, t0 = (int64_t)it.tt * (TB * 32);
+    const int f0 = FW * (it.panel % PARTS);
+    const uint32_t lane16 = lane * 16, lds0 = lds_address(lds), ring0 = lds0 + kg * (RING * SU::BYTES);
+    constexpr int SCALES = KG * RING * SU::BYTES;
+    // scales: the channels of lane half 0 and 1 (16 FW each, 64 apart in the panel), then those of the tokens
+    if (MM::SCALED) {
+        if (wave_all == 0) {
+            const int64_t c = panel * PANEL + 64 * qb + 16 * f0 + n, last = O - 1;
+            lds_dma4_at(reinterpret_cast<const uint8_t*>(s_w + panel * PANEL), (uint32_t)((c < last ? c : last) - panel * PANEL) * 4, lds0 + SCALES);
+        }
+        if (wave_all < (TB + 1) / 2) lds_dma_scales(s_x, t0 + wave_all * 64, M, lane, lds0 + SCALES + 256 + 256 * wave_all);
+    }
+    // this group's share of the units, not empty (KG <= U_all)
+    const int both = U_all / KG, more = U_all % KG, u_first = kg * both + min(kg, more), U = both + (kg < more);
+    const int rot = (int)(blockIdx.x & 7) * U >> 3;                      // as in gemm_mid.hip
+    const uint8_t* const x_src = Xq + t0 * ldxb + (int64_t)u_first * ROWB;
+    uint32_t off[4];
+    {
+        const int64_t left = M - t0;                                     // >= 1
+        const int last = left > TB * 32 - 1 ? TB * 32 - 1 : (int)left - 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = (t * 4 + i) * 8 + (lane >> 3);
+            off[i] = (uint32_t)(row < last ? row : last) * (uint32_t)ldxb + (((lane & 7) ^ swz(row)) << 4);
+        }
+    }
+    const uint8_t* const av_src = w_vals + ((panel * U_all + u_first) * NS * FRAGS_PER_PANEL + f0) * 1024;
+    const uint8_t* const am_src = w_meta + (panel * U_all + u_first) * (NS * 1024);
+    const bool tail = t + (E - 1) * TB < SU::PIECES;                     // this wavefront's last piece exists
+    const uint32_t tail_half = __builtin_amdgcn_readfirstlane(tail ? ~0u : 0u);
+    const uint64_t tail_lanes = (uint64_t)tail_half << 32 | tail_half;
+    auto issue = [&](int v, uint32_t slot) __attribute__((always_inline)) {
+        const int u = v + rot < U ? v + rot : v + rot - U;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lds_dma16_at(x_src + (int64_t)u * ROWB, off[i], ring0 + slot + (t * 4 + i) * 1024);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int a = t + e * TB;
+            const uint8_t* src = a < FW * NS ? av_src + (int64_t)u * (NS * 4096) + (a / FW) * 4096 + (a % FW) * 1024 : am_src + (int64_t)u * (NS * 1024) + (a - FW * NS) * 1024;
+            if (E * TB == SU::PIECES || e + 1 < E) lds_dma16_at(src, lane16, ring0 + slot + SU::TOK + a * 1024);
+            else lds_dma16_lanes_at(src, lane16, ring0 + slot + SU::TOK + a * 1024, tail_lanes);      // no lanes, no address
+        }
+    };
+    uint32_t vb[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int row = t * 32 + n;
+        vb[c] = row * ROWB + (((FUSED ? 4 * qb + c : 4 * (c >> 1) + 2 * qb + (c & 1)) ^ swz(row)) << 4);
+    }
+    const uint8_t* const smem = lds + kg * (RING * SU::BYTES);
+    typename MM::acc_t acc[FW];
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[f][r] = 0;
+    uint32_t slot = 0, lslot = (RING - 1) * SU::BYTES;
+    auto multiply = [&]() __attribute__((always_inline)) {
+        const uint8_t* st = smem + slot;
+        typedef int idx_t __attribute__((ext_vector_type(FW)));
+        v4i a[NS][FW], x[4];
+        idx_t ix[NS];
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+#pragma unroll
+            for (int f = 0; f < FW; ++f) a[h][f] = *reinterpret_cast<const v4i*>(st + SU::TOK + (FW * h + f) * 1024 + lane16);
+            ix[h] = *reinterpret_cast<const idx_t*>(st + SU::TOK + SU::AV + h * 1024 + lane16 + 4 * f0);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = *reinterpret_cast<const v4i*>(st + vb[c]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int f = 0; f < FW; ++f)
+                acc[f] = MM::sparse(a[h][f], v8i{x[2 * h][0], x[2 * h][1], x[2 * h][2], x[2 * h][3], x[2 * h + 1][0], x[2 * h + 1][1], x[2 * h + 1][2], x[2 * h + 1][3]}, acc[f], ix[h][f]);
+        if constexpr (FUSED) {                                           // middle windows: see gemm_mid.hip
+            v8i m;
+#pragma unroll
+            for (int jd = 0; jd < 8; ++jd) {
+                auto w = [&](int k) { return (uint32_t)x[k >> 2][k & 3]; };
+                if constexpr (MM::ES == 1) m[jd] = (int)__builtin_amdgcn_alignbyte(w(2 * jd + 1), w(2 * jd), 2);
+                else m[jd] = (int)w(4 * (jd >> 1) + 1 + (jd & 1));
+            }
+#pragma unroll
+            for (int f = 0; f < FW; ++f) acc[f] = MM::sparse(a[2][f], m, acc[f], ix[2][f]);
+        }
+        slot = slot == (RING - 1) * SU::BYTES ? 0u : slot + SU::BYTES;
+    };
+#pragma unroll
+    for (int i = 0; i < RING - 1; ++i)
+        if (i < U) issue(i, i * SU::BYTES);
+    for (int u = 0; u < both; ++u) {
+        if (u + RING - 1 <= U) wait_vmcnt<(RING - 2) * SU::LPU>(); else wait_vmcnt<0>();
+        wg_barrier();                                                    // unit u has landed, unit u - 1 is read
+        if (u + RING - 1 < U) issue(u + RING - 1, lslot);
+        multiply();
+        lslot = lslot == (RING - 1) * SU::BYTES ? 0u : lslot + SU::BYTES;
+    }
+    if (more) {                                                          // the first groups have one more
+        wait_vmcnt<0>();
+        wg_barrier();
+        if (kg < more) multiply();
+    }
+    wait_lgkm0();
+    wg_barrier();                                                        // nobody reads operands any more
+    typedef decltype(acc[0][0] + acc[0][0]) elem_t;
+    typedef elem_t quad_t __attribute__((ext_vector_type(4)));
+    // the groups' sums, added in their order by the first
+    v4i* const x = reinterpret_cast<v4i*>(lds) + t * (FW * 256) + lane;
+    constexpr int GROUP = TB * FW * 256;
+    if (kg > 0) {
+#pragma unroll
+        for (int f = 0; f < FW; ++f)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                x[(kg - 1) * GROUP + (f * 4 + r4) * 64] = __builtin_bit_cast(v4i, (quad_t){acc[f][4 * r4], acc[f][4 * r4 + 1], acc[f][4 * r4 + 2], acc[f][4 * r4 + 3]});
+        wait_lgkm0();
+    }
+    wg_barrier();
+    if (kg > 0) return;
+#pragma unroll
+    for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+        for (int f = 0; f < FW; ++f)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const quad_t q = __builtin_bit_cast(quad_t, x[k * GROUP + (f * 4 + r4) * 64]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[f][4 * r4 + e] += q[e];
+            }
+    const float *const sw = reinterpret_cast<const float*>(lds + SCALES) + 32 * qb, *const sx = reinterpret_cast<const float*>(lds + SCALES) + 64;
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+        store_block16<MM::SCALED>(acc[f], MM::SCALED ? sx[t * 32 + n] : 1.0f, sw + 16 * f, Y, ldy, M, O, panel * PANEL + 64 * qb + 16 * (f0 + f), t0 + t * 32 + n);
+}
+
+}  // namespace ss
+
+using namespace ss;
+
+template <int DT, int FW, int TB, int KG, bool FUSED>
+static ss_status launch_small_one(const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O, int U, int64_t ldxb,
+                                 void* Y, int64_t ldy, hipStream_t stream)
+{
+    typedef SmallUnit<FW, TB, KG, FUSED> SU;
+    const int tiles_t = (int)((M + TB * 32 - 1) / (TB * 32));
+    const int64_t ntiles = (O + PANEL - 1) / PANEL * (FRAGS_PER_PANEL / FW) * tiles_t;
+    static_assert(SU::LDS <= 160 * 1024 && (KG - 1) * TB * FW * 4096 <= KG * SU::RING * SU::BYTES, "the rings, then the sums that are handed over");
+    if (allow_dynamic_lds<k_sparse_small<DT, FW, TB, KG, FUSED>>(SU::LDS) != SS_OK) return SS_ERR_HIP;
+    hipLaunchKernelGGL((k_sparse_small<DT, FW, TB, KG, FUSED>), dim3((unsigned)ntiles), dim3(64 * TB * KG), SU::LDS, stream, static_cast<const uint8_t*>(Xq), s_x,
+                       static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy,
+                       mid_order(ntiles, tiles_t, 1, false, U));
+    return launch_status();
+}
+
+namespace ss {
+
+ss_status launch_sparse_small(bool fused, const void* Xq, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                             int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, small_tile tile, hipStream_t stream)
+{
+#define SS_SM(DT, FW, TB, KG) \
+    if (tile.fw == FW && tile.tb == TB && tile.kg == KG) \
+        return fused ? launch_small_one<DT, FW, TB, KG, true>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream) \
+                     : launch_small_one<DT, FW, TB, KG, false>(Xq, s_x, w_vals, w_meta, s_w, M, O, U, ldxb, Y, ldy, stream)
+#define SS_S(DT) SS_SM(DT, 1, 1, 4); SS_SM(DT, 2, 1, 4); SS_SM(DT, 2, 2, 2); SS_SM(DT, 2, 3, 2); SS_SM(DT, 2, 4, 2); break
+    switch (dtype) {
+    case SS_I8: SS_S(SS_I8);
+    case SS_FP8_E4M3: SS_S(SS_FP8_E4M3);
+    case SS_BF16: SS_S(SS_BF16);
+    case SS_FP16: SS_S(SS_FP16);
+    }
+#undef SS_S
+#undef SS_SM
+    return SS_ERR_DTYPE;
+}
+
+}  // namespace ss

@@ -1,6 +1,7 @@
 // Matrix instructions of gfx950 per operand type, shared by the GEMM kernels.
 #pragma once
 #include "ss_common.h"
+#include "packed_layout.h"
 #include "device_info.h"
 
 namespace ss {
@@ -212,6 +213,33 @@ inline int wide_fragments(ss_kind kind, int64_t M, int64_t O, int64_t cus)
     return f == 7 ? 8 : (int)f;
 }
 
+// Small unsplit tiles (gemm_small.hip): fw fragments x tb blocks of 32 tokens, kg groups of wavefronts.  Operands as above.
+struct small_tile { int fw, tb, kg; };
+ss_status launch_sparse_small(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
+                              int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, small_tile tile, hipStream_t stream);
+inline int64_t small_workgroups(int64_t M, int64_t O, small_tile t) { return (O + 127) / 128 * (FRAGS_PER_PANEL / t.fw) * ((M + 32 * t.tb - 1) / (32 * t.tb)); }
+// the smallest that gives no compute unit two workgroups; fw = 0: none does
+inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
+{
+    for (small_tile t : {small_tile{1, 1, 4}, {2, 1, 4}, {2, 2, 2}, {2, 3, 2}, {2, 4, 2}})
+        if (units >= t.kg && M > 32 * (t.tb - 1) && small_workgroups(M, O, t) <= cus) return t;
+    return {0, 0, 0};
+}
+// Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before, all types, M = 17 .. 1000, 520 calls,
+// weights from HBM / hot (the largest of each):
+//   not split (also: no workspace)              0.33 .. 1.01 / 0.38 .. 1.00
+//   split, M <= 32            up to 3000 lines  0.98 / 0.95, to 4000 1.16 / 0.94, more 0.78 .. 2.2
+//   split, M <= 64            up to 3000 lines  0.81 / 0.73; to 4000 on 128 workgroups and more 0.95 / 0.79, on fewer 1.07 / 1.06; more 0.92 .. 1.8
+//   split, M > 64, 32 tokens  up to 3800 lines  0.92 / 0.87, to 5000 1.06 / 0.93, to 6500 1.31 / 1.13
+//   split, M > 64, 64 tokens  up to 6500 lines  0.88 / 0.92, to 8000 1.11 / 1.15, more 1.47; 96 and 128 tokens up to 8000 lines 0.92 / 1.02, more 1.20
+inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroups, bool fused, bool split)
+{
+    if (t.fw == 0) return false;
+    const int64_t lines = units * (32 * t.tb + (t.fw + 1) * (fused ? 24 : 16));
+    if (!split) return true;
+    if (M <= 64) return lines <= (M > 32 && workgroups >= 128 ? 4000 : 3000);
+    return lines <= (t.tb == 1 ? 3800 : t.tb == 2 ? 6500 : 8000);
+}
 // Up to 16 tokens with a workgroup for every 16 channels (gemm_slim.hip), unsplit; operands as above.
 ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                              int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
@@ -297,8 +325,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             (fp8 4096 -> 6144 at M = 2048, 192 tiles against 384: 41 against 54).
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
-enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE, SS_PATH_SLIM };
-struct ss_plan { ss_path path; int S; int64_t tile_o = 0; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
+enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE, SS_PATH_SLIM, SS_PATH_SMALL };
+struct ss_plan { ss_path path; int S; int64_t tile_o = 0; small_tile small = {0, 0, 0}; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
 // unit, the rest goes to those (M = 8192, 3584 -> 4608, 2.25 rounds: bf16 210 -> 194 us, INT8 120 -> 116).  With two of them per
@@ -324,6 +352,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
+    const small_tile small = M > 16 ? small_shape(M, O, units, cus) : small_tile{0, 0, 0};
     if (kind == SS_KIND_LIFTED && two_groups(M, O, units, cus)) return {SS_PATH_MID, 1};
     if (units >= 16 && wide_fragments(kind, M, O, cus)) return {SS_PATH_WIDE, 1};
     if (M > 64) {
@@ -331,12 +360,15 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         const bool many = 4 * tiles > 7 * cus;                          // more than 448
         const int64_t long_row = kind == SS_KIND_FUSED ? (many ? 24 : 12) : (many ? 48 : 24);
         if (tiles > 2 * cus || (4 * tiles > 5 * cus && units < long_row)) return {SS_PATH_TILE, 1, tile_channels(kind, M, O, units, cus)};
-        return {SS_PATH_MID, mid_splits(kind, M, O, units, ws_bytes)};
+        const int S = mid_splits(kind, M, O, units, ws_bytes);
+        if (small_pays(M, units, small, small.fw ? small_workgroups(M, O, small) : 0, kind == SS_KIND_FUSED, S > 1)) return {SS_PATH_SMALL, 1, 0, small};
+        return {SS_PATH_MID, S};
     }
     const int S = mid_splits(kind, M, O, units, ws_bytes);
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
-    const bool mid = wide || (S > 1 && (M > 32 || 2 * units + M >= 128));
+    const bool mid = wide || M > 32 || (S > 1 && 2 * units + M >= 128);
     if (!wide && slim_pays(M, O, units, cus, mid)) return {SS_PATH_SLIM, 1};
+    if (small_pays(M, units, small, small.fw ? small_workgroups(M, O, small) : 0, kind == SS_KIND_FUSED, mid && S > 1)) return {SS_PATH_SMALL, 1, 0, small};
     return mid ? ss_plan{SS_PATH_MID, S} : ss_plan{SS_PATH_SKINNY, 1};
 }
 

@@ -12,6 +12,7 @@ import test_gpu_mid_tiles
 import test_gpu_narrow_tiles
 import test_gpu_replay
 import test_gpu_slim
+import test_gpu_small_tiles
 import test_gpu_wide_layers
 from paper_2603_05232_amd import binding, build
 
@@ -28,11 +29,11 @@ int main()
         const int rest = cut == 0 || cut == O ? -1 : kind == SS_KIND_FUSED && narrow_pays(M, O - cut, cu_count()) ? SS_PATH_NARROW : SS_PATH_MID;
         const bool groups = kind == SS_KIND_LIFTED && p.path == SS_PATH_MID && two_groups(M, O, units, cu_count());
         const bool stream = p.path == SS_PATH_WIDE || (kind != SS_KIND_DENSE && p.path == SS_PATH_MID && M <= 32 && !groups && (O + 127) / 128 * p.S <= cu_count());
-        printf("%d %d %lld %d %d %d %d\\n", (int)p.path, p.S, cut, rest, cu_count(), groups, stream);
+        printf("%d %d %lld %d %d %d %d %d %d\\n", (int)p.path, p.S, cut, rest, cu_count(), groups, stream, p.small.fw, p.small.tb);
     }
 }
 """
-MID, NARROW, TILE, WIDE, SLIM = 1, 2, 3, 4, 5
+MID, NARROW, TILE, WIDE, SLIM, SMALL = 1, 2, 3, 4, 5, 6
 LIFTED, FUSED = 0, 1
 
 
@@ -50,10 +51,10 @@ def plan(tmp_path_factory):
 
     def ask(kind, M, O, units, ws=0):
         out = subprocess.run([str(d / "plan")], input=f"{kind} {M} {O} {units} {ws}\n", stdout=subprocess.PIPE, text=True, check=True).stdout
-        path, S, cut, rest, cus, groups, stream = map(int, out.split())
+        path, S, cut, rest, cus, groups, stream, fw, tb = map(int, out.split())
         if cus != 256:
             pytest.skip("the shapes are chosen for 256 compute units")
-        return {"path": path, "S": S, "cut": cut, "rest": rest, "groups": bool(groups), "stream": bool(stream), "large_tiles": -(-cut // 256) * -(-M // 256)}
+        return {"path": path, "S": S, "cut": cut, "rest": rest, "groups": bool(groups), "stream": bool(stream), "large_tiles": -(-cut // 256) * -(-M // 256), "small": (fw, tb)}
     return ask
 
 
@@ -163,3 +164,13 @@ def test_sixteen_channels(plan):
             assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] == SLIM, (kind, M, O, units)
         for M, O, units, with_ws in test_gpu_slim.BESIDE:
             assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] != SLIM, (kind, M, O, units)
+
+
+def test_small_tiles(plan):
+    for M, O, units, with_ws, fw, tb in test_gpu_small_tiles.SHAPES:
+        for kind in (FUSED, LIFTED):
+            p = plan(kind, M, O, units, 1 << 30 if with_ws else 0)
+            assert p["path"] == SMALL and p["small"] == (fw, tb) and p["S"] == 1, (kind, M, O, units, p)
+    for M, O, units, with_ws in test_gpu_small_tiles.BESIDE:
+        for kind in (FUSED, LIFTED):
+            assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] != SMALL, (kind, M, O, units)
