@@ -221,24 +221,23 @@ inline int64_t small_workgroups(int64_t M, int64_t O, small_tile t) { return (O 
 // the smallest that gives no compute unit two workgroups; fw = 0: none does
 inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
 {
-    for (small_tile t : {small_tile{1, 1, 4}, {2, 1, 4}, {2, 2, 2}, {2, 3, 2}, {2, 4, 2}})
+    for (small_tile t : {small_tile{1, 1, 4}, {2, 1, 4}, {2, 2, 3}, {2, 3, 2}, {2, 4, 2}})
         if (units >= t.kg && M > 32 * (t.tb - 1) && small_workgroups(M, O, t) <= cus) return t;
     return {0, 0, 0};
 }
-// Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before, all types, M = 17 .. 1000, 520 calls,
-// weights from HBM / hot (the largest of each):
-//   not split (also: no workspace)              0.33 .. 1.01 / 0.38 .. 1.00
-//   split, M <= 32            up to 3000 lines  0.98 / 0.95, to 4000 1.16 / 0.94, more 0.78 .. 2.2
-//   split, M <= 64            up to 3000 lines  0.81 / 0.73; to 4000 on 128 workgroups and more 0.95 / 0.79, on fewer 1.07 / 1.06; more 0.92 .. 1.8
-//   split, M > 64, 32 tokens  up to 3800 lines  0.92 / 0.87, to 5000 1.06 / 0.93, to 6500 1.31 / 1.13
-//   split, M > 64, 64 tokens  up to 6500 lines  0.88 / 0.92, to 8000 1.11 / 1.15, more 1.47; 96 and 128 tokens up to 8000 lines 0.92 / 1.02, more 1.20
+// Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before, 404 calls of
+// M = 17 .. 1450, 2 to 128 panels, 4 to 72 units, all types, weights from HBM / hot: 0.34 .. 1.03 (mean 0.71) / 0.34 .. 1.08 (0.67);
+//   no workspace 0.34 .. 1.00 / 0.34 .. 1.02
+//   split, M <= 32 0.70 .. 1.00 (0.86) / 0.53 .. 1.01 (0.75), M = 33 .. 64 0.42 .. 1.00 (0.65) / 0.40 .. 1.08 (0.58)
+//   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.92 / 0.87 .. 1.04
+// Beyond those lines: M <= 32 1.03 .. 2.2, M <= 64 1.04 .. 1.8, M > 64 0.9 .. 1.9 (all with the first form of the kernel, groups of a wavefront for each 32 tokens).
 inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroups, bool fused, bool split)
 {
     if (t.fw == 0) return false;
-    const int64_t lines = units * (32 * t.tb + (t.fw + 1) * (fused ? 24 : 16));
+    const int64_t lines = units * (32 * t.tb + t.fw * (fused ? 30 : 20));
     if (!split) return true;
-    if (M <= 64) return lines <= (M > 32 && workgroups >= 128 ? 4000 : 3000);
-    return lines <= (t.tb == 1 ? 3800 : t.tb == 2 ? 6500 : 8000);
+    if (M <= 64) return lines <= (M > 32 && workgroups >= 128 ? 3200 : 2400);
+    return lines <= (t.tb == 1 ? 3100 : t.tb == 2 ? 5900 : 7400);
 }
 // Up to 16 tokens with a workgroup for every 16 channels (gemm_slim.hip), unsplit; operands as above.
 ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
@@ -300,9 +299,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             0.89 / 1.07, 32 0.90 / 1.03, 16-bit 12 1.00 / 1.09, 24 0.94 / 1.03, 32 0.80 / 1.03.  449 .. 512 tiles, fused 8-bit 16 0.96 / 1.07, 24 0.92 /
 //             1.08, 32 0.88 / 1.05, 16-bit 24 0.97 / 1.05; lifted 8-bit 32 0.97 / 1.13, 48 0.95 / 1.09, 16-bit 48 0.92 / 1.07.  The lines go by
 //             the first figure, a layer's weights coming from HBM in a model of many.
-//   M 33..64  tiles of 64 tokens where the panels alone fill the chip (3584 -> 37888: 37 against 50) or the rows are long
-//             and can be split (bf16 3584 -> 4608: 13.9 against 23.6; fp8 lifted 4096 -> 6144: 13.9 against 19.9; unsplit
-//             18944 -> 3584: 64 against 31), few-token kernels otherwise (3584 -> 4608 unsplit: 15.9 against 14.4).
+//   M > 16    on at most half as many 128 x 128 tiles as compute units small unsplit tiles, unless the rows are long and can be split (small_pays).
+//   M 33..64  tiles of 64 tokens otherwise (3584 -> 37888: 37 against the few-token kernel's 50; split: bf16 3584 -> 4608 13.9 against 23.6, fp8 lifted 4096 -> 6144 13.9 against 19.9).
 //   M <= 32   a workgroup per panel (and k range; gemm_wide.hip) where there are more panels than half of the compute units (rows of 16 units and more: 3584 -> 18944
 //             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
