@@ -228,6 +228,7 @@ inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
 // Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before, 404 calls of
 // M = 17 .. 1450, 2 to 128 panels, 4 to 72 units, all types, weights from HBM / hot: 0.34 .. 1.03 (mean 0.71) / 0.34 .. 1.08 (0.67);
 //   no workspace 0.34 .. 1.00 / 0.34 .. 1.02
+//   M <= 16 (where gemm_slim.hip does not serve the call), not split: 33 to 64 panels 0.82 .. 1.01 / 0.74 .. 1.02; split 0.83 .. 2.2, so those stay
 //   split, M <= 32 0.70 .. 1.00 (0.86) / 0.53 .. 1.01 (0.75), M = 33 .. 64 0.42 .. 1.00 (0.65) / 0.40 .. 1.08 (0.58)
 //   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.92 / 0.87 .. 1.04
 // Beyond those lines: M <= 32 1.03 .. 2.2, M <= 64 1.04 .. 1.8, M > 64 0.9 .. 1.9 (all with the first form of the kernel, groups of a wavefront for each 32 tokens).
@@ -236,6 +237,7 @@ inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroup
     if (t.fw == 0) return false;
     const int64_t lines = units * (32 * t.tb + t.fw * (fused ? 30 : 20));
     if (!split) return true;
+    if (M <= 16) return false;
     if (M <= 64) return lines <= (M > 32 && workgroups >= 128 ? 3200 : 2400);
     return lines <= (t.tb == 1 ? 3100 : t.tb == 2 ? 5900 : 7400);
 }
@@ -299,7 +301,7 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             0.89 / 1.07, 32 0.90 / 1.03, 16-bit 12 1.00 / 1.09, 24 0.94 / 1.03, 32 0.80 / 1.03.  449 .. 512 tiles, fused 8-bit 16 0.96 / 1.07, 24 0.92 /
 //             1.08, 32 0.88 / 1.05, 16-bit 24 0.97 / 1.05; lifted 8-bit 32 0.97 / 1.13, 48 0.95 / 1.09, 16-bit 48 0.92 / 1.07.  The lines go by
 //             the first figure, a layer's weights coming from HBM in a model of many.
-//   M > 16    on at most half as many 128 x 128 tiles as compute units small unsplit tiles, unless the rows are long and can be split (small_pays).
+//   on at most half as many 128 x 128 tiles as compute units small unsplit tiles, unless the rows are long and can be split (small_pays) or 16 channels a workgroup serve them (slim_pays).
 //   M 33..64  tiles of 64 tokens otherwise (3584 -> 37888: 37 against the few-token kernel's 50; split: bf16 3584 -> 4608 13.9 against 23.6, fp8 lifted 4096 -> 6144 13.9 against 19.9).
 //   M <= 32   a workgroup per panel (and k range; gemm_wide.hip) where there are more panels than half of the compute units (rows of 16 units and more: 3584 -> 18944
 //             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
@@ -350,7 +352,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
         return {SS_PATH_MID, S};
     }
     const int64_t tiles = mid_tiles(M, O), cus = cu_count();
-    const small_tile small = M > 16 ? small_shape(M, O, units, cus) : small_tile{0, 0, 0};
+    const small_tile small = small_shape(M, O, units, cus);
     if (kind == SS_KIND_LIFTED && two_groups(M, O, units, cus)) return {SS_PATH_MID, 1};
     if (units >= 16 && wide_fragments(kind, M, O, cus)) return {SS_PATH_WIDE, 1};
     if (M > 64) {

@@ -9,7 +9,7 @@ from test_gpu_mid_tiles import _linear, _rows
 pytestmark = pytest.mark.gpu
 
 # tokens, channels, units per row, with a workspace, fragments, blocks of 32 tokens
-SHAPES = [(17, 5, 4, True, 1, 1), (32, 64 * 128, 5, False, 1, 1), (33, 32 * 128 - 3, 6, True, 1, 1), (64, 28 * 128, 28, True, 1, 1), (100, 300, 19, True, 1, 1), (1000, 2 * 128 - 5, 9, True, 1, 1), (63, 1000, 131, False, 1, 1),
+SHAPES = [(8, 36 * 128, 30, True, 1, 1), (16, 64 * 128 - 1, 40, True, 1, 1), (17, 5, 4, True, 1, 1), (32, 64 * 128, 5, False, 1, 1), (33, 32 * 128 - 3, 6, True, 1, 1), (64, 28 * 128, 28, True, 1, 1), (100, 300, 19, True, 1, 1), (1000, 2 * 128 - 5, 9, True, 1, 1), (63, 1000, 131, False, 1, 1),
           (20, 65 * 128, 7, True, 2, 1), (64, 64 * 128 - 1, 30, True, 2, 1), (129, 24 * 128 + 4, 22, True, 2, 1), (31, 127 * 128, 90, False, 2, 1), (700, 5 * 128, 4, False, 2, 1),
           (33, 65 * 128, 3, True, 2, 2), (65, 60 * 128 - 7, 3, True, 2, 2), (250, 32 * 128, 41, True, 2, 2), (128, 64 * 128 - 9, 100, False, 2, 2),
           (256, 42 * 128, 35, True, 2, 3), (193, 42 * 128 - 5, 8, False, 2, 3), (90, 127 * 128, 2, True, 2, 3),
