@@ -13,6 +13,7 @@
 //   dense:  a unit is a 16 KB token tile plus a 16 KB tile of weight rows, both XOR-swizzled; the inner loop
 //           is left to the compiler's scheduler.
 // The epilogue writes each lane's 16 consecutive channels of a token straight to Y.
+// Sparse calls with at most half as many of these tiles as compute units, unless their rows are long, are on smaller tiles (gemm_small.hip).
 #include "ss_common.h"
 #include "packed_layout.h"
 #include "mma_types.h"

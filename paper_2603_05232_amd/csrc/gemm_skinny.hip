@@ -1,8 +1,9 @@
-// slide_sparse_gemm and dense_gemm for few tokens (M <= 64): the decode regime, bound by streaming the
-// weights from HBM once, not by the matrix cores.
+// dense_gemm for up to 64 tokens, and the sparse GEMMs of up to 32 that no other kernel of few tokens serves better: rows of fewer than four units
+// (gemm_small.hip has none for them) and, up to 16 tokens, short rows on 65 to 191 panels (plan_gemm, mma_types.h).  Bound by streaming the weights from HBM once,
+// not by the matrix cores.
 //
-// A workgroup of four wavefronts owns FPW x 32 output channels (FPW matrix-instruction fragments, one or, for at most
-// 32 tokens, two: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (4,
+// A workgroup of four wavefronts owns FPW x 32 output channels (FPW matrix-instruction fragments, one or, for
+// sparse weights, two: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (4,
 // or 8 when there are fewer workgroups than compute units) split the k range by units of 128 bytes of a row
 // (unit u goes to wavefront u mod the number of wavefronts), so every workgroup is
 // four independent load streams, enough of them in flight on every compute unit to keep the memory system
