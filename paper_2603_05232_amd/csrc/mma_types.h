@@ -231,7 +231,7 @@ inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
 //   M <= 16 (where gemm_slim.hip does not serve the call), not split: 33 to 64 panels 0.79 .. 1.03 / 0.69 .. 1.03, 65 to 128 panels and 15 units and more 0.72 .. 1.02 /
 //     0.54 .. 1.04 (mean 0.86 / 0.82), 4 to 9 units, which stay on gemm_skinny.hip, 0.90 .. 1.11 / 0.86 .. 1.10; split 0.83 .. 2.2, so those stay where they are
 //   split, M <= 32 0.70 .. 1.00 (0.86) / 0.53 .. 1.01 (0.75), M = 33 .. 64 0.42 .. 1.00 (0.65) / 0.40 .. 1.08 (0.58)
-//   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.92 / 0.87 .. 1.04
+//   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.98 / 0.87 .. 1.04 (5200 lines and more to 1.09)
 // Beyond those lines: M <= 32 1.03 .. 2.2, M <= 64 1.04 .. 1.8, M > 64 0.9 .. 1.9 (all with the first form of the kernel, groups of a wavefront for each 32 tokens).
 inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroups, bool fused, bool split)
 {
@@ -240,7 +240,7 @@ inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroup
     if (M <= 16) return !split && (t.fw == 1 || units >= 12);
     if (!split) return true;
     if (M <= 64) return lines <= (M > 32 && workgroups >= 128 ? 3200 : 2400);
-    return lines <= (t.tb == 1 ? 3100 : t.tb == 2 ? 5900 : 7400);
+    return lines <= (t.tb == 1 ? 3100 : t.tb == 2 ? 5900 : t.tb == 3 ? 7400 : 5000);
 }
 // Up to 16 tokens with a workgroup for every 16 channels (gemm_slim.hip), unsplit; operands as above.
 ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
