@@ -95,8 +95,9 @@ __device__ inline void store_through(uint2* p, uint2 v)
 __device__ inline void store_through(uint4* p, uint4 v)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    // (a vector instruction must not overwrite the data of a store of more than 8 bytes right behind it, which the compiler does not see here)
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"((u32x4){v.x, v.y, v.z, v.w}) : "memory");
+    // A vector instruction may overwrite the data of a store of more than 8 bytes after two wait states, not sooner.  The compiler, which gives its own stores these, does not see
+    // this one, so they are part of the statement.
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"((u32x4){v.x, v.y, v.z, v.w}) : "memory");
 }
 
 // ---- scalar format conversions (device) --------------------------------------------------

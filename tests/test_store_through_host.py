@@ -1,0 +1,46 @@
+"""Stores through the L2 are assembly, where the compiler does not see the wait states that a store of 16 bytes needs before its data may be overwritten: two of them behind
+every such store, as the compiler's own stores get, whatever it schedules there."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2603_05232_amd import build
+
+PROBE = """
+#include "ss_common.h"
+__global__ void probe(uint4* p, uint32_t a, uint32_t b, uint32_t n)
+{
+    uint4 v = make_uint4(a + threadIdx.x, b, threadIdx.x, a * threadIdx.x);
+    for (uint32_t i = 0; i < n; ++i) {
+        ss::store_through(p + threadIdx.x + i * 64, v);
+        v.x = v.x * 3 + i; v.y ^= v.x; v.z += v.y; v.w -= v.z;
+    }
+}
+"""
+
+
+def _assembly(source, target):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if shutil.which(hipcc) is None:
+        pytest.skip("no hipcc")
+    subprocess.run([hipcc, *build.FLAGS, "-S", "--cuda-device-only", str(source), "-o", str(target)], check=True, stderr=subprocess.DEVNULL)
+    with open(target) as f:
+        return f.read()
+
+
+def _own_wait_states(text):
+    """For each 16-byte store through the L2: the wait states that its statement ends with."""
+    found = []
+    for behind in re.findall(r"global_store_dwordx4 [^\n]* sc0 sc1\n(.*?);;#ASMEND", text, re.S):
+        lines = [line.split() for line in behind.splitlines() if line.strip()]
+        found.append(sum(int(line[1]) + 1 if line[0] == "s_nop" else 1 for line in lines))
+    return found
+
+
+def test_wait_states_behind_a_store_of_16_bytes(tmp_path):
+    (tmp_path / "probe.hip").write_text(PROBE)
+    states = _own_wait_states(_assembly(tmp_path / "probe.hip", tmp_path / "probe.s"))
+    assert states and min(states) >= 2, states
