@@ -49,6 +49,9 @@ template <typename TIN, int N> struct PruneUnit {
     static constexpr int E = UB * 2 * N;                                       // elements per unit
     static constexpr int MAXU = CH <= 2 ? 4 : 2;                               // units a thread holds in registers (16 .. 56 of them)
     static constexpr int MAX_THREADS = CH >= 5 ? 512 : 1024;                   // register-heavy units leave room for fewer
+    template <int ES> static constexpr int OW = CH * (4 / ESI) * ES;           // output dwords per unit, of codes of ES bytes
+    template <int ES> static constexpr int VW = OW<ES> % 4 == 0 ? 4 : OW<ES> % 2 == 0 ? 2 : 1;      // of one output store
+    template <int ES> static constexpr bool MAY_THROUGH = ES == 1 && VW<ES> >= 2 && OW<ES> == VW<ES>;      // see launch_prune_rows
 };
 
 __device__ inline void unpack_word(uint32_t w, float* f, float) { f[0] = __uint_as_float(w); }
@@ -61,7 +64,8 @@ __global__ __launch_bounds__((PruneUnit<TIN, N>::MAX_THREADS)) void k_prune_rows
     typedef PruneUnit<TIN, N> PU;
     constexpr int ES = OUT >= 2 ? 2 : 1, ESI = PU::ESI, CH = PU::CH, EPW = 4 / ESI, L = 2 * N;
     constexpr int CW = 4 * EPW * ES / 4;                  // output dwords per input vector
-    constexpr int OW = CH * CW;                           // output dwords per unit
+    constexpr int OW = PU::template OW<ES>, VW = PU::template VW<ES>;
+    static_assert(OW == CH * CW, "output dwords per unit");
     __shared__ float red[PU::MAX_THREADS / 64];
     const int64_t o = blockIdx.x;
     const int t = threadIdx.x, T = blockDim.x;
@@ -162,22 +166,17 @@ __global__ __launch_bounds__((PruneUnit<TIN, N>::MAX_THREADS)) void k_prune_rows
             else ow[k] = code[2 * k] | (code[2 * k + 1] << 16);
         }
         uint32_t* dst = out + (int64_t)u * OW;
-        constexpr int VW = OW % 4 == 0 ? 4 : OW % 2 == 0 ? 2 : 1;
         if (vec_out && (u + 1) * CH <= nvec) {
+            auto put = [&](auto* p, auto x) __attribute__((always_inline)) {
+                if constexpr (PU::template MAY_THROUGH<ES>) {
+                    if (through) store_through(p, x);
+                    else *p = x;
+                } else *p = x;
+            };
 #pragma unroll
             for (int k = 0; k < OW / VW; ++k) {
-                if constexpr (VW == 4) {
-                    uint4* const p = reinterpret_cast<uint4*>(dst) + k;
-                    const uint4 x = make_uint4(ow[4 * k], ow[4 * k + 1], ow[4 * k + 2], ow[4 * k + 3]);
-                    if (through) store_through(p, x);
-                    else *p = x;
-                }
-                else if constexpr (VW == 2) {
-                    uint2* const p = reinterpret_cast<uint2*>(dst) + k;
-                    const uint2 x = make_uint2(ow[2 * k], ow[2 * k + 1]);
-                    if (through) store_through(p, x);
-                    else *p = x;
-                }
+                if constexpr (VW == 4) put(reinterpret_cast<uint4*>(dst) + k, make_uint4(ow[4 * k], ow[4 * k + 1], ow[4 * k + 2], ow[4 * k + 3]));
+                else if constexpr (VW == 2) put(reinterpret_cast<uint2*>(dst) + k, make_uint2(ow[2 * k], ow[2 * k + 1]));
                 else dst[k] = ow[k];
             }
         } else {
@@ -234,12 +233,11 @@ static bool launch_prune_rows(const TIN* W, int64_t O, int64_t K, uint8_t* Wq, f
     const int64_t nunits = (K + PU::E - 1) / PU::E;
     if ((K * PU::ESI) % 16 != 0 || ((uintptr_t)W & 15) || ((uintptr_t)Wq & 3) || nunits > (int64_t)PU::MAXU * PU::MAX_THREADS) return false;
     const int T = (int)((nunits + PU::MAXU - 1) / PU::MAXU + 63) / 64 * 64;
-    constexpr int OW = PU::CH * (4 / PU::ESI) * ES;
-    constexpr int VB = OW % 4 == 0 ? 16 : OW % 2 == 0 ? 8 : 4;           // bytes of one output store
+    constexpr int VB = 4 * PU::template VW<ES>;                          // bytes of one output store
     const int vec_out = (K * ES) % VB == 0 && ((uintptr_t)Wq % VB) == 0;
-    // Stores through the L2 (store_through): 8-bit codes of 4 MB and more, a unit in one store of 8 or 16 bytes (time over plain stores 0.90 .. 0.99, 1 MB 1.03; 16-bit codes 1.03, units in
-    // several stores 1.34).
-    const bool through = ES == 1 && OW >= 2 && OW * 4 == VB && O * K >= (4 << 20);
+    // Stores through the L2 (store_through): 8-bit codes of 4 MB and more, a unit in one store of 8 or 16 bytes (time over plain
+    // stores 0.90 .. 0.99, 1 MB 1.03; 16-bit codes 1.03, units in several stores 1.34).
+    const bool through = PU::template MAY_THROUGH<ES> && O * K >= (4 << 20);
     hipLaunchKernelGGL((k_prune_rows<TIN, OUT, N>), dim3((unsigned)O), dim3(T), 0, st, W, (int)K, (int)nunits, Wq, s_w, vec_out,
                        O * K * PU::ESI >= CACHED_BYTES, through);
     return true;

@@ -44,3 +44,21 @@ def test_wait_states_behind_a_store_of_16_bytes(tmp_path):
     (tmp_path / "probe.hip").write_text(PROBE)
     states = _own_wait_states(_assembly(tmp_path / "probe.hip", tmp_path / "probe.s"))
     assert states and min(states) >= 2, states
+
+
+def test_pruning_has_them_only_where_they_are_taken(tmp_path):
+    """k_prune_rows<TIN, OUT, N>: 8-bit codes (OUT 0 and 1) whose unit, the fewest blocks of 2N weights that fill 16-byte vectors, is one store of 8 or 16 bytes."""
+    text = _assembly(os.path.join(build.CSRC, "prune_quant.hip"), tmp_path / "prune_quant.s")
+    have = set()
+    for name, body in re.findall(r"^(_ZN2ss12k_prune_rows\w+):(.*?)s_endpgm", text, re.M | re.S):
+        tin, out, n = re.match(r"_ZN2ss12k_prune_rowsI(\w)Li(\d)ELi(\d)E", name).groups()
+        if " sc0 sc1" in body:
+            have.add(({"f": 4, "t": 2}[tin], int(out), int(n)))
+    wanted = set()
+    for size in (2, 4):
+        for n in range(2, 9):
+            block = 2 * n * size
+            codes = next(b for b in (1, 2, 4) if b * block % 16 == 0) * 2 * n
+            if codes in (8, 16):
+                wanted |= {(size, 0, n), (size, 1, n)}
+    assert have == wanted, (sorted(have - wanted), sorted(wanted - have))
