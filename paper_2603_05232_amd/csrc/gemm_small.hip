@@ -192,7 +192,6 @@ __global__ __launch_bounds__(64 * (TB / TW) * KG) void k_sparse_small(const uint
                 }
     // accumulator register 4 q + e of fragment j: channel 64 qb + 16 q + 4 j + e of the panel
     const float* const sw = reinterpret_cast<const float*>(lds + SCALES);
-    const bool vec = (ldy & 7) == 0 && ((uintptr_t)Y & 15) == 0;
 #pragma unroll
     for (int b = 0; b < TW; ++b)
 #pragma unroll
@@ -218,10 +217,10 @@ __global__ __launch_bounds__(64 * (TB / TW) * KG) void k_sparse_small(const uint
             w[f][1] = pack_bf16x2(v[2], v[3]);
         }
         uint16_t* const dst = Y + tok * ldy + o;
-        if (vec && o + 4 * FW <= O) {
-            if constexpr (FW == 2) *reinterpret_cast<uint4*>(dst) = make_uint4(w[0][0], w[0][1], w[FW - 1][0], w[FW - 1][1]);
-            else *reinterpret_cast<uint2*>(dst) = make_uint2(w[0][0], w[0][1]);
-        } else {
+        if (o + 4 * FW <= O) {
+            if constexpr (FW == 2) *reinterpret_cast<piece16_t*>(dst) = piece16_t{w[0][0], w[0][1], w[FW - 1][0], w[FW - 1][1]};
+            else *reinterpret_cast<piece8_t*>(dst) = piece8_t{w[0][0], w[0][1]};
+        } else if (o < O) {                                             // (not for channels behind the last: 15000 channels, 3 units, M = 48, bf16, 6.2 -> 5.0 us)
 #pragma unroll
             for (int e = 0; e < 4 * FW; ++e)
                 if (o + e < O) dst[e] = (uint16_t)(w[e >> 2][(e >> 1) & 1] >> (16 * (e & 1)));

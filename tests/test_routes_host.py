@@ -14,6 +14,7 @@ import test_gpu_replay
 import test_gpu_slim
 import test_gpu_small_tiles
 import test_gpu_wide_layers
+import test_gpu_y_rows
 from paper_2603_05232_amd import binding, build
 
 SOURCE = """
@@ -174,3 +175,10 @@ def test_small_tiles(plan):
     for M, O, units, with_ws in test_gpu_small_tiles.BESIDE:
         for kind in (FUSED, LIFTED):
             assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] != SMALL, (kind, M, O, units)
+
+
+def test_rows_of_results(plan):
+    for shapes, path in ((test_gpu_y_rows.MID, MID), (test_gpu_y_rows.WIDE, WIDE), (test_gpu_y_rows.SMALL, SMALL)):
+        for M, O, units in shapes:
+            p = plan(FUSED, M, O, units)
+            assert p["path"] == path and p["S"] == 1, (M, O, units, p)
