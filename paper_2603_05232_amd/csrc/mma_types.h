@@ -239,10 +239,12 @@ inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
 //     0.54 .. 1.04 (mean 0.86 / 0.82), 4 to 9 units, which stay on gemm_skinny.hip, 0.90 .. 1.11 / 0.86 .. 1.10; split 0.83 .. 2.2, so those stay where they are
 //   split, M <= 32 0.70 .. 1.00 (0.86) / 0.53 .. 1.01 (0.75), M = 33 .. 64 0.42 .. 1.00 (0.65) / 0.40 .. 1.08 (0.58)
 //   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.98 / 0.87 .. 1.04 (5200 lines and more to 1.09)
+//   three units, 33 to 48 tokens, on the tiles of three groups 0.97 .. 1.08 of the few-token kernel of before, on the 64-token tiles of gemm_mid.hip 0.71 .. 0.96 / 0.71 .. 1.03, which take them;
+//     with 64 tokens level (0.82 .. 1.00 and 0.78 .. 0.94), and off a 16-byte line of Y the small tiles are the faster (0.54 .. 0.79 and 0.55 .. 0.87)
 // Beyond those lines: M <= 32 1.03 .. 2.2, M <= 64 1.04 .. 1.8, M > 64 0.9 .. 1.9 (all with the first form of the kernel, groups of a wavefront for each 32 tokens).
 inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroups, bool fused, bool split)
 {
-    if (t.fw == 0) return false;
+    if (t.fw == 0 || (M <= 48 && units < 4)) return false;
     const int64_t lines = units * (32 * t.tb + t.fw * (fused ? 30 : 20));
     if (M <= 16) return !split && (t.fw == 1 || units >= 12);
     if (!split) return true;

@@ -11,11 +11,11 @@ pytestmark = pytest.mark.gpu
 # tokens, channels, units per row, with a workspace, fragments, blocks of 32 tokens
 SHAPES = [(8, 36 * 128, 30, True, 1, 1), (16, 64 * 128 - 1, 40, True, 1, 1), (17, 5, 4, True, 1, 1), (32, 64 * 128, 5, False, 1, 1), (33, 32 * 128 - 3, 6, True, 1, 1), (64, 28 * 128, 28, True, 1, 1), (100, 300, 19, True, 1, 1), (1000, 2 * 128 - 5, 9, True, 1, 1), (63, 1000, 131, False, 1, 1),
           (12, 96 * 128 - 2, 12, True, 2, 1), (20, 65 * 128, 7, True, 2, 1), (64, 64 * 128 - 1, 30, True, 2, 1), (129, 24 * 128 + 4, 22, True, 2, 1), (31, 127 * 128, 90, False, 2, 1), (700, 5 * 128, 4, False, 2, 1),
-          (33, 65 * 128, 3, True, 2, 2), (65, 60 * 128 - 7, 3, True, 2, 2), (250, 32 * 128, 41, True, 2, 2), (128, 64 * 128 - 9, 100, False, 2, 2),
+          (49, 65 * 128, 3, True, 2, 2), (65, 60 * 128 - 7, 3, True, 2, 2), (250, 32 * 128, 41, True, 2, 2), (128, 64 * 128 - 9, 100, False, 2, 2),
           (256, 42 * 128, 35, True, 2, 3), (193, 42 * 128 - 5, 8, False, 2, 3), (90, 127 * 128, 2, True, 2, 3),
           (128, 128 * 128 - 100, 12, True, 2, 4), (512, 32 * 128, 31, True, 2, 4), (97, 120 * 128, 5, False, 2, 4), (4000, 4 * 128 - 3, 6, True, 2, 4)]
-# beside them: split rows of more lines, fewer units than groups on both tiles, more panels, and few tokens
-BESIDE = [(32, 20 * 128, 60, True), (40, 300, 64, True), (128, 20 * 128, 64, True), (40, 300, 1, True), (64, 129 * 128, 5, False), (129, 65 * 128, 20, False), (16, 300, 90, True), (16, 65 * 128, 11, True)]
+# beside them: split rows of more lines, fewer units than groups and three with up to 48 tokens, more panels, and few tokens
+BESIDE = [(33, 65 * 128, 3, True), (48, 727, 3, False), (32, 20 * 128, 60, True), (40, 300, 64, True), (128, 20 * 128, 64, True), (40, 300, 1, True), (64, 129 * 128, 5, False), (129, 65 * 128, 20, False), (16, 300, 90, True), (16, 65 * 128, 11, True)]
 
 
 @pytest.mark.parametrize("dtype,N", [("i8", 4), ("bf16", 4), ("fp8", 3), ("fp16", 5)])
