@@ -318,7 +318,10 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
 //             56 units: M = 1 11.8 against 11.5, M = 16 12.4 against 13.9; 48 units: M = 16 11.0 against 10.7, M = 32 11.3
 //             against 12.8); lifted rows by two_groups.  The few-token kernels otherwise (28 units, 3584 -> 4608, M = 1: 7.8 against 10.4), up to 16 tokens
-//             mostly those of 16 channels a workgroup (slim_pays).
+//             mostly those of 16 channels a workgroup (slim_pays).  Half as many panels as compute units, 16 to 32 tokens: the stream has one workgroup for a panel,
+//             small tiles two, and unlifted rows are streamed the faster from HBM once they are long.  Small tiles over the stream, 900 calls, all types, from HBM / hot,
+//             means by units: 4 to 39 0.86 .. 0.90 / 0.62 .. 0.85, 40 to 42 0.89 .. 0.97, 43 and 44 1.05, 48 to 63 1.00 .. 1.03 / 0.76, 84 to 130 1.08 .. 1.14 / 0.76
+//             (at most 1.20); lifted rows run on two groups of wavefronts there.
 // M <= 64 and 257 .. 512 panels, fused 97 .. 128 tokens and 257 .. 384 panels: workgroups of five, six or eight fragments (gemm_wide.hip), one for each
 //             compute unit.  Time over that of a panel for each workgroup, 16 units and more, weights from HBM / hot: M <= 64, INT8, bf16 and fp8 lifted, 120 calls
 //             0.64 .. 0.98 / 0.72 .. 1.11 (3584 -> 37888 at M = 1: INT8 29.3 -> 22.1, bf16 53.5 -> 37.9).  Fused, 257 .. 384 panels, two cards, means by tokens: 65 0.94 and
@@ -377,6 +380,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
     const int S = mid_splits(kind, M, O, units, ws_bytes);
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
     const bool mid = wide || M > 32 || (S > 1 && 2 * units + M >= 128);
+    if (kind == SS_KIND_FUSED && wide && M <= 32 && units > 42) return {SS_PATH_MID, S};
     if (!wide && slim_pays(M, O, units, cus, mid)) return {SS_PATH_SLIM, 1};
     if (small_pays(M, units, small, small.fw ? small_workgroups(M, O, small) : 0, kind == SS_KIND_FUSED, mid && S > 1)) return {SS_PATH_SMALL, 1, 0, small};
     return mid ? ss_plan{SS_PATH_MID, S} : ss_plan{SS_PATH_SKINNY, 1};

@@ -153,6 +153,16 @@ def test_stream_of_a_panel(dtype, fused, M, O, units, with_ws):
     _linear(M, O, max(K, 2 * N), N, dtype, fused, with_ws, units)
 
 
+# the same on half as many panels as compute units, unlifted rows of more than 42 units
+LONG_ROWS = [(16, 128 * 128, 43), (25, 128 * 128 - 5, 68), (32, 128 * 128, 97)]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
+@pytest.mark.parametrize("M,O,units", LONG_ROWS)
+def test_stream_of_half_as_many_panels(dtype, M, O, units):
+    _linear(M, O, _rows(units, 4, dtype, True), 4, dtype, True, False, units)
+
+
 # packed weights of 80 MB and more, which are loaded non-temporally: unsplit panels and split rows, the weight stream (3 tokens) and tiles of 64 tokens
 # (8-bit types; 16-bit ones from 256 MB on)
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])

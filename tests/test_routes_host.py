@@ -102,6 +102,11 @@ def test_up_to_32_tokens(plan):
         for kind in (FUSED, LIFTED):
             p = plan(kind, M, O, units, 1 << 30 if with_ws else 0)
             assert p["stream"] and (p["S"] > 1) == with_ws, (kind, M, O, units)
+    for M, O, units in test_gpu_mid_tiles.LONG_ROWS:
+        for ws in (0, 1 << 30):
+            p = plan(FUSED, M, O, units, ws)
+            assert p["path"] == MID and p["stream"] and p["S"] == 1, (M, O, units, p)
+            assert plan(FUSED, M, O, 42, ws)["path"] == plan(FUSED, M, 127 * 128, units, ws)["path"] == SMALL
 
 
 def test_large_weights(plan):
