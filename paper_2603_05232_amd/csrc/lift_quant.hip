@@ -91,7 +91,7 @@ __global__ __launch_bounds__(THREADS) void k_act_lift_quant(const TIN* __restric
                         else
                             w[k] = quant1<OUT>(f[2 * k], r) | (quant1<OUT>(f[2 * k + 1], r) << 16);
                     }
-                    if constexpr (OW == 1) put(out32 + idx, w[0]);
+                    if constexpr (OW == 1) out32[idx] = w[0];
                     else if constexpr (OW == 2) put(reinterpret_cast<uint2*>(out32) + idx, make_uint2(w[0], w[1]));
                     else put(reinterpret_cast<uint4*>(out32) + idx, make_uint4(w[0], w[1], w[2], w[3]));
                 }
@@ -189,11 +189,7 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const int Kp = (int)lifted_ld(K, N, ES);
     const int Kz = (int)lift_lds_elems(K, N, ES);
     const bool line_ok = (K % IV::N == 0) && (ldx % IV::N == 0) && (((uintptr_t)X & 15) == 0);
-    // Stores through the L2 (store_through): 8-bit codes, 4 to 32 MB of them, unless a lane's stores are of four bytes.  Time over plain stores: the kernel alone, below 1 MB 1.03 .. 1.06, 1 to 4 MB
-    // 0.86 .. 1.05, more 0.85 .. 1.04 (bf16 -> fp8 2048 x 4096 7.7 -> 7.0 us, with lifting 10.1 -> 8.8); with its GEMM, 4 to 32 MB, M = 300 .. 5000, 0.93 .. 1.00 (bf16 -> fp8 2048 x 8192, 8192 -> 4096 63.1 ->
-    // 61.4 us).  fp32 to 8 bits without lifting 0.98 .. 1.05; beyond 32 MB, which the L2s do not hold, the kernel gains 1 % and the GEMM behind it loses as much (fp32 -> INT8 4:6, 8192 x 6144, both
-    // 1.014).  16-bit codes with their GEMM: rows of 1024 and 2048 elements 1.05 .. 1.18 (fp32 -> bf16 5000 x 1024, 1024 -> 3008 34.1 -> 40.3 us), longer ones 0.95 .. 1.06 without a line to draw.
-    const bool through = ES == 1 && M * Kp >= (4 << 20) && M * Kp <= (32 << 20) && !(N == 2 && line_ok && IV::N == 4);
+    const bool through = lift_through(ES, IV::N, M, Kp, N);
     const bool element_ok = (uintptr_t)X % sizeof(TIN) == 0;
     // a ragged row: up to IV::N - 1 codes more in LDS, ahead of it in its first line
     const int64_t nvec = K / IV::N;                           // whole 16-byte vectors per row, at most
@@ -202,7 +198,9 @@ static ss_status launch_lift(const void* X, int64_t M, int64_t K, int64_t ldx, i
     const uint32_t inv = N > 2 ? (uint32_t)(((1ull << 32) + N - 2) / (N - 1)) : 0u;
     const TIN* x = static_cast<const TIN*>(X);
     uint8_t* xl = static_cast<uint8_t*>(XL);
-#define SS_LQ(MAXV, T, RAGGED) hipLaunchKernelGGL((through ? k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, (OUT < 2)> : k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, false>), grid, dim3(T), RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
+#define SS_LQ(MAXV, T, RAGGED) \
+    hipLaunchKernelGGL((through ? k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, (OUT < 2)> : k_act_lift_quant<TIN, OUT, MAXV, T, RAGGED, false>), grid, dim3(T), \
+                       RAGGED ? ragged_bytes : lds_bytes, st, x, ldx, (int)K, N, xl, s_x, Kp, Kz, inv)
 #define SS_LQ_ROWS(RAGGED)                             \
     if (spread && nvec <= 2 * 512) SS_LQ(2, 512, RAGGED);        \
     else if (spread && nvec <= 2 * 1024) SS_LQ(2, 1024, RAGGED); \

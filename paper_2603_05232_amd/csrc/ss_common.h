@@ -86,7 +86,6 @@ __device__ inline void store_once(uint4* p, uint4 v)
 // written through, it leaves while the kernel still reads.  Where a wavefront writes whole lines and megabytes of
 // them: part of a line goes to memory as such (fp32 4:6 pruning 1.34 of the time), and a kernel of little output waits for the acknowledgement (1.03 .. 1.06).  Partial sums
 // of split rows gain nothing (four layers at M = 64 1.009, M = 256 0.997): their kernels write at their end.
-__device__ inline void store_through(uint32_t* p, uint32_t v) { asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory"); }
 __device__ inline void store_through(uint2* p, uint2 v)
 {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

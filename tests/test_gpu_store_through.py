@@ -1,4 +1,5 @@
-"""Quantisation, lifting and pruning on either side of the lines (4 MB of output, quantiser also 32 MB) between which they store through the L2: the rows of one call are those of calls on a few rows each."""
+"""Quantisation, lifting and pruning on either side of the lines between which they store through the L2 (pruning from 4 MB of output; the quantiser from 4 to 16 MB with short rows, to 8 MB
+with longer ones): the rows of one call are those of calls on a few rows each."""
 import pytest
 import torch
 
@@ -7,12 +8,19 @@ from paper_2603_05232_amd import binding
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("act,dtype,K,N", [("bf16", "i8", 4096, 2), ("bf16", "fp8", 4096, 4), ("fp32", "fp8", 4096, 2), ("fp32", "i8", 1003, 3), ("bf16", "bf16", 2051, 5), ("fp32", "fp16", 1024, 2)])
-@pytest.mark.parametrize("megabytes", [4, 32])
-@pytest.mark.parametrize("beyond", [0, 1])
-def test_quantiser(act, dtype, K, N, megabytes, beyond):
-    row = binding.slide_lifted_ld(K, N, dtype) * (1 if dtype in ("i8", "fp8") else 2)
-    M = (megabytes << 20) // row + beyond
+# whole and ragged rows, from either type, lifted and not; the last MB with stores through the L2
+ROWS = [("bf16", "i8", 1024, 2, 16), ("bf16", "fp8", 1671, 2, 16), ("bf16", "fp8", 4096, 4, 8), ("fp32", "fp8", 2048, 4, 8), ("fp32", "i8", 1003, 3, 16), ("bf16", "i8", 2051, 5, 8)]
+
+
+def rows_of(megabytes, beyond, dtype, K, N):
+    return (megabytes << 20) // binding.slide_lifted_ld(K, N, dtype) + beyond
+
+
+@pytest.mark.parametrize("act,dtype,K,N,last", ROWS)
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("beyond", [-1, 1])
+def test_quantiser(act, dtype, K, N, last, first, beyond):
+    M = rows_of(4 if first else last, beyond, dtype, K, N)
     gen = torch.Generator(device="cuda").manual_seed(K)
     X = torch.randn((M, K), generator=gen, device="cuda").to(torch.float32 if act == "fp32" else torch.bfloat16)
     q, s = binding.act_lift_quant(X, N, dtype)

@@ -7,7 +7,8 @@ import subprocess
 
 import pytest
 
-from paper_2603_05232_amd import build
+import test_gpu_store_through
+from paper_2603_05232_amd import binding, build
 
 PROBE = """
 #include "ss_common.h"
@@ -62,3 +63,41 @@ def test_pruning_has_them_only_where_they_are_taken(tmp_path):
             if codes in (8, 16):
                 wanted |= {(size, 0, n), (size, 1, n)}
     assert have == wanted, (sorted(have - wanted), sorted(wanted - have))
+
+
+RULE = """
+#include "quant_common.h"
+#include <stdio.h>
+int main()
+{
+    int es, vec, N; long long M, row;
+    while (scanf("%d %d %lld %lld %d", &es, &vec, &M, &row, &N) == 5) printf("%d\\n", (int)ss::lift_through(es, vec, M, row, N));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def through(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if shutil.which(hipcc) is None:
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("rule")
+    (d / "rule.cpp").write_text(RULE)
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-I" + os.path.join(build.ROOT, "include"), "-I" + build.CSRC,
+                    str(d / "rule.cpp"), "-o", str(d / "rule")], check=True)
+
+    def ask(es, vec, M, row, N):
+        return subprocess.run([str(d / "rule")], input=f"{es} {vec} {M} {row} {N}\n", stdout=subprocess.PIPE, text=True, check=True).stdout.strip() == "1"
+    return ask
+
+
+def test_quantiser_rule(through):
+    for act, dtype, K, N, last in test_gpu_store_through.ROWS:
+        vec, row = (4 if act == "fp32" else 8), binding.slide_lifted_ld(K, N, dtype)
+        for megabytes, beyond, expected in ((4, -1, False), (4, 1, True), (last, -1, True), (last, 1, False)):
+            assert through(1, vec, test_gpu_store_through.rows_of(megabytes, beyond, dtype, K, N), row, N) == expected, (act, dtype, K, N, megabytes, beyond)
+    # rows that a GEMM of few channels would then wait for: unlifted ones of more than 1792 bytes, those of 2048 bytes, lifted long ones of more than 8 MB; 16-bit codes, and stores of four bytes
+    for row in (1920, 2048, 4096, 18944):
+        assert not any(through(1, 8, (mb << 20) // row, row, 2) for mb in (5, 7, 12, 24))
+    assert not through(1, 8, 2600, 2048, 4) and not through(1, 4, 2600, 2048, 3) and not through(1, 8, 3000, 4096, 4) and through(1, 8, 1500, 4096, 4)
+    assert not through(2, 8, 3000, 2048, 4) and not through(1, 4, 5000, 1024, 2)
