@@ -109,7 +109,7 @@ def test_qwen25_7b_float_m8192(dtype, name, K, O):
 @pytest.mark.parametrize("M", [128, 256])
 @pytest.mark.parametrize("name,K,O", [synth.QWEN25_7B[0], synth.QWEN25_7B[3]])
 def test_qwen25_7b_mid_m_with_workspace(dtype, M, name, K, O):
-    """Token counts between decode and prefill: 128 x 128 tiles with the k range split through a workspace."""
+    """Token counts between decode and prefill, with a workspace: small unsplit tiles (qkv in 8-bit types), 128 x 128 tiles with the k range split (the others)."""
     Y, Yd, sample, ref = _run_and_sample(M, K, O, 4, dtype, seed=M + 1, use_workspace=True)
     if dtype == "i8":
         assert np.array_equal(sample(Y), ref["Y"])
@@ -122,9 +122,9 @@ def test_qwen25_7b_mid_m_with_workspace(dtype, M, name, K, O):
 @pytest.mark.parametrize("M,O", [(3, 40), (65, 16)])
 def test_longest_rows_int8(M, O):
     """Rows at the documented maximum of the GEMMs (2^23 bytes; here K' = 65535 units of 128 bytes) on the
-    few-token kernels (M = 3) and the 128 x 128-tile kernels with and without split (M = 65): 32-bit lane offsets
-    and unit counters at their limits.  Operands are generated quantised (the lifting kernel keeps a row in LDS and
-    stops at 64 KiB); the oracle lifts and multiplies."""
+    kernels of 16 channels a workgroup (M = 3) and of small tiles (M = 65) without a workspace, on the weight stream and 128 x 128 tiles
+    in split rows with one: 32-bit lane offsets and unit counters at their limits.  Operands are generated quantised (the lifting kernel keeps a row in
+    LDS and stops at 64 KiB); the oracle lifts and multiplies."""
     from oracle import gemm_ref
     N = 4
     K = 65535 * 128 * 2 // 3                                   # K' = 1.5 K = 65535 * 128

@@ -34,8 +34,8 @@ def test_fused_gemm_int8(M, O, K):
     assert np.array_equal(bits16(Y), ref["Y"])
 
 
-# shapes that take the few-token kernels (M <= 64: one and two token blocks, single fragments, whole panels, eight
-# wavefronts) and the 128 x 128-tile kernels, with and without a workspace (k range split through it)
+# few tokens (16 channels a workgroup, small tiles, split rows of the weight stream and of 64-token tiles) and 128 x 128 or small tiles, with and without
+# a workspace (through which long rows are split)
 SMALL = [(1, 384, 128), (1, 4608, 3584), (7, 640, 1024), (16, 37888 // 8, 512), (32, 130, 2048), (33, 3584, 1024), (64, 260, 18944 // 2),
          (16, 3584, 18944), (64, 3584, 18944), (65, 512, 512), (100, 256, 128), (129, 300, 256), (70, 130, 384), (128, 4608, 3584), (200, 700, 1152), (256, 3584, 4736), (1024, 1100, 640)]
 
@@ -188,12 +188,15 @@ def test_fused_random_shapes_float_end_to_end(dtype, M, O, K, with_ws):
     _float_gemm_check(bits16(Y), ref, dtype)
 
 
-@pytest.mark.parametrize("M", [16, 128, 600])
-def test_fused_hip_graph_replay(M):
-    """Quantisation + fused GEMM (few-token kernel; 128 x 128 tiles with split k and their reduction, one and five token tiles)
+REPLAYED = [(16, 2048, False), (128, 2048, False), (600, 2048, False), (64, 6656, True), (128, 6656, True), (600, 6656, True)]      # tokens, elements per row, split
+
+
+@pytest.mark.parametrize("M,K,split", REPLAYED)
+def test_fused_hip_graph_replay(M, K, split):
+    """Quantisation + fused GEMM (16 channels a workgroup; small tiles; tiles of 64 and 128 tokens with split k and their reduction, one and five token tiles)
     recorded into a HIP graph: nothing is allocated and nothing synchronises.  Every replay is checked against the oracle,
     with new activations written into the captured input buffer between replays."""
-    K, O = 2048, 640
+    O = 640
     W = synth.weights(O, K, seed=3)
     Wq, s_w = binding.slide_prune_quant(dev(W), N, "i8")
     w_vals, w_meta = binding.slide_decompose_fused(Wq, N, "i8")
@@ -202,8 +205,9 @@ def test_fused_hip_graph_replay(M):
     Xq, s_x = binding.act_lift_quant(x_in, 2, "i8")              # warm-up outside the capture (first-use set-up)
     Y = torch.empty((M, O), dtype=torch.bfloat16, device=DEV)
     n = binding.slide_gemm_workspace_bytes(M, O, K, "i8")
-    ws = torch.empty((max(n, 16),), dtype=torch.uint8, device=DEV)
+    ws = torch.full((max(n, 16),), 0x5A, dtype=torch.uint8, device=DEV)
     binding.slide_sparse_gemm_fused(Xq, s_x, w_vals, w_meta, s_w, O, K, N, "i8", out=Y, workspace=ws)
+    assert bool((ws != 0x5A).any()) == split                     # partial sums were written
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):

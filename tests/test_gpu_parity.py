@@ -340,16 +340,21 @@ def _workspace(M, O, Kp, dtype, fill, scale=1.0):
     return need, torch.full((n,), fill, dtype=torch.uint8, device=DEV)
 
 
+SPLIT = [(4, 100, 384, 8192),       # 3 tiles of 128 x 128, K' = 12288: 96 units (8-bit types)
+         (4, 48, 200, 8192),        # 32 < M <= 64 with long rows
+         (3, 300, 130, 8192),       # ragged tokens and channels, K' = 10928
+         (2, 129, 257, 8192),       # native 2:4
+         (5, 64, 128, 10240),       # K' = 16384
+         (5, 16, 200, 10240),       # long rows of few tokens: weight stream (sparse), few-token kernel (dense)
+         (4, 24, 130, 16384)]       # ... (K' = 24576)
+# shorter rows, which the sparse kernels do not split (small tiles) in 8-bit types; the dense ones do
+SPLIT_DENSE = [(4, 100, 384, 2048), (3, 300, 130, 3072), (2, 129, 257, 4096)]
+
+
 @pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
-@pytest.mark.parametrize("N,M,O,K", [(4, 100, 384, 2048),       # 3 tiles of 128 x 128, K' = 3072: 24 units
-                                     (4, 48, 200, 8192),        # 32 < M <= 64 with long rows
-                                     (3, 300, 130, 3072),       # ragged tokens and channels, K' = 4096
-                                     (2, 129, 257, 4096),       # native 2:4
-                                     (5, 64, 128, 10240),       # K' = 16384
-                                     (5, 16, 200, 10240),       # long rows of few tokens: tiles of 32 tokens (sparse), few-token kernel (dense)
-                                     (4, 24, 130, 16384)])      # ... (K' = 24576)
+@pytest.mark.parametrize("N,M,O,K", SPLIT + SPLIT_DENSE)
 def test_gemm_split_k_with_workspace(dtype, N, M, O, K):
-    """The 128-channel tile kernels (and, for few tokens on long rows, the dense few-token kernel) with the k range split
+    """The 128-channel tile kernels (and, for few tokens on long rows, the weight stream and the dense few-token kernel) with the k range split
     over several workgroups: partial sums go through the caller's workspace and are added in a fixed order.  INT8 must equal the oracle bit for bit (and
     so the call without workspace); floats stay within the GEMM tolerance and are reproducible bit for bit."""
     X = synth.activations(M, K, seed=M + K, n_outliers=2)
@@ -361,8 +366,9 @@ def test_gemm_split_k_with_workspace(dtype, N, M, O, K):
     XL, s_x = binding.act_lift_quant(Xd, N, dtype)
     Xq, s_x2 = binding.act_lift_quant(Xd, 2, dtype)
     need, ws = _workspace(M, O, XL.shape[1], dtype, fill=0xFF)             # 0xFF..: NaN patterns, contents must not matter
-    assert need > 0, "shape chosen so that the k range is split"
+    assert need > 0
     Ys = binding.slide_sparse_gemm(XL, s_x, w_vals, w_meta, s_w, O, dtype, workspace=ws)
+    assert (N, M, O, K) in SPLIT_DENSE or bool((ws != 0xFF).any()), "shape chosen so that the k range is split"
     need_d, ws_d = _workspace(M, O, K, dtype, fill=0x7F)
     Yd = binding.dense_gemm(Xq, s_x2, Wq, s_w, dtype, workspace=ws_d)
     if dtype == "i8":
@@ -455,12 +461,15 @@ def test_random_shapes_float_end_to_end(dtype, N, M, O, K):
 
 
 # ------------------------------------------------------------------ capture into a HIP graph
-@pytest.mark.parametrize("M,use_ws", [(16, False), (128, True)])
-def test_hip_graph_replay(M, use_ws):
-    """The per-call path (lift + quantise, sparse GEMM; with M = 128 the split-k kernels and their reduction) records
+REPLAYED = [(16, 2048, False), (128, 2048, False), (64, 5632, True), (128, 5632, True)]      # tokens, elements per row, split
+
+
+@pytest.mark.parametrize("M,K,split", REPLAYED)
+def test_hip_graph_replay(M, K, split):
+    """The per-call path (lift + quantise, sparse GEMM: 16 channels a workgroup, small tiles, tiles of 64 and 128 tokens with split k and their reduction) records
     into a HIP graph: the library allocates nothing and never synchronises.  Every replay is checked against the
     oracle, with new activations written into the captured input buffer between replays."""
-    N, K, O = 4, 2048, 640
+    N, O = 4, 640
     W = synth.weights(O, K, seed=3)
     Wq, s_w = binding.slide_prune_quant(dev(W), N, "i8")
     w_vals, w_meta = binding.slide_decompose(Wq, N, "i8")
@@ -469,11 +478,12 @@ def test_hip_graph_replay(M, use_ws):
     XL, s_x = binding.act_lift_quant(x_in, N, "i8")              # warm-up outside the capture (first-use set-up)
     Y = torch.empty((M, O), dtype=torch.bfloat16, device=DEV)
     ws = None
-    if use_ws:
+    if M > 16:
         n = binding.slide_gemm_workspace_bytes(M, O, XL.shape[1], "i8")
         assert n > 0
-        ws = torch.empty((n,), dtype=torch.uint8, device=DEV)
+        ws = torch.full((n,), 0x5A, dtype=torch.uint8, device=DEV)
     binding.slide_sparse_gemm(XL, s_x, w_vals, w_meta, s_w, O, "i8", out=Y, workspace=ws)
+    assert (ws is not None and bool((ws != 0x5A).any())) == split          # partial sums were written
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):

@@ -6,16 +6,19 @@ import subprocess
 
 import pytest
 
+import test_gpu_fused
 import test_gpu_large_tiles
 import test_gpu_lifted_tiles
 import test_gpu_mid_tiles
 import test_gpu_narrow_tiles
+import test_gpu_parity
 import test_gpu_replay
 import test_gpu_slim
 import test_gpu_small_tiles
 import test_gpu_wide_layers
 import test_gpu_y_rows
-from paper_2603_05232_amd import binding, build
+import test_zz_no_alloc
+from paper_2603_05232_amd import binding, build, synth
 
 SOURCE = """
 #include "mma_types.h"
@@ -34,8 +37,8 @@ int main()
     }
 }
 """
-MID, NARROW, TILE, WIDE, SLIM, SMALL = 1, 2, 3, 4, 5, 6
-LIFTED, FUSED = 0, 1
+SKINNY, MID, NARROW, TILE, WIDE, SLIM, SMALL = range(7)
+LIFTED, FUSED, DENSE = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -152,6 +155,14 @@ def test_replayed_routes(plan):
             assert p["groups"] and not with_ws, name
         elif "panel" in name:
             assert p["path"] == MID and p["stream"] and (p["S"] > 1) == with_ws, name
+        elif "sixteen" in name:
+            assert p["path"] == SLIM, name
+        elif "small tiles" in name:
+            assert p["path"] == SMALL and f"{p['small'][0]} x {p['small'][1]}" in name, name
+        elif "few-token" in name:
+            assert p["path"] == SKINNY, name
+        elif "split tiles" in name:
+            assert p["path"] == MID and p["S"] > 1 and ("64" in name) == (M <= 64), name
         elif name == "five fragments a workgroup":
             assert p["path"] == WIDE, name
         elif name == "narrow tiles":
@@ -191,3 +202,33 @@ def test_rows_of_results(plan):
         for M, O, units in shapes:
             p = plan(FUSED, M, O, units)
             assert p["path"] == path and p["S"] == 1, (M, O, units, p)
+
+
+def _lifted_units(K, N):
+    return binding.slide_lifted_ld(K, N, "i8") // 128
+
+
+def test_split_rows(plan):
+    """The INT8 calls that a test names for split rows are split, those for small tiles are not."""
+    many = 1 << 30
+    for split, cases in ((True, test_gpu_parity.SPLIT), (False, test_gpu_parity.SPLIT_DENSE)):
+        for N, M, O, K in cases:
+            p = plan(LIFTED, M, O, _lifted_units(K, N), many)
+            assert (p["path"] == MID and p["S"] > 1) if split else p["path"] == SMALL, (N, M, O, K, p)
+            if not split:
+                assert plan(DENSE, M, O, K // 128, many)["S"] > 1, (M, O, K)
+    for cases, split in ((test_zz_no_alloc.CASES, True), (test_zz_no_alloc.UNSPLIT, False)):
+        for M, O, K in cases:
+            p = plan(LIFTED, M, O, _lifted_units(K, 4), binding.slide_static_scratch_bytes())
+            assert (p["path"] == MID and p["S"] > 1) if split else p["path"] == SMALL, (M, O, K, p)
+    for kind, cases in ((LIFTED, test_gpu_parity.REPLAYED), (FUSED, test_gpu_fused.REPLAYED)):
+        for M, K, split in cases:
+            p = plan(kind, M, 640, K // 128 if kind == FUSED else _lifted_units(K, 4), many)
+            assert (p["path"] == MID and p["S"] > 1) if split else p["path"] == (SLIM if M == 16 else SMALL), (kind, M, K, p)
+    for M in (128, 256):
+        for i, expected in ((0, SMALL), (3, MID)):
+            name, K, O = synth.QWEN25_7B[i]
+            p = plan(LIFTED, M, O, _lifted_units(K, 4), many)
+            assert p["path"] == expected and (p["S"] > 1) == (i == 3), (name, M, p)
+    for M, O, alone in ((3, 40, SLIM), (65, 16, SMALL)):                    # the longest rows
+        assert plan(LIFTED, M, O, 65535)["path"] == alone and plan(LIFTED, M, O, 65535, many)["S"] > 1

@@ -9,6 +9,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+# tokens, channels, elements per row: split rows on 15 tiles of 128 x 128, on fewer (the start of the same scratch array again), and of few tokens; then unsplit ones on small tiles
+CASES = [(300, 640, 8192), (130, 384, 8192), (16, 3584, 18944)]
+UNSPLIT = [(300, 640, 2048), (130, 384, 2048)]
+
+
 def _case(M, O, K, N, seed):
     X = torch.from_numpy(synth.activations(M, K, seed=seed)).to(DEV)
     W = torch.from_numpy(synth.weights(O, K, seed=seed)).to(DEV)
@@ -16,20 +21,20 @@ def _case(M, O, K, N, seed):
     w_vals, w_meta = binding.slide_decompose(Wq, N, "i8")
     XL, s_x = binding.act_lift_quant(X, N, "i8")
     n = binding.slide_gemm_workspace_bytes(M, O, XL.shape[1], "i8")
-    assert 0 < n <= binding.slide_static_scratch_bytes(), "the case must split its k range"
-    ws = torch.empty((n,), dtype=torch.uint8, device=DEV)
+    assert 0 < n <= binding.slide_static_scratch_bytes()
+    ws = torch.full((n,), 0x5A, dtype=torch.uint8, device=DEV)
     Y_ws = binding.slide_sparse_gemm(XL, s_x, w_vals, w_meta, s_w, O, "i8", workspace=ws)
     Y_st = torch.full((M, O), -1.0, dtype=torch.bfloat16, device=DEV)
     binding.slide_sparse_gemm_static(XL, s_x, w_vals, w_meta, s_w, O, "i8", out=Y_st)
     torch.cuda.synchronize()
     assert torch.equal(Y_st.view(torch.int16), Y_ws.view(torch.int16))
+    assert bool((ws != 0x5A).any()) == ((M, O, K) in CASES), "partial sums were written where the k range is split, and nowhere else"
 
 
 def test_static_scratch_matches_workspace_call_twice():
     assert binding.slide_static_scratch_bytes() == 16 << 20
-    _case(300, 640, 2048, 4, seed=1)        # 15 tiles of 128 x 128, k range split
-    _case(130, 384, 2048, 4, seed=2)        # smaller: reuses the start of the same scratch array
-    _case(16, 3584, 18944, 4, seed=3)       # few-token kernels with split k (long rows)
+    for seed, (M, O, K) in enumerate(CASES + UNSPLIT):
+        _case(M, O, K, 4, seed=seed + 1)
 
 
 def test_static_scratch_rejects_bad_arguments():
