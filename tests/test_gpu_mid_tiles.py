@@ -88,11 +88,11 @@ def test_shared_pipelines_and_bands(dtype, M, O, units, N, fused):
     _linear(M, O, _rows(units, N, dtype, fused), N, dtype, fused, False, units)
 
 
-# Both sides of every line of the kernel choice for sparse calls, for 256 compute units: tiles (320, 448, 512) and units
-# per row (12 and 24 fused, 24 and 48 lifted) between 128 x 128 and 256 x 256 tiles; panels (128 and 192) and rows (48 units;
-# 2 units + tokens = 128) between few-token kernels and tiles of 32 and 64 tokens, with the workspace the rows are split
-# in; a rest of a round of exactly one tile per compute unit and of one panel more, and, fused, of up to one 128 x 256 tile (16 units and
-# more).
+# Both sides of lines of the kernel choice for sparse calls, for 256 compute units: tiles (320, 448, 512) and units
+# per row (12 and 24 fused, 24 and 48 lifted) between 128 x 128 and 256 x 256 tiles; panels (128 and 192) between the few-token kernel and the weight
+# stream of 32 tokens, on either side of half as many panels as compute units with 64 tokens (small tiles on both); rows (1 token 64 units, 32 to 64 tokens 48) between
+# unsplit kernels and, with the workspace, split ones; a rest of a round of exactly one tile per compute unit and of one panel more, and, fused, of up to one 128 x 256
+# tile (16 units and more).
 @pytest.mark.parametrize("M,O,units,ws", [(65, 128 * 320, 3, False), (65, 128 * 321, 11, False), (65, 128 * 321, 12, False), (65, 128 * 321, 23, False),
                                           (65, 128 * 321, 24, False), (65, 128 * 448, 12, False), (65, 128 * 449, 23, False), (65, 128 * 449, 24, False),
                                           (65, 128 * 449, 47, False), (65, 128 * 449, 48, False), (65, 128 * 512, 48, False), (65, 128 * 513, 48, False),
@@ -106,7 +106,7 @@ def test_lines_of_the_kernel_choice(M, O, units, ws, fused):
     _linear(M, O, _rows(units, 4, "i8", fused), 4, "i8", fused, ws, units)
 
 
-# one workgroup per compute unit or several, split or not, tokens at the edges of the tiles, 16-bit and lifted forms
+# split rows and unsplit ones (of up to 33 units: small tiles and 128 x 128 ones), tokens at the edges of the tiles, 16-bit and lifted forms
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "fp16"])
 @pytest.mark.parametrize("M,O,units,N,fused", [(1, 520, 72, 4, True), (31, 130, 65, 4, True), (32, 384, 50, 4, True), (33, 260, 48, 4, True), (64, 1100, 57, 4, True),
                                                (65, 128, 9, 4, True), (128, 300, 1, 4, True), (129, 640, 17, 4, True), (200, 4224, 6, 4, True), (300, 10000, 3, 4, True),
@@ -161,6 +161,19 @@ LONG_ROWS = [(16, 128 * 128, 43), (25, 128 * 128 - 5, 68), (32, 128 * 128, 97)]
 @pytest.mark.parametrize("M,O,units", LONG_ROWS)
 def test_stream_of_half_as_many_panels(dtype, M, O, units):
     _linear(M, O, _rows(units, 4, dtype, True), 4, dtype, True, False, units)
+
+
+# the few-token kernel: rows of up to three units for 17 to 32 tokens, on few panels and on up to half as many as compute units; up to 16 tokens short rows on 65 to 128
+# panels and, a workgroup for two fragments, on up to 191
+FEW_TOKENS = [(17, 300, 1), (32, 63 * 128 - 5, 3), (20, 64 * 128, 2), (31, 127 * 128 - 3, 3), (5, 65 * 128, 11), (16, 100 * 128 - 4, 9), (15, 127 * 128, 8),
+              (1, 100 * 128, 11), (15, 129 * 128, 3), (3, 160 * 128 - 1, 8), (15, 191 * 128, 15)]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "fp8", "bf16", "fp16"])
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("M,O,units", FEW_TOKENS)
+def test_few_tokens(dtype, fused, M, O, units):
+    _linear(M, O, _rows(units, 4, dtype, fused), 4, dtype, fused, False, units)
 
 
 # packed weights of 80 MB and more, which are loaded non-temporally: unsplit panels and split rows, the weight stream (3 tokens) and tiles of 64 tokens

@@ -89,11 +89,15 @@ def test_shared_compute_units(plan):
 
 
 def test_lines_of_the_kernel_choice(plan):
-    """Each line of the 65-token rows of test_gpu_mid_tiles.test_lines_of_the_kernel_choice has a row on either side."""
+    """Each line of test_gpu_mid_tiles.test_lines_of_the_kernel_choice has a row on either side."""
     for kind, line, many in ((FUSED, 12, 24), (LIFTED, 24, 48)):
         for panels, units in ((321, line), (449, many)):
             assert plan(kind, 65, 128 * panels, units - 1)["path"] == TILE and plan(kind, 65, 128 * panels, units)["path"] == MID
         assert plan(kind, 65, 128 * 320, 3)["path"] == MID and plan(kind, 65, 128 * 513, 48)["path"] == TILE
+        for M, panels, path in ((15, 191, SKINNY), (15, 192, MID), (16, 127, SKINNY), (16, 128, MID), (64, 127, SMALL), (64, 128, SMALL)):
+            assert plan(kind, M, 128 * panels, 3)["path"] == path, (M, panels)
+        for M, line, path in ((1, 64, SLIM), (32, 48, SMALL), (33, 48, SMALL), (64, 48, SMALL)):
+            assert plan(kind, M, 500, line - 1, 1 << 30)["path"] == path and plan(kind, M, 500, line, 1 << 30)["S"] > 1, (M, line)
 
 
 def test_up_to_32_tokens(plan):
@@ -105,6 +109,9 @@ def test_up_to_32_tokens(plan):
         for kind in (FUSED, LIFTED):
             p = plan(kind, M, O, units, 1 << 30 if with_ws else 0)
             assert p["stream"] and (p["S"] > 1) == with_ws, (kind, M, O, units)
+    for M, O, units in test_gpu_mid_tiles.FEW_TOKENS:
+        for kind in (FUSED, LIFTED):
+            assert plan(kind, M, O, units)["path"] == SKINNY, (kind, M, O, units)
     for M, O, units in test_gpu_mid_tiles.LONG_ROWS:
         for ws in (0, 1 << 30):
             p = plan(FUSED, M, O, units, ws)
