@@ -3,8 +3,8 @@
 // not by the matrix cores.
 //
 // A workgroup of four wavefronts owns FPW x 32 output channels (FPW matrix-instruction fragments, one or, for
-// sparse weights, two: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (4,
-// or 8 when there are fewer workgroups than compute units) split the k range by units of 128 bytes of a row
+// sparse weights, two: as many as still leave at least one workgroup per compute unit) and all tokens; the wavefronts (eight in the dense kernel when there
+// are fewer workgroups than compute units) split the k range by units of 128 bytes of a row
 // (unit u goes to wavefront u mod the number of wavefronts), so every workgroup is
 // four independent load streams, enough of them in flight on every compute unit to keep the memory system
 // busy.  More fragments per workgroup mean fewer re-reads of the token rows (sparse kernel only: the dense
@@ -28,8 +28,6 @@
 
 namespace ss {
 
-// wavefronts per workgroup: 4, or 8 when there are fewer workgroups than compute units (more load streams per unit)
-
 // units a wavefront keeps in flight in registers: 4 where a workgroup is a single fragment (few workgroups, each
 // wavefront a chain of load round trips), 2 where it holds several fragments (many workgroups per compute unit)
 template <int FPW, int TB> constexpr int SK_DEPTH = FPW == 1 ? (TB == 1 ? 4 : 3) : 2;
@@ -41,7 +39,7 @@ template <typename ACC> __device__ inline void sk_zero(ACC& a)
 }
 
 // Sum of the wavefronts' partial accumulators, in wavefront order, returned in wavefront 0.
-template <int SK_WAVES, typename ACC, int TB>
+template <int WAVES, typename ACC, int TB>
 __device__ inline void sk_reduce(ACC (&acc)[TB], uint8_t* red, int wave, int lane)
 {
     // red: [wave 1..][accumulator][reg 16][lane 64] 4-byte words
@@ -56,7 +54,7 @@ __device__ inline void sk_reduce(ACC (&acc)[TB], uint8_t* red, int wave, int lan
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
-        for (int w = 1; w < SK_WAVES; ++w)
+        for (int w = 1; w < WAVES; ++w)
 #pragma unroll
             for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
@@ -127,7 +125,9 @@ __device__ inline void sk_store_partial(const ACC (&acc)[NACC], void* ws, int co
 // not 1.5 times.
 template <int TB, int FPW, int NS> struct SkSparseUnit { v4i a[NS][FPW]; int idx[NS][FPW]; v4i b[TB][4]; };
 
-template <int DT, int TB, int FPW, int SK_WAVES, bool FUSED>
+constexpr int SK_WAVES = 4;       // eight on few workgroups, whose rows have up to three units: 1.01 .. 1.36 of the time (mean 1.05), hot 0.99 .. 1.13 (1.06)
+
+template <int DT, int TB, int FPW, bool FUSED>
 __global__ __launch_bounds__(64 * SK_WAVES) void k_sparse_skinny(const uint8_t* __restrict__ XL, const float* __restrict__ s_x,
                                                                const uint8_t* __restrict__ w_vals, const uint8_t* __restrict__ w_meta,
                                                                const float* __restrict__ s_w, int64_t M, int64_t O, int U, int64_t ldxb,
@@ -268,16 +268,16 @@ __device__ inline int sk_frag_row(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >
 
 template <int TB, int FPW> struct SkDenseUnit { v4i a[FPW][4]; v4i b[TB][4]; };
 
-template <int DT, int TB, int FPW, int SK_WAVES>
-__global__ __launch_bounds__(64 * SK_WAVES) void k_dense_skinny(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
+template <int DT, int TB, int FPW, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_dense_skinny(const uint8_t* __restrict__ Xq, const float* __restrict__ s_x,
                                                               const uint8_t* __restrict__ Wq, const float* __restrict__ s_w, int64_t M,
                                                               int64_t O, int64_t Kb, uint16_t* __restrict__ Y, int64_t ldy, void* __restrict__ ws)
 {
     typedef Mma<DT> MM;
     typedef typename MM::dfrag_t frag_t;
     constexpr int SUB = MM::DENSE_SUB, NSUB = 128 / SUB, RPF = SUB / 32;   // k-bytes per instruction, instructions per unit, 16-byte pieces per fragment
-    __shared__ __attribute__((aligned(16))) uint8_t red[(SK_WAVES - 1) * FPW * TB * 16 * 64 * 4];
-    __shared__ __attribute__((aligned(128))) uint8_t tile[SK_WAVES][FPW * 32 * 128];   // per wavefront: FPW x 32 weight rows x 128 bytes
+    __shared__ __attribute__((aligned(16))) uint8_t red[(WAVES - 1) * FPW * TB * 16 * 64 * 4];
+    __shared__ __attribute__((aligned(128))) uint8_t tile[WAVES][FPW * 32 * 128];   // per wavefront: FPW x 32 weight rows x 128 bytes
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t o0 = (int64_t)blockIdx.x * (32 * FPW);
     const int U = (int)(Kb / 128);
@@ -338,11 +338,11 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_dense_skinny(const uint8_t* _
     const int u0 = (int)((int64_t)blockIdx.y * U / gridDim.y) + wave;
 #pragma unroll
     for (int d = 0; d < D; ++d)
-        if (u0 + d * SK_WAVES < u_end) load(st[d], u0 + d * SK_WAVES);
-    for (int ub = u0; ub < u_end; ub += D * SK_WAVES) {
+        if (u0 + d * WAVES < u_end) load(st[d], u0 + d * WAVES);
+    for (int ub = u0; ub < u_end; ub += D * WAVES) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        const int u = ub + d * SK_WAVES;
+        const int u = ub + d * WAVES;
         if (u >= u_end) continue;
         SkDenseUnit<TB, FPW>& cur = st[d];
         // lines -> wavefront-private LDS tile -> fragments (LDS operations of one wavefront execute in order)
@@ -373,10 +373,10 @@ __global__ __launch_bounds__(64 * SK_WAVES) void k_dense_skinny(const uint8_t* _
                 for (int tb = 0; tb < TB; ++tb) acc[f * TB + tb] = MM::dense(a, b[tb], acc[f * TB + tb]);
             }
         }
-        if (u + D * SK_WAVES < u_end) load(cur, u + D * SK_WAVES);
+        if (u + D * WAVES < u_end) load(cur, u + D * WAVES);
       }
     }
-    sk_reduce<SK_WAVES, typename MM::acc_t, FPW * TB>(acc, red, wave, lane);
+    sk_reduce<WAVES, typename MM::acc_t, FPW * TB>(acc, red, wave, lane);
     if (wave == 0) {
         if (gridDim.y > 1) { sk_store_partial<typename MM::acc_t, FPW * TB>(acc, ws, (int)blockIdx.x, lane); return; }
 #pragma unroll
@@ -452,12 +452,8 @@ static ss_status launch_sparse_one(const void* XL, const float* s_x, const void*
 {
     const int64_t npanels = (O + PANEL - 1) / PANEL;
     const unsigned grid = (unsigned)(npanels * (FRAGS_PER_PANEL / FPW));
-#define SS_SK(F, WAVES) hipLaunchKernelGGL((k_sparse_skinny<DT, TB, F, WAVES, FUSED>), dim3(grid), dim3(64 * WAVES), 0, stream, \
-                       static_cast<const uint8_t*>(XL), s_x, static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, \
-                       static_cast<uint16_t*>(Y), ldy)
-    if (FPW == 1 && (int)grid < cu_count()) SS_SK(1, 8);
-    else SS_SK(FPW, 4);
-#undef SS_SK
+    hipLaunchKernelGGL((k_sparse_skinny<DT, TB, FPW, FUSED>), dim3(grid), dim3(64 * SK_WAVES), 0, stream, static_cast<const uint8_t*>(XL), s_x,
+                       static_cast<const uint8_t*>(w_vals), static_cast<const uint8_t*>(w_meta), s_w, M, O, U, ldxb, static_cast<uint16_t*>(Y), ldy);
     return launch_status();
 }
 
