@@ -1,5 +1,5 @@
-"""Quantisation, lifting and pruning on either side of the lines between which they store through the L2 (pruning from 4 MB of output; the quantiser from 4 to 16 MB with short rows, to 8 MB
-with longer ones): the rows of one call are those of calls on a few rows each."""
+"""Quantisation, lifting and pruning on either side of the lines between which they store through the L2 (pruning from 4 MB of output; the quantiser from 4 MB to 8, 16 or 32 MB,
+by the length of the rows): the rows of one call are those of calls on a few rows each."""
 import pytest
 import torch
 
@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 # whole and ragged rows, from either type, lifted and not; the last MB with stores through the L2
-ROWS = [("bf16", "i8", 1024, 2, 16), ("bf16", "fp8", 1671, 2, 16), ("bf16", "fp8", 4096, 4, 8), ("fp32", "fp8", 2048, 4, 8), ("fp32", "i8", 1003, 3, 16), ("bf16", "i8", 2051, 5, 8)]
+ROWS = [("bf16", "i8", 1024, 2, 16), ("bf16", "fp8", 1671, 2, 16), ("bf16", "i8", 4096, 2, 8), ("bf16", "fp8", 4096, 4, 32), ("fp32", "fp8", 2048, 4, 8), ("fp32", "i8", 1003, 3, 16), ("bf16", "i8", 2051, 5, 8),
+        ("bf16", "fp8", 8192, 2, 32)]
 
 
 def rows_of(megabytes, beyond, dtype, K, N):

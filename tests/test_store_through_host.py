@@ -96,8 +96,10 @@ def test_quantiser_rule(through):
         vec, row = (4 if act == "fp32" else 8), binding.slide_lifted_ld(K, N, dtype)
         for megabytes, beyond, expected in ((4, -1, False), (4, 1, True), (last, -1, True), (last, 1, False)):
             assert through(1, vec, test_gpu_store_through.rows_of(megabytes, beyond, dtype, K, N), row, N) == expected, (act, dtype, K, N, megabytes, beyond)
-    # rows that a GEMM of few channels would then wait for: unlifted ones of more than 1792 bytes, those of 2048 bytes, lifted long ones of more than 8 MB; 16-bit codes, and stores of four bytes
-    for row in (1920, 2048, 4096, 18944):
+    # rows of a length that a GEMM of few channels would wait for; 16-bit codes, and stores of four bytes
+    for row in (1920, 2048, 2944):
         assert not any(through(1, 8, (mb << 20) // row, row, 2) for mb in (5, 7, 12, 24))
-    assert not through(1, 8, 2600, 2048, 4) and not through(1, 4, 2600, 2048, 3) and not through(1, 8, 3000, 4096, 4) and through(1, 8, 1500, 4096, 4)
+    for row in (2048, 3072, 4096, 5504):
+        for N in (2, 4):
+            assert not any(through(1, 8, (mb << 20) // row, row, N) for mb in (9, 12, 24)) and through(1, 8, (5 << 20) // row, row, N) == (N == 4 or row >= 3072)
     assert not through(2, 8, 3000, 2048, 4) and not through(1, 4, 5000, 1024, 2)
