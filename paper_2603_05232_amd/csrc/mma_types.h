@@ -258,16 +258,15 @@ ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const 
 // all types, weights from HBM / hot, M = 1 .. 16:
 //   at most one workgroup per compute unit, not split: 1 to 56 units 0.57 .. 0.83 / 0.55 .. 0.82, without a workspace 72 to 256 units 0.48 .. 0.77 / 0.44 .. 0.88
 //   the same, split, 8 panels and more, by units (M + 8): up to 1000 0.82 .. 1.01 / 0.59 .. 0.89, 1000 .. 1400 0.93 .. 1.33 / 0.66 .. 1.03, more 1.1 .. 2.0.  Fewer
-//     panels would leave most compute units idle, which their ranges do not; unlifted rows of a few tokens, whose units are longer, feel that up to 11 panels: 8 panels, 80
-//     units and more 1.01 .. 1.07 / 0.72, 9 and 95 1.02 .. 1.08 / 0.73, 10 and 105 1.02 .. 1.06 / 0.74, 11 and 110 1.02 / 0.72, shorter ones 0.91 .. 1.04 (means up to 1.00)
+//     panels would leave most compute units idle, which their ranges do not
 //   some compute units with two of them, by units (M + 2): up to 120 0.76 .. 0.99 / 0.76 .. 1.00 (3584 -> 4608 INT8 at M = 1 7.2 -> 6.9 us, hot 5.7 -> 4.4), 120 ..
 //     170 0.88 .. 1.10 / 0.79 .. 0.98
-inline bool slim_pays(int64_t M, int64_t O, int64_t units, int64_t cus, bool fused, bool split)
+inline bool slim_pays(int64_t M, int64_t O, int64_t units, int64_t cus, bool split)
 {
     const int64_t panels = (O + 127) / 128, wgs = 8 * panels;
     if (M > 16 || wgs > 2 * cus) return false;
     if (wgs > cus) return units * (M + 2) <= 120;
-    return !split || (panels >= 8 && units * (M + 8) <= 1000 && (!fused || 2 * units <= 19 * panels));
+    return !split || (panels >= 8 && units * (M + 8) <= 1000);
 }
 
 // Up to 32 tokens of lifted rows on half to two thirds as many panels as compute units: tiles of 32 tokens in two groups of wavefronts (gemm_mid.hip),
@@ -382,7 +381,7 @@ inline ss_plan plan_gemm(ss_kind kind, int64_t M, int64_t O, int64_t units, size
     const bool wide = 4 * tiles >= (M < 16 ? 3 : 2) * cus;
     const bool mid = wide || M > 32 || (S > 1 && 2 * units + M >= 128);
     if (kind == SS_KIND_FUSED && wide && M <= 32 && units > 42) return {SS_PATH_MID, S};
-    if (!wide && slim_pays(M, O, units, cus, kind == SS_KIND_FUSED, mid)) return {SS_PATH_SLIM, 1};
+    if (!wide && slim_pays(M, O, units, cus, mid)) return {SS_PATH_SLIM, 1};
     if (small_pays(M, units, small, small.fw ? small_workgroups(M, O, small) : 0, kind == SS_KIND_FUSED, mid && S > 1)) return {SS_PATH_SMALL, 1, 0, small};
     return mid ? ss_plan{SS_PATH_MID, S} : ss_plan{SS_PATH_SKINNY, 1};
 }

@@ -15,12 +15,9 @@ SHAPES = [(1, 5, 1, False), (16, 130, 2, False), (8, 300, 3, True), (9, 1000, 15
 # beside them: longer split rows, more panels, more tokens, few panels of split rows
 BESIDE = [(1, 12 * 128, 112, True), (16, 8 * 128, 57, True), (1, 33 * 128, 41, True), (16, 40 * 128, 7, True), (1, 65 * 128, 9, True), (17, 300, 16, True), (5, 7 * 128, 64, True)]
 
-# the longest split rows of 8 to 11 panels: lifted ones here, unlifted ones in ranges
-FEW_PANELS = [(1, 8 * 128, 77, True), (3, 9 * 128 - 5, 86, True), (1, 10 * 128, 96, True), (1, 11 * 128, 105, True)]
-
 
 @pytest.mark.parametrize("dtype,N", [("i8", 4), ("bf16", 4), ("fp8", 3), ("fp16", 5)])
-@pytest.mark.parametrize("M,O,units,with_ws", SHAPES + BESIDE + FEW_PANELS)
+@pytest.mark.parametrize("M,O,units,with_ws", SHAPES + BESIDE)
 def test_sixteen_channels(dtype, N, M, O, units, with_ws):
     for fused in ([True, False] if N == 4 else [False]):
         _linear(M, O, _rows(units, N, dtype, fused), N, dtype, fused, with_ws, units)

@@ -188,10 +188,6 @@ def test_sixteen_channels(plan):
             assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] == SLIM, (kind, M, O, units)
         for M, O, units, with_ws in test_gpu_slim.BESIDE:
             assert plan(kind, M, O, units, 1 << 30 if with_ws else 0)["path"] != SLIM, (kind, M, O, units)
-    for M, O, units, with_ws in test_gpu_slim.FEW_PANELS:
-        assert plan(LIFTED, M, O, units, 1 << 30)["path"] == plan(FUSED, M, O, units - 1, 1 << 30)["path"] == SLIM, (M, O, units)
-        p = plan(FUSED, M, O, units, 1 << 30)
-        assert p["path"] == MID and p["S"] > 1, (M, O, units, p)
 
 
 def test_small_tiles(plan):
