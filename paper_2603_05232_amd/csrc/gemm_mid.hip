@@ -446,7 +446,10 @@ __global__ __launch_bounds__(MD_THREADS * KG, (KG == 1 && RING * MidUnit<TM, FUS
         }
     }
     if (order.S > 1) mid_store_partial(acc, ws, item, wave, lane, (int)(M - t_wave));
-    else mid_store<MM::SCALED>(acc, reinterpret_cast<const float*>(lds + SCALES) + PANEL + wt * (32 * TB), reinterpret_cast<const float*>(lds + SCALES) + 16 * FW * wo, Y, ldy, M, O, o_wave, t_wave, lane);
+    else {
+        const float* const sw = reinterpret_cast<const float*>(lds + SCALES);
+        mid_store<MM::SCALED>(acc, sw + PANEL + wt * (32 * TB), sw + 16 * FW * wo, Y, ldy, M, O, o_wave, t_wave, lane);
+    }
 }
 
 // ---- dense ----------------------------------------------------------------------------------------------
@@ -523,7 +526,10 @@ __global__ __launch_bounds__(MD_THREADS) void k_dense_mid(const uint8_t* __restr
         lslot = lslot == RING - 1 ? 0 : lslot + 1;
     }
     if (order.S > 1) mid_store_partial(acc, ws, (int64_t)it.range * order.nt + it.tile, wave, lane, (int)(M - t0) - wt * 64);
-    else mid_store<MM::SCALED>(acc, reinterpret_cast<const float*>(smem + RING * MD_D_UNIT) + PANEL + wt * 64, reinterpret_cast<const float*>(smem + RING * MD_D_UNIT) + 32 * wo, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
+    else {
+        const float* const sw = reinterpret_cast<const float*>(smem + RING * MD_D_UNIT);
+        mid_store<MM::SCALED>(acc, sw + PANEL + wt * 64, sw + 32 * wo, Y, ldy, M, O, panel * PANEL + 32 * wo, t0 + wt * 64, lane);
+    }
 }
 
 }  // namespace ss
@@ -571,7 +577,7 @@ static ss_status launch_sparse_mid_dt(const void* Xq, const float* s_x, const vo
     const int64_t ntiles = npanels * tiles_t;
     // Ring depth: with more workgroups than compute units, as deep as lets two of them share a compute unit's LDS and cover
     // each other's waits.  A workgroup alone: the whole ring is requested at once, so that a deeper one delays the first
-    // unit (3584 -> 4608 at M = 256, 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
+    // unit (3584 -> 4608 at M = 256, which small tiles serve now, in 3 ranges: 20.6 us with five units, 20.4 with four, 20.0 with three), but covers longer
     // waits (5003 -> 4099 fp16 8:10 at M = 777: 65.7, 63.7, 70.9).  32 tokens at most and no more workgroups than compute units:
     // the weight stream of gemm_wide.hip (both sides there), or two groups of wavefronts with a ring of four each (two_groups).
     const bool shared = ntiles * S > cu_count();
@@ -645,9 +651,9 @@ static size_t mid_tile_bytes(ss_kind kind, int64_t M) { return (size_t)MD_TILE *
 // 16th of the tiles x ranges written and read back, and 2 more where the ranges take over 7/8 of the compute units: on two of
 // three cards a split launch of that many workgroups ends 3 to 4 us late (8192 -> 2048 lifted INT8 at M = 192: 16.4 us in 6 ranges of
 // 32 tiles, 16.4 in 8 on one card, 21.3 on others).  The unsplit kernel is fast enough that a few ranges more than
-// that cost more than they save (fused INT8, weights from HBM): 2048 -> 8192 at M = 256 (16 units, 128 tiles) 15.1 us unsplit, 21.0 in 2
-// ranges; 2048 -> 2048 at M = 640 (16 units, 80 tiles) 11.3 unsplit, 16.1 in 2; 4096 -> 4096 at M = 512 (32 units, 128 tiles) 22.4 unsplit, 22.0
-// in 2 (hot 17.4 and 20.4); 18944 -> 3584 at M = 256 (148 units, 56 tiles) 83 unsplit, 33.0 in 4.
+// that cost more than they save (fused INT8 on these tiles, weights from HBM; the first three calls are on small tiles now, gemm_small.hip): 2048 -> 8192
+// at M = 256 (16 units, 128 tiles) 15.1 us unsplit, 21.0 in 2 ranges; 2048 -> 2048 at M = 640 (16 units, 80 tiles) 11.3 unsplit, 16.1 in 2; 4096 -> 4096 at M = 512
+// (32 units, 128 tiles) 22.4 unsplit, 22.0 in 2 (hot 17.4 and 20.4); 18944 -> 3584 at M = 256 (148 units, 56 tiles) 83 unsplit, 33.0 in 4.
 // Over 2520 calls (five operand forms, 12 layers, M = 65 .. 512, three cards) 0.960 of the time before the pipeline with weights from
 // HBM (77 more than 3 % slower) and 0.865 hot (none); a 20th and nothing for the last workgroups 0.974 (188) and 0.891 (49).
 int mid_splits(ss_kind kind, int64_t M, int64_t O, int64_t units, size_t ws_bytes)

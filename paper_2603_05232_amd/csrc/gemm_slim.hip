@@ -1,10 +1,10 @@
 // Sparse GEMMs of up to 16 tokens with a workgroup for every 16 output channels: layers whose 32-channel workgroups (gemm_skinny.hip) leave
 // most compute units idle, and whose k ranges need not be split then.
 //
-// What bounds it.  A compute unit gets about 200 cache lines a microsecond from beyond its L2, so a layer of 4096 channels on half of the
-// compute units waits for loads while the other half has none.  Eight workgroups for a panel put it on all of them.  A workgroup takes rows 8 j .. 8 j + 7
-// of two fragments of the panel: eight rows are one whole line of stored values (rows of all four fragments in runs of four, half
-// lines: 1.05 .. 1.8 of the time), and two workgroups share the lines of index words.  Eight wavefronts take stages of the row in
+// What bounds it.  A compute unit gets 80 (one token, three quarters of them from beyond its L2) to 160 (16, a third) cache lines a microsecond (counted, with
+// the launch), so a layer of 4096 channels on half of the compute units waits for loads while the other half has none.  Eight workgroups for a panel put it
+// on all of them.  A workgroup takes rows 8 j .. 8 j + 7 of two fragments of the panel: eight rows are one whole line of stored values (rows of all four
+// fragments in runs of four, half lines: 1.05 .. 1.8 of the time), and two workgroups share the lines of index words.  Eight wavefronts take stages of the row in
 // turn, two stages in flight each (three or four, or sixteen wavefronts: 0.99 .. 1.15); operands go from memory to registers, and the sums meet in
 // LDS in the order of the wavefronts.  The price is the token rows, which every workgroup reads whole: the kernel loses its lead with M times the
 // length of the row (slim_pays, mma_types.h).  Reading them as whole lines, two lanes trading halves, changed nothing (1.00 .. 1.07).

@@ -1,14 +1,16 @@
-// Sparse GEMMs on small unsplit tiles: 32 or 64 channels (one or two fragments of a panel) x 32 to 128 tokens, for layers that have too few tiles of 128 channels to
-// occupy the compute units and would split their rows.
+// Sparse GEMMs on small unsplit tiles: 32 or 64 channels (one or two fragments of a panel) x 32 to 128 tokens, for layers that have too few tiles of
+// 128 channels to occupy the compute units and would split their rows.
 //
-// A split row costs its partial sums twice (6 MB at M = 64 leave the L2s in 2.4 us between the two kernels, 14 MB at M = 256 in 3.2) and a second launch, 4 to 8 us of a call
-// together.  Small tiles read more: what a compute unit loads grows from 8 to 28 super-units of fewer lines each (3584 -> 3584 INT8 at M = 256 2300 -> 3500 lines), at 270 lines
-// a microsecond and compute unit with weights from HBM, 430 hot.  So they win until rows are long, the more the more tokens there are to sum up (small_pays, mma_types.h).
-// Within a workgroup the row is still split: KG groups of wavefronts, each with a KG-th of the row and a ring of its own, whose sums meet in LDS in the order of the groups.  The loop is
-// plain: wait for a unit, request a later one, read the operands, multiply.  Wavefronts that meet at every unit do all of that in step and nothing overlaps, so where the ring allows it a group is one
-// wavefront, which needs no meeting (32 and 64 tokens; against groups of a wavefront for each 32 tokens 0.97 .. 1.03 from HBM, 0.85 .. 0.95 hot); with 96 and 128 tokens two wavefronts or three.
-// us, weights from HBM / hot, split and now: INT8 3584 -> 4608 at M = 256 19.4 / 17.2 -> 13.0 / 12.0, 3584 -> 3584 at M = 256 16.8 / 15.4 -> 11.4 / 9.0, at M = 64 13.5 / 11.9 -> 7.7 / 5.2,
-// at M = 32 9.4 / 7.9 -> 7.8 / 5.1; fp8 lifted 4096 -> 4096 at M = 64 11.7 / 10.5 -> 9.4 / 6.3.
+// A split row costs its partial sums twice (6 MB at M = 64 leave the L2s in about 2.4 us between the two kernels, 14 MB at M = 256 in 3.2) and a second
+// launch, 4 to 8 us of a call together.  Small tiles read more: what a compute unit loads grows from 8 to 28 super-units of fewer lines each (3584 ->
+// 3584 INT8 at M = 256 2300 -> 3500 lines), at 200 to 270 lines a microsecond and compute unit with weights from HBM (counted, with the launch), 340 to 390
+// hot.  So they win until rows are long, the more the more tokens there are to sum up (small_pays, mma_types.h).
+// Within a workgroup the row is still split: KG groups of wavefronts, each with a KG-th of the row and a ring of its own, whose sums meet in LDS in the
+// order of the groups.  The loop is plain: wait for a unit, request a later one, read the operands, multiply.  Wavefronts that meet at every unit do all of
+// that in step and nothing overlaps, so where the ring allows it a group is one wavefront, which needs no meeting (32 and 64 tokens; against groups of a
+// wavefront for each 32 tokens 0.97 .. 1.03 from HBM, 0.85 .. 0.95 hot); with 96 and 128 tokens two wavefronts or three.
+// us, weights from HBM / hot, split and now: INT8 3584 -> 4608 at M = 256 19.4 / 17.2 -> 13.0 / 12.0, 3584 -> 3584 at M = 256 16.8 / 15.4 -> 11.4 / 9.0, at
+// M = 64 13.5 / 11.9 -> 7.7 / 5.2, at M = 32 9.4 / 7.9 -> 7.8 / 5.1; fp8 lifted 4096 -> 4096 at M = 64 11.7 / 10.5 -> 9.4 / 6.3.
 #include "ss_common.h"
 #include "packed_layout.h"
 #include "mma_types.h"
@@ -18,10 +20,12 @@
 
 namespace ss {
 
-// A workgroup has FW matrix-instruction fragments of 32 channels and TB blocks of 32 tokens, in KG groups of TB / TW wavefronts (TW blocks each).  Fragment j of a panel is rows 8 j .. 8 j + 7 of its four packed fragments: lines of values are whole, and so are those of index words, of which a packed fragment
-// by itself would use a quarter (62 lines a super-unit instead of 80 with 32 channels
-// and tokens: 0.97 .. 1.02 of the time from HBM, 0.93 .. 0.99 hot).
-// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [step][fragment][lane][16 B], index words [fragment][step][half 2][row 8][packed fragment 4][4 B] in 1 KB
+// A workgroup has FW matrix-instruction fragments of 32 channels and TB blocks of 32 tokens, in KG groups of TB / TW wavefronts (TW blocks each).
+// Fragment j of a panel is rows 8 j .. 8 j + 7 of its four packed fragments: lines of values are whole, and so are those of index words, of which a
+// packed fragment by itself would use a quarter (62 lines a super-unit instead of 80 with 32 channels and tokens: 0.97 .. 1.02 of the time from HBM,
+// 0.93 .. 0.99 hot).
+// A unit of 128 bytes of a token row in LDS: token rows (swizzled), values [step][fragment][lane][16 B], index words
+// [fragment][step][half 2][row 8][packed fragment 4][4 B] in 1 KB
 template <int FW, int TB, int TW, int KG, bool FUSED> struct SmallUnit {
     static constexpr int GW = TB / TW;                                    // wavefronts of a group
     static constexpr int NS = FUSED ? 3 : 2;
@@ -75,8 +79,10 @@ __global__ __launch_bounds__(64 * (TB / TW) * KG) void k_sparse_small(const uint
         const uint64_t lanes = a < NS * FW ? ~0ull : a < SU::PIECES ? (1ull << (16 * NS)) - 1 : 0ull;
         e_lanes[e] = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(lanes >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)lanes);
     }
-    // lane l brings row 8 j + (l & 7) of values: packed fragment (l >> 3) & 3, half l >> 5, which is where lane l of the matrix instruction reads them; of index words: step l >> 4, half (l >> 3) & 1
-    const uint32_t row16 = (8 * j0 + (lane & 7)) * 16, v_off = ((lane >> 3) & 3) * 1024 + (lane >> 5) * 512 + row16, i_off = (lane >> 4) * 1024 + ((lane >> 3) & 1) * 512 + row16;
+    // lane l brings row 8 j + (l & 7) of values: packed fragment (l >> 3) & 3, half l >> 5, which is where lane l of the matrix instruction reads them;
+    // of index words: step l >> 4, half (l >> 3) & 1
+    const uint32_t row16 = (8 * j0 + (lane & 7)) * 16, v_off = ((lane >> 3) & 3) * 1024 + (lane >> 5) * 512 + row16;
+    const uint32_t i_off = (lane >> 4) * 1024 + ((lane >> 3) & 1) * 512 + row16;
     const uint8_t* const av_src = w_vals + (panel * U_all + u_first) * (NS * 4096);
     const uint8_t* const am_src = w_meta + (panel * U_all + u_first) * (NS * 1024);
     // piece a of a unit: fragment a % FW of step a / FW of the values, then the index words of fragment a % FW; beyond the last: nothing
@@ -128,8 +134,10 @@ __global__ __launch_bounds__(64 * (TB / TW) * KG) void k_sparse_small(const uint
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int f = 0; f < FW; ++f)
-                    acc[f][b] = MM::sparse(a[h][f], v8i{x[2 * h][0], x[2 * h][1], x[2 * h][2], x[2 * h][3], x[2 * h + 1][0], x[2 * h + 1][1], x[2 * h + 1][2], x[2 * h + 1][3]}, acc[f][b], ix[h][f]);
+                for (int f = 0; f < FW; ++f) {
+                    const v4i lo = x[2 * h], hi = x[2 * h + 1];
+                    acc[f][b] = MM::sparse(a[h][f], v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, acc[f][b], ix[h][f]);
+                }
             if constexpr (FUSED) {                                       // middle windows: see gemm_mid.hip
                 v8i m;
 #pragma unroll
@@ -172,8 +180,10 @@ __global__ __launch_bounds__(64 * (TB / TW) * KG) void k_sparse_small(const uint
 #pragma unroll
             for (int b = 0; b < TW; ++b)
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4)
-                    x[(kg - 1) * GROUP + ((f * TW + b) * 4 + r4) * 64] = __builtin_bit_cast(v4i, (quad_t){acc[f][b][4 * r4], acc[f][b][4 * r4 + 1], acc[f][b][4 * r4 + 2], acc[f][b][4 * r4 + 3]});
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const quad_t q = {acc[f][b][4 * r4], acc[f][b][4 * r4 + 1], acc[f][b][4 * r4 + 2], acc[f][b][4 * r4 + 3]};
+                    x[(kg - 1) * GROUP + ((f * TW + b) * 4 + r4) * 64] = __builtin_bit_cast(v4i, q);
+                }
         wait_lgkm0();
     }
     wg_barrier();

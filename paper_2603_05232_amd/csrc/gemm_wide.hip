@@ -5,7 +5,8 @@
 // A wavefront owns one fragment and all tokens.  The loop is plain: wait for a unit, meet, request a later one, read the operands,
 // multiply; the order is left to the compiler.  A unit takes a compute unit 1500 cycles to stream and its operand reads and
 // matrix instructions a third of that, so a software pipeline in two groups of wavefronts, each with half of the k range (KG = 2 in gemm_mid.hip),
-// does not pay but for the lifted rows it has kept.  NF = 4 over it with the same kind of loads, INT8 and bf16 fused, fp8 and bf16 lifted, M = 1 .. 32, weights from HBM / hot:
+// does not pay but for the lifted rows it has kept.  NF = 4 over it with the same kind of loads, INT8 and bf16 fused, fp8 and bf16 lifted, M = 1 .. 32,
+// weights from HBM / hot:
 // rows of 64 to 200 units in ranges, 300 calls 0.91 .. 1.02 (mean 0.96) / 0.91 .. 1.12 (0.97), 129 to 256 panels in 12 to 100 units, fused, 168 calls 0.91 .. 1.02
 // (0.96) / 0.87 .. 1.15 (0.97), and in 1 to 15 units, 216 calls 0.86 .. 1.02 (0.95) / 0.81 .. 1.10 (0.95).  There is no line by the length of a row: two to ten units gain
 // most, and the calls that lose 5 % hot and more, 12 to 16 units whose weights the L2 holds (129 panels, lifted rows 192) and single longer ones, gain 1 to 5 % from HBM.
@@ -60,7 +61,8 @@ __global__ __launch_bounds__(64 * NF) void k_sparse_wide(const uint8_t* __restri
     const int frag = min(f_first + wave, nfrags - 1), panel = frag / FRAGS_PER_PANEL, f = frag % FRAGS_PER_PANEL;     // beyond the last: that one again, not stored
     const uint32_t lane16 = lane * 16, lds0 = lds_address(smem);
 
-    // The scales, asked for ahead of the first unit (else the epilogue starts with a trip to memory: 3584 -> 37888 INT8 at M = 1 22.1 -> 21.6 us, at M = 100 33.8 -> 33.2).  NF = 6 with 128 tokens has no room for them but in the ring, when all units are read.
+    // The scales, asked for ahead of the first unit (else the epilogue starts with a trip to memory: 3584 -> 37888 INT8 at M = 1 22.1 -> 21.6 us, at
+    // M = 100 33.8 -> 33.2).  NF = 6 with 128 tokens has no room for them but in the ring, when all units are read.
     constexpr int SCALES = WU::SCALES_FIT ? RING * WU::BYTES : 0, PIECES = WU::SCALES / 256;
     auto scales = [&]() __attribute__((always_inline)) {
 #pragma unroll

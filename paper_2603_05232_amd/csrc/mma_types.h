@@ -206,7 +206,8 @@ inline bool weights_stream(int64_t O, int64_t lifted, int64_t limit) { return O 
 
 enum ss_kind { SS_KIND_LIFTED, SS_KIND_FUSED, SS_KIND_DENSE };      // sparse from lifted rows, sparse that lifts itself, dense
 
-// Few tokens as a stream of weights (gemm_wide.hip): up to 32 tokens on as many panels as compute units or fewer, up to 64 on up to twice, unlifted rows of 97 to 128 on up to one and a half times as many.
+// Few tokens as a stream of weights (gemm_wide.hip): up to 32 tokens on as many panels as compute units or fewer, up to 64 on up to twice, unlifted rows of
+// 97 to 128 on up to one and a half times as many.
 // X: lifted rows, or unlifted ones and weights of slide_decompose_fused; U units of 128 bytes per row, ldxb bytes between rows.
 // S > 1 (NF = 4): partial sums as of the 32-token tiles of gemm_mid.hip go through `ws`.
 ss_status launch_sparse_wide(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
@@ -232,16 +233,25 @@ inline small_tile small_shape(int64_t M, int64_t O, int64_t units, int64_t cus)
         if (units >= t.kg && M > 32 * (t.tb - 1) && small_workgroups(M, O, t) <= cus) return t;
     return {0, 0, 0};
 }
-// Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before, 404 calls of
-// M = 17 .. 1450, 2 to 128 panels, 4 to 72 units, all types, weights from HBM / hot: 0.34 .. 1.03 (mean 0.71) / 0.34 .. 1.08 (0.67);
-//   no workspace 0.34 .. 1.00 / 0.34 .. 1.02
-//   M <= 16 (where gemm_slim.hip does not serve the call), not split: 33 to 64 panels 0.79 .. 1.03 / 0.69 .. 1.03, 65 to 128 panels and 15 units and more 0.72 .. 1.02 /
-//     0.54 .. 1.04 (mean 0.86 / 0.82), 4 to 9 units, which stay on gemm_skinny.hip, 0.90 .. 1.11 / 0.86 .. 1.10; split 0.83 .. 2.2, so those stay where they are
-//   split, M <= 32 0.70 .. 1.00 (0.86) / 0.53 .. 1.01 (0.75), M = 33 .. 64 0.42 .. 1.00 (0.65) / 0.40 .. 1.08 (0.58)
-//   split, M > 64, tiles of 32 tokens 0.48 .. 0.86 / 0.45 .. 0.74, 64 0.54 .. 1.03 / 0.52 .. 0.92, 96 0.61 .. 0.93 / 0.63 .. 0.91, 128 0.76 .. 0.98 / 0.87 .. 1.04 (5200 lines and more to 1.09)
-//   three units, 33 to 48 tokens, on the tiles of three groups 0.97 .. 1.08 of the few-token kernel of before, on the 64-token tiles of gemm_mid.hip 0.71 .. 0.96 / 0.71 .. 1.03, which take them;
-//     with 64 tokens level (0.82 .. 1.00 and 0.78 .. 0.94), and off a 16-byte line of Y the small tiles are the faster (0.54 .. 0.79 and 0.55 .. 0.87)
-// Beyond those lines: M <= 32 1.03 .. 2.2, M <= 64 1.04 .. 1.8, M > 64 0.9 .. 1.9 (all with the first form of the kernel, groups of a wavefront for each 32 tokens).
+// Where they are used, by the lines a workgroup loads for its row.  `split`: the call would otherwise be split into k ranges.  Time over the kernels
+// before these, 5700 calls on 80 to 100 % of the compute units or just within a line, all types, weights from HBM / hot, means in parentheses:
+//   not split  M <= 16 (where gemm_slim.hip does not serve the call) on 33 to 64 panels 0.87 .. 1.03 (0.94) / 0.68 .. 0.99 (0.84), on 65 to 128 with 12 units
+//              and more 0.80 .. 1.04 (0.93; of 600 others at most 1.07) / 0.66 .. 1.06 (0.87); 4 to 9 units, which stay on gemm_skinny.hip, 0.90 .. 1.11 /
+//              0.86 .. 1.10;  M <= 32 0.68 .. 1.04 (0.89) / 0.48 .. 0.97 (0.74), M <= 64 0.48 .. 1.04 (0.71) / 0.35 .. 1.01 (0.59)
+//              M > 64, tiles of 32 tokens 0.27 .. 0.72 (0.48) / 0.24 .. 0.68 (0.46), 64 0.34 .. 0.81 (0.60) / 0.32 .. 0.81 (0.62), 96 0.30 .. 0.94 (0.69) /
+//              0.28 .. 0.91 (0.71), 128 0.33 .. 0.91 (0.73) / 0.32 .. 1.06 (0.79)
+//   split      M <= 64 0.71 .. 1.01 (0.88) / 0.64 .. 0.75 (0.69)
+//              M > 64, tiles of 32 tokens 0.49 .. 0.92 (0.69) / 0.41 .. 0.71 (0.56), 64 0.53 .. 1.01 (0.78) / 0.48 .. 0.94 (0.69), 96 0.51 .. 1.03 (0.80) /
+//              0.46 .. 0.98 (0.77), 128 0.67 .. 0.98 / 0.57 .. 1.04 (5200 lines and more to 1.09)
+//   three units, 33 to 48 tokens, on the tiles of three groups 0.97 .. 1.08 of the few-token kernel of before, on the 64-token tiles of gemm_mid.hip
+//              0.71 .. 0.96 / 0.71 .. 1.03, which take them; with 64 tokens level (0.82 .. 1.00 and 0.78 .. 0.94), and off a 16-byte line of Y the small tiles
+//              are the faster (0.54 .. 0.79 and 0.55 .. 0.87)
+// Beyond the lines, these tiles over the ranges that run there, 2100 calls, means by how far beyond:
+//   M <= 16    40 to 59 units 1.00 (0.88 .. 1.17); 60 to 79 on 8 to 15 panels 1.17, 16 to 23 1.10, 24 to 35 1.02, 36 to 64 0.94 (0.85 .. 1.01) / 0.85; 80 to 99
+//              on 36 to 64 0.97 (0.89 .. 1.14) / 0.86, on fewer 1.06 .. 1.33; 100 and more 1.01 .. 1.66.  No line is drawn around those that gain
+//   M <= 32    up to 1.2 times the line 1.01 (0.96 .. 1.18) / 0.99, 1.4 1.10 / 0.94, 1.6 1.18 / 0.91;  M <= 64 1.00 (0.85 .. 1.13) / 0.93, 1.04 / 0.89, 1.08 / 0.91
+//   M > 64     32 tokens 0.84 (0.63 .. 1.05) / 0.71, 0.91 (0.63 .. 1.18) / 0.75, 0.97 / 0.77; 64 0.95 (0.82 .. 1.08) / 0.86, 0.99 / 0.90, 1.06 / 0.96;
+//              96 0.98 (0.86 .. 1.19) / 0.96, 0.96 / 0.99, 1.06 / 1.11; 128 0.94 / 0.93, 0.97 / 0.97
 inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroups, bool fused, bool split)
 {
     if (t.fw == 0 || (M <= 48 && units < 4)) return false;
@@ -254,11 +264,12 @@ inline bool small_pays(int64_t M, int64_t units, small_tile t, int64_t workgroup
 // Up to 16 tokens with a workgroup for every 16 channels (gemm_slim.hip), unsplit; operands as above.
 ss_status launch_sparse_slim(bool fused, const void* X, const float* s_x, const void* w_vals, const void* w_meta, const float* s_w, int64_t M, int64_t O,
                              int U, int64_t ldxb, ss_dtype dtype, void* Y, int64_t ldy, hipStream_t stream);
-// Every one of its workgroups reads all token rows, so the lines go by units and tokens.  `split`: the call would otherwise be split into k ranges.  Time over the kernels of before,
-// all types, weights from HBM / hot, M = 1 .. 16:
-//   at most one workgroup per compute unit, not split: 1 to 56 units 0.57 .. 0.83 / 0.55 .. 0.82, without a workspace 72 to 256 units 0.48 .. 0.77 / 0.44 .. 0.88
-//   the same, split, 8 panels and more, by units (M + 8): up to 1000 0.82 .. 1.01 / 0.59 .. 0.89, 1000 .. 1400 0.93 .. 1.33 / 0.66 .. 1.03, more 1.1 .. 2.0.  Fewer
-//     panels would leave most compute units idle, which their ranges do not
+// Every one of its workgroups reads all token rows, so the lines go by units and tokens.  `split`: the call would otherwise be split into k ranges.  Time
+// over the kernels of before, all types, weights from HBM / hot, M = 1 .. 16:
+//   at most one workgroup per compute unit, not split: 1 to 56 units 0.57 .. 0.90 / 0.55 .. 0.82, without a workspace 72 to 256 units 0.48 .. 0.93 / 0.44 .. 0.92
+//   the same, split, 8 panels and more, by units (M + 8): up to 1000 0.74 .. 1.04 (mean 0.88) / 0.54 .. 0.89 (0.68), 1000 .. 1400 0.93 .. 1.33 / 0.66 .. 1.03, more
+//     1.1 .. 2.0.  The worst are unlifted rows of one to four tokens on 8 to 10 panels, 9.5 units a panel and more: 1.00 .. 1.08 from HBM, but 0.70 .. 0.77 hot, so they
+//     stay here (in ranges they were 0.97 of the time from HBM and 1.35 hot).  Fewer panels would leave most compute units idle, which their ranges do not
 //   some compute units with two of them, by units (M + 2): up to 120 0.76 .. 0.99 / 0.76 .. 1.00 (3584 -> 4608 INT8 at M = 1 7.2 -> 6.9 us, hot 5.7 -> 4.4), 120 ..
 //     170 0.88 .. 1.10 / 0.79 .. 0.98
 inline bool slim_pays(int64_t M, int64_t O, int64_t units, int64_t cus, bool split)
@@ -311,8 +322,10 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 //             0.89 / 1.07, 32 0.90 / 1.03, 16-bit 12 1.00 / 1.09, 24 0.94 / 1.03, 32 0.80 / 1.03.  449 .. 512 tiles, fused 8-bit 16 0.96 / 1.07, 24 0.92 /
 //             1.08, 32 0.88 / 1.05, 16-bit 24 0.97 / 1.05; lifted 8-bit 32 0.97 / 1.13, 48 0.95 / 1.09, 16-bit 48 0.92 / 1.07.  The lines go by
 //             the first figure, a layer's weights coming from HBM in a model of many.
-//   on at most half as many 128 x 128 tiles as compute units small unsplit tiles, unless the rows are long and can be split (small_pays) or 16 channels a workgroup serve them (slim_pays).
-//   M 33..64  tiles of 64 tokens otherwise (3584 -> 37888: 37 against the few-token kernel's 50; split: bf16 3584 -> 4608 13.9 against 23.6, fp8 lifted 4096 -> 6144 13.9 against 19.9).
+//   on at most half as many 128 x 128 tiles as compute units small unsplit tiles, unless the rows are long and can be split (small_pays) or 16 channels a
+//             workgroup serve them (slim_pays).
+//   M 33..64  tiles of 64 tokens otherwise (3584 -> 37888: 37 against the few-token kernel's 50; split: bf16 3584 -> 4608 13.9 against 23.6, fp8 lifted
+//             4096 -> 6144 13.9 against 19.9).
 //   M <= 32   a workgroup per panel (and k range; gemm_wide.hip) where there are more panels than half of the compute units (rows of 16 units and more: 3584 -> 18944
 //             at M = 1, 148 panels: INT8 14.4 against 17.3, bf16 21.2 against 29.6; shorter ones by `wide` below) or the rows are long
 //             and can be split (18944 -> 3584, M = 1: 19 against 23; 64 units, 4096 channels bf16, M = 1: 13 against 18;
@@ -339,7 +352,8 @@ inline int64_t narrow_tiles(int64_t M, int64_t O) { return ((O + 127) / 128) * (
 // The dense kernels keep tiles of 128 tokens and their own lines: M <= 32, and M <= 64 unless the rows are at least 96
 // units long and can be split, few-token; up to 320 tiles 128 x 128.
 enum ss_path { SS_PATH_SKINNY, SS_PATH_MID, SS_PATH_NARROW, SS_PATH_TILE, SS_PATH_WIDE, SS_PATH_SLIM, SS_PATH_SMALL };
-struct ss_plan { ss_path path; int S; int64_t tile_o = 0; small_tile small = {0, 0, 0}; };      // tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
+// tile_o: channels the 256 x 256 tiles take, the rest goes to 128 x 128 or 128 x 256 tiles
+struct ss_plan { ss_path path; int S; int64_t tile_o = 0; small_tile small = {0, 0, 0}; };
 // The 256 x 256 tile kernels run one tile per compute unit and round; a last round that is nearly empty costs as much as a
 // full one.  If whole rounds can be cut off along the channels so that the rest is at most one 128 x 128 tile per compute
 // unit, the rest goes to those (M = 8192, 3584 -> 4608, 2.25 rounds: bf16 210 -> 194 us, INT8 120 -> 116).  With two of them per

@@ -22,13 +22,16 @@ __device__ inline float load_scalar(const float* p) { return *p; }
 __device__ inline float load_scalar(const uint16_t* p) { return bf16_bits_to_f32(*p); }
 
 // Whether act_lift_quant stores its M rows of row_bytes (elements of es bytes, from input vectors of `vec` elements) through the L2
-// (store_through).  A GEMM of few channels behind it is short and waits for its tokens, which plain stores leave nearer; rows of 2 to 5 KB are the worst.  Time over
-// plain stores, quantiser and a GEMM of 128 to 12000 channels, 9900 calls, by rows and MB of them:
-//   up to 1792 bytes       lifted 4 .. 16 0.86 .. 1.05 (mean 0.94), unlifted 0.89 .. 1.03 (0.95); more 0.96 .. 1.05
-//   1793 .. 5631 bytes     lifted 4 .. 8 0.88 .. 1.08 (0.95), unlifted of 3072 bytes and more 0.93 .. 1.04 (0.97), shorter 0.90 .. 1.27 (INT8 2399 x 2048, 1024 channels 22.4 -> 25.9 us);
-//                          8 .. 32 with up to 1024 channels lifted 0.90 .. 1.16 (1.01), unlifted 0.94 .. 1.19 (1.03), with more 0.91 .. 1.06 (0.99)
-//   5632 bytes and more    lifted 4 .. 8 0.92 .. 1.02 (0.96), 8 .. 16 0.90 .. 1.04 (0.97), 16 .. 32 0.93 .. 1.06 (0.99); unlifted 0.93 .. 1.03 (0.98), 0.95 .. 1.05 (0.99), 0.95 .. 1.04 (0.99)
-//   fp32 to 8 bits unlifted, stores of four bytes, 0.98 .. 1.05; 16-bit codes 0.95 .. 1.18 without a line to draw; the kernel alone below 1 MB 1.03 .. 1.06, 1 to 4 MB 0.86 .. 1.05
+// (store_through).  A GEMM of few channels behind it is short and waits for its tokens, which plain stores leave nearer; rows of 2 to 5 KB are the worst.
+// Time over plain stores, quantiser and a GEMM of 128 to 12000 channels, 9900 calls, by rows and MB of them:
+//   up to 1792 bytes     lifted 4 .. 16 0.86 .. 1.05 (mean 0.94), unlifted 0.89 .. 1.03 (0.95); more 0.96 .. 1.05
+//   1793 .. 5631 bytes   lifted 4 .. 8 0.88 .. 1.10 (0.95); unlifted of 3072 bytes and more 0.93 .. 1.04 (0.97), shorter 0.90 .. 1.27 (INT8 2399 x 2048, 1024
+//                        channels 22.4 -> 25.9 us); 8 .. 32 with up to 1024 channels lifted 0.90 .. 1.16 (1.01), unlifted 0.94 .. 1.19 (1.03), with more
+//                        0.92 .. 1.07 (0.99)
+//   5632 bytes and more  lifted 4 .. 8 0.92 .. 1.02 (0.96), 8 .. 16 0.90 .. 1.04 (0.97), 16 .. 32 0.93 .. 1.06 (0.99); unlifted 0.93 .. 1.03 (0.98),
+//                        0.95 .. 1.05 (0.99), 0.95 .. 1.04 (0.99)
+//   fp32 to 8 bits unlifted, stores of four bytes, 0.98 .. 1.05; 16-bit codes 0.95 .. 1.18 without a line to draw; the kernel alone below 1 MB 1.03 .. 1.06,
+//   1 to 4 MB 0.86 .. 1.05
 inline bool lift_through(int es, int vec, int64_t M, int64_t row_bytes, int N)
 {
     const bool is_short = row_bytes <= 1792, is_long = row_bytes >= 5632;
